@@ -9,21 +9,25 @@
 // The two operands reach the matrix cores by different roads, which splits the traffic between
 // LDS and the vector memory path instead of loading one of them with everything:
 //   * w is shared by the four waves: one 64-deep unit (4 blocks of 4 KB, already in MFMA operand
-//     order, so they are copied to LDS as they are and read back conflict-free) is staged per
-//     step in one of three LDS stages.  The global loads of unit u + 2 go out at the top of
-//     unit u, land in registers meanwhile and are written to LDS during its last chunk; the one
-//     barrier per unit then makes stage u + 2 visible a whole unit before it is read, so the first
-//     fragments of unit u + 1 are read before the barrier that ends unit u and no wave starts a
-//     unit waiting for LDS.
+//     order, so they are copied to LDS as they are and read back conflict-free) per step, in one of
+//     four LDS stages.  Buffer loads that write LDS directly bring unit u + 3 while unit u is
+//     multiplied; the one barrier per unit waits for those of unit u + 2 only (a counted wait), so
+//     the first fragments of unit u + 1 are read before the barrier that ends unit u and no wave
+//     starts a unit waiting for LDS.
 //   * a rows belong to one wave only, and the tiled layout holds them in operand order: a wave
 //     loads its fragments straight from memory into the registers the MFMAs read (1 KB per wave
-//     and fragment, fully coalesced), one unit ahead, refilling each fragment's registers as soon
+//     and fragment, fully coalesced), two units ahead, refilling each fragment's registers as soon
 //     as the chunk that used them has been issued.
+// A wave's loads return in the order in which they were issued, so the wait for the oldest a fragment
+// is also a wait for every weight load before it: both kinds run two units ahead, or the shorter
+// distance would rule.  (With w through registers, one unit ahead, a unit took the latency of an
+// HBM load however little there was to multiply: 300 x 4096 x 14336 181 -> 135 us, 1024 rows
+// 190 -> 170 us; at 8192 rows, where L2 serves most loads, 750 -> 731 us.)
+// The loads into LDS are buffer loads because the compiler counts those: after a global (flat) load
+// into LDS it waits for everything in flight before the next use of any load.
 // Per 16-deep chunk a wave reads 4 fragments from LDS, loads 2 from memory and issues 8 MFMAs.
-// With both operands in LDS (the earlier form: 256 x 256 per 8-wave workgroup) the matrix pipes
-// were busy 61 % and the LDS 63 %; this form reaches 75 % at a lower clock: the part is then at
-// its power limit, and variants that differ in barrier scope or fragment look-ahead all
-// land on the same rate.
+// At 8192 rows the part is at its power limit (the matrix pipes are 81 % busy at a lowered clock),
+// and variants that differ in barrier scope or fragment look-ahead land on the same rate.
 //
 // Workgroup numbering follows the hardware's round-robin deal of workgroups to the 8 XCDs: the
 // ids that land on one XCD walk a compact patch of output tiles (8 row tiles deep), so that XCD's
@@ -73,6 +77,16 @@ enum { GEMM_STORE = 0, GEMM_SWIGLU = 1, GEMM_ROPE = 2, GEMM_ACCUM = 3 };
 // that the 16-byte writes of eight lanes (eight rows) fall into different banks
 constexpr int kParkStride = 132;
 
+// All but the newest N vector memory operations of this wave have landed, loads into LDS among them,
+// then the workgroup's barrier.  (__syncthreads() would wait for every load in flight.)
+template <int N>
+__device__ inline void wait_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);    // vmcnt <= N; the other counters free
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
@@ -86,9 +100,8 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
   constexpr int AB = 8;                    // 32-row tiles of a per workgroup: 256 rows
   constexpr int WB = TN;                   // blocks of each weight matrix per unit (workgroup)
   constexpr int NBW = NW * WB;             // 4 weight blocks of 256 chunks per unit
-  constexpr int kStages = 3;
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_lds[];
-  v4u *lds = (v4u *)gemm_lds;              // [kStages][NBW][256]
+  v4u *lds = (v4u *)gemm_lds;              // [4 stages][NBW][256]
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave;
@@ -98,16 +111,12 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
   const int mt0 = tm * AB, nt0 = tn * WB;  // first 32-row tile of a / of each weight matrix
   const int m_tiles = (M + 31) >> 5;
 
-  // weight staging: thread t carries chunk t of every block of the unit
-  const char *src[NBW];
-#pragma unroll
-  for (int i = 0; i < NBW; ++i) {
-    // blocks of the unit: w first, then w2
-    const bf16_t *p = i < WB ? w + (size_t)(nt0 + i) * U * 2048 : w2 + (size_t)(nt0 + i - WB) * U * 2048;
-    src[i] = (const char *)p;
-  }
+  // weight staging: thread t brings chunk t of every block of the unit, w's blocks first, then w2's
+  const __amdgpu_buffer_rsrc_t wsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void *)(w + (size_t)nt0 * U * 2048), 0, WB * U * 4096, 0x00020000);
+  const __amdgpu_buffer_rsrc_t w2src =
+      SWIGLU ? __builtin_amdgcn_make_buffer_rsrc((void *)(w2 + (size_t)nt0 * U * 2048), 0, WB * U * 4096, 0x00020000) : wsrc;
   const uint32_t s_off = tid * 16u;
-  const int s_lds = tid;       // + (stage * NBW + i) * 256
   // the rows of a come straight from memory in operand order: a chunk of a tile is 1 KB, 16 bytes per lane
   const char *asrc[TM];
 #pragma unroll
@@ -124,22 +133,20 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
       for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
 
   // Loads past the last unit re-read the last unit (in bounds, never used), so that every
-  // iteration issues the same loads and the compiler's load counters stay exact.
-  v4u st[NBW];
-  auto load_w = [&](int u) __attribute__((always_inline)) {
-    const uint32_t at = s_off + (uint32_t)min(u, U - 1) * 4096u;
+  // iteration issues the same loads and the load counters stay exact.
+  auto load_w = [&](int u, int stage) __attribute__((always_inline)) {
+    const uint32_t at = (uint32_t)min(u, U - 1) * 4096u;
+    v4u *dst = lds + stage * NBW * 256 + wave * 64;
 #pragma unroll
-    for (int i = 0; i < NBW; ++i) st[i] = *(const v4u *)(src[i] + at);
+    for (int i = 0; i < NBW; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(i < WB ? wsrc : w2src, (__attribute__((address_space(3))) void *)(dst + i * 256),
+                                               16, s_off, at + (uint32_t)((i < WB ? i : i - WB) * U) * 4096u, 0, 0);
   };
-  auto store_w = [&](int stage) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NBW; ++i) lds[(stage * NBW + i) * 256 + s_lds] = st[i];
-  };
-  v4u fa[4][TM];
-  auto load_a = [&](int u, int c) __attribute__((always_inline)) {
+  v4u fa[2][4][TM];
+  auto load_a = [&](int slot, int u, int c) __attribute__((always_inline)) {
     const uint32_t at = a_off + (uint32_t)min(u, U - 1) * 4096u + (uint32_t)c * 1024u;
 #pragma unroll
-    for (int y = 0; y < TM; ++y) fa[c][y] = *(const v4u *)(asrc[y] + at);
+    for (int y = 0; y < TM; ++y) fa[slot][c][y] = *(const v4u *)(asrc[y] + at);
   };
   auto read_w = [&](v4u (&fw)[WT], int stage, int c) __attribute__((always_inline)) {
     const v4u *cw = lds + stage * NBW * 256 + lane + c * 64;
@@ -157,53 +164,48 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
   };
 
   v4u fw[2][WT];
-  load_w(0);
 #pragma unroll
-  for (int c = 0; c < 4; ++c) load_a(0, c);
-  store_w(0);
-  load_w(1);
-  store_w(1);
-  __syncthreads();
+  for (int d = 0; d < 3; ++d) load_w(d, d);
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      load_a(d, d, c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  wait_barrier<0>();
   read_w(fw[0], 0, 0);
-  int cur = 0, nxt = 1, wr = 2;
-  for (int u = 0; u < U; ++u) {
-    load_w(u + 2);
+  // Stage (u + 3) % 4 was last read during unit u - 1, which every wave left before the barrier that
+  // ended it.  At the barrier that ends unit u everything older than the fragments of a for unit
+  // u + 1 has landed: the weights of unit u + 2, issued at the top of unit u - 1, before them.
+  auto unit = [&](int u, int slot) __attribute__((always_inline)) {
+    const int cur = u & 3, nxt = (u + 1) & 3;
+    load_w(u + 3, (u + 3) & 3);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      read_w(fw[(c + 1) & 1], cur, c + 1);
-      multiply(fa[c], fw[c & 1]);
-      load_a(u + 1, c);
+    for (int c = 0; c < 4; ++c) {
+      if (c < 3) read_w(fw[(c + 1) & 1], cur, c + 1);
+      else read_w(fw[0], nxt, 0);
+      multiply(fa[slot][c], fw[c & 1]);
+      load_a(slot, u + 2, c);
 #pragma unroll
       for (int i = 0; i < WT; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // one LDS read
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // one MFMA
       }
       __builtin_amdgcn_sched_group_barrier(0x008, TM * WT - WT, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, TM, 0);     // the loads of a for the next unit
+      __builtin_amdgcn_sched_group_barrier(0x020, TM, 0);     // the loads of a
       __builtin_amdgcn_sched_barrier(0);
     }
-    // stage wr was last read during unit u - 1, which every wave left before the barrier that
-    // ended it; stage nxt was written during unit u - 1 and is complete since that barrier
-    store_w(wr);
-    read_w(fw[0], nxt, 0);
-    multiply(fa[3], fw[1]);
-    load_a(u + 1, 3);
-#pragma unroll
-    for (int i = 0; i < NBW; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA
-      __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);      // one LDS write
-    }
-#pragma unroll
-    for (int i = 0; i < WT; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // one LDS read
-    }
-    __builtin_amdgcn_sched_group_barrier(0x020, TM, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    const int t = cur; cur = nxt; nxt = wr; wr = t;
-  }
+    wait_barrier<8 * TM + NBW>();            // a of units u + 1 and u + 2, w of unit u + 3 may be in flight
+  };
+  int u = 0;
+  do {                                     // U is even and at least 2
+    unit(u, 0);
+    unit(u + 1, 1);
+    u += 2;
+  } while (u < U);
+  wait_barrier<0>();                         // no load into LDS outlives the loop
 
   // weight rows are the A operand: a lane holds column m = j of the tile and, per register quad,
   // four consecutive n
@@ -311,7 +313,7 @@ int launch_mfma_probe(hipStream_t st, const void *operands, float *out, int n_wo
 
 bool gemm256_supported(int M, int N, int K, bool swiglu) {
   (void)swiglu;
-  return M >= 1 && K >= 64 && K % 64 == 0 && N % 128 == 0;
+  return M >= 1 && K >= 128 && K % 128 == 0 && N % 128 == 0;      // whole pairs of 64-deep units
 }
 
 int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const void *w,
@@ -325,8 +327,8 @@ int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const voi
   const int mode = swiglu ? GEMM_SWIGLU : rope ? GEMM_ROPE : accumulate ? GEMM_ACCUM : GEMM_STORE;
   const int tiles_m = (M + 255) / 256, tiles_n = N / (swiglu ? 64 : 128);
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  // three stages of 4 weight blocks; the parking areas of the rotation epilogue need a little more
-  const size_t lds = std::max<size_t>(3 * 4 * 4096, mode == GEMM_ROPE ? 4 * 32 * kParkStride * sizeof(float) : 0);
+  // four stages of 4 weight blocks; the parking areas of the rotation epilogue need a little more
+  const size_t lds = std::max<size_t>(4 * 4 * 4096, mode == GEMM_ROPE ? 4 * 32 * kParkStride * sizeof(float) : 0);
   const void *kernels[4] = {(const void *)gemm256_kernel<GEMM_STORE>, (const void *)gemm256_kernel<GEMM_SWIGLU>,
                             (const void *)gemm256_kernel<GEMM_ROPE>, (const void *)gemm256_kernel<GEMM_ACCUM>};
   // the largest request of this mode (the rotation epilogue's parking areas included)

@@ -98,7 +98,7 @@ __device__ inline void rope_store_quad(const RopeOut &ro, int m, int n, float4 s
 }
 
 // Many-row GEMM (more than 64 rows): fp32 out, or the SwiGLU form with bf16 tiled out.  N % 128
-// == 0, K % 64 == 0.  256 x 128 output tile per workgroup (256 x 64 of each weight matrix in the
+// == 0, K % 128 == 0.  256 x 128 output tile per workgroup (256 x 64 of each weight matrix in the
 // SwiGLU form), XCD-aware tile order.
 bool gemm256_supported(int M, int N, int K, bool swiglu);
 // rope != nullptr: the fused QKV layer as in launch_linear_skinny (N = (Hq + 2 Hkv) hd, hd % 4 == 0).
