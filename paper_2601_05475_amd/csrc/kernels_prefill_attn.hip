@@ -39,19 +39,30 @@ constexpr int PPG = 64;                       // keys per page
 template <int HD> struct PTile {
   static constexpr int K_ELEMS = PPG * HD, V_ELEMS = PPG * HD, PAGE_ELEMS = K_ELEMS + V_ELEMS;
   static constexpr int NF = HD / 16;          // 1 KB fragments per 32-key block (K and V alike)
+  static constexpr int CPT = PPG * HD / 8 / 512;            // 16-byte loads per thread and K (or V) page
   static constexpr int LDS_BYTES = 3 * PAGE_ELEMS * 2;      // three page buffers
-  static constexpr int CPT = PPG * HD / 8 / 512;
 };
 
 constexpr int kPrefillMaxPids = 1024;
 
+// All but the newest N vector memory operations of this wave have landed, loads into LDS among them,
+// then the workgroup's barrier.  (__syncthreads() would wait for every load in flight.)
+template <int N>
+__device__ inline void wait_barrier_p() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);    // vmcnt <= N; the other counters free
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <int HD>
-__global__ __launch_bounds__(512)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void prefill_attention_kernel(PrefillAttnArgs a) {
   using TL = PTile<HD>;
   extern __shared__ __attribute__((aligned(16))) unsigned char plds_raw[];
   bf16_t *lds = (bf16_t *)plds_raw;
-  int *pids = (int *)(plds_raw + TL::LDS_BYTES);
+  typedef __attribute__((address_space(3))) int lds_int;
+  lds_int *pids = (lds_int *)(plds_raw + TL::LDS_BYTES);
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hw = wave & 3, half = wave >> 2;    // head within the group, half of the item's rows
@@ -99,44 +110,55 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f;                 // l: this lane's half of its column's sum
 
   const size_t page_stride = (size_t)Hkv * PPG * HD, head_off = (size_t)kvh * PPG * HD;
   const bf16_t *kA = (const bf16_t *)a.k_prefix, *vA = (const bf16_t *)a.v_prefix;
   const bf16_t *kB = (const bf16_t *)a.k_suffix, *vB = (const bf16_t *)a.v_suffix;
   // Pages go from global memory straight into LDS (lane i of a wave-wide 16-byte load lands at
   // the wave's base + 16 i: the page is copied as it is), two pages ahead of the one in use, into
-  // three buffers.  The same number of loads is issued whether or not the page exists (a page
-  // past the end re-reads 16 bytes of page 0 into a buffer nobody reads), so the wait before the
-  // barrier can count: all but the newest page's loads have landed.
-  auto issue = [&](int pi, int buf) __attribute__((always_inline)) {
-    const bool real = pi < n_pages;
-    const int p = real ? pi : 0;
-    const bool in_a = p < nPA;
-    const int page = in_a ? p : (pids_in_lds ? pids[p - nPA] : table[p - nPA]);
-    const bf16_t *kp = (in_a ? kA : kB) + (size_t)page * page_stride + head_off;
-    const bf16_t *vp = (in_a ? vA : vB) + (size_t)page * page_stride + head_off;
-    const size_t lane_off = real ? (size_t)tid * 8 : 0, step = real ? 512 * 8 : 0;
+  // three buffers.  The same number of loads is issued whether or not the page exists (a page past
+  // the end has a range of no bytes: nothing is fetched), so the wait before the barrier can
+  // count: all but the newest page's loads have landed.  They are buffer loads because the compiler
+  // counts those; after a global (flat) load into LDS it waits for everything in flight before the
+  // next use of any load.
+  auto page_of = [&](int pi) __attribute__((always_inline)) -> int {
+    if (pi >= n_pages) return 0;
+    if (pi < nPA) return pi;
+    if (pids_in_lds) return __builtin_amdgcn_readfirstlane(pids[pi - nPA]);
+    return __builtin_amdgcn_readfirstlane(table[pi - nPA]);
+  };
+  auto issue = [&](int pi, int page, int buf) __attribute__((always_inline)) {
+    const bool in_a = pi < nPA;
+    const size_t at = (size_t)page * page_stride + head_off;
+    const int bytes = pi < n_pages ? PPG * HD * (int)sizeof(bf16_t) : 0;
+    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)((in_a ? kA : kB) + at), 0, bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)((in_a ? vA : vB) + at), 0, bytes, 0x00020000);
     bf16_t *kt = lds + buf * TL::PAGE_ELEMS + wave * 512, *vt = kt + TL::K_ELEMS;
 #pragma unroll
     for (int i = 0; i < TL::CPT; ++i) {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kp + lane_off + step * i),
-                                       (__attribute__((address_space(3))) void *)(kt + 4096 * i), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(vp + lane_off + step * i),
-                                       (__attribute__((address_space(3))) void *)(vt + 4096 * i), 16, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void *)(kt + 4096 * i), 16, tid * 16, 8192 * i, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void *)(vt + 4096 * i), 16, tid * 16, 8192 * i, 0, 0);
     }
   };
   // one 32-key block whose key 0 sits at absolute position abs0; n_valid keys exist
   auto process = [&](int buf, int blk, int n_valid, int abs0) __attribute__((always_inline)) {
     const bf16_t *kt = lds + buf * TL::PAGE_ELEMS, *vt = kt + TL::K_ELEMS;
     const bf16_t *kblk = kt + (blk * TL::NF * 64 + lane) * 8, *vblk = vt + (blk * TL::NF * 64 + lane) * 8;
+    // all key fragments are asked for before the first MFMA, a value fragment after each: they
+    // arrive under the score MFMAs and the softmax
+    v4u kf[TL::NF], vf[TL::NF];
+#pragma unroll
+    for (int c = 0; c < TL::NF; ++c) kf[c] = *(const v4u *)(kblk + c * 512);
+    __builtin_amdgcn_sched_barrier(0);
     f32x16 s;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-    for (int c = 0; c < HD / 16; ++c) {
-      const v4u kf = *(const v4u *)(kblk + c * 512);
-      s = mfma32p(kf, qf[c], s);
+    for (int c = 0; c < TL::NF; ++c) {
+      s = mfma32p(kf[c], qf[c], s);
+      vf[c] = *(const v4u *)(vblk + c * 512);
+      __builtin_amdgcn_sched_barrier(0);
     }
     // key of register r: 8 (r / 4) + 4 h + r % 4; it is masked if it does not exist or lies
     // after this lane's query position
@@ -178,7 +200,6 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
         rs += p[r];
       }
     }
-    rs += swap_halves(rs, swap_addr);
     l += rs;
     v4u pb[2];
     pb[0] = v4u{pack2p_bf16(p[0], p[1]), pack2p_bf16(p[2], p[3]), pack2p_bf16(p[4], p[5]), pack2p_bf16(p[6], p[7])};
@@ -186,10 +207,7 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
 #pragma unroll
     for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
-      for (int sl = 0; sl < 2; ++sl) {
-        const v4u vf = *(const v4u *)(vblk + (dt * 2 + sl) * 512);
-        o[dt] = mfma32p(vf, pb[sl], o[dt]);
-      }
+      for (int sl = 0; sl < 2; ++sl) o[dt] = mfma32p(vf[dt * 2 + sl], pb[sl], o[dt]);
   };
   auto consume = [&](int pi, int buf) __attribute__((always_inline)) {
     if (!wave_active) return;
@@ -203,20 +221,21 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
     }
   };
 
-  issue(0, 0);
-  issue(1, 1);
-  int buf = 0;
+  issue(0, page_of(0), 0);
+  issue(1, page_of(1), 1);
+  int buf = 0, next_page = page_of(2);
   for (int pi = 0; pi < n_pages; ++pi) {
-    // page pi has landed once at most the loads of page pi + 1 are outstanding
-    if (TL::CPT == 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    __syncthreads();                             // ... for every wave; and page pi - 1 is no longer read
-    issue(pi + 2, buf >= 1 ? buf - 1 : 2);       // into page pi - 1's buffer, (buf + 2) % 3
+    // page pi has landed once at most the loads of page pi + 1 are outstanding; past the barrier
+    // that holds for every wave, and page pi - 1 is no longer read
+    wait_barrier_p<2 * TL::CPT>();
+    issue(pi + 2, next_page, buf >= 1 ? buf - 1 : 2);       // into page pi - 1's buffer, (buf + 2) % 3
+    next_page = page_of(pi + 3);
     consume(pi, buf);
     buf = buf == 2 ? 0 : buf + 1;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the workgroup
+  wait_barrier_p<0>();                         // no load into LDS outlives the workgroup
 
+  l += swap_halves(l, swap_addr);
   if (wave_active && col_valid) {
     const float inv = 1.0f / l;                  // l > 0: every row sees at least its own key
     bf16_t *out = (bf16_t *)a.out;
