@@ -5,10 +5,14 @@
 // positions 32 (w / 4) .. + 31 of the item, which are its MFMA columns.  Two waves per SIMD let
 // one wave's softmax run under the other's MFMAs, and the LDS only reaches its full read rate
 // with eight waves per CU.
-// Keys are streamed page by page (64 keys) through LDS and shared by the four waves: first the
+// Where that gives fewer workgroups than the chip has compute units, the waves split the keys as
+// well: with 2 (4) key groups a workgroup has one half of the item's rows and 4 (2) heads, every
+// group takes every second (fourth) 32-key block, and the groups' states of the same columns are
+// merged in LDS at the end (300 positions after 4096 keys of the 8B shape: 106 -> 45 us).
+// Keys are streamed page by page (64 keys) through LDS and shared by the waves: first the
 // shared-prefix pages that are visible to the block, then (scoring) the sequence's own suffix
 // pages.  Pages are stored in MFMA fragment order, so a page is copied to LDS as it is (by
-// loads that write LDS directly, two pages ahead, three buffers) and an operand is one
+// loads that write LDS directly, one or two steps ahead) and an operand is one
 // conflict-free 16-byte read per lane.  Each item sees all keys of its rows, so
 // it normalises and writes bf16 itself.  Operand mapping and the softmax scheme are those of
 // the decode kernel (transposed scores, lazy base-2 reference maximum); the addition is the
@@ -40,7 +44,18 @@ template <int HD> struct PTile {
   static constexpr int K_ELEMS = PPG * HD, V_ELEMS = PPG * HD, PAGE_ELEMS = K_ELEMS + V_ELEMS;
   static constexpr int NF = HD / 16;          // 1 KB fragments per 32-key block (K and V alike)
   static constexpr int CPT = PPG * HD / 8 / 512;            // 16-byte loads per thread and K (or V) page
-  static constexpr int LDS_BYTES = 3 * PAGE_ELEMS * 2;      // three page buffers
+};
+
+// KS = key groups of a workgroup (see the head of the file): pages staged per step, steps held in
+// LDS, query heads and 32-row halves of an item per workgroup.
+template <int HD, int KS> struct PSplit {
+  static constexpr int PP = KS == 4 ? 2 : 1;
+  static constexpr int STEPS = KS == 4 && HD == 128 ? 2 : 3;
+  static constexpr int HEADS = KS == 4 ? 2 : 4, HALVES = KS == 1 ? 2 : 1;
+  static constexpr int LPS = 2 * PTile<HD>::CPT * PP;       // loads into LDS per wave and step
+  static constexpr int LDS_BYTES = STEPS * PP * PTile<HD>::PAGE_ELEMS * 2;
+  // the states that the key groups 1 .. KS - 1 hand over at the end use the page buffers
+  static_assert((KS - 1) * (8 / KS) * 64 * (HD / 2 + 2) * 4 <= LDS_BYTES, "states fit the page buffers");
 };
 
 constexpr int kPrefillMaxPids = 1024;
@@ -55,29 +70,35 @@ __device__ inline void wait_barrier_p() {
   asm volatile("" ::: "memory");
 }
 
-template <int HD>
+template <int HD, int KS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void prefill_attention_kernel(PrefillAttnArgs a) {
   using TL = PTile<HD>;
+  using SP = PSplit<HD, KS>;
   extern __shared__ __attribute__((aligned(16))) unsigned char plds_raw[];
   bf16_t *lds = (bf16_t *)plds_raw;
   typedef __attribute__((address_space(3))) int lds_int;
-  lds_int *pids = (lds_int *)(plds_raw + TL::LDS_BYTES);
+  lds_int *pids = (lds_int *)(plds_raw + SP::LDS_BYTES);
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int hw = wave & 3, half = wave >> 2;    // head within the group, half of the item's rows
   const int swap_addr = (lane ^ 32) << 2;       // ds_bpermute address of the lane with the other 16 keys
-  const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, HG = (G + 3) / 4;
+  const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, HG = (G + SP::HEADS - 1) / SP::HEADS;
 
   int id = blockIdx.x;
-  const int hg = id % HG; id /= HG;
+  // KV heads first: with eight of them an XCD (workgroups are dealt to the eight in turn) meets one
+  // head's keys and values only
   const int kvh = id % Hkv; id /= Hkv;
+  const int hg = id % HG; id /= HG;
+  // head within the group, half of the item's rows, key group
+  const int hw = wave % SP::HEADS, half = KS == 1 ? wave >> 2 : (id & 1), kg = KS == 1 ? 0 : wave / SP::HEADS;
+  if (KS > 1) id >>= 1;
   const int4 item = a.items[id];               // row_start, n_rows (<= 64), pos_start, table row
   const int n_rows = item.y, tab = item.w;
   const int row_start = item.x + 32 * half;     // this wave's rows and their first position
   const int pos_start = item.z + 32 * half;
   const int my_rows = min(32, n_rows - 32 * half);
-  const int g = 4 * hg + hw;
+  if (KS > 1 && my_rows <= 0) return;           // the whole workgroup: the item has no second half
+  const int g = SP::HEADS * hg + hw;
   const bool wave_active = g < G && my_rows > 0;   // uniform per wave
   const int head = kvh * G + (g < G ? g : 0);
   const bool col_valid = col < my_rows;
@@ -85,7 +106,7 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   const int my_last = pos_start + my_rows - 1;     // last position of this wave's rows
 
   // visible keys: prefix [0, nA), then own suffix [0, nB) at absolute positions prefix_len + j
-  const int last_pos = item.z + n_rows - 1;        // of the whole item: pages every wave helps to stage
+  const int last_pos = KS == 1 ? item.z + n_rows - 1 : my_last;   // of the workgroup: pages every wave helps to stage
   const int nA = min(a.prefix_len, last_pos + 1);
   const int nB = (tab >= 0 && last_pos >= a.prefix_len) ? last_pos - a.prefix_len + 1 : 0;
   const int nPA = (nA + PPG - 1) / PPG, nPB = (nB + PPG - 1) / PPG, n_pages = nPA + nPB;
@@ -116,8 +137,8 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   const bf16_t *kA = (const bf16_t *)a.k_prefix, *vA = (const bf16_t *)a.v_prefix;
   const bf16_t *kB = (const bf16_t *)a.k_suffix, *vB = (const bf16_t *)a.v_suffix;
   // Pages go from global memory straight into LDS (lane i of a wave-wide 16-byte load lands at
-  // the wave's base + 16 i: the page is copied as it is), two pages ahead of the one in use, into
-  // three buffers.  The same number of loads is issued whether or not the page exists (a page past
+  // the wave's base + 16 i: the page is copied as it is), SP::STEPS - 1 steps of SP::PP pages ahead
+  // of the one in use.  The same number of loads is issued whether or not the page exists (a page past
   // the end has a range of no bytes: nothing is fetched), so the wait before the barrier can
   // count: all but the newest page's loads have landed.  They are buffer loads because the compiler
   // counts those; after a global (flat) load into LDS it waits for everything in flight before the
@@ -134,7 +155,7 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
     const int bytes = pi < n_pages ? PPG * HD * (int)sizeof(bf16_t) : 0;
     const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)((in_a ? kA : kB) + at), 0, bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)((in_a ? vA : vB) + at), 0, bytes, 0x00020000);
-    bf16_t *kt = lds + buf * TL::PAGE_ELEMS + wave * 512, *vt = kt + TL::K_ELEMS;
+    bf16_t *kt = lds + buf * TL::PAGE_ELEMS + wave * 512, *vt = kt + TL::K_ELEMS;   // buf: of a page
 #pragma unroll
     for (int i = 0; i < TL::CPT; ++i) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void *)(kt + 4096 * i), 16, tid * 16, 8192 * i, 0, 0);
@@ -209,32 +230,84 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
 #pragma unroll
       for (int sl = 0; sl < 2; ++sl) o[dt] = mfma32p(vf[dt * 2 + sl], pb[sl], o[dt]);
   };
-  auto consume = [&](int pi, int buf) __attribute__((always_inline)) {
-    if (!wave_active) return;
+  auto consume = [&](int pi, int buf, int blk) __attribute__((always_inline)) {
     const bool in_a = pi < nPA;
     const int abs_page = in_a ? pi * PPG : a.prefix_len + (pi - nPA) * PPG;
     const int keys_here = in_a ? min(PPG, nA - pi * PPG) : min(PPG, nB - (pi - nPA) * PPG);
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      const int nv = min(32, keys_here - 32 * blk);
-      if (nv > 0 && abs_page + 32 * blk <= my_last) process(buf, blk, nv, abs_page + 32 * blk);   // else all masked
-    }
+    const int nv = min(32, keys_here - 32 * blk);
+    if (nv > 0 && abs_page + 32 * blk <= my_last) process(buf, blk, nv, abs_page + 32 * blk);   // else all masked
   };
 
-  issue(0, page_of(0), 0);
-  issue(1, page_of(1), 1);
-  int buf = 0, next_page = page_of(2);
-  for (int pi = 0; pi < n_pages; ++pi) {
-    // page pi has landed once at most the loads of page pi + 1 are outstanding; past the barrier
-    // that holds for every wave, and page pi - 1 is no longer read
-    wait_barrier_p<2 * TL::CPT>();
-    issue(pi + 2, next_page, buf >= 1 ? buf - 1 : 2);       // into page pi - 1's buffer, (buf + 2) % 3
-    next_page = page_of(pi + 3);
-    consume(pi, buf);
-    buf = buf == 2 ? 0 : buf + 1;
+  int next_page[SP::PP];
+  auto issue_step = [&](int step, int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < SP::PP; ++i) {
+      issue(step * SP::PP + i, next_page[i], slot * SP::PP + i);
+      next_page[i] = page_of((step + 1) * SP::PP + i);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < SP::PP; ++i) next_page[i] = page_of(i);
+#pragma unroll
+  for (int st = 0; st + 1 < SP::STEPS; ++st) issue_step(st, st);
+  const int n_steps = (n_pages + SP::PP - 1) / SP::PP;
+  int slot = 0;
+  for (int st = 0; st < n_steps; ++st) {
+    // the pages of this step have landed once at most the loads of the later ones that were issued
+    // are outstanding; past the barrier that holds for every wave, and the last step's pages are no
+    // longer read
+    wait_barrier_p<(SP::STEPS - 2) * SP::LPS>();
+    issue_step(st + SP::STEPS - 1, slot >= 1 ? slot - 1 : SP::STEPS - 1);
+    if (wave_active) {
+      if (KS == 1) {
+        consume(st, slot, 0);
+        consume(st, slot, 1);
+      } else {
+        const int pi = st * SP::PP + (kg >> 1) % SP::PP;
+        if (pi < n_pages) consume(pi, slot * SP::PP + (kg >> 1) % SP::PP, kg & 1);
+      }
+    }
+    slot = slot == SP::STEPS - 1 ? 0 : slot + 1;
   }
-  wait_barrier_p<0>();                         // no load into LDS outlives the workgroup
+  wait_barrier_p<0>();                         // no load into LDS outlives the loop
 
+  if (KS > 1) {
+    // the key groups' states of the same columns meet in LDS: group 0 merges the others' into its own
+    constexpr int WPG = 8 / KS, REGS = HD / 2;  // waves per key group; accumulator registers of a lane
+    float *so = (float *)plds_raw;              // [KS - 1][WPG][REGS + 2][64]
+    if (kg > 0) {
+      float *dst = so + ((kg - 1) * WPG + hw) * (REGS + 2) * 64 + lane;
+#pragma unroll
+      for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dst[(dt * 16 + r) * 64] = o[dt][r];
+      dst[REGS * 64] = m;
+      dst[(REGS + 1) * 64] = l;
+    }
+    __syncthreads();
+    if (kg > 0) return;
+    const float *src = so + hw * (REGS + 2) * 64 + lane;
+    float M = m;
+#pragma unroll
+    for (int k = 0; k < KS - 1; ++k) M = fmaxf(M, src[(k * WPG * (REGS + 2) + REGS) * 64]);
+    // a group that saw no key of the column has m = -inf and no weight
+    const float f0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+    l *= f0;
+#pragma unroll
+    for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[dt][r] *= f0;
+#pragma unroll 1
+    for (int k = 0; k < KS - 1; ++k) {
+      const float *ks = src + k * WPG * (REGS + 2) * 64;
+      const float mk = ks[REGS * 64], fk = mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk - M);
+      l += fk * ks[(REGS + 1) * 64];
+#pragma unroll
+      for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] += fk * ks[(dt * 16 + r) * 64];
+    }
+  }
   l += swap_halves(l, swap_addr);
   if (wave_active && col_valid) {
     const float inv = 1.0f / l;                  // l > 0: every row sees at least its own key
@@ -258,23 +331,42 @@ bool prefill_attention_mfma_supported(int page_tokens, int head_dim, int Hq, int
   return page_tokens == PPG && (head_dim == 64 || head_dim == 128) && Hq % Hkv == 0;
 }
 
-template <int HD>
+template <int HD, int KS>
+static long prefill_grid(const PrefillAttnArgs &a) {
+  using SP = PSplit<HD, KS>;
+  const int G = a.n_q_heads / a.n_kv_heads;
+  return (long)a.n_items * (2 / SP::HALVES) * a.n_kv_heads * ((G + SP::HEADS - 1) / SP::HEADS);
+}
+
+template <int HD, int KS>
 static int launch_prefill_t(hipStream_t st, const PrefillAttnArgs &a) {
-  using TL = PTile<HD>;
-  const int G = a.n_q_heads / a.n_kv_heads, HG = (G + 3) / 4;
-  const size_t lds = TL::LDS_BYTES + kPrefillMaxPids * sizeof(int);
-  MC_TRY(raise_dynamic_lds_limit((const void *)prefill_attention_kernel<HD>, 160 * 1024 - 1024));
-  const unsigned grid = (unsigned)a.n_items * a.n_kv_heads * HG;
-  prefill_attention_kernel<HD><<<grid, 512, lds, st>>>(a);
+  using SP = PSplit<HD, KS>;
+  const int lds = SP::LDS_BYTES + kPrefillMaxPids * (int)sizeof(int);
+  MC_TRY(raise_dynamic_lds_limit((const void *)prefill_attention_kernel<HD, KS>, lds));
+  prefill_attention_kernel<HD, KS><<<(unsigned)prefill_grid<HD, KS>(a), 512, lds, st>>>(a);
   MC_HIP(hipGetLastError());
   return MC_OK;
+}
+
+template <int HD>
+static int launch_prefill_hd(hipStream_t st, const PrefillAttnArgs &a) {
+  // A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a
+  // compute unit holds one) leaves units idle, more of them with fewer columns each are faster; a
+  // second round costs what the split gains.  8B heads, one sequence after 4096 keys, us with 1 / 2 /
+  // 4 key groups: 65 rows 100 / 60 / 43, 300 rows 106 / 64 / 45, 512 rows (256 workgroups with four
+  // groups) 112 / 68 / 53, 800 rows 119 / 76 / 92, 1024 rows (256 with two) 125 / 86 / 100; four
+  // sequences of 400 rows 123 / 133 / 171.
+  constexpr long kComputeUnits = 256;
+  if (prefill_grid<HD, 4>(a) <= kComputeUnits) return launch_prefill_t<HD, 4>(st, a);
+  if (prefill_grid<HD, 2>(a) <= kComputeUnits) return launch_prefill_t<HD, 2>(st, a);
+  return launch_prefill_t<HD, 1>(st, a);
 }
 
 int launch_attention_prefill_mfma(hipStream_t st, const PrefillAttnArgs &a) {
   if (a.n_items <= 0) return MC_OK;
   if (!prefill_attention_mfma_supported(a.page_tokens, a.head_dim, a.n_q_heads, a.n_kv_heads))
     MC_FAIL(MC_ERR_UNSUPPORTED, "prefill attention: shape not covered");
-  return a.head_dim == 128 ? launch_prefill_t<128>(st, a) : launch_prefill_t<64>(st, a);
+  return a.head_dim == 128 ? launch_prefill_hd<128>(st, a) : launch_prefill_hd<64>(st, a);
 }
 
 }  // namespace mc

@@ -735,6 +735,21 @@ def test_attention_prefill_item_sizes(item_rows):
     assert worst < ATT_REL["bf16"], worst
 
 
+@pytest.mark.parametrize("Hq,Hkv,hd,P,seqs,stride", [
+    # four key groups: two pages a step, an odd number of pages, a prefix that ends inside its last
+    # page's first block, groups without a visible key, three query heads for two per workgroup
+    (8, 2, 128, 97, [(97, 40), (97, 1)], 1), (6, 2, 128, 300, [(300, 50)], 1), (8, 2, 64, 20, [(0, 20)], 1),
+    # two key groups (too many items for four): a whole prefix, suffixes of one page each
+    (32, 8, 64, 530, [(0, 530)], 61), (32, 8, 128, 70, [(70, 64)] * 10, 97),
+    # the last item count of each group count, and the first of the next
+    (32, 8, 128, 512, [(0, 512)], 401), (32, 8, 64, 513, [(0, 513)], 401), (32, 8, 128, 1024, [(0, 1024)], 1601),
+    (32, 8, 64, 1025, [(0, 1025)], 1601),
+])
+def test_attention_prefill_key_groups(Hq, Hkv, hd, P, seqs, stride):
+    worst, _ = prefill_case(Hq, Hkv, hd, P, seqs, stride)
+    assert worst < ATT_REL["bf16"], worst
+
+
 def test_attention_prefill_tiled_output_matches():
     a, _ = prefill_case(8, 2, 128, 100, [(100, 40), (100, 9)], out_tiled=True)
     assert a < ATT_REL["bf16"], a
