@@ -2,9 +2,8 @@
 //   out[m][n] = sum_k a[m][k] w[n][k]                 (fp32, row-major), or
 //   out_t[m][n] = silu(a . wg[n]) * (a . wu[n])        (bf16, tiled; the SwiGLU form).
 //
-// A workgroup of 4 waves owns 256 (few tiles: 128) rows of a and 128 rows of w (64 of wg and of wu in
-// the SwiGLU form); a wave keeps 8 (4) accumulator tiles of 32 x 32 (its own 64 (32) rows of a x all
-// 128 rows of w).
+// A workgroup of 4 waves owns 256 rows of a and 128 rows of w (64 of wg and of wu in the SwiGLU
+// form); a wave keeps 8 accumulator tiles of 32 x 32 (its own 64 rows of a x all 128 rows of w).
 // Two workgroups share a CU (two waves per SIMD, 215 registers each): they run out of step, so
 // the barrier, prologue and epilogue of one are covered by the matrix work of the other.
 // The two operands reach the matrix cores by different roads, which splits the traffic between
@@ -37,7 +36,6 @@
 #include "kernels_mfma.h"
 
 #include <algorithm>
-#include <type_traits>
 
 namespace mc {
 
@@ -89,19 +87,17 @@ __device__ inline void wait_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// TM: 32-row tiles of a per wave, 2 or 1 (256 or 128 rows of a per workgroup).  gridDim.y > 1: the
-// workgroups of split y take units [y, y + 1) * units_per_split of K and store their sums to
-// out + y * M * N.
-template <int MODE, int TM>
+template <int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void gemm256_kernel(int M, int N, int K, int units_per_split, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
+void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
                     const bf16_t *__restrict__ w, const bf16_t *__restrict__ w2,
                     float *__restrict__ out, bf16_t *__restrict__ out_t, RopeOut ro) {
   constexpr bool SWIGLU = MODE == GEMM_SWIGLU;
   constexpr int NW = SWIGLU ? 2 : 1;       // weight matrices
+  constexpr int TM = 2;                    // 32-row tiles of a per wave
   constexpr int TN = SWIGLU ? 2 : 4;       // 32-row tiles of each weight matrix per wave
   constexpr int WT = NW * TN;              // weight tiles of one wave (4)
-  constexpr int AB = 4 * TM;               // 32-row tiles of a per workgroup
+  constexpr int AB = 8;                    // 32-row tiles of a per workgroup: 256 rows
   constexpr int WB = TN;                   // blocks of each weight matrix per unit (workgroup)
   constexpr int NBW = NW * WB;             // 4 weight blocks of 256 chunks per unit
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_lds[];
@@ -111,22 +107,21 @@ void gemm256_kernel(int M, int N, int K, int units_per_split, int tiles_m, int t
   const int wm = wave;
   int tm, tn;
   if (!gemm_tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-  const int KU = K >> 6, u_first = blockIdx.y * units_per_split, U = min(units_per_split, KU - u_first);
-  if (MODE == GEMM_STORE) out += (size_t)blockIdx.y * M * N;
+  const int U = K >> 6;
   const int mt0 = tm * AB, nt0 = tn * WB;  // first 32-row tile of a / of each weight matrix
   const int m_tiles = (M + 31) >> 5;
 
   // weight staging: thread t brings chunk t of every block of the unit, w's blocks first, then w2's
   const __amdgpu_buffer_rsrc_t wsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void *)(w + (size_t)nt0 * KU * 2048), 0, WB * KU * 4096, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc((void *)(w + (size_t)nt0 * U * 2048), 0, WB * U * 4096, 0x00020000);
   const __amdgpu_buffer_rsrc_t w2src =
-      SWIGLU ? __builtin_amdgcn_make_buffer_rsrc((void *)(w2 + (size_t)nt0 * KU * 2048), 0, WB * KU * 4096, 0x00020000) : wsrc;
+      SWIGLU ? __builtin_amdgcn_make_buffer_rsrc((void *)(w2 + (size_t)nt0 * U * 2048), 0, WB * U * 4096, 0x00020000) : wsrc;
   const uint32_t s_off = tid * 16u;
   // the rows of a come straight from memory in operand order: a chunk of a tile is 1 KB, 16 bytes per lane
   const char *asrc[TM];
 #pragma unroll
   for (int y = 0; y < TM; ++y)
-    asrc[y] = (const char *)(a + ((size_t)min(mt0 + TM * wm + y, m_tiles - 1) * KU + u_first) * 2048);
+    asrc[y] = (const char *)(a + (size_t)min(mt0 + TM * wm + y, m_tiles - 1) * U * 2048);
   const uint32_t a_off = lane * 16u;
 
   f32x16 acc[WT][TM];
@@ -140,12 +135,12 @@ void gemm256_kernel(int M, int N, int K, int units_per_split, int tiles_m, int t
   // Loads past the last unit re-read the last unit (in bounds, never used), so that every
   // iteration issues the same loads and the load counters stay exact.
   auto load_w = [&](int u, int stage) __attribute__((always_inline)) {
-    const uint32_t at = (uint32_t)(u_first + min(u, U - 1)) * 4096u;
+    const uint32_t at = (uint32_t)min(u, U - 1) * 4096u;
     v4u *dst = lds + stage * NBW * 256 + wave * 64;
 #pragma unroll
     for (int i = 0; i < NBW; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(i < WB ? wsrc : w2src, (__attribute__((address_space(3))) void *)(dst + i * 256),
-                                               16, s_off, at + (uint32_t)((i < WB ? i : i - WB) * KU) * 4096u, 0, 0);
+                                               16, s_off, at + (uint32_t)((i < WB ? i : i - WB) * U) * 4096u, 0, 0);
   };
   v4u fa[2][4][TM];
   auto load_a = [&](int slot, int u, int c) __attribute__((always_inline)) {
@@ -279,152 +274,6 @@ void gemm256_kernel(int M, int N, int K, int units_per_split, int tiles_m, int t
   }
 }
 
-// =====================================================================================
-// The same products for a few hundred rows.  One 256 x 128 tile per workgroup leaves most of the
-// chip idle there (300 x 4096 x 14336: 64 workgroups for 256 compute units, each a serial chain of
-// 224 units), and a split of K over workgroups needs a place for partial sums.  Here the tile is 64
-// rows of a x 32 WT rows of w and K is split over the eight WAVES of a workgroup: wave s takes units
-// s, s + 8, ... with the whole tile in its accumulators, streams both operands from memory straight
-// into MFMA operand registers (the tiled layout is the operand order; 1 KB per load, a chunk's
-// registers are refilled for the wave's next unit right after the MFMAs that read them) and meets the
-// other seven in LDS at the end.  No barrier and no LDS in the loop; complete sums in a fixed order,
-// so every epilogue of the large kernel works on them and results do not depend on scheduling.
-// What bounds it: a workgroup pulls its 64 + 32 WT operand rows through one compute unit's L1 at
-// 60-70 GB/s (100 when few workgroups run); neither two units in flight per wave nor other K orders
-// nor leaving the MFMAs out changed that.  300 x 4096 x 14336: 135 -> 82 us (181 with the weights
-// through registers), 128 x 4096 x 14336: 128 -> 46 us, 300 x 6144 x 4096: 44 -> 26 us.
-// =====================================================================================
-constexpr int kSlices = 8;                 // waves per workgroup, one K slice each
-
-template <int MODE, int WT>
-__global__ __launch_bounds__(64 * kSlices) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void gemm_kslice_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
-                        const bf16_t *__restrict__ w, const bf16_t *__restrict__ w2,
-                        float *__restrict__ out, bf16_t *__restrict__ out_t, RopeOut ro) {
-  constexpr bool SWIGLU = MODE == GEMM_SWIGLU;
-  constexpr int NW = SWIGLU ? 2 : 1;       // weight matrices
-  constexpr int TN = WT / NW;              // 32-row tiles of each weight matrix
-  constexpr int TM = 2;                    // 32-row tiles of a
-  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_lds[];
-  float4 *red = (float4 *)gemm_lds;        // [kSlices][WT][4 quads][64 slots]
-  const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // consecutive ids of one XCD walk the row tiles of one weight tile first: its L2 hands the
-  // weights to all of them
-  const int total = tiles_m * tiles_n, per_xcd = (total + 7) >> 3;
-  const int L = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per_xcd || L >= total) return;
-  const int tm = L % tiles_m, tn = L / tiles_m;
-  const int U = K >> 6, mt0 = tm * TM, nt0 = tn * TN, m_tiles = (M + 31) >> 5;
-
-  const char *src[TM + WT];
-#pragma unroll
-  for (int y = 0; y < TM; ++y) src[y] = (const char *)(a + (size_t)min(mt0 + y, m_tiles - 1) * U * 2048);
-#pragma unroll
-  for (int x = 0; x < WT; ++x)
-    src[TM + x] = (const char *)(x < TN ? w + (size_t)(nt0 + x) * U * 2048 : w2 + (size_t)(nt0 + x - TN) * U * 2048);
-  const uint32_t lane_off = lane * 16u;
-
-  f32x16 acc[WT][TM];
-#pragma unroll
-  for (int x = 0; x < WT; ++x)
-#pragma unroll
-    for (int y = 0; y < TM; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-
-  v4u f[4][TM + WT];
-  auto load = [&](int u, int c) __attribute__((always_inline)) {
-    const uint32_t at = lane_off + (uint32_t)u * 4096u + (uint32_t)c * 1024u;
-#pragma unroll
-    for (int i = 0; i < TM + WT; ++i) f[c][i] = *(const v4u *)(src[i] + at);
-  };
-  auto multiply = [&](int c) __attribute__((always_inline)) {
-#pragma unroll
-    for (int y = 0; y < TM; ++y)
-#pragma unroll
-      for (int x = 0; x < WT; ++x) acc[x][y] = mfma32g(f[c][TM + x], f[c][y], acc[x][y]);
-  };
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    load(min(wave, U - 1), c);
-    __builtin_amdgcn_sched_barrier(0);         // in the order of the loop, whose waits then leave the later loads in flight
-  }
-  int u = wave;
-  for (; u + kSlices < U; u += kSlices)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      multiply(c);
-      load(u + kSlices, c);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  if (u < U)                                   // (a short K leaves the last waves without a unit)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) multiply(c);
-
-  // A lane holds column j of a row tile and, per register quad, four consecutive n.  Quad (x, r4)
-  // of lane (j, h) sits in slot 2 j + h, rotated by twice the quad's number: the 32 quads of one
-  // row then fall into different banks, and so do the quads of a wave that walks rows.
-#pragma unroll
-  for (int y = 0; y < TM; ++y) {
-    const int m0 = 32 * (mt0 + y);
-    if (m0 >= M) break;                                  // uniform
-    if (y) __syncthreads();                              // the first half has been read
-#pragma unroll
-    for (int x = 0; x < WT; ++x)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const f32x16 &g = acc[x][y];
-        red[((wave * WT + x) * 4 + r4) * 64 + ((2 * j + h + 2 * (4 * x + r4)) & 63)] =
-            make_float4(g[4 * r4], g[4 * r4 + 1], g[4 * r4 + 2], g[4 * r4 + 3]);
-      }
-    __syncthreads();
-    auto sum = [&](int x, int r4, int row, int hh) __attribute__((always_inline)) {
-      const float4 *p = red + (x * 4 + r4) * 64 + ((2 * row + hh + 2 * (4 * x + r4)) & 63);
-      float4 t = p[0];
-#pragma unroll
-      for (int s = 1; s < kSlices; ++s) {
-        const float4 v = p[s * WT * 256];
-        t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
-      }
-      return t;
-    };
-    if (SWIGLU) {
-      // tiled output: 32 rows x 16 bytes of one chunk are neighbours, so lanes walk the rows
-      for (int e = tid; e < TN * 256; e += 64 * kSlices) {
-        const int x = e >> 8, r4 = (e >> 6) & 3, hh = e & 1, row = (e >> 1) & 31;
-        const int m = m0 + row, n = 32 * (nt0 + x) + 8 * r4 + 4 * hh;
-        const float4 g = sum(x, r4, row, hh), v = sum(TN + x, r4, row, hh);
-        if (m < M) {
-          uint2 pk;
-          pk.x = pack2g_bf16(silu_g(g.x) * v.x, silu_g(g.y) * v.y);
-          pk.y = pack2g_bf16(silu_g(g.z) * v.z, silu_g(g.w) * v.w);
-          *(uint2 *)(out_t + tiled_offset(m, n, N)) = pk;
-        }
-      }
-    } else {
-      // row-major output: consecutive lanes take consecutive quads of one row
-      for (int e = tid; e < WT * 256; e += 64 * kSlices) {
-        const int row = e / (8 * WT), q = e % (8 * WT);
-        const int m = m0 + row, n = 32 * nt0 + 4 * q;
-        const float4 t = sum(q >> 3, (q >> 1) & 3, row, q & 1);
-        if (m >= M) continue;
-        if (MODE == GEMM_ROPE) {
-          rope_store_quad(ro, m, n, t, rope_load_quad(ro, m, n));
-        } else {
-          float4 *p = (float4 *)(out + (size_t)m * N + n);
-          if (MODE == GEMM_ACCUM) {
-            const float4 old = *p;
-            *p = make_float4(old.x + t.x, old.y + t.y, old.z + t.z, old.w + t.w);
-          } else {
-            *p = t;
-          }
-        }
-      }
-    }
-  }
-}
-
 // Matrix-core rate with nothing else going on: every wave keeps 8 accumulator tiles and issues
 // MFMAs on operands it loaded once.  What this reaches with realistic operand values is the
 // practical ceiling of any GEMM on the part (the clock follows the power drawn, which depends on
@@ -467,53 +316,6 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
   return M >= 1 && K >= 128 && K % 128 == 0 && N % 128 == 0;      // whole pairs of 64-deep units
 }
 
-constexpr int kComputeUnits = 256;
-
-// Weight tiles per workgroup of the K-slice kernel, or 0 where the large tiles are better: the fewest
-// with which one round of workgroups (a compute unit holds one) covers the product.  More rounds
-// repeat its start and its reduction, and the large tiles move fewer operand bytes.
-// Large tiles / 4 / 2 / 1 weight tiles, us, at the largest row counts that take each and past them:
-// 4096 x 14336 (N x K): 128 rows 128 / 91 / 62 / 46, 256 rows 133 / 80 / 55 / 73, 512 rows 125 / 85 /
-// 117 / 159, 768 rows 130 / 160 / 178 / 278; SwiGLU 8192 x 2048: 128 rows 21 / 19 / 24.
-static int kslice_tiles(int M, int N, bool swiglu) {
-  const long row_tiles = (M + 63) / 64;
-  for (int wt = swiglu ? 2 : 1; wt <= 4; wt *= 2)
-    if (row_tiles * (N / 32) * (swiglu ? 2 : 1) / wt <= kComputeUnits) return wt;
-  return 0;
-}
-
-// 128 instead of 256 rows of a per workgroup: where the chip holds all of those tiles at once, one to
-// a compute unit (1024 x 4096 x 14336: 170 -> 132 us; 1024 x 6144 x 4096, 384 tiles: 54 -> 68 us), or
-// the row count would leave half of a large tile empty (128 rows of SwiGLU 14336 x 4096: 62 -> 49 us).
-static bool gemm_half_rows(int M, int N, bool swiglu) {
-  return M <= 128 || (long)((M + 127) / 128) * (N / (swiglu ? 64 : 128)) <= kComputeUnits;
-}
-
-template <int MODE, int TM>
-static int launch_gemm256_t(hipStream_t st, int M, int N, int K, int n_splits, const bf16_t *a, const bf16_t *w,
-                            const bf16_t *w2, float *out, bf16_t *out_t, const RopeOut &ro) {
-  const int tiles_m = (M + 128 * TM - 1) / (128 * TM), tiles_n = N / (MODE == GEMM_SWIGLU ? 64 : 128);
-  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  const int units = K / 64, per_split = (units / 2 + n_splits - 1) / n_splits * 2;      // whole pairs of units
-  // four stages of 4 weight blocks; the parking areas of the rotation epilogue need a little more
-  const int lds = std::max<int>(4 * 4 * 4096, MODE == GEMM_ROPE ? 4 * 32 * kParkStride * (int)sizeof(float) : 0);
-  MC_TRY(raise_dynamic_lds_limit((const void *)gemm256_kernel<MODE, TM>, lds));
-  gemm256_kernel<MODE, TM><<<dim3(8 * per_xcd, n_splits), 256, lds, st>>>(M, N, K, per_split, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
-  MC_HIP(hipGetLastError());
-  return MC_OK;
-}
-
-template <int MODE, int WT>
-static int launch_kslice_t(hipStream_t st, int M, int N, int K, const bf16_t *a, const bf16_t *w, const bf16_t *w2,
-                           float *out, bf16_t *out_t, const RopeOut &ro) {
-  const int tiles_m = (M + 63) / 64, tiles_n = N / 32 * (MODE == GEMM_SWIGLU ? 2 : 1) / WT;
-  const int per_xcd = (tiles_m * tiles_n + 7) / 8, lds = kSlices * WT * 4096;
-  MC_TRY(raise_dynamic_lds_limit((const void *)gemm_kslice_kernel<MODE, WT>, lds));
-  gemm_kslice_kernel<MODE, WT><<<8 * per_xcd, 64 * kSlices, lds, st>>>(M, N, K, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
-  MC_HIP(hipGetLastError());
-  return MC_OK;
-}
-
 int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const void *w,
                    const void *w2, float *out, void *out_t, const RopeOut *rope, int accumulate) {
   const bool swiglu = w2 != nullptr;
@@ -522,23 +324,27 @@ int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const voi
     MC_FAIL(MC_ERR_INVALID, "GEMM: one output form at a time");
   if (rope && (rope->hd % 4 || N != (rope->Hq + 2 * rope->Hkv) * rope->hd))
     MC_FAIL(MC_ERR_INVALID, "fused QKV output: N = (Hq + 2 Hkv) hd, hd %% 4 == 0");
+  const int mode = swiglu ? GEMM_SWIGLU : rope ? GEMM_ROPE : accumulate ? GEMM_ACCUM : GEMM_STORE;
+  const int tiles_m = (M + 255) / 256, tiles_n = N / (swiglu ? 64 : 128);
+  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
+  // four stages of 4 weight blocks; the parking areas of the rotation epilogue need a little more
+  const size_t lds = std::max<size_t>(4 * 4 * 4096, mode == GEMM_ROPE ? 4 * 32 * kParkStride * sizeof(float) : 0);
+  const void *kernels[4] = {(const void *)gemm256_kernel<GEMM_STORE>, (const void *)gemm256_kernel<GEMM_SWIGLU>,
+                            (const void *)gemm256_kernel<GEMM_ROPE>, (const void *)gemm256_kernel<GEMM_ACCUM>};
+  // the largest request of this mode (the rotation epilogue's parking areas included)
+  MC_TRY(raise_dynamic_lds_limit(kernels[mode], (int)lds));
+  const RopeOut none{};
   const bf16_t *A = (const bf16_t *)a, *W = (const bf16_t *)w, *W2 = (const bf16_t *)w2;
   bf16_t *OT = (bf16_t *)out_t;
-  const int wt = kslice_tiles(M, N, swiglu);
-  auto run = [&](auto mode) -> int {
-    constexpr int MODE = decltype(mode)::value;
-    const RopeOut ro = rope ? *rope : RopeOut{};
-    if (wt == 4) return launch_kslice_t<MODE, 4>(st, M, N, K, A, W, W2, out, OT, ro);
-    if (wt == 2) return launch_kslice_t<MODE, 2>(st, M, N, K, A, W, W2, out, OT, ro);
-    if constexpr (MODE != GEMM_SWIGLU)
-      if (wt == 1) return launch_kslice_t<MODE, 1>(st, M, N, K, A, W, W2, out, OT, ro);
-    return gemm_half_rows(M, N, swiglu) ? launch_gemm256_t<MODE, 1>(st, M, N, K, 1, A, W, W2, out, OT, ro)
-                                        : launch_gemm256_t<MODE, 2>(st, M, N, K, 1, A, W, W2, out, OT, ro);
-  };
-  if (swiglu) return run(std::integral_constant<int, GEMM_SWIGLU>{});
-  if (rope) return run(std::integral_constant<int, GEMM_ROPE>{});
-  if (accumulate) return run(std::integral_constant<int, GEMM_ACCUM>{});
-  return run(std::integral_constant<int, GEMM_STORE>{});
+  const dim3 grid(8 * per_xcd);
+  switch (mode) {
+    case GEMM_SWIGLU: gemm256_kernel<GEMM_SWIGLU><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, none); break;
+    case GEMM_ROPE: gemm256_kernel<GEMM_ROPE><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, *rope); break;
+    case GEMM_ACCUM: gemm256_kernel<GEMM_ACCUM><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, none); break;
+    default: gemm256_kernel<GEMM_STORE><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, none); break;
+  }
+  MC_HIP(hipGetLastError());
+  return MC_OK;
 }
 
 }  // namespace mc
