@@ -3,14 +3,16 @@
 //   out_t[m][n] = silu(a . wg[n]) * (a . wu[n])        (bf16, tiled; the SwiGLU form).
 //
 // A workgroup of 4 waves owns 256 rows of a and 128 rows of w (64 of wg and of wu in the SwiGLU
-// form); a wave keeps 8 accumulator tiles of 32 x 32 (its own 64 rows of a x all 128 rows of w).
+// form); a wave keeps 8 accumulator tiles of 32 x 32 (its own 64 rows of a x all 128 rows of w).  Few
+// tiles take narrower ones: 128 rows of a and 128, 64 or 32 rows of w (see gemm_form); an output's
+// sum runs over K in the same order in all of them, so they give the same bits.
 // Two workgroups share a CU (two waves per SIMD, 215 registers each): they run out of step, so
 // the barrier, prologue and epilogue of one are covered by the matrix work of the other.
 // The two operands reach the matrix cores by different roads, which splits the traffic between
 // LDS and the vector memory path instead of loading one of them with everything:
 //   * w is shared by the four waves: one 64-deep unit (4 blocks of 4 KB, already in MFMA operand
 //     order, so they are copied to LDS as they are and read back conflict-free) per step, in one of
-//     four LDS stages.  Buffer loads that write LDS directly bring unit u + 3 while unit u is
+//     four LDS stages (with operands two units ahead; the narrow tiles run four ahead).  Buffer loads that write LDS directly bring unit u + 3 while unit u is
 //     multiplied; the one barrier per unit waits for those of unit u + 2 only (a counted wait), so
 //     the first fragments of unit u + 1 are read before the barrier that ends unit u and no wave
 //     starts a unit waiting for LDS.
@@ -36,6 +38,7 @@
 #include "kernels_mfma.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mc {
 
@@ -87,21 +90,22 @@ __device__ inline void wait_barrier() {
   asm volatile("" ::: "memory");
 }
 
-template <int MODE>
+// TM: 32-row tiles of a per wave; TN: 32-row tiles of each weight matrix per workgroup; D: units by which
+// the operands run ahead.
+template <int MODE, int TM, int TN, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
                     const bf16_t *__restrict__ w, const bf16_t *__restrict__ w2,
                     float *__restrict__ out, bf16_t *__restrict__ out_t, RopeOut ro) {
   constexpr bool SWIGLU = MODE == GEMM_SWIGLU;
   constexpr int NW = SWIGLU ? 2 : 1;       // weight matrices
-  constexpr int TM = 2;                    // 32-row tiles of a per wave
-  constexpr int TN = SWIGLU ? 2 : 4;       // 32-row tiles of each weight matrix per wave
-  constexpr int WT = NW * TN;              // weight tiles of one wave (4)
-  constexpr int AB = 8;                    // 32-row tiles of a per workgroup: 256 rows
+  constexpr int WT = NW * TN;              // weight tiles of one wave
+  constexpr int AB = 4 * TM;               // 32-row tiles of a per workgroup
   constexpr int WB = TN;                   // blocks of each weight matrix per unit (workgroup)
-  constexpr int NBW = NW * WB;             // 4 weight blocks of 256 chunks per unit
+  constexpr int NBW = NW * WB;             // weight blocks of 256 chunks per unit
+  constexpr int S = D + 2;                 // LDS stages of one unit each
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_lds[];
-  v4u *lds = (v4u *)gemm_lds;              // [4 stages][NBW][256]
+  v4u *lds = (v4u *)gemm_lds;              // [S][NBW][256]
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave;
@@ -142,7 +146,7 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
       __builtin_amdgcn_raw_ptr_buffer_load_lds(i < WB ? wsrc : w2src, (__attribute__((address_space(3))) void *)(dst + i * 256),
                                                16, s_off, at + (uint32_t)((i < WB ? i : i - WB) * U) * 4096u, 0, 0);
   };
-  v4u fa[2][4][TM];
+  v4u fa[D][4][TM];
   auto load_a = [&](int slot, int u, int c) __attribute__((always_inline)) {
     const uint32_t at = a_off + (uint32_t)min(u, U - 1) * 4096u + (uint32_t)c * 1024u;
 #pragma unroll
@@ -165,9 +169,9 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
 
   v4u fw[2][WT];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) load_w(d, d);
+  for (int d = 0; d <= D; ++d) load_w(d, d);
 #pragma unroll
-  for (int d = 0; d < 2; ++d)
+  for (int d = 0; d < D; ++d)
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       load_a(d, d, c);
@@ -175,35 +179,39 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
     }
   wait_barrier<0>();
   read_w(fw[0], 0, 0);
-  // Stage (u + 3) % 4 was last read during unit u - 1, which every wave left before the barrier that
-  // ended it.  At the barrier that ends unit u everything older than the fragments of a for unit
-  // u + 1 has landed: the weights of unit u + 2, issued at the top of unit u - 1, before them.
+  // Unit u sits in stage u % S.  The stage that takes unit u + D + 1 was last read during unit u - 1,
+  // which every wave left before the barrier that ended it.  At the barrier that ends unit u
+  // everything older than the fragments of a for unit u + 1 has landed: the weights of unit u + 2,
+  // issued just before them, among it.
+  int cur = 0;
   auto unit = [&](int u, int slot) __attribute__((always_inline)) {
-    const int cur = u & 3, nxt = (u + 1) & 3;
-    load_w(u + 3, (u + 3) & 3);
+    const int nxt = cur == S - 1 ? 0 : cur + 1;
+    load_w(u + D + 1, cur == 0 ? S - 1 : cur - 1);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       if (c < 3) read_w(fw[(c + 1) & 1], cur, c + 1);
       else read_w(fw[0], nxt, 0);
       multiply(fa[slot][c], fw[c & 1]);
-      load_a(slot, u + 2, c);
+      load_a(slot, u + D, c);
+      constexpr int kPairs = TM * WT < WT ? TM * WT : WT;
 #pragma unroll
-      for (int i = 0; i < WT; ++i) {
+      for (int i = 0; i < kPairs; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // one LDS read
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // one MFMA
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, TM * WT - WT, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, TM * WT - kPairs, 0);
       __builtin_amdgcn_sched_group_barrier(0x020, TM, 0);     // the loads of a
       __builtin_amdgcn_sched_barrier(0);
     }
-    wait_barrier<8 * TM + NBW>();            // a of units u + 1 and u + 2, w of unit u + 3 may be in flight
+    wait_barrier<4 * TM + (D - 1) * (NBW + 4 * TM)>();
+    cur = nxt;
   };
   int u = 0;
-  do {                                     // U is even and at least 2
-    unit(u, 0);
-    unit(u + 1, 1);
-    u += 2;
+  do {                                     // U is a multiple of D
+#pragma unroll
+    for (int d = 0; d < D; ++d) unit(u + d, d);
+    u += D;
   } while (u < U);
   wait_barrier<0>();                         // no load into LDS outlives the loop
 
@@ -313,7 +321,40 @@ int launch_mfma_probe(hipStream_t st, const void *operands, float *out, int n_wo
 
 bool gemm256_supported(int M, int N, int K, bool swiglu) {
   (void)swiglu;
-  return M >= 1 && K >= 128 && K % 128 == 0 && N % 128 == 0;      // whole pairs of 64-deep units
+  return M >= 1 && K >= 256 && K % 256 == 0 && N % 128 == 0;      // whole groups of four 64-deep units
+}
+
+// Row tiles per wave and weight tiles per workgroup: the narrowest workgroup with which one round (one
+// to each of the 256 compute units) covers the product, else the 256 x 128 tile, which moves the
+// fewest operand bytes per flop; up to 128 rows at least not its empty half.  A workgroup is a serial
+// chain over K whose pace is set by the loads (0.3 - 0.5 us per unit), hardly by its width, so with few
+// tiles the time goes with the number of workgroups.  us with 256 x 128 / 128 x 128 / 128 x 64 /
+// 128 x 32 tiles, N x K = 4096 x 14336: 128 rows 139 / 127 / 84 / 66, 256 rows 161 / 125 / 83 / 68, 300
+// rows 135 / 102 / 70 / 102, 512 rows 160 / 124 / 84 / 130, 1024 rows 161 / 128 / 168 / 240, 1500 rows
+// 167 / 207 / 225 / 328; 6144 x 4096: 300 rows 47 / 33 / 39 / 44; SwiGLU 14336 x 4096 (2 x 64, 2 x 32 wide): 128 rows
+// 77 / 49 / 62, 256 rows 61 / 77 / 105.
+struct GemmForm { int tm, tn; };
+static GemmForm gemm_form(int M, int N, bool swiglu) {
+  constexpr long kComputeUnits = 256;
+  const long row_tiles = (M + 127) / 128;
+  const int widest = swiglu ? 2 : 4;
+  for (int tn = 1; tn <= widest; tn *= 2)
+    if (row_tiles * (N / 32) / tn <= kComputeUnits) return GemmForm{1, tn};
+  return GemmForm{M <= 128 ? 1 : 2, widest};
+}
+
+template <int MODE, int TM, int TN, int D>
+static int launch_gemm256_t(hipStream_t st, int M, int N, int K, const bf16_t *a, const bf16_t *w,
+                            const bf16_t *w2, float *out, bf16_t *out_t, const RopeOut &ro) {
+  const int tiles_m = (M + 128 * TM - 1) / (128 * TM), tiles_n = N / (32 * TN);
+  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
+  // D + 2 stages of the unit's weight blocks; the parking areas of the rotation epilogue may need more
+  const int lds = std::max<int>((D + 2) * TN * (MODE == GEMM_SWIGLU ? 2 : 1) * 4096,
+                                MODE == GEMM_ROPE ? 4 * 32 * kParkStride * (int)sizeof(float) : 0);
+  MC_TRY(raise_dynamic_lds_limit((const void *)gemm256_kernel<MODE, TM, TN, D>, lds));
+  gemm256_kernel<MODE, TM, TN, D><<<8 * per_xcd, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
+  MC_HIP(hipGetLastError());
+  return MC_OK;
 }
 
 int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const void *w,
@@ -324,27 +365,27 @@ int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const voi
     MC_FAIL(MC_ERR_INVALID, "GEMM: one output form at a time");
   if (rope && (rope->hd % 4 || N != (rope->Hq + 2 * rope->Hkv) * rope->hd))
     MC_FAIL(MC_ERR_INVALID, "fused QKV output: N = (Hq + 2 Hkv) hd, hd %% 4 == 0");
-  const int mode = swiglu ? GEMM_SWIGLU : rope ? GEMM_ROPE : accumulate ? GEMM_ACCUM : GEMM_STORE;
-  const int tiles_m = (M + 255) / 256, tiles_n = N / (swiglu ? 64 : 128);
-  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  // four stages of 4 weight blocks; the parking areas of the rotation epilogue need a little more
-  const size_t lds = std::max<size_t>(4 * 4 * 4096, mode == GEMM_ROPE ? 4 * 32 * kParkStride * sizeof(float) : 0);
-  const void *kernels[4] = {(const void *)gemm256_kernel<GEMM_STORE>, (const void *)gemm256_kernel<GEMM_SWIGLU>,
-                            (const void *)gemm256_kernel<GEMM_ROPE>, (const void *)gemm256_kernel<GEMM_ACCUM>};
-  // the largest request of this mode (the rotation epilogue's parking areas included)
-  MC_TRY(raise_dynamic_lds_limit(kernels[mode], (int)lds));
-  const RopeOut none{};
   const bf16_t *A = (const bf16_t *)a, *W = (const bf16_t *)w, *W2 = (const bf16_t *)w2;
   bf16_t *OT = (bf16_t *)out_t;
-  const dim3 grid(8 * per_xcd);
-  switch (mode) {
-    case GEMM_SWIGLU: gemm256_kernel<GEMM_SWIGLU><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, none); break;
-    case GEMM_ROPE: gemm256_kernel<GEMM_ROPE><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, *rope); break;
-    case GEMM_ACCUM: gemm256_kernel<GEMM_ACCUM><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, none); break;
-    default: gemm256_kernel<GEMM_STORE><<<grid, 256, lds, st>>>(M, N, K, tiles_m, tiles_n, A, W, W2, out, OT, none); break;
-  }
-  MC_HIP(hipGetLastError());
-  return MC_OK;
+  const GemmForm f = gemm_form(M, N, swiglu);
+  auto run = [&](auto mode) -> int {
+    constexpr int MODE = decltype(mode)::value;
+    const RopeOut ro = rope ? *rope : RopeOut{};
+    if constexpr (MODE == GEMM_SWIGLU) {
+      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 2, 2>(st, M, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 2>(st, M, N, K, A, W, W2, out, OT, ro);
+      return launch_gemm256_t<MODE, 1, 1, 2>(st, M, N, K, A, W, W2, out, OT, ro);
+    } else {
+      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 4, 2>(st, M, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 4) return launch_gemm256_t<MODE, 1, 4, 2>(st, M, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4>(st, M, N, K, A, W, W2, out, OT, ro);
+      return launch_gemm256_t<MODE, 1, 1, 4>(st, M, N, K, A, W, W2, out, OT, ro);
+    }
+  };
+  if (swiglu) return run(std::integral_constant<int, GEMM_SWIGLU>{});
+  if (rope) return run(std::integral_constant<int, GEMM_ROPE>{});
+  if (accumulate) return run(std::integral_constant<int, GEMM_ACCUM>{});
+  return run(std::integral_constant<int, GEMM_STORE>{});
 }
 
 }  // namespace mc

@@ -26,6 +26,13 @@ __device__ inline float swap_halves(float x, int addr) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(addr, __builtin_bit_cast(int, x)));
 }
 
+// x of lane (l ^ 32) by the lane swap of the vector unit: no trip through LDS.
+__device__ inline float other_half(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // {lower half's x, upper half's x} in all lanes
+  return __builtin_bit_cast(float, (uint32_t)((threadIdx.x & 32) ? r[0] : r[1]));
+}
+
 // All operands of these linear kernels are in the tiled layout (see tiled_offset).
 // Few-row linear layer (M <= 64): out = a w^T streamed once over the weights.
 // w2 != nullptr selects the SwiGLU form (out_t = silu(a wg^T) * (a wu^T), bf16, tiled).
@@ -98,8 +105,8 @@ __device__ inline void rope_store_quad(const RopeOut &ro, int m, int n, float4 s
 }
 
 // Many-row GEMM (more than 64 rows): fp32 out, or the SwiGLU form with bf16 tiled out.  N % 128
-// == 0, K % 128 == 0.  256 x 128 output tile per workgroup (256 x 64 of each weight matrix in the
-// SwiGLU form), XCD-aware tile order.
+// == 0, K % 256 == 0.  256 x 128 output tile per workgroup (256 x 64 of each weight matrix in the
+// SwiGLU form; narrower where few tiles would leave compute units idle), XCD-aware tile order.
 bool gemm256_supported(int M, int N, int K, bool swiglu);
 // rope != nullptr: the fused QKV layer as in launch_linear_skinny (N = (Hq + 2 Hkv) hd, hd % 4 == 0).
 // accumulate: out[m][n] += the product (the residual stream updated in place) instead of a store.

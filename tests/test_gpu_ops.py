@@ -575,6 +575,27 @@ def test_linear_swiglu_tiled(M, N, K):
     np.testing.assert_allclose(out, want, rtol=0, atol=TOL["bf16"] * np.abs(want).max())
 
 
+# A few hundred rows: the 128-row GEMM tiles with one, two and four weight tiles per workgroup (one and
+# more groups of four units of K, a last workgroup with few rows, the last row count that takes each
+# form and the first past it).
+@pytest.mark.parametrize("M,N,K", [(65, 4096, 256), (128, 4096, 768), (129, 4096, 256), (256, 4096, 1280), (257, 4096, 768),
+                                   (300, 4096, 512), (512, 4096, 256), (513, 4096, 512), (1023, 2048, 768)])
+def test_linear_few_hundred_rows(M, N, K):
+    test_linear_tiled(M, N, K, 1)
+    test_linear_accumulate_tiled(M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K", [(65, 2048, 256), (128, 2048, 768), (130, 4096, 256), (200, 2048, 1280), (300, 8192, 256)])
+def test_linear_swiglu_few_hundred_rows(M, N, K):
+    test_linear_swiglu_tiled(M, N, K)
+
+
+@pytest.mark.parametrize("rows,Hq,Hkv,hd,K", [(65, 8, 2, 64, 256), (100, 32, 8, 64, 512), (200, 32, 8, 128, 256), (330, 32, 8, 128, 768),
+                                              (700, 12, 2, 128, 256)])
+def test_linear_qkv_rope_few_hundred_rows(rows, Hq, Hkv, hd, K):
+    test_linear_qkv_rope_fused(rows, Hq, Hkv, hd, K)
+
+
 def test_scoring_size_gemms_on_sampled_rows():
     """The many-row GEMMs at the sizes one scoring chunk of the 8B shape launches (8192 rows):
     gate/up + SwiGLU 8192 x 14336 x 4096, down with the residual update 8192 x 4096 x 14336, QKV
