@@ -81,7 +81,6 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   lds_int *pids = (lds_int *)(plds_raw + SP::LDS_BYTES);
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int swap_addr = (lane ^ 32) << 2;       // ds_bpermute address of the lane with the other 16 keys
   const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, HG = (G + SP::HEADS - 1) / SP::HEADS;
 
   int id = blockIdx.x;
@@ -131,7 +130,7 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-  float m = -INFINITY, l = 0.f;                 // l: this lane's half of its column's sum
+  float m = -INFINITY, l = 0.f;
 
   const size_t page_stride = (size_t)Hkv * PPG * HD, head_off = (size_t)kvh * PPG * HD;
   const bf16_t *kA = (const bf16_t *)a.k_prefix, *vA = (const bf16_t *)a.v_prefix;
@@ -203,7 +202,7 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
     }
     if (__any(!(rs <= kSoftmaxSumLimit))) {
       float mx = max16f(s);
-      mx = fmaxf(mx, swap_halves(mx, swap_addr));
+      mx = fmaxf(mx, other_half(mx));
       const float m_new = fmaxf(m, mx * scale2);    // stays -inf for a column that has seen no key
       const float corr = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
       l *= corr;
@@ -221,6 +220,7 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
         rs += p[r];
       }
     }
+    rs += other_half(rs);
     l += rs;
     v4u pb[2];
     pb[0] = v4u{pack2p_bf16(p[0], p[1]), pack2p_bf16(p[2], p[3]), pack2p_bf16(p[4], p[5]), pack2p_bf16(p[6], p[7])};
@@ -308,7 +308,6 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
         for (int r = 0; r < 16; ++r) o[dt][r] += fk * ks[(dt * 16 + r) * 64];
     }
   }
-  l += swap_halves(l, swap_addr);
   if (wave_active && col_valid) {
     const float inv = 1.0f / l;                  // l > 0: every row sees at least its own key
     bf16_t *out = (bf16_t *)a.out;
@@ -356,7 +355,12 @@ static int launch_prefill_hd(hipStream_t st, const PrefillAttnArgs &a) {
   // 4 key groups: 65 rows 100 / 60 / 43, 300 rows 106 / 64 / 45, 512 rows (256 workgroups with four
   // groups) 112 / 68 / 53, 800 rows 119 / 76 / 92, 1024 rows (256 with two) 125 / 86 / 100; four
   // sequences of 400 rows 123 / 133 / 171.
+  // Up to 2560 shared keys the split saves 10 - 30 us a layer, and there the order of additions of one
+  // group is kept: the ids that a session samples and the ranks that it gives follow the last bits of
+  // its prefill.
   constexpr long kComputeUnits = 256;
+  constexpr int kShortChain = 2560;
+  if (a.prefix_len <= kShortChain) return launch_prefill_t<HD, 1>(st, a);
   if (prefill_grid<HD, 4>(a) <= kComputeUnits) return launch_prefill_t<HD, 4>(st, a);
   if (prefill_grid<HD, 2>(a) <= kComputeUnits) return launch_prefill_t<HD, 2>(st, a);
   return launch_prefill_t<HD, 1>(st, a);

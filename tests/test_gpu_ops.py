@@ -758,13 +758,15 @@ def test_attention_prefill_item_sizes(item_rows):
 
 @pytest.mark.parametrize("Hq,Hkv,hd,P,seqs,stride", [
     # four key groups: two pages a step, an odd number of pages, a prefix that ends inside its last
-    # page's first block, groups without a visible key, three query heads for two per workgroup
-    (8, 2, 128, 97, [(97, 40), (97, 1)], 1), (6, 2, 128, 300, [(300, 50)], 1), (8, 2, 64, 20, [(0, 20)], 1),
-    # two key groups (too many items for four): a whole prefix, suffixes of one page each
-    (32, 8, 64, 530, [(0, 530)], 61), (32, 8, 128, 70, [(70, 64)] * 10, 97),
+    # page's first block, three query heads for two per workgroup; more of a prefix, scored suffixes
+    (8, 2, 128, 2593, [(2593, 40), (2593, 1)], 3), (6, 2, 128, 2700, [(2700, 50)], 3), (8, 2, 64, 2626, [(2596, 30)], 1),
+    # two key groups (too many items for four): suffixes of one page each, a late part of a prefix
+    (32, 8, 128, 2570, [(2570, 64)] * 10, 97), (32, 8, 64, 3130, [(2600, 530)], 211),
     # the last item count of each group count, and the first of the next
-    (32, 8, 128, 512, [(0, 512)], 401), (32, 8, 64, 513, [(0, 513)], 401), (32, 8, 128, 1024, [(0, 1024)], 1601),
-    (32, 8, 64, 1025, [(0, 1025)], 1601),
+    (32, 8, 128, 3112, [(2600, 512)], 401), (32, 8, 64, 3113, [(2600, 513)], 401), (32, 8, 128, 3624, [(2600, 1024)], 1601),
+    (32, 8, 64, 3625, [(2600, 1025)], 1601),
+    # the longest prefix that keeps one group, and one key more: groups that see no key of their own
+    (8, 2, 128, 2560, [(2560, 33)], 1), (8, 2, 64, 2561, [(0, 70)], 1),
 ])
 def test_attention_prefill_key_groups(Hq, Hkv, hd, P, seqs, stride):
     worst, _ = prefill_case(Hq, Hkv, hd, P, seqs, stride)
