@@ -108,7 +108,7 @@ __host__ __device__ inline size_t tiled_offset(int row, int k, int K) {
 struct AttnArgs {
   const void *q;                 // (T)[rows][Hq][hd]
   const void *k_prefix, *v_prefix, *k_suffix, *v_suffix;   // page pools of this layer
-  const int32_t *row_pos;        // [rows] absolute position of each query row
+  const int32_t *row_pos;        // [rows] absolute position of each query row; nullptr: a decode step, below
   const int32_t *row_tab;        // [rows] page-table row of the query's sequence (unused if no suffix)
   const int32_t *page_table;     // [*][table_stride] suffix page ids
   int32_t table_stride;
@@ -116,6 +116,9 @@ struct AttnArgs {
   int32_t prefix_len;            // keys at positions < prefix_len live in prefix pages pos / page_tokens
   void *out;                     // (T)[rows][Hq][hd], or the tiled [rows][Hq*hd] layout
   int32_t out_tiled;
+  // decode step (row_pos == nullptr): the suffix keys and page-table rows as in DecodeAttnArgs
+  const int32_t *row_len = nullptr, *row_cand = nullptr;
+  int32_t suffix_len = 0;
 };
 
 struct DecodeAttnArgs {

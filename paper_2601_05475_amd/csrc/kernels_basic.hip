@@ -266,11 +266,97 @@ __global__ __launch_bounds__(256) void linear_generic_kernel(
   }
 }
 
+// The same for few rows (decode steps of fp32 models and of shapes the tiled kernels do not cover).
+// With 64 x 64 tiles a 4 x 256 x 688 product is four workgroups that walk K in barriered slabs of 16,
+// 34 us for 0.7 MB; here every wave takes one output column: its lanes stride over K with 16-byte
+// loads, keep MR rows' sums and meet by shuffles.  What bounds it is the launch and one trip to memory
+// (4 x 256 x 688: 34 -> 3.2 us, SwiGLU 4 x 688 x 256: 54 -> 4.0 us, LM head 4 x 4096 x 256: 26 -> 3.7 us).
+template <typename T> struct Vec16;              // 16 bytes of T as floats
+template <> struct Vec16<float> {
+  static constexpr int N = 4;
+  __device__ static void load(const float *p, float *v) {
+    const float4 t = *(const float4 *)p;
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  }
+};
+template <> struct Vec16<bf16_t> {
+  static constexpr int N = 8;
+  __device__ static void load(const bf16_t *p, float *v) {
+    const uint4 t = *(const uint4 *)p;
+    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = bf16_to_f32((bf16_t)(w[i] & 0xFFFF));
+      v[2 * i + 1] = bf16_to_f32((bf16_t)(w[i] >> 16));
+    }
+  }
+};
+
+template <typename T, bool SWIGLU, int MR>
+__global__ __launch_bounds__(256) void linear_few_rows_kernel(
+    int M, int N, int K, int k_per_split, const T *__restrict__ a, const T *__restrict__ w,
+    const T *__restrict__ w2, float *__restrict__ out, T *__restrict__ out_t) {
+  constexpr int V = Vec16<T>::N;
+  const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int m0 = blockIdx.y * MR, split = blockIdx.z;
+  if (n >= N) return;
+  const int k_begin = split * k_per_split, k_end = min(K, k_begin + k_per_split);
+  float acc[MR] = {}, acc2[MR] = {};
+  for (int k = k_begin + lane * V; k < k_end; k += 64 * V) {
+    float wv[V], uv[V];
+    Vec16<T>::load(w + (size_t)n * K + k, wv);
+    if (SWIGLU) Vec16<T>::load(w2 + (size_t)n * K + k, uv);
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      float av[V];
+      Vec16<T>::load(a + (size_t)min(m0 + m, M - 1) * K + k, av);
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        acc[m] += av[j] * wv[j];
+        if (SWIGLU) acc2[m] += av[j] * uv[j];
+      }
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MR; ++m) {
+    acc[m] = wave_sum(acc[m]);
+    if (SWIGLU) acc2[m] = wave_sum(acc2[m]);
+  }
+#pragma unroll
+  for (int m = 0; m < MR; ++m)
+    if (lane == m && m0 + m < M) {
+      const float g = acc[m];
+      if (SWIGLU) out_t[(size_t)(m0 + m) * N + n] = Cvt<T>::from_f32(g / (1.0f + expf(-g)) * acc2[m]);
+      else out[((size_t)split * M + m0 + m) * N + n] = g;
+    }
+}
+
+// Up to 32 rows, K in whole 16-byte pieces and pointers that allow them.
+static bool few_rows_ok(int dtype, int M, int K, const void *a, const void *w, const void *w2) {
+  return M <= 32 && K % (dtype == MC_F32 ? 4 : 8) == 0 && (((uintptr_t)a | (uintptr_t)w | (uintptr_t)w2) & 15) == 0;
+}
+
+template <typename T, bool SWIGLU>
+static void launch_few_rows(hipStream_t st, int M, int N, int K, int kps, int n_splits, const void *a, const void *w,
+                            const void *w2, float *out, void *out_t) {
+  const int mr = M <= 4 ? 4 : 8;
+  const dim3 grid((N + 3) / 4, (M + mr - 1) / mr, n_splits);
+  const T *A = (const T *)a, *W = (const T *)w, *W2 = (const T *)w2;
+  if (mr == 4) linear_few_rows_kernel<T, SWIGLU, 4><<<grid, 256, 0, st>>>(M, N, K, kps, A, W, W2, out, (T *)out_t);
+  else linear_few_rows_kernel<T, SWIGLU, 8><<<grid, 256, 0, st>>>(M, N, K, kps, A, W, W2, out, (T *)out_t);
+}
+
 int launch_linear_generic(hipStream_t st, int dtype, int M, int N, int K, const void *a,
                           const void *w, float *out, int n_splits) {
   if (M <= 0 || N <= 0) return MC_OK;
   int kps = (K + n_splits - 1) / n_splits;
   kps = (kps + 15) / 16 * 16;
+  if (few_rows_ok(dtype, M, K, a, w, nullptr)) {
+    if (dtype == MC_F32) launch_few_rows<float, false>(st, M, N, K, kps, n_splits, a, w, nullptr, out, nullptr);
+    else launch_few_rows<bf16_t, false>(st, M, N, K, kps, n_splits, a, w, nullptr, out, nullptr);
+    MC_HIP(hipGetLastError());
+    return MC_OK;
+  }
   dim3 grid((N + 63) / 64, (M + 63) / 64, n_splits);
   if (dtype == MC_F32)
     linear_generic_kernel<float, false><<<grid, 256, 0, st>>>(
@@ -285,6 +371,12 @@ int launch_linear_generic(hipStream_t st, int dtype, int M, int N, int K, const 
 int launch_linear_swiglu_generic(hipStream_t st, int dtype, int M, int N, int K, const void *a,
                                  const void *wg, const void *wu, void *out) {
   if (M <= 0 || N <= 0) return MC_OK;
+  if (few_rows_ok(dtype, M, K, a, wg, wu)) {
+    if (dtype == MC_F32) launch_few_rows<float, true>(st, M, N, K, K, 1, a, wg, wu, nullptr, out);
+    else launch_few_rows<bf16_t, true>(st, M, N, K, K, 1, a, wg, wu, nullptr, out);
+    MC_HIP(hipGetLastError());
+    return MC_OK;
+  }
   dim3 grid((N + 63) / 64, (M + 63) / 64, 1);
   if (dtype == MC_F32)
     linear_generic_kernel<float, true><<<grid, 256, 0, st>>>(
@@ -390,108 +482,147 @@ int launch_rope_kv(hipStream_t st, int dtype, int rows, int Hq, int Hkv, int hd,
 }
 
 // ------------------------------------------------------------------ generic attention
-// One wave per (query row, query head).  Keys 0..pos of the row's sequence are walked 64 at a
-// time with a running (max, sum, weighted value) state.  Lane j scores key j of the block; then
-// lane d accumulates coordinates d, d+64, ... of the value sum.
-template <typename T>
-__global__ __launch_bounds__(64) void attention_generic_kernel(AttnArgs a) {
+// One workgroup per (query row, query head); its four waves take 64-key blocks in turn, first of the
+// prefix keys the row sees, then of its own suffix keys, each with a running (max, sum, weighted
+// value) state, and meet in LDS at the end.  Inside a block lane j scores key j (its row of K in
+// pieces of four coordinates), then lane d accumulates coordinates d, d + 64, ... of the value sum,
+// four consecutive keys per load: both page layouts keep them together, and a page holds whole
+// quads of keys unless page_tokens is 1 or 2, when keys are taken one by one.
+// At the tiny fp32 shape (16 workgroups, 136 keys) the time is the latency of a few rounds of loads:
+// 23 us with one wave per workgroup and 4-byte loads, 9 us so.
+template <typename T> __device__ inline float4 load4(const T *p);
+template <> __device__ inline float4 load4<float>(const float *p) { return *(const float4 *)p; }
+template <> __device__ inline float4 load4<bf16_t>(const bf16_t *p) {
+  const uint2 t = *(const uint2 *)p;
+  return make_float4(bf16_to_f32((bf16_t)(t.x & 0xFFFF)), bf16_to_f32((bf16_t)(t.x >> 16)),
+                     bf16_to_f32((bf16_t)(t.y & 0xFFFF)), bf16_to_f32((bf16_t)(t.y >> 16)));
+}
+
+constexpr int kAttnWaves = 4;
+
+// V4: head_dim and page_tokens are multiples of 4 and the pools are aligned for loads of four
+// elements (K in both layouts, V in quads of keys)
+template <typename T, bool V4>
+__global__ __launch_bounds__(64 * kAttnWaves) void attention_generic_kernel(AttnArgs a) {
   constexpr int MAXD = 4;   // head_dim <= 256
-  __shared__ float qs[256];
-  __shared__ float ps[64];
-  __shared__ long long kbase[64];   // element offset of the key's page+head base, -1 if masked
-  __shared__ int koff[64];
-  const int r = blockIdx.x, qh = blockIdx.y, lane = threadIdx.x;
+  __shared__ __attribute__((aligned(16))) float qs[256];
+  __shared__ __attribute__((aligned(16))) float ps[kAttnWaves][64];
+  __shared__ float sm[kAttnWaves], sl[kAttnWaves], so[kAttnWaves][256];
+  const int r = blockIdx.x, qh = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int hd = a.head_dim, pg = a.page_tokens, Hkv = a.n_kv_heads;
   const int kvh = qh / (a.n_q_heads / Hkv);
-  const int pos = a.row_pos[r];
-  const int n_keys = pos + 1;
-  const int n_pre = min(n_keys, a.prefix_len);
-  const size_t pelems = (size_t)Hkv * hd * pg;
+  int pos, tab_row = 0;
+  if (a.row_pos) {
+    pos = a.row_pos[r];
+    if (a.page_table) tab_row = a.row_tab[r];
+  } else {                                   // a decode step: one row per candidate, its last key is its own
+    const int len = (a.row_len && a.suffix_len) ? min(max(a.row_len[r], 1), a.suffix_len) : a.suffix_len;
+    pos = a.prefix_len + len - 1;
+    tab_row = a.row_cand ? a.row_cand[r] : r;
+  }
+  const int n_keys = pos + 1, n_pre = min(n_keys, a.prefix_len);
+  const size_t pelems = (size_t)Hkv * hd * pg, head_off = (size_t)kvh * hd * pg;
   const T *q = (const T *)a.q + ((size_t)r * a.n_q_heads + qh) * hd;
-  for (int i = lane; i < hd; i += 64) qs[i] = Cvt<T>::to_f32(q[i]);
-  const int32_t *tab = a.page_table ? a.page_table + (size_t)a.row_tab[r] * a.table_stride : nullptr;
+  for (int i = threadIdx.x; i < hd; i += 64 * kAttnWaves) qs[i] = Cvt<T>::to_f32(q[i]);
+  const int32_t *tab = a.page_table ? a.page_table + (size_t)tab_row * a.table_stride : nullptr;
   const float scale = 1.0f / sqrtf((float)hd);
   float m = -INFINITY, l = 0.f, o[MAXD] = {0.f, 0.f, 0.f, 0.f};
   __syncthreads();
-  for (int j0 = 0; j0 < n_keys; j0 += 64) {
-    const int j = j0 + lane;
-    float s = -INFINITY;
-    long long base = -1;
-    int off = 0;
-    bool in_prefix = true;
-    if (j < n_keys) {
-      int page;
-      if (j < n_pre) {
-        page = j / pg;
-        off = j % pg;
-      } else {
-        const int jj = j - a.prefix_len;
-        page = tab[jj / pg];
-        off = jj % pg;
-        in_prefix = false;
+  const int blocks_pre = (n_pre + 63) / 64, blocks_all = blocks_pre + (n_keys - n_pre + 63) / 64;
+  for (int blk = wave; blk < blocks_all; blk += kAttnWaves) {
+    const bool in_prefix = blk < blocks_pre;
+    const int j0 = 64 * (in_prefix ? blk : blk - blocks_pre), n_seg = in_prefix ? n_pre : n_keys - n_pre;
+    const int nblk = min(64, n_seg - j0), j = j0 + min(lane, nblk - 1);   // lanes past the end look at its last key
+    const int page = in_prefix ? j / pg : tab[j / pg], off = j % pg;
+    const size_t base = (size_t)page * pelems + head_off;
+    const T *kp = (const T *)(in_prefix ? a.k_prefix : a.k_suffix) + base;
+    const T *vpool = (const T *)(in_prefix ? a.v_prefix : a.v_suffix);
+    float dot = 0.f;
+    if (V4) {
+#pragma unroll 4
+      for (int i = 0; i < hd; i += 4) {
+        const float4 k4 = load4<T>(kp + k_elem_offset(off, i, pg, hd)), q4 = *(const float4 *)(qs + i);
+        dot += q4.x * k4.x; dot += q4.y * k4.y; dot += q4.z * k4.z; dot += q4.w * k4.w;
       }
-      base = (long long)((size_t)page * pelems + (size_t)kvh * hd * pg);
-      const T *kp = (const T *)(in_prefix ? a.k_prefix : a.k_suffix) + base;
-      float dot = 0.f;
-      if (kv_fragment_layout(pg, hd)) {
-        for (int i = 0; i < hd; i += 8) {
-          const T *k8 = kp + k_elem_offset(off, i, pg, hd);      // 8 consecutive d are contiguous
-#pragma unroll
-          for (int j = 0; j < 8; ++j) dot += qs[i + j] * Cvt<T>::to_f32(k8[j]);
-        }
-      } else {
-        kp += (size_t)off * hd;
-        for (int i = 0; i < hd; ++i) dot += qs[i] * Cvt<T>::to_f32(kp[i]);
-      }
-      s = dot * scale;
+    } else {
+      for (int i = 0; i < hd; ++i) dot += qs[i] * Cvt<T>::to_f32(kp[k_elem_offset(off, i, pg, hd)]);
     }
-    // bit 62 marks "suffix pool" so that the value pass picks the right pool
-    kbase[lane] = (base < 0) ? -1 : (in_prefix ? base : (base | (1ll << 62)));
-    koff[lane] = off;
+    const float s = lane < nblk ? dot * scale : -INFINITY;
     const float m_new = fmaxf(m, wave_max(s));
-    const float p = (j < n_keys) ? expf(s - m_new) : 0.f;
+    const float p = lane < nblk ? expf(s - m_new) : 0.f;
     const float corr = expf(m - m_new);      // m = -inf on the first block: exp(-inf) = 0
     l = l * corr + wave_sum(p);
-    ps[lane] = p;
+    ps[wave][lane] = p;                      // read by this wave only, in order behind the write
     m = m_new;
-    __syncthreads();
-    const int nblk = min(64, n_keys - j0);
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int c = 0; c < MAXD; ++c) {
       const int d = lane + 64 * c;
-      if (d < hd) {
-        float acc = o[c] * corr;
-        for (int t = 0; t < nblk; ++t) {
-          const long long kb = kbase[t];
-          const T *vp = (const T *)((kb >> 62) & 1 ? a.v_suffix : a.v_prefix) +
-                        (kb & ~(1ll << 62)) + v_elem_offset(koff[t], d, pg, hd);
-          acc += ps[t] * Cvt<T>::to_f32(*vp);
+      if (64 * c >= hd) break;               // uniform
+      float acc = o[c] * corr;
+      if (V4) {
+        // the last quad may reach past the sequence's end: its page holds the bytes, their weight is
+        // not taken
+#pragma unroll 4
+        for (int t = 0; t < nblk; t += 4) {
+          const size_t vb = __shfl((unsigned long long)base, t, 64);
+          const int vo = __shfl(off, t, 64);
+          const float4 w4 = *(const float4 *)(&ps[wave][t]);
+          if (d < hd) {
+            const float4 v4 = load4<T>(vpool + vb + v_elem_offset(vo, d, pg, hd));
+            acc += w4.x * v4.x;
+            if (t + 1 < nblk) acc += w4.y * v4.y;
+            if (t + 2 < nblk) acc += w4.z * v4.z;
+            if (t + 3 < nblk) acc += w4.w * v4.w;
+          }
         }
-        o[c] = acc;
+      } else {
+        for (int t = 0; t < nblk; ++t) {
+          const size_t vb = __shfl((unsigned long long)base, t, 64);
+          const int vo = __shfl(off, t, 64);
+          if (d < hd) acc += ps[wave][t] * Cvt<T>::to_f32(vpool[vb + v_elem_offset(vo, d, pg, hd)]);
+        }
       }
+      o[c] = acc;
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (lane == 0) { sm[wave] = m; sl[wave] = l; }
+#pragma unroll
+  for (int c = 0; c < MAXD; ++c)
+    if (lane + 64 * c < hd) so[wave][lane + 64 * c] = o[c];
+  __syncthreads();
+  float M = sm[0];
+  for (int w = 1; w < kAttnWaves; ++w) M = fmaxf(M, sm[w]);
+  float f[kAttnWaves], den = 0.f;
+  for (int w = 0; w < kAttnWaves; ++w) {
+    f[w] = sm[w] == -INFINITY ? 0.f : expf(sm[w] - M);    // a wave that saw no key has no weight
+    den += f[w] * sl[w];
   }
   T *out = (T *)a.out;
-#pragma unroll
-  for (int c = 0; c < MAXD; ++c) {
-    const int d = lane + 64 * c;
-    if (d < hd) {
-      const size_t at = a.out_tiled ? tiled_offset(r, qh * hd + d, a.n_q_heads * hd)
-                                    : ((size_t)r * a.n_q_heads + qh) * hd + d;
-      out[at] = Cvt<T>::from_f32(o[c] / l);
-    }
+  for (int d = threadIdx.x; d < hd; d += 64 * kAttnWaves) {
+    float num = 0.f;
+    for (int w = 0; w < kAttnWaves; ++w) num += f[w] * so[w][d];
+    const size_t at = a.out_tiled ? tiled_offset(r, qh * hd + d, a.n_q_heads * hd)
+                                  : ((size_t)r * a.n_q_heads + qh) * hd + d;
+    out[at] = Cvt<T>::from_f32(num / den);
   }
+}
+
+template <typename T>
+static void launch_attention_generic_t(hipStream_t st, const AttnArgs &a) {
+  const uintptr_t pools = (uintptr_t)a.k_prefix | (uintptr_t)a.v_prefix | (uintptr_t)a.k_suffix | (uintptr_t)a.v_suffix;
+  const bool v4 = a.head_dim % 4 == 0 && a.page_tokens % 4 == 0 && pools % (4 * sizeof(T)) == 0;
+  const dim3 grid(a.rows, a.n_q_heads);
+  if (v4) attention_generic_kernel<T, true><<<grid, 64 * kAttnWaves, 0, st>>>(a);
+  else attention_generic_kernel<T, false><<<grid, 64 * kAttnWaves, 0, st>>>(a);
 }
 
 int launch_attention_generic(hipStream_t st, int dtype, const AttnArgs &a) {
   if (a.rows <= 0) return MC_OK;
   if (a.head_dim > 256) MC_FAIL(MC_ERR_UNSUPPORTED, "head_dim %d > 256", a.head_dim);
-  dim3 grid(a.rows, a.n_q_heads);
-  if (dtype == MC_F32)
-    attention_generic_kernel<float><<<grid, 64, 0, st>>>(a);
-  else
-    attention_generic_kernel<bf16_t><<<grid, 64, 0, st>>>(a);
+  if (dtype == MC_F32) launch_attention_generic_t<float>(st, a);
+  else launch_attention_generic_t<bf16_t>(st, a);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }

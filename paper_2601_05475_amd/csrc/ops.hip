@@ -107,18 +107,6 @@ int launch_linear_swiglu(hipStream_t st, int dtype, int M, int N, int K, const v
 }
 
 // ---- decode attention: MFMA split-K kernel when the shape allows, else the generic kernel ---
-__global__ void fill_decode_rows_kernel(int B, int prefix_len, int suffix_len,
-                                        const int32_t *__restrict__ row_len,
-                                        const int32_t *__restrict__ row_cand,
-                                        int32_t *row_pos, int32_t *row_tab) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) {
-    const int len = (row_len && suffix_len) ? min(max(row_len[b], 1), suffix_len) : suffix_len;
-    row_pos[b] = prefix_len + len - 1;          // the row sees the keys at positions <= this one
-    row_tab[b] = row_cand ? row_cand[b] : b;
-  }
-}
-
 size_t decode_attention_ws_bytes(int n_cands, int Hq, int Hkv, int hd, int prefix_len,
                                  int suffix_len, int page_tokens) {
   size_t generic = (size_t)n_cands * 2 * sizeof(int32_t) + 256;
@@ -132,13 +120,10 @@ int launch_attention_decode(hipStream_t st, int dtype, const DecodeAttnArgs &a) 
     return launch_attention_decode_mfma(st, a);
   if (a.workspace_bytes < (size_t)a.n_cands * 2 * sizeof(int32_t))
     MC_FAIL(MC_ERR_INVALID, "attention workspace too small");
-  int32_t *row_pos = (int32_t *)a.workspace, *row_tab = row_pos + a.n_cands;
-  fill_decode_rows_kernel<<<(a.n_cands + 63) / 64, 64, 0, st>>>(
-      a.n_cands, a.prefix_len, a.suffix_len, a.row_len, a.row_cand, row_pos, row_tab);
-  MC_HIP(hipGetLastError());
   AttnArgs g;
   g.q = a.q; g.k_prefix = a.k_prefix; g.v_prefix = a.v_prefix; g.k_suffix = a.k_suffix;
-  g.v_suffix = a.v_suffix; g.row_pos = row_pos; g.row_tab = row_tab; g.page_table = a.page_table;
+  g.v_suffix = a.v_suffix; g.row_pos = nullptr; g.row_tab = nullptr; g.page_table = a.page_table;
+  g.row_len = a.row_len; g.row_cand = a.row_cand; g.suffix_len = a.suffix_len;
   g.table_stride = a.table_stride; g.rows = a.n_cands; g.n_q_heads = a.n_q_heads;
   g.n_kv_heads = a.n_kv_heads; g.head_dim = a.head_dim; g.page_tokens = a.page_tokens;
   g.prefix_len = a.prefix_len; g.out = a.out; g.out_tiled = a.out_tiled;

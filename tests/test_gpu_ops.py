@@ -57,6 +57,18 @@ def test_linear(dtype, M, N, K, S):
     np.testing.assert_allclose(out, want, rtol=0, atol=2e-5 * np.abs(want).max() + 1e-6)
 
 
+# One output column per wave, up to 32 rows: both row groups, rows past a group, columns past a
+# workgroup, K shorter and longer than one pass of the lanes, splits with a short and an empty range.
+@pytest.mark.parametrize("dtype,M,N,K,S", [
+    ("f32", 1, 5, 4, 1), ("f32", 4, 256, 688, 2), ("f32", 5, 66, 260, 1), ("f32", 9, 7, 1028, 3), ("f32", 32, 130, 512, 4),
+    ("bf16", 3, 9, 8, 1), ("bf16", 8, 33, 520, 1), ("bf16", 17, 64, 1032, 2), ("f32", 2, 6, 20, 3),
+])
+def test_linear_few_rows_generic(dtype, M, N, K, S):
+    test_linear(dtype, M, N, K, S)
+    if S == 1:
+        test_linear_swiglu(dtype, M, N, K)
+
+
 @pytest.mark.parametrize("dtype,M,N,K", [("f32", 5, 70, 100), ("bf16", 4, 96, 200), ("bf16", 32, 512, 256),
                                          ("bf16", 150, 128, 128)])
 def test_linear_swiglu(dtype, M, N, K):
@@ -168,6 +180,17 @@ def attention_case(dtype, B, Hq, Hkv, hd, pg, P, t, splits=0, seed=20, stride=1,
     (5, 6, 2, 64, 16, 77, 0), (1, 4, 1, 128, 64, 1, 1), (32, 32, 8, 128, 64, 1024, 130),
 ])
 def test_attention_decode(dtype, B, Hq, Hkv, hd, pg, P, t):
+    worst, _, _ = attention_case(dtype, B, Hq, Hkv, hd, pg, P, t)
+    assert worst < ATT_REL[dtype], worst
+
+
+# The generic kernel's quads of keys and coordinates: head_dim or page sizes that do not allow them, the
+# largest head_dim, a prefix and suffixes that end inside a quad, more blocks than waves and fewer.
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,hd,pg,P,t", [
+    ("f32", 2, 4, 2, 6, 8, 21, 3), ("f32", 3, 2, 1, 64, 2, 9, 5), ("bf16", 2, 4, 2, 64, 1, 7, 2), ("f32", 1, 2, 1, 256, 4, 130, 70),
+    ("bf16", 2, 6, 2, 20, 8, 66, 65), ("f32", 2, 4, 4, 64, 4, 700, 63), ("bf16", 1, 4, 2, 256, 32, 65, 1),
+])
+def test_attention_decode_generic_quads(dtype, B, Hq, Hkv, hd, pg, P, t):
     worst, _, _ = attention_case(dtype, B, Hq, Hkv, hd, pg, P, t)
     assert worst < ATT_REL[dtype], worst
 
