@@ -471,13 +471,26 @@ def kv_pages_unpack(kp, vp, page_tokens: int, head_dim: int):
     return k, v
 
 
+def _tiled_out(rows: int, K: int, dtype, device):
+    """A tiled [rows, K] buffer for a kernel that writes every row: only the padding rows, which lie in
+    the last tile of 32, are zero-filled."""
+    import torch
+    n = load_library().mc_op_tiled_bytes(rows, K) // 2
+    if rows < 32:
+        return torch.zeros(n, dtype=dtype, device=device)
+    out = torch.empty(n, dtype=dtype, device=device)
+    if rows % 32:
+        out[-32 * K:].zero_()
+    return out
+
+
 def op_add_rmsnorm(x, partials, gain, eps: float, tiled: bool = False):
     """x: fp32 [rows, d] (updated in place); partials: fp32 [S, rows, d] or None.  Returns h
     ([rows, d], or the flat tiled buffer when tiled)."""
     import torch
     rows, d = x.shape
     if tiled:
-        h = torch.zeros(load_library().mc_op_tiled_bytes(rows, d) // 2, dtype=gain.dtype, device=x.device)
+        h = _tiled_out(rows, d, gain.dtype, x.device)
     else:
         h = torch.empty((rows, d), dtype=gain.dtype, device=x.device)
     S = 0 if partials is None else partials.shape[0]
@@ -547,7 +560,7 @@ def op_linear_swiglu(a, w_gate, w_up, tiled_shape=None):
         out = torch.empty((M, N), dtype=a.dtype, device=a.device)
     else:
         M, N, K = tiled_shape
-        out = torch.zeros(load_library().mc_op_tiled_bytes(M, N) // 2, dtype=a.dtype, device=a.device)
+        out = _tiled_out(M, N, a.dtype, a.device)
     _check(load_library().mc_op_linear_swiglu(_stream(), _code_of(a), M, N, K, a.data_ptr(),
                                               w_gate.data_ptr(), w_up.data_ptr(), out.data_ptr(),
                                               int(tiled_shape is not None)))
@@ -582,7 +595,7 @@ def op_attention_decode(q, k_prefix, v_prefix, k_suffix, v_suffix, page_table, p
     Hkv = (k_prefix if k_prefix is not None else k_suffix).shape[1]
     if out is None:
         if out_tiled:
-            out = torch.zeros(lib.mc_op_tiled_bytes(B, Hq * hd) // 2, dtype=q.dtype, device=q.device)
+            out = _tiled_out(B, Hq * hd, q.dtype, q.device)
         else:
             out = torch.empty_like(q)
     p = lambda t: None if t is None else t.data_ptr()
@@ -676,7 +689,7 @@ def op_lm_head(a, w, tiled_shape):
     nbytes = lib.mc_op_top_list_bytes(M, N)
     if nbytes == 0:
         raise McError(-1, "N must be a positive multiple of 64")
-    lists = torch.zeros((M, N // 64, 4, 2), dtype=torch.int32, device=a.device)
+    lists = torch.empty((M, N // 64, 4, 2), dtype=torch.int32, device=a.device)
     _check(lib.mc_op_lm_head(_stream(), M, N, K, a.data_ptr(), w.data_ptr(), logits.data_ptr(), lists.data_ptr()))
     return logits, lists
 
