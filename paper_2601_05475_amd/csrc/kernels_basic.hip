@@ -714,30 +714,6 @@ __device__ inline void scan_row(const float *row, int V, F f) {
   }
 }
 
-// The same walk over a list of (value bits, id) pairs: the per-group top lists the LM head leaves
-// beside the logits (n even).
-template <typename F>
-__device__ inline void scan_pairs(const uint2 *list, int n, F f) {
-  constexpr int NB = 4;
-  const int tid = threadIdx.x;
-  const int n2 = n / 2;
-  const uint4 *l4 = (const uint4 *)list;
-  for (int g0 = 0; g0 < n2; g0 += NB * 1024) {
-    uint4 e[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int g = g0 + j * 1024 + tid;
-      e[j] = (g < n2) ? l4[g] : make_uint4(0u, 0u, 0u, 0u);
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const bool ok = g0 + j * 1024 + tid < n2;
-      f(ok, __uint_as_float(e[j].x), (int)e[j].y);
-      f(ok, __uint_as_float(e[j].z), (int)e[j].w);
-    }
-  }
-}
-
 // LDS of the sampling kernel
 struct SampleShared {
   unsigned long long sel[MC_MAX_TOP_K];
@@ -748,7 +724,7 @@ struct SampleShared {
   unsigned int s_bin, s_above, s_cnt, s_cnt2;
 };
 
-// Threshold selection of the k largest keys of the elements `scan` walks (k <= 1024, at least
+// Threshold selection of the k largest keys of the elements `scan` walks (224 < k <= 1024, at least
 // 4096 elements, every thread sees some and no two threads see the same): pass 1 takes every
 // thread's largest value; the threads form n_g >= k groups (n_g the next power of two), and the
 // smallest of the n_g group maxima, L, is a lower bound of the k-th largest value (n_g >= k
@@ -937,9 +913,176 @@ __device__ inline void sort_selected(int n_sel, SampleShared &sh) {
   }
 }
 
+// An undivided value and its id (kEndsGroup: the last entry of a group's top list) for group_select
+constexpr uint32_t kEndsGroup = 0x80000000u;
+__device__ inline void list_candidate(SampleShared &sh, unsigned int at, float z, uint32_t id) {
+  if (at < MC_MAX_TOP_K) sh.sel[at] = ((unsigned long long)__float_as_uint(z) << 32) | id;
+}
+
+// Two walks over one row for group_select: the largest value of this thread's elements, then a list
+// of all elements >= z_low.  Rows of up to 4 * NB * 1024 values (32768) stay in registers between the two;
+// longer ones are read again, from L2.  Rows that are not 16-byte aligned go element by element.
+struct RowScan {
+  static constexpr int NB = 8;
+  const float *row;
+  int V, V4;
+  float4 z[NB];
+  __device__ RowScan(const float *r, int v) : row(r), V(v), V4((((uintptr_t)r & 15) == 0) ? v / 4 : 0) {}
+  __device__ inline void load(int g0) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int g = g0 + j * 1024 + (int)threadIdx.x;
+      z[j] = (g < V4) ? ((const float4 *)row)[g] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    }
+  }
+  __device__ inline float largest() {
+    float m = -INFINITY;
+    for (int g0 = 0; g0 < V4; g0 += NB * 1024) {
+      load(g0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) m = fmaxf(fmaxf(fmaxf(m, z[j].x), fmaxf(z[j].y, z[j].z)), z[j].w);
+    }
+    for (int v = 4 * V4 + (int)threadIdx.x; v < V; v += 1024) m = fmaxf(m, row[v]);
+    return m;
+  }
+  __device__ inline void above(float z_low, SampleShared &sh) {
+    for (int g0 = 0; g0 < V4; g0 += NB * 1024) {
+      if (V4 > NB * 1024) load(g0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int g = g0 + j * 1024 + (int)threadIdx.x;
+        if (!(fmaxf(fmaxf(z[j].x, z[j].y), fmaxf(z[j].z, z[j].w)) >= z_low) || g >= V4) continue;
+        const bool wx = z[j].x >= z_low, wy = z[j].y >= z_low, wz = z[j].z >= z_low, ww = z[j].w >= z_low;
+        unsigned int at = atomicAdd(&sh.s_cnt, (unsigned int)(wx + wy + wz + ww));
+        if (wx) list_candidate(sh, at++, z[j].x, 4 * g);
+        if (wy) list_candidate(sh, at++, z[j].y, 4 * g + 1);
+        if (wz) list_candidate(sh, at++, z[j].z, 4 * g + 2);
+        if (ww) list_candidate(sh, at, z[j].w, 4 * g + 3);
+      }
+    }
+    for (int v = 4 * V4 + (int)threadIdx.x; v < V; v += 1024) {
+      const float x = row[v];
+      if (x >= z_low) list_candidate(sh, atomicAdd(&sh.s_cnt, 1u), x, v);
+    }
+  }
+};
+
+// The same over the (value bits, id) pairs the LM head leaves beside the logits, four per group of
+// 64 ids: lists of up to 2 * NB * 1024 pairs (a vocabulary of 262144) stay in registers.
+struct ListScan {
+  static constexpr int NB = 8;
+  const uint4 *l4;
+  int n2;
+  uint4 e[NB];
+  __device__ ListScan(const uint2 *list, int n) : l4((const uint4 *)list), n2(n / 2) {}
+  __device__ inline void load(int g0) {
+    const uint32_t none = __float_as_uint(-INFINITY);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int g = g0 + j * 1024 + (int)threadIdx.x;
+      e[j] = (g < n2) ? l4[g] : make_uint4(none, 0u, none, 0u);
+    }
+  }
+  __device__ inline float largest() {
+    float m = -INFINITY;
+    for (int g0 = 0; g0 < n2; g0 += NB * 1024) {
+      load(g0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) m = fmaxf(fmaxf(m, __uint_as_float(e[j].x)), __uint_as_float(e[j].z));
+    }
+    return m;
+  }
+  __device__ inline void above(float z_low, SampleShared &sh) {
+    for (int g0 = 0; g0 < n2; g0 += NB * 1024) {
+      if (n2 > NB * 1024) load(g0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int g = g0 + j * 1024 + (int)threadIdx.x;
+        const float x = __uint_as_float(e[j].x), y = __uint_as_float(e[j].z);
+        const bool wx = x >= z_low, wy = y >= z_low;
+        if (!(wx || wy) || g >= n2) continue;
+        unsigned int at = atomicAdd(&sh.s_cnt, (unsigned int)(wx + wy));
+        if (wx) list_candidate(sh, at++, x, e[j].y);
+        if (wy) list_candidate(sh, at, y, e[j].w | ((g & 1) ? kEndsGroup : 0u));
+      }
+    }
+  }
+};
+
+// Selection of the k <= kGroupSelectMaxK largest keys, in order: the threads form n_g = 128 groups of
+// eight (k <= 64) or 256 of four, and the k-th largest of the groups' maxima, L, is a lower bound of
+// the k-th largest value (k distinct elements are >= L), a tight one: with the largest values spread at
+// random n_g ln(n_g / (n_g - k)) elements of a row are >= L, 63 for k = 50 and 389 for k = 200.  Those go to a
+// list in LDS, and every one's rank is the number of larger keys in it (keys are distinct, the id is
+// part of them), counted by 16 lanes per key.  One pass over memory and five barriers.  Returns
+// where the k sorted keys lie, or nullptr where L is no bound (fewer than k groups with a
+// value) or the list overflowed (thousands of equal values).  NaN is passed over, as by the
+// threshold selection.
+// last_ob: largest order bits, after the division, of this thread's listed elements that end a
+// group's list (0: none).
+constexpr int kGroupSelectMaxK = 224, kRankMax = 384;
+template <typename Scan>
+__device__ inline const unsigned long long *group_select(Scan scan, float temperature, int k, SampleShared &sh,
+                                                         unsigned int &last_ob) {
+  const int tid = threadIdx.x;
+  float m = scan.largest();
+  const int gs = k <= 64 ? 3 : 2, sub = tid & ((1 << gs) - 1);   // log2 of a group's threads; index in the group
+  m = fmaxf(m, __shfl_xor(m, 1, 64));
+  m = fmaxf(m, __shfl_xor(m, 2, 64));
+  if (gs == 3) m = fmaxf(m, __shfl_xor(m, 4, 64));
+  if (sub == 0) sh.hist[tid >> gs] = float_order_bits(m);
+  if (tid == 0) { sh.s_cnt = 0; sh.s_bin = 0xFFFFFFFFu; }
+  __syncthreads();
+  {
+    const unsigned int v = sh.hist[tid >> gs];     // a group's threads count the maxima above its own
+    int gt = 0;
+#pragma unroll 4
+    for (int j = 0; j < (gs == 3 ? 4 : 16); ++j) {
+      const uint4 u = *(const uint4 *)&sh.hist[((j << gs) + sub) * 4];
+      gt += (u.x > v) + (u.y > v) + (u.z > v) + (u.w > v);
+    }
+    gt += __shfl_xor(gt, 1, 64);
+    gt += __shfl_xor(gt, 2, 64);
+    if (gs == 3) gt += __shfl_xor(gt, 4, 64);
+    if (sub == 0 && gt < k) atomicMin(&sh.s_bin, v);
+  }
+  __syncthreads();
+  const float z_l = float_from_order_bits(sh.s_bin);
+  if (!(z_l > -INFINITY)) return nullptr;
+  // a value below this cannot reach L after the division, as in threshold_select
+  scan.above(z_l - fabsf(z_l) * 3.8147e-06f - 1e-30f, sh);
+  __syncthreads();
+  const int n = (int)sh.s_cnt;
+  if (n < k || n > MC_MAX_TOP_K) return nullptr;
+  last_ob = 0;
+  for (int i = tid; i < n; i += 1024) {            // listed values become keys
+    const unsigned long long c = sh.sel[i];
+    const uint32_t id = (uint32_t)c;
+    const unsigned long long key = sample_key(__fdiv_rn(__uint_as_float((uint32_t)(c >> 32)), temperature), (int)(id & ~kEndsGroup));
+    if (id & kEndsGroup) last_ob = max(last_ob, (unsigned int)(key >> 32));
+    sh.sel[i] = key;
+  }
+  __syncthreads();
+  if (n > kRankMax) {
+    sort_selected(n, sh);
+    return sh.sel;
+  }
+  unsigned long long *sorted = (unsigned long long *)sh.hist;   // the maxima are no longer read
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int i = i0 + (tid >> 4);
+    const unsigned long long key = i < n ? sh.sel[i] : ~0ull;
+    int ahead = 0;
+    for (int j = tid & 15; j < n; j += 16) ahead += sh.sel[j] > key;
+    for (int o = 1; o < 16; o <<= 1) ahead += __shfl_xor(ahead, o, 64);
+    if ((tid & 15) == 0 && i < n && ahead < k) sorted[ahead] = key;
+  }
+  __syncthreads();
+  return sorted;
+}
+
 // One block of 1024 threads per candidate: exact top-k of z / T under the order (value
-// descending, id ascending), a bitonic sort of the survivors in LDS, then the softmax and the
-// cumulative walk done left to right by one thread, as the rule demands.
+// descending, id ascending), then the softmax and the cumulative walk, whose additions run left
+// to right as the rule demands.
 //
 // Where the LM head left per-group top lists beside the logits (top != nullptr: for every group
 // of 64 consecutive ids its kTopListLen largest (value, id) pairs in order) and k <= kTopListMaxK,
@@ -947,8 +1090,13 @@ __device__ inline void sort_selected(int n_sel, SampleShared &sh) {
 // no group's last listed entry reaches the k-th selected value after the division (then an
 // unlisted element of that group could belong to the top k, or tie with its last member): that
 // is checked, and such a row is selected from the whole row instead, so the ids are the rule's
-// in every case.  Selection from a row: threshold selection (two passes, k <= 1024, V >= 4096),
-// else radix selection.
+// in every case.  Selection from a row: group_select for k <= 224, threshold selection for k <= 1024
+// (two passes over the row), radix selection for the rest and where those two give up.  A launch has as
+// many blocks as rows, a few of the 256 CUs, and what bounds it is one block's chain of launch, memory
+// and LDS round trips and barriers, so the steps of that chain were taken out: a second pass over
+// the row, a histogram, a bitonic sort, two serial walks over LDS by one thread.  Top 50 of 8 x 32000:
+// 25.6 -> 10.1 us, 4 x 4096: 20 -> 8.2 us, 32 x 128256 from lists: 24 -> 10 us, from whole rows (wall
+// time) 39 -> 17 us; top 200 of 64 x 152064: 87 -> 41 us; arg max of 64 x 152064: 54 -> 24 us.
 constexpr int kTopListLen = 4, kTopListMaxK = 64;
 __global__ __launch_bounds__(1024) void sample_kernel(
     int V, const float *__restrict__ logits, size_t row_stride, const uint2 *__restrict__ top,
@@ -969,10 +1117,10 @@ __global__ __launch_bounds__(1024) void sample_kernel(
         best = key > best ? key : best;
       }
     } else {
-      for (int v = tid; v < V; v += 1024) {
-        const unsigned long long key = sample_key(row[v], v);
+      scan_row(row, V, [&](bool ok, float z, int v) {
+        const unsigned long long key = ok ? sample_key(z, v) : 0ull;
         best = key > best ? key : best;
-      }
+      });
     }
     best = block_max_u64(best, sh.scratch64);
     if (tid == 0) {
@@ -983,48 +1131,58 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     return;
   }
   const int k = (top_k <= 0 || top_k >= V) ? V : top_k;
-  int n_sel = 0;                                   // keys in sel[] (>= k; the top k are among them)
+  const float u = uniforms[b];
+  const unsigned long long *sorted = nullptr;      // the top k keys in order, in LDS
+  unsigned int last_ob = 0;
 
   if (list && k <= kTopListMaxK && n_groups * kTopListLen >= 4096) {
-    n_sel = threshold_select([&](auto f) { scan_pairs(list, n_groups * kTopListLen, f); }, temperature, k, sh);
-    if (n_sel) {
-      sort_selected(n_sel, sh);
-      // conclusive only if every group's last listed entry stays below the k-th selected value
-      const unsigned int z_k = (unsigned int)(sh.sel[k - 1] >> 32);
-      unsigned int open = 0;
-      for (int g = tid; g < n_groups; g += 1024) {
-        const uint2 e = list[(size_t)g * kTopListLen + kTopListLen - 1];
-        open |= float_order_bits(__fdiv_rn(__uint_as_float(e.x), temperature)) >= z_k ? 1u : 0u;
-      }
-      if (block_reduce_u32(open, true, sh.scratch32)) n_sel = 0;
-      __syncthreads();
-    }
+    sorted = group_select(ListScan(list, n_groups * kTopListLen), temperature, k, sh, last_ob);
+    // conclusive only if every group's last listed entry stays below the k-th selected value
+    // (an entry that did not reach the list is below it)
+    if (sorted && __syncthreads_or(last_ob >= (unsigned int)(sorted[k - 1] >> 32))) sorted = nullptr;
   }
-  if (n_sel == 0) {
-    if (k <= 1024 && V >= 4096)
+  if (!sorted && k <= kGroupSelectMaxK && V >= 4096) {
+    __syncthreads();
+    sorted = group_select(RowScan(row, V), temperature, k, sh, last_ob);
+  }
+  if (!sorted) {
+    __syncthreads();
+    int n_sel = 0;                                 // keys in sel[] (>= k; the top k are among them)
+    if (k > kGroupSelectMaxK && k <= 1024 && V >= 4096)
       n_sel = threshold_select([&](auto f) { scan_row(row, V, f); }, temperature, k, sh);
     if (n_sel == 0) n_sel = radix_select(row, V, temperature, k, sh);
     sort_selected(n_sel, sh);
+    sorted = sh.sel;
   }
-  const float z0 = float_from_order_bits((uint32_t)(sh.sel[0] >> 32));
-  for (int i = tid; i < k; i += 1024)
-    sh.ev[i] = expf(float_from_order_bits((uint32_t)(sh.sel[i] >> 32)) - z0);
+  const float z0 = float_from_order_bits((uint32_t)(sorted[0] >> 32));
   if (out_topk)
     for (int i = tid; i < k; i += 1024)
-      out_topk[(size_t)b * k + i] = (int)(0xFFFFFFFFu - (uint32_t)(sh.sel[i] & 0xFFFFFFFFull));
-  __syncthreads();
-  if (tid == 0) {
-    float total = 0.f;
-    for (int i = 0; i < k; ++i) total += sh.ev[i];
-    const float u = uniforms[b];
-    float run = 0.f;
-    int pick = k - 1;
-    for (int i = 0; i < k; ++i) {
-      run += sh.ev[i];
-      if (__fdiv_rn(run, total) > u) { pick = i; break; }
+      out_topk[(size_t)b * k + i] = (int)(0xFFFFFFFFu - (uint32_t)(sorted[i] & 0xFFFFFFFFull));
+  if (tid >= 64) return;
+  // One wave, 64 entries at a time: lane i holds the weight of entry i, the running sum takes the
+  // lanes' weights in order, and lane i keeps its value after entry i.
+  float run = 0.f, kept = 0.f;
+  for (int i0 = 0; i0 < k; i0 += 64) {
+    const int i = i0 + tid, nn = min(64, k - i0);
+    const float e = i < k ? expf(float_from_order_bits((uint32_t)(sorted[i] >> 32)) - z0) : 0.f;
+    for (int j = 0; j < nn; ++j) {
+      run += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e), j));
+      kept = tid == j ? run : kept;
     }
-    out_tokens[b] = (int)(0xFFFFFFFFu - (uint32_t)(sh.sel[pick] & 0xFFFFFFFFull));
+    if (k > 64 && i < k) sh.ev[i] = kept;
   }
+  const float total = run;
+  int pick = k - 1;
+  for (int i0 = 0; i0 < k; i0 += 64) {
+    const int i = i0 + tid;
+    const float c = k > 64 ? (i < k ? sh.ev[i] : 0.f) : kept;   // each lane reads what it wrote
+    const unsigned long long hit = __ballot(i < k && __fdiv_rn(c, total) > u);
+    if (hit) {
+      pick = i0 + __ffsll((long long)hit) - 1;
+      break;
+    }
+  }
+  if (tid == 0) out_tokens[b] = (int)(0xFFFFFFFFu - (uint32_t)(sorted[pick] & 0xFFFFFFFFull));
 }
 
 int launch_sample(hipStream_t st, int n_cands, int vocab, const float *logits, size_t row_stride,

@@ -394,6 +394,29 @@ def test_sample_selection_paths(V, k, T, scale):
         check_sampler_on_logits(lg[b], T, k, us[b], toks[b], topk[b])
 
 
+@pytest.mark.parametrize("V,k", [(4096, 2), (4096, 224), (4099, 50), (32768, 50), (32768, 225), (32772, 64), (32771, 128),
+                                 (65536, 224)])
+def test_sample_group_selection(V, k):
+    """The one-pass selection at the edges of its rule (k = 224, rows of 32768 values in registers,
+    rows not a multiple of 16 bytes): a random row, rows that rise and fall (the largest
+    values lie in a few thread groups, so the candidate list is sixteen times k or overflows), a
+    row with fewer values than k above -inf, and a row of twelve distinct values.  Ids bit-exact."""
+    import torch
+    T = 0.7
+    lg = rnd(530 + k, (5, V), 1.28)
+    ramp = np.arange(V, dtype=np.float32) * np.float32(1e-4)
+    lg[1], lg[2] = ramp, -ramp
+    lg[3] = -np.inf
+    lg[3, 7: 7 + (k + 1) // 2] = rnd(531, ((k + 1) // 2,), 1.0)
+    lg[4] = np.round(lg[4] * 1.5) / 1.5
+    us = synth.uniforms(532, 1, (5,))
+    print("case: sample groups", V, k, flush=True)
+    toks, topk = binding.op_sample(torch.from_numpy(lg).cuda(), T, k, torch.from_numpy(us).cuda(), want_topk=True)
+    toks, topk = toks.cpu().numpy(), topk.cpu().numpy()
+    for b in range(5):
+        check_sampler_on_logits(lg[b], T, k, us[b], toks[b], topk[b])
+
+
 def _top4_per_group(row):
     """Reference for the LM head's lists: ids of the four largest of every 64 consecutive logits
     under (value descending, id ascending)."""
