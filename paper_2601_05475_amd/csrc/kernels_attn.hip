@@ -14,7 +14,8 @@
 //     in rb only and are numbered a multiple of 8 apart: workgroups are dealt round-robin to the
 //     8 XCDs, so they share one L2 and the keys come from HBM once.
 //     With eight or more row blocks per KV head an item takes four of them instead, one per wave:
-//     every wave walks all blocks of the range and nothing is merged across waves.
+//     every wave walks all blocks of the range, nothing is merged across waves, and the blocks do go
+//     through LDS, brought once for the four waves.
 //   suffix item (candidate b, kv head, key split): columns are b's G query heads.
 // Every item leaves an un-normalised partial (max m, sum l, weighted values o) per query head;
 // a second small kernel merges the partials of each (candidate, head) and writes bf16.  (An item
@@ -62,6 +63,15 @@ struct AttnItems {
   int rb_per_item;                           // prefix: row blocks per item, 1 (waves split the keys) or 4 (one per wave)
 };
 
+// A barrier behind which at most N of this wave's vector-memory loads, and no LDS read, are open.
+template <int N>
+__device__ inline void wait_barrier_d() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <int HD>
 __global__ __launch_bounds__(256, 2)
 void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__ part_o,
@@ -74,7 +84,6 @@ void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__
   // the wave index as a scalar: block ranges, page ids and addresses derived from it stay in
   // scalar registers and the loop branches are uniform
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int swap_addr = (lane ^ 32) << 2;    // ds_bpermute address of the lane with the other 16 keys
   const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, B = a.n_cands;
   const bool is_prefix = (int)blockIdx.x < it.n_prefix_items;
 
@@ -84,11 +93,11 @@ void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__
   const bf16_t *kpool, *vpool;
   const int32_t *table = nullptr;
   // Many query rows per KV head (more than 7 blocks of 32): a prefix item takes four row blocks,
-  // one per wave, and every wave walks all key blocks of the item's range.  The four waves ask
-  // for the same key and value fragments at about the same time, so the range crosses the L2-to-CU
-  // path about once per item instead of once per row block, which is what bounds the kernel
-  // there; nothing is merged across waves.  With few row blocks (wave_rows false) the waves
-  // split the key blocks of one row block instead, which keeps more items in flight.
+  // one per wave, and every wave walks all key blocks of the item's range, which crosses the L2-to-CU
+  // path once per item instead of once per row block; nothing is merged across waves.  A wave's
+  // chain of products, exponentials and products is what bounds it then (0.65 us per block
+  // with two waves per SIMD).  With few row blocks (wave_rows false) the waves split the key
+  // blocks of one row block instead, which keeps more items in flight.
   const bool wave_rows = is_prefix && it.rb_per_item == 4;
   if (is_prefix) {
     const int rbg = blockIdx.x / it.prefix_stride, grp = blockIdx.x % it.prefix_stride;
@@ -123,16 +132,16 @@ void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__
   const int rho = n_cols > 0 ? col0 + (col_valid ? col : 0) : 0;   // a wave without columns reads row 0 (never stored)
   const int b_of_col = (b_item >= 0) ? b_item : rho / G;
   const int head = kvh * G + rho % G;
-  const int bstep = wave_rows ? 1 : 4;                       // distance between this wave's key blocks
-  const int blk_begin = first_blk + (wave_rows ? 0 : wave);
-  const int n_mine = n_cols > 0 ? (blk_end - blk_begin + bstep - 1) / bstep : 0;   // <= 0: idle wave
+  constexpr int bstep = 4;                                   // distance between this wave's key blocks
+  const int blk_begin = first_blk + wave;
+  const int n_mine = wave_rows ? 0 : (blk_end - blk_begin + bstep - 1) / bstep;   // <= 0: idle wave
 
   // ---- query fragments: B operand of S^T = K Q^T, lane (col, h) holds Q[row][16c + 8h .. +7].
   // They are parked in LDS (each lane reads back only what it wrote) to leave the registers to
   // the accumulators and the fragments in flight.
   v4u *qs = (v4u *)lds_raw + wave * NF * 64 + lane;
-  {
-    const bf16_t *qrow = (const bf16_t *)a.q + ((size_t)b_of_col * Hq + head) * HD + 8 * h;
+  const bf16_t *qrow = (const bf16_t *)a.q + ((size_t)b_of_col * Hq + head) * HD + 8 * h;
+  if (!wave_rows) {
 #pragma unroll
     for (int c = 0; c < NF; ++c) qs[c * 64] = *(const v4u *)(qrow + 16 * c);
   }
@@ -145,8 +154,114 @@ void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
   float m = -INFINITY, l = 0.f;
 
+  // Scores of one block to its probabilities, packed as the B operand of the value MFMAs.
+  auto softmax_block = [&](f32x16 &s, int n_valid, v4u (&pb)[2]) __attribute__((always_inline)) {
+    // s[r] = raw score of key kmap(r) = 8 (r / 4) + 4 h + r % 4 against this lane's query column.
+    // The running maximum m lives in the base-2 domain: m = max(score * scale * log2(e)).
+    if (n_valid < 32) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (8 * (r >> 2) + 4 * h + (r & 3) >= n_valid) s[r] = -INFINITY;
+    }
+    // Lazy reference: sums and weighted values are all taken against the same m, so the
+    // normalised result does not depend on it; m only has to keep the numbers in range.  The
+    // probabilities are therefore computed against m as it stands, and only if a lane's sum
+    // leaves the range (a score far above m, or the first block, where m = -inf gives inf or
+    // NaN) the block's maximum is taken, m moved there and the 16 * HD/32 accumulators
+    // rescaled.  The common case spends no instruction on maxima.
+    f32x16 p;
+    float rs = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -m));
+      rs += p[r];
+    }
+    if (__any(!(rs <= kSoftmaxSumLimit))) {
+      float mx = max16f(s);
+      mx = fmaxf(mx, other_half(mx));
+      const float m_new = fmaxf(m, mx * scale2);              // finite: a processed block has a valid key
+      const float corr = __builtin_amdgcn_exp2f(m - m_new);   // m = -inf at the start: 0
+      l *= corr;
+      m = m_new;
+#pragma unroll
+      for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] *= corr;
+      rs = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -m));
+        rs += p[r];
+      }
+    }
+    rs += other_half(rs);
+    l += rs;
+    // probabilities as the B operand: slab sl holds keys kmap(8 sl .. 8 sl + 7)
+    pb[0] = make_v4u(pack2_bf16(p[0], p[1]), pack2_bf16(p[2], p[3]), pack2_bf16(p[4], p[5]), pack2_bf16(p[6], p[7]));
+    pb[1] = make_v4u(pack2_bf16(p[8], p[9]), pack2_bf16(p[10], p[11]), pack2_bf16(p[12], p[13]), pack2_bf16(p[14], p[15]));
+  };
+
   const size_t page_stride = (size_t)Hkv * PG * HD;           // elements per page (all kv heads)
   const size_t head_off = (size_t)kvh * PG * HD;
+  if (wave_rows) {
+    // Blocks go through a ring of four LDS stages, filled three blocks ahead by direct loads that
+    // the four waves share (each brings a quarter).  The waits are counted: entering block j a
+    // wave waits for its own loads of that block only, and for its LDS reads of block j - 1, whose
+    // stage is refilled behind the barrier.  With every wave loading the fragments for itself,
+    // 64 candidates x 40 heads, prefix 16384, suffix 512 took 48.2 us, so 44.8.  Loads past the last block have an empty range: they
+    // bring zeros, no memory traffic, and keep the count.
+    constexpr int LPB = 2 * (NF / 4);                           // loads per block and wave
+    v4u qf[NF];
+#pragma unroll
+    for (int c = 0; c < NF; ++c) qf[c] = *(const v4u *)(qrow + 16 * c);
+    bf16_t *ring = (bf16_t *)lds_raw;
+    const int nb = blk_end - first_blk;
+    auto stage = [&](int j) __attribute__((always_inline)) {
+      const int g = first_blk + j, bytes = j < nb ? BLK * (int)sizeof(bf16_t) : 0;
+      const size_t at = (size_t)(g >> 1) * page_stride + head_off + (size_t)(g & 1) * BLK;
+      const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)(kpool + at), 0, bytes, 0x00020000);
+      const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)(vpool + at), 0, bytes, 0x00020000);
+      bf16_t *kt = ring + (j & 3) * 2 * BLK + wave * 512, *vt = kt + BLK;
+#pragma unroll
+      for (int i = 0; i < NF / 4; ++i) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void *)(kt + 2048 * i), 16, tid * 16, 4096 * i, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void *)(vt + 2048 * i), 16, tid * 16, 4096 * i, 0, 0);
+      }
+    };
+    stage(0);
+    stage(1);
+    stage(2);
+#pragma unroll
+    for (int c = 0; c < NF; ++c) asm volatile("" : "+v"(qf[c]));   // the queries are waited for here, not in the loop
+    for (int j = 0; j < nb; ++j) {
+      wait_barrier_d<2 * LPB>();
+      stage(j + 3);
+      if (n_cols == 0) continue;                                // a wave past the last row block only brings its quarter
+      const bf16_t *kb = ring + (j & 3) * 2 * BLK, *vb = kb + BLK;
+      const int n_valid = min(32, len - 32 * (first_blk + j));
+      // lanes all of whose keys lie past the end read the fragment's first piece, as below
+      const int koff = col < n_valid ? lane * 8 : 0;
+      v4u kf[NF], vf[NF];
+#pragma unroll
+      for (int c = 0; c < NF; ++c) kf[c] = *(const v4u *)(kb + 512 * c + koff);
+      __builtin_amdgcn_sched_barrier(0);                        // all reads out before the first product
+      f32x16 s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NF; ++c) s = mfma32a(kf[c], qf[c], s);
+#pragma unroll
+      for (int c = 0; c < NF; ++c)
+        vf[c] = *(const v4u *)(vb + 512 * c + ((16 * (c & 1) + 4 * h >= n_valid) ? 0 : lane * 8));
+      v4u pb[2];
+      softmax_block(s, n_valid, pb);
+#pragma unroll
+      for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) o[dt] = mfma32a(vf[dt * 2 + sl], pb[sl], o[dt]);
+    }
+    wait_barrier_d<0>();                                        // the ring becomes the epilogue's buffer
+  }
   v4u kf[NF], vf[NF];
   // Page ids of the next 64 blocks of this wave, one per lane; block j of the window reads lane j.
   int my_pid = 0;
@@ -209,50 +324,8 @@ void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__
 #pragma unroll
       for (int c = 0; c < NF; ++c) s = mfma32a(kf[c], qs[c * 64 + q_at], s);
       issue_k(w0, j + 1, wn);
-      // s[r] = raw score of key kmap(r) = 8 (r / 4) + 4 h + r % 4 against this lane's query column.
-      // The running maximum m lives in the base-2 domain: m = max(score * scale * log2(e)).
-      if (n_valid < 32) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (8 * (r >> 2) + 4 * h + (r & 3) >= n_valid) s[r] = -INFINITY;
-      }
-      // Lazy reference: sums and weighted values are all taken against the same m, so the
-      // normalised result does not depend on it; m only has to keep the numbers in range.  The
-      // probabilities are therefore computed against m as it stands, and only if a lane's sum
-      // leaves the range (a score far above m, or the first block, where m = -inf gives inf or
-      // NaN) the block's maximum is taken, m moved there and the 16 * HD/32 accumulators
-      // rescaled.  The common case spends no instruction on maxima.
-      f32x16 p;
-      float rs = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -m));
-        rs += p[r];
-      }
-      if (__any(!(rs <= kSoftmaxSumLimit))) {
-        float mx = max16f(s);
-        mx = fmaxf(mx, swap_halves(mx, swap_addr));
-        const float m_new = fmaxf(m, mx * scale2);              // finite: a processed block has a valid key
-        const float corr = __builtin_amdgcn_exp2f(m - m_new);   // m = -inf at the start: 0
-        l *= corr;
-        m = m_new;
-#pragma unroll
-        for (int dt = 0; dt < HD / 32; ++dt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[dt][r] *= corr;
-        rs = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -m));
-          rs += p[r];
-        }
-      }
-      rs += swap_halves(rs, swap_addr);
-      l += rs;
-      // probabilities as the B operand: slab sl holds keys kmap(8 sl .. 8 sl + 7)
       v4u pb[2];
-      pb[0] = make_v4u(pack2_bf16(p[0], p[1]), pack2_bf16(p[2], p[3]), pack2_bf16(p[4], p[5]), pack2_bf16(p[6], p[7]));
-      pb[1] = make_v4u(pack2_bf16(p[8], p[9]), pack2_bf16(p[10], p[11]), pack2_bf16(p[12], p[13]), pack2_bf16(p[14], p[15]));
+      softmax_block(s, n_valid, pb);
 #pragma unroll
       for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
@@ -465,14 +538,24 @@ static AttnItems plan_items(const DecodeAttnArgs &a) {
     it.blocks_per_split = (it.n_prefix_blocks + splits - 1) / splits;
     splits = (it.n_prefix_blocks + it.blocks_per_split - 1) / it.blocks_per_split;   // drop empty splits
   }
-  // many row blocks: four per item (one per wave), and key splits for about 384 items
+  // Many row blocks: four per item, one per wave.  An item costs about 6 us beside its blocks (0.65 to
+  // 0.85 us each) and every split a partial state per row, so short contexts take 16 blocks per
+  // item and long ones as many splits as give 256 to 384 items, sixteen (the parts that the merge
+  // fetches in one batch) where that is enough.  Measured, attention + merge, 64 candidates:
+  //   40 heads, prefix  4096: 16 splits 28 + 7 us,  8 splits 23 + 5;   16384: 10: 50 + 5, 15: 45 + 6, 16: 47 + 6, 21: 54 + 8
+  //   32 heads, prefix  4096: 24 splits 25 + 7 us,  8 splits 21 + 4;   16384: 12: 44 + 5, 16: 38 + 5, 24: 42 + 7
   it.rb_per_item = it.row_blocks >= 8 ? 4 : 1;
   const int rb_groups = (it.row_blocks + it.rb_per_item - 1) / it.rb_per_item;
   if (it.rb_per_item == 4 && it.n_prefix_blocks > 0) {
-    const int max_splits = (it.n_prefix_blocks + 3) / 4;
-    splits = a.prefix_splits > 0 ? a.prefix_splits : (384 + a.n_kv_heads * rb_groups - 1) / (a.n_kv_heads * rb_groups);
-    // 16 partial states per row are what the merge kernel fetches in one batch: leave one to the suffix
-    if (a.prefix_splits <= 0 && a.suffix_len > 0 && splits == 16) splits = 15;
+    const int max_splits = (it.n_prefix_blocks + 3) / 4, groups = a.n_kv_heads * rb_groups;
+    auto splits_for = [&](int items) { return (items + groups - 1) / groups; };
+    splits = a.prefix_splits;
+    if (splits <= 0) {
+      splits = std::min(splits_for(384), std::max(16, splits_for(256)));
+      splits = std::min(splits, std::max(it.n_prefix_blocks / 16, splits_for(128)));
+      // more items than CUs: leave one of the sixteen parts to the suffix
+      if (a.suffix_len > 0 && splits == 16 && groups > 16) splits = 15;
+    }
     splits = std::max(1, std::min(splits, max_splits));
     it.blocks_per_split = (it.n_prefix_blocks + splits - 1) / splits;
     splits = (it.n_prefix_blocks + it.blocks_per_split - 1) / it.blocks_per_split;
@@ -522,8 +605,10 @@ static int launch_decode_attention_t(hipStream_t st, const DecodeAttnArgs &a, co
   const int G = a.n_q_heads / a.n_kv_heads;
   // query fragments of four waves, later reused by the suffix items' merge
   const int max_cols = (a.prefix_len > 0) ? std::min(32, a.n_cands * G) : G;
-  const size_t lds = std::max((size_t)4 * (HD / 16) * 1024, (size_t)(320 + 4 * max_cols * (HD + 4)) * sizeof(float));
   const AttnItems &it = it_in;
+  const size_t loop_lds = (it.rb_per_item == 4 && it.splits > 0) ? (size_t)4 * 2 * 32 * HD * sizeof(bf16_t)   // ring of four stages
+                                                                 : (size_t)4 * (HD / 16) * 1024;               // query fragments
+  const size_t lds = std::max(loop_lds, (size_t)(320 + 4 * max_cols * (HD + 4)) * sizeof(float));
   MC_TRY(raise_dynamic_lds_limit((const void *)decode_attention_kernel<HD>, 160 * 1024 - 1024));
   // events offered by a profiling scope: begin of the first kernel, end of the last
   const LaunchEvents ev = take_launch_events();

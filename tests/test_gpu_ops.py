@@ -256,6 +256,16 @@ def test_attention_decode_mfma_shapes(B, Hq, Hkv, hd, P, t, stride):
     assert worst < ATT_REL["bf16"], worst
 
 
+@pytest.mark.parametrize("Hq,hd,B,P", [(8, 128, 57, 20), (8, 64, 57, 33), (8, 128, 57, 96), (8, 64, 72, 127), (8, 128, 72, 160),
+                                       (10, 128, 64, 415)])
+def test_attention_decode_ring(Hq, hd, B, P):
+    """Many query rows, blocks through the ring of LDS stages: ranges shorter than the ring (1 to 3
+    blocks), one round and more (4, 5, 13 blocks, in one split), a last block that is partly
+    empty, row blocks of four rows and waves without any."""
+    worst, _, _ = attention_case("bf16", B, Hq, 2, hd, 64, P, 3, splits=1)
+    assert worst < ATT_REL["bf16"], worst
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,hd,P,t,plant", [
     # 8B headline shape at its last step: one key deep inside the last prefix split, one in the
     # last 32-key block of a candidate's last suffix page, one in a middle page
