@@ -47,8 +47,8 @@ bool tiled_shapes_ok(int M, int N, int K) {
   return N % 128 == 0 && K % 256 == 0;
 }
 
-// Many-row products on tiled operands all go to the one MFMA GEMM (it beats a 128 x 128-tile
-// kernel from 128 rows up, measured).
+// Many-row products on tiled operands all go to the one MFMA GEMM, which picks its tile by the
+// number of tiles the product has.
 static bool use_gemm256(int M, int N, int K, bool swiglu) { return M > 64 && gemm256_supported(M, N, K, swiglu); }
 
 int linear_auto_splits(int dtype, int M, int N, int K, int tiled) {
