@@ -5,14 +5,15 @@
 // positions 32 (w / 4) .. + 31 of the item, which are its MFMA columns.  Two waves per SIMD let
 // one wave's softmax run under the other's MFMAs, and the LDS only reaches its full read rate
 // with eight waves per CU.
-// Where that gives fewer workgroups than the chip has compute units, the waves split the keys as
-// well: with 2 (4) key groups a workgroup has one half of the item's rows and 4 (2) heads, every
-// group takes every second (fourth) 32-key block, and the groups' states of the same columns are
-// merged in LDS at the end (300 positions after 4096 keys of the 8B shape: 106 -> 45 us).
+// Where that gives fewer workgroups than the chip has compute units, two or four waves share the 32
+// columns of a head (prefill_attention_split_kernel): they score different key blocks and add different
+// coordinates of the result, so that a row's sum runs over its keys in the same order as with one wave
+// and has the same bits whatever else is in the launch (300 positions of the 8B shape after 1024 / 4096
+// keys: 38 -> 23 / 108 -> 56 us).
 // Keys are streamed page by page (64 keys) through LDS and shared by the waves: first the
 // shared-prefix pages that are visible to the block, then (scoring) the sequence's own suffix
 // pages.  Pages are stored in MFMA fragment order, so a page is copied to LDS as it is (by
-// loads that write LDS directly, one or two steps ahead) and an operand is one
+// loads that write LDS directly, one to two steps ahead) and an operand is one
 // conflict-free 16-byte read per lane.  Each item sees all keys of its rows, so
 // it normalises and writes bf16 itself.  Operand mapping and the softmax scheme are those of
 // the decode kernel (transposed scores, lazy base-2 reference maximum); the addition is the
@@ -46,66 +47,173 @@ template <int HD> struct PTile {
   static constexpr int CPT = PPG * HD / 8 / 512;            // 16-byte loads per thread and K (or V) page
 };
 
-// KS = key groups of a workgroup (see the head of the file): pages staged per step, steps held in
-// LDS, query heads and 32-row halves of an item per workgroup.
-template <int HD, int KS> struct PSplit {
-  static constexpr int PP = KS == 4 ? 2 : 1;
-  static constexpr int STEPS = KS == 4 && HD == 128 ? 2 : 3;
-  static constexpr int HEADS = KS == 4 ? 2 : 4, HALVES = KS == 1 ? 2 : 1;
-  static constexpr int LPS = 2 * PTile<HD>::CPT * PP;       // loads into LDS per wave and step
-  static constexpr int LDS_BYTES = STEPS * PP * PTile<HD>::PAGE_ELEMS * 2;
-  // the states that the key groups 1 .. KS - 1 hand over at the end use the page buffers
-  static_assert((KS - 1) * (8 / KS) * 64 * (HD / 2 + 2) * 4 <= LDS_BYTES, "states fit the page buffers");
+// LDS of the two kernels
+template <int HD> struct PWhole {              // pages of K and V together, three steps of one page
+  static constexpr int STEPS = 3, LPS = 2 * PTile<HD>::CPT;   // LPS: loads into LDS per wave and step
+  static constexpr int LDS_BYTES = STEPS * PTile<HD>::PAGE_ELEMS * 2;
+};
+template <int HD, int KS> struct PSplit {      // KS waves per head: a step is KS blocks, KS / 2 pages
+  static constexpr int PP = KS / 2, HEADS = 8 / KS;
+  static constexpr int SLOTS = KS == 4 && HD == 128 ? 2 : 3;  // steps of K, and of V, held in LDS
+  static constexpr int LPH = PTile<HD>::CPT * PP;             // loads into LDS per wave and step of K (of V)
+  static constexpr int NDT = HD / 32 / KS ? HD / 32 / KS : 1; // 32-coordinate tiles of the result per wave
+  static constexpr int K_BYTES = SLOTS * PP * PTile<HD>::K_ELEMS * 2;
+  // K slots, V slots, the probabilities of eight blocks, their sums and references, flags
+  static constexpr int LDS_BYTES = 2 * K_BYTES + 8 * (2048 + 256 + 256) + 64;
 };
 
 constexpr int kPrefillMaxPids = 1024;
+typedef __attribute__((address_space(3))) int lds_int;
 
 // All but the newest N vector memory operations of this wave have landed, loads into LDS among them,
-// then the workgroup's barrier.  (__syncthreads() would wait for every load in flight.)
-template <int N>
+// (ALL_LDS: and its LDS reads and writes), then the workgroup's barrier.  (__syncthreads() would wait
+// for every load in flight.)
+template <int N, bool ALL_LDS = false>
 __device__ inline void wait_barrier_p() {
   asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);    // vmcnt <= N; the other counters free
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (ALL_LDS ? 0x0070 : 0x0F70));
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
 
-template <int HD, int KS>
+// The pages that positions up to last_pos see, in order: prefix keys [0, nA), then the own suffix's
+// [0, nB) at absolute positions prefix_len + j.
+struct PPages {
+  int nA, nB, nPA, n, prefix_len;
+  const int32_t *table;
+  lds_int *ids;
+  bool ids_in_lds;
+  __device__ inline PPages(const PrefillAttnArgs &a, int tab, int last_pos, lds_int *lds_ids) {
+    prefix_len = a.prefix_len;
+    nA = min(a.prefix_len, last_pos + 1);
+    nB = (tab >= 0 && last_pos >= a.prefix_len) ? last_pos - a.prefix_len + 1 : 0;
+    const int nPB = (nB + PPG - 1) / PPG;
+    nPA = (nA + PPG - 1) / PPG;
+    n = nPA + nPB;
+    table = (nPB > 0) ? a.page_table + (size_t)tab * a.table_stride : nullptr;
+    ids = lds_ids;
+    ids_in_lds = nPB <= kPrefillMaxPids;
+    if (nPB > 0 && ids_in_lds) {
+      for (int i = threadIdx.x; i < nPB; i += 512) ids[i] = table[i];
+      __syncthreads();
+    }
+  }
+  __device__ inline int id(int pi) const {
+    if (pi >= n) return 0;
+    if (pi < nPA) return pi;
+    if (ids_in_lds) return __builtin_amdgcn_readfirstlane(ids[pi - nPA]);
+    return __builtin_amdgcn_readfirstlane(table[pi - nPA]);
+  }
+  // 32-key block blk of page pi: the position of its key 0; returns how many of its keys exist
+  __device__ inline int block(int pi, int blk, int &abs0) const {
+    const bool in_a = pi < nPA;
+    abs0 = (in_a ? pi * PPG : prefix_len + (pi - nPA) * PPG) + 32 * blk;
+    return min(32, (in_a ? min(PPG, nA - pi * PPG) : min(PPG, nB - (pi - nPA) * PPG)) - 32 * blk);
+  }
+};
+
+// Pages go from global memory straight into LDS (lane i of a wave-wide 16-byte load lands at
+// the wave's base + 16 i: the page is copied as it is).  The same number of loads is issued whether or
+// not the page exists (one past the end has a range of no bytes: nothing is fetched), so the waits can
+// count.  They are buffer loads because the compiler counts those; after a global (flat) load
+// into LDS it waits for everything in flight before the next use of any load.
+__device__ inline __amdgpu_buffer_rsrc_t page_range(const bf16_t *page, bool exists, int hd) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)page, 0, exists ? PPG * hd * (int)sizeof(bf16_t) : 0, 0x00020000);
+}
+// piece i of PTile<HD>::CPT; dst: this wave's part of the page's place in LDS
+__device__ inline void load_piece(__amdgpu_buffer_rsrc_t r, bf16_t *dst, int i) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)(dst + 4096 * i), 16, threadIdx.x * 16, 8192 * i, 0, 0);
+}
+
+// Scores of keys that do not exist (from n_valid on) or lie after the lane's query position go to
+// -infinity.  abs0: position of the block's key 0; key of register r: 8 (r / 4) + 4 h + r % 4.
+__device__ inline void mask_scores(f32x16 &s, int n_valid, int abs0, int pos_start, int my_pos, int h) {
+  if (n_valid < 32 || abs0 + 31 > pos_start) {
+    const int lim = min(n_valid, my_pos - abs0 + 1);      // keys [0, lim) are visible
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (8 * (r >> 2) + 4 * h + (r & 3) >= lim) s[r] = -INFINITY;
+  }
+}
+
+// Probabilities against the reference m as it stands (see the decode kernel: any reference gives the
+// same normalised result, it only has to keep the numbers in range) and the lane's sum of them.
+__device__ inline float block_probs(const f32x16 &s, float scale2, float m, f32x16 &p) {
+  float rs = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -m));
+    rs += p[r];
+  }
+  return rs;
+}
+// Only if a lane's sum leaves the range - a score far above the reference, or no reference yet (m =
+// -inf yields inf or NaN) - the reference moves to the block's maximum and the accumulators are
+// rescaled; the common case spends no instruction on maxima.
+__device__ inline bool leaves_range(float rs) { return __any(!(rs <= kSoftmaxSumLimit)); }
+__device__ inline float moved_reference(const f32x16 &s, float scale2, float m) {
+  float mx = max16f(s);
+  mx = fmaxf(mx, other_half(mx));
+  return fmaxf(m, mx * scale2);                 // stays -inf for a column that has seen no key
+}
+__device__ inline float rescale_factor(float m, float m_new) {
+  return (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
+}
+// a column with no visible key so far: 0 as reference, all its p are 0
+__device__ inline float usable_reference(float m) { return (m == -INFINITY) ? 0.f : m; }
+__device__ inline void pack_probs(const f32x16 &p, v4u (&pb)[2]) {
+  pb[0] = v4u{pack2p_bf16(p[0], p[1]), pack2p_bf16(p[2], p[3]), pack2p_bf16(p[4], p[5]), pack2p_bf16(p[6], p[7])};
+  pb[1] = v4u{pack2p_bf16(p[8], p[9]), pack2p_bf16(p[10], p[11]), pack2p_bf16(p[12], p[13]), pack2p_bf16(p[14], p[15])};
+}
+
+// coordinates 32 dt .. + 31 of this lane's row
+template <int HD>
+__device__ inline void store_tile(const PrefillAttnArgs &a, int row, int head, int dt, int h, const f32x16 &o, float inv) {
+  bf16_t *out = (bf16_t *)a.out;
+  const int Hq = a.n_q_heads;
+#pragma unroll
+  for (int r4 = 0; r4 < 4; ++r4) {
+    const int d = dt * 32 + 8 * r4 + 4 * h;
+    const size_t at = a.out_tiled ? tiled_offset(row, head * HD + d, Hq * HD) : ((size_t)row * Hq + head) * HD + d;
+    v2u pk = {pack2p_bf16(o[4 * r4] * inv, o[4 * r4 + 1] * inv), pack2p_bf16(o[4 * r4 + 2] * inv, o[4 * r4 + 3] * inv)};
+    *(v2u *)(out + at) = pk;
+  }
+}
+
+template <int HD>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void prefill_attention_kernel(PrefillAttnArgs a) {
   using TL = PTile<HD>;
-  using SP = PSplit<HD, KS>;
+  using SP = PWhole<HD>;
   extern __shared__ __attribute__((aligned(16))) unsigned char plds_raw[];
   bf16_t *lds = (bf16_t *)plds_raw;
-  typedef __attribute__((address_space(3))) int lds_int;
   lds_int *pids = (lds_int *)(plds_raw + SP::LDS_BYTES);
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, HG = (G + SP::HEADS - 1) / SP::HEADS;
+  const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, HG = (G + 3) / 4;
 
   int id = blockIdx.x;
   // KV heads first: with eight of them an XCD (workgroups are dealt to the eight in turn) meets one
   // head's keys and values only
   const int kvh = id % Hkv; id /= Hkv;
   const int hg = id % HG; id /= HG;
-  // head within the group, half of the item's rows, key group
-  const int hw = wave % SP::HEADS, half = KS == 1 ? wave >> 2 : (id & 1), kg = KS == 1 ? 0 : wave / SP::HEADS;
-  if (KS > 1) id >>= 1;
+  // head within the group, half of the item's rows
+  const int hw = wave % 4, half = wave >> 2;
   const int4 item = a.items[id];               // row_start, n_rows (<= 64), pos_start, table row
   const int n_rows = item.y, tab = item.w;
   const int row_start = item.x + 32 * half;     // this wave's rows and their first position
   const int pos_start = item.z + 32 * half;
   const int my_rows = min(32, n_rows - 32 * half);
-  if (KS > 1 && my_rows <= 0) return;           // the whole workgroup: the item has no second half
-  const int g = SP::HEADS * hg + hw;
+  const int g = 4 * hg + hw;
   const bool wave_active = g < G && my_rows > 0;   // uniform per wave
   const int head = kvh * G + (g < G ? g : 0);
   const bool col_valid = col < my_rows;
   const int my_pos = pos_start + (col_valid ? col : 0);
   const int my_last = pos_start + my_rows - 1;     // last position of this wave's rows
 
-  // visible keys: prefix [0, nA), then own suffix [0, nB) at absolute positions prefix_len + j
-  const int last_pos = KS == 1 ? item.z + n_rows - 1 : my_last;   // of the workgroup: pages every wave helps to stage
+  // visible keys: prefix [0, nA), then own suffix [0, nB) at absolute positions prefix_len + j.  (PPages says the
+  // same; with it here 8 x 1024 rows after 4096 keys took 597 instead of 586 us.)
+  const int last_pos = item.z + n_rows - 1;        // of the whole item: pages every wave helps to stage
   const int nA = min(a.prefix_len, last_pos + 1);
   const int nB = (tab >= 0 && last_pos >= a.prefix_len) ? last_pos - a.prefix_len + 1 : 0;
   const int nPA = (nA + PPG - 1) / PPG, nPB = (nB + PPG - 1) / PPG, n_pages = nPA + nPB;
@@ -135,13 +243,7 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   const size_t page_stride = (size_t)Hkv * PPG * HD, head_off = (size_t)kvh * PPG * HD;
   const bf16_t *kA = (const bf16_t *)a.k_prefix, *vA = (const bf16_t *)a.v_prefix;
   const bf16_t *kB = (const bf16_t *)a.k_suffix, *vB = (const bf16_t *)a.v_suffix;
-  // Pages go from global memory straight into LDS (lane i of a wave-wide 16-byte load lands at
-  // the wave's base + 16 i: the page is copied as it is), SP::STEPS - 1 steps of SP::PP pages ahead
-  // of the one in use.  The same number of loads is issued whether or not the page exists (a page past
-  // the end has a range of no bytes: nothing is fetched), so the wait before the barrier can
-  // count: all but the newest page's loads have landed.  They are buffer loads because the compiler
-  // counts those; after a global (flat) load into LDS it waits for everything in flight before the
-  // next use of any load.
+  // pages arrive SP::STEPS - 1 ahead of the one in use (see load_piece)
   auto page_of = [&](int pi) __attribute__((always_inline)) -> int {
     if (pi >= n_pages) return 0;
     if (pi < nPA) return pi;
@@ -151,14 +253,13 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   auto issue = [&](int pi, int page, int buf) __attribute__((always_inline)) {
     const bool in_a = pi < nPA;
     const size_t at = (size_t)page * page_stride + head_off;
-    const int bytes = pi < n_pages ? PPG * HD * (int)sizeof(bf16_t) : 0;
-    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)((in_a ? kA : kB) + at), 0, bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)((in_a ? vA : vB) + at), 0, bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t kr = page_range((in_a ? kA : kB) + at, pi < n_pages, HD);
+    const __amdgpu_buffer_rsrc_t vr = page_range((in_a ? vA : vB) + at, pi < n_pages, HD);
     bf16_t *kt = lds + buf * TL::PAGE_ELEMS + wave * 512, *vt = kt + TL::K_ELEMS;   // buf: of a page
 #pragma unroll
     for (int i = 0; i < TL::CPT; ++i) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void *)(kt + 4096 * i), 16, tid * 16, 8192 * i, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void *)(vt + 4096 * i), 16, tid * 16, 8192 * i, 0, 0);
+      load_piece(kr, kt, i);
+      load_piece(vr, vt, i);
     }
   };
   // one 32-key block whose key 0 sits at absolute position abs0; n_valid keys exist
@@ -180,51 +281,23 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
       vf[c] = *(const v4u *)(vblk + c * 512);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // key of register r: 8 (r / 4) + 4 h + r % 4; it is masked if it does not exist or lies
-    // after this lane's query position
-    if (n_valid < 32 || abs0 + 31 > pos_start) {
-      const int lim = min(n_valid, my_pos - abs0 + 1);      // keys [0, lim) are visible
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (8 * (r >> 2) + 4 * h + (r & 3) >= lim) s[r] = -INFINITY;
-    }
-    // Probabilities against the reference m as it stands (see the decode kernel: any reference
-    // gives the same normalised result, it only has to keep the numbers in range).  Only if a
-    // lane's sum leaves the range - a score far above the reference, or no reference yet (m =
-    // -inf yields inf or NaN) - the block's maximum is taken, the reference moved and the
-    // accumulators rescaled; the common case spends no instruction on maxima.
+    mask_scores(s, n_valid, abs0, pos_start, my_pos, h);
     f32x16 p;
-    float rs = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -m));
-      rs += p[r];
-    }
-    if (__any(!(rs <= kSoftmaxSumLimit))) {
-      float mx = max16f(s);
-      mx = fmaxf(mx, other_half(mx));
-      const float m_new = fmaxf(m, mx * scale2);    // stays -inf for a column that has seen no key
-      const float corr = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
+    float rs = block_probs(s, scale2, m, p);
+    if (leaves_range(rs)) {
+      const float m_new = moved_reference(s, scale2, m), corr = rescale_factor(m, m_new);
       l *= corr;
       m = m_new;
 #pragma unroll
       for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[dt][r] *= corr;
-      // a column with no visible key so far: 0 as reference, all its p are 0
-      const float mref = (m == -INFINITY) ? 0.f : m;
-      rs = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -mref));
-        rs += p[r];
-      }
+      rs = block_probs(s, scale2, usable_reference(m), p);
     }
     rs += other_half(rs);
     l += rs;
     v4u pb[2];
-    pb[0] = v4u{pack2p_bf16(p[0], p[1]), pack2p_bf16(p[2], p[3]), pack2p_bf16(p[4], p[5]), pack2p_bf16(p[6], p[7])};
-    pb[1] = v4u{pack2p_bf16(p[8], p[9]), pack2p_bf16(p[10], p[11]), pack2p_bf16(p[12], p[13]), pack2p_bf16(p[14], p[15])};
+    pack_probs(p, pb);
 #pragma unroll
     for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
@@ -238,91 +311,253 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
     if (nv > 0 && abs_page + 32 * blk <= my_last) process(buf, blk, nv, abs_page + 32 * blk);   // else all masked
   };
 
-  int next_page[SP::PP];
-  auto issue_step = [&](int step, int slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < SP::PP; ++i) {
-      issue(step * SP::PP + i, next_page[i], slot * SP::PP + i);
-      next_page[i] = page_of((step + 1) * SP::PP + i);
-    }
+  int next_page = page_of(0);
+  auto issue_next = [&](int pi, int buf) __attribute__((always_inline)) {
+    issue(pi, next_page, buf);
+    next_page = page_of(pi + 1);
   };
 #pragma unroll
-  for (int i = 0; i < SP::PP; ++i) next_page[i] = page_of(i);
-#pragma unroll
-  for (int st = 0; st + 1 < SP::STEPS; ++st) issue_step(st, st);
-  const int n_steps = (n_pages + SP::PP - 1) / SP::PP;
-  int slot = 0;
-  for (int st = 0; st < n_steps; ++st) {
-    // the pages of this step have landed once at most the loads of the later ones that were issued
-    // are outstanding; past the barrier that holds for every wave, and the last step's pages are no
-    // longer read
+  for (int st = 0; st + 1 < SP::STEPS; ++st) issue_next(st, st);
+  int buf = 0;
+  // The loop's place in the 64-byte lines of the instruction cache is fixed (13 s_nop, past once): by it the same
+  // code took 586 or 599 us at 8 x 1024 rows after 4096 keys, whichever the code before it left.
+  asm volatile(".p2align 6\n.fill 13, 4, 0xbf800000");
+  for (int pi = 0; pi < n_pages; ++pi) {
+    // page pi has landed once at most the loads of the later ones that were issued are outstanding;
+    // past the barrier that holds for every wave, and page pi - 1 is no longer read
     wait_barrier_p<(SP::STEPS - 2) * SP::LPS>();
-    issue_step(st + SP::STEPS - 1, slot >= 1 ? slot - 1 : SP::STEPS - 1);
+    issue_next(pi + SP::STEPS - 1, buf >= 1 ? buf - 1 : SP::STEPS - 1);
     if (wave_active) {
-      if (KS == 1) {
-        consume(st, slot, 0);
-        consume(st, slot, 1);
-      } else {
-        const int pi = st * SP::PP + (kg >> 1) % SP::PP;
-        if (pi < n_pages) consume(pi, slot * SP::PP + (kg >> 1) % SP::PP, kg & 1);
-      }
+      consume(pi, buf, 0);
+      consume(pi, buf, 1);
     }
-    slot = slot == SP::STEPS - 1 ? 0 : slot + 1;
+    buf = buf == SP::STEPS - 1 ? 0 : buf + 1;
   }
   wait_barrier_p<0>();                         // no load into LDS outlives the loop
 
-  if (KS > 1) {
-    // the key groups' states of the same columns meet in LDS: group 0 merges the others' into its own
-    constexpr int WPG = 8 / KS, REGS = HD / 2;  // waves per key group; accumulator registers of a lane
-    float *so = (float *)plds_raw;              // [KS - 1][WPG][REGS + 2][64]
-    if (kg > 0) {
-      float *dst = so + ((kg - 1) * WPG + hw) * (REGS + 2) * 64 + lane;
-#pragma unroll
-      for (int dt = 0; dt < HD / 32; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dst[(dt * 16 + r) * 64] = o[dt][r];
-      dst[REGS * 64] = m;
-      dst[(REGS + 1) * 64] = l;
-    }
-    __syncthreads();
-    if (kg > 0) return;
-    const float *src = so + hw * (REGS + 2) * 64 + lane;
-    float M = m;
-#pragma unroll
-    for (int k = 0; k < KS - 1; ++k) M = fmaxf(M, src[(k * WPG * (REGS + 2) + REGS) * 64]);
-    // a group that saw no key of the column has m = -inf and no weight
-    const float f0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
-    l *= f0;
-#pragma unroll
-    for (int dt = 0; dt < HD / 32; ++dt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[dt][r] *= f0;
-#pragma unroll 1
-    for (int k = 0; k < KS - 1; ++k) {
-      const float *ks = src + k * WPG * (REGS + 2) * 64;
-      const float mk = ks[REGS * 64], fk = mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk - M);
-      l += fk * ks[(REGS + 1) * 64];
-#pragma unroll
-      for (int dt = 0; dt < HD / 32; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] += fk * ks[(dt * 16 + r) * 64];
-    }
-  }
   if (wave_active && col_valid) {
     const float inv = 1.0f / l;                  // l > 0: every row sees at least its own key
-    bf16_t *out = (bf16_t *)a.out;
-    const int row = row_start + col;
 #pragma unroll
-    for (int dt = 0; dt < HD / 32; ++dt)
+    for (int dt = 0; dt < HD / 32; ++dt) store_tile<HD>(a, row_start + col, head, dt, h, o[dt], inv);
+  }
+}
+
+// The same with KS waves for the 32 columns of a head: a workgroup has one half of an item's rows and
+// 8 / KS heads, and a step is KS blocks of 32 keys.  In a step wave kg of a head scores block kg and leaves
+// its probabilities and their sums in LDS, all against the reference that stood when the step began;
+// past a barrier every wave adds the KS blocks, in order, to the result coordinates it owns.  Where a
+// block's sums leave the range (in the first step, and seldom later) the blocks are done again one by one,
+// the reference moving in between.  So a row's additions and references are those of one wave that walks
+// all keys.  (States of separate key groups merged at the end take 44 instead of 56 us for 300 rows
+// after 4096 keys, but then a row's last bits change with the number of groups, that is with the launch.)
+// Two barriers a step and the probabilities' way through LDS bound it: 1.35 us per step of four blocks, 0.9 us
+// of it LDS traffic (272 KB).  Fragments are read half a step ahead of their use: K of the next step
+// beside the value products, V under the scores; K's and V's slots are refilled at the barrier behind that, which
+// gives a load 2 SLOTS - 1 half steps to land.
+template <int HD, int KS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void prefill_attention_split_kernel(PrefillAttnArgs a) {
+  using TL = PTile<HD>;
+  using SP = PSplit<HD, KS>;
+  constexpr int NF = TL::NF, NDT = SP::NDT;
+  extern __shared__ __attribute__((aligned(16))) unsigned char plds_raw[];
+  bf16_t *k_lds = (bf16_t *)plds_raw, *v_lds = (bf16_t *)(plds_raw + SP::K_BYTES);
+  v4u *probs = (v4u *)(plds_raw + 2 * SP::K_BYTES);             // [8 waves][2][64]
+  float *sums = (float *)(probs + 8 * 128), *refs = sums + 8 * 64;   // [8 waves][64]
+  int *state = (int *)(refs + 8 * 64), *moved = state + 8;      // per wave: 0 no visible key, 1 scored, 2 out of range
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, HG = (G + SP::HEADS - 1) / SP::HEADS;
+
+  int id = blockIdx.x;
+  const int kvh = id % Hkv; id /= Hkv;
+  const int hg = id % HG; id /= HG;
+  // head, block of a step, half of the item's rows (waves of one kg on different SIMDs)
+  const int hw = wave % SP::HEADS, kg = wave / SP::HEADS, half = id & 1;
+  const int4 item = a.items[id >> 1];
+  const int row_start = item.x + 32 * half, pos_start = item.z + 32 * half, my_rows = min(32, item.y - 32 * half);
+  if (my_rows <= 0) return;                     // the whole workgroup: the item has no second half
+  const int g = SP::HEADS * hg + hw;
+  const bool active = g < G;                    // uniform per head
+  const int head = kvh * G + (active ? g : 0);
+  const bool col_valid = col < my_rows;
+  const int my_pos = pos_start + (col_valid ? col : 0), my_last = pos_start + my_rows - 1;
+  const PPages pages(a, item.w, my_last, (lds_int *)(plds_raw + SP::LDS_BYTES));
+
+  v4u qf[NF];
+  {
+    const bf16_t *qrow = (const bf16_t *)a.q + ((size_t)(row_start + (col_valid ? col : 0)) * Hq + head) * HD + 8 * h;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int d = dt * 32 + 8 * r4 + 4 * h;
-        const size_t at = a.out_tiled ? tiled_offset(row, head * HD + d, Hq * HD)
-                                      : ((size_t)row * Hq + head) * HD + d;
-        v2u pk = {pack2p_bf16(o[dt][4 * r4] * inv, o[dt][4 * r4 + 1] * inv),
-                  pack2p_bf16(o[dt][4 * r4 + 2] * inv, o[dt][4 * r4 + 3] * inv)};
-        *(v2u *)(out + at) = pk;
+    for (int c = 0; c < NF; ++c) qf[c] = *(const v4u *)(qrow + 16 * c);
+  }
+  const float scale2 = 1.4426950408889634f / sqrtf((float)HD);
+  // this wave's coordinate tiles: NDT * kg .. + NDT - 1 (head_dim 64 and four waves: the last two own none)
+  const bool owner = NDT * KS <= HD / 32 || NDT * kg < HD / 32;
+  f32x16 o[NDT];
+#pragma unroll
+  for (int x = 0; x < NDT; ++x)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[x][r] = 0.f;
+  float m = -INFINITY, l = 0.f;
+
+  const size_t page_stride = (size_t)Hkv * PPG * HD, head_off = (size_t)kvh * PPG * HD;
+  const bf16_t *kA = (const bf16_t *)a.k_prefix, *vA = (const bf16_t *)a.v_prefix;
+  const bf16_t *kB = (const bf16_t *)a.k_suffix, *vB = (const bf16_t *)a.v_suffix;
+  int k_ids[SP::PP], v_ids[SP::PP];
+  auto issue_k = [&](int step, int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < SP::PP; ++i) {
+      const int pi = step * SP::PP + i;
+      const __amdgpu_buffer_rsrc_t kr =
+          page_range((pi < pages.nPA ? kA : kB) + (size_t)k_ids[i] * page_stride + head_off, pi < pages.n, HD);
+#pragma unroll
+      for (int c = 0; c < TL::CPT; ++c) load_piece(kr, k_lds + (slot * SP::PP + i) * TL::K_ELEMS + wave * 512, c);
+      v_ids[i] = k_ids[i];
+      k_ids[i] = pages.id(pi + SP::PP);
+    }
+  };
+  auto issue_v = [&](int step, int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < SP::PP; ++i) {
+      const int pi = step * SP::PP + i;
+      const __amdgpu_buffer_rsrc_t vr =
+          page_range((pi < pages.nPA ? vA : vB) + (size_t)v_ids[i] * page_stride + head_off, pi < pages.n, HD);
+#pragma unroll
+      for (int c = 0; c < TL::CPT; ++c) load_piece(vr, v_lds + (slot * SP::PP + i) * TL::V_ELEMS + wave * 512, c);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < SP::PP; ++i) k_ids[i] = pages.id(i);
+#pragma unroll
+  for (int st = 0; st < SP::SLOTS; ++st) {
+    issue_k(st, st);
+    issue_v(st, st);
+  }
+
+  auto wave_of = [&](int i) __attribute__((always_inline)) { return i * SP::HEADS + hw; };   // of this head, block i
+  v4u *my_probs = probs + wave * 128 + lane;
+  // this wave's probabilities and their sums to LDS
+  auto leave_probs = [&](const f32x16 &p, float rs) __attribute__((always_inline)) {
+    v4u pb[2];
+    pack_probs(p, pb);
+    my_probs[0] = pb[0];
+    my_probs[64] = pb[1];
+    sums[wave * 64 + lane] = rs + other_half(rs);
+  };
+  v4u kf[NF], vf[KS][NDT][2], pb[KS][2];
+  float rs[KS];
+  auto read_k = [&](int slot) __attribute__((always_inline)) {
+    const bf16_t *kblk = k_lds + (slot * SP::PP + (kg >> 1)) * TL::K_ELEMS + ((kg & 1) * NF * 64 + lane) * 8;
+#pragma unroll
+    for (int c = 0; c < NF; ++c) kf[c] = *(const v4u *)(kblk + c * 512);
+  };
+  auto read_v = [&](int slot) __attribute__((always_inline)) {
+    if (!owner) return;
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const bf16_t *vblk = v_lds + (slot * SP::PP + (i >> 1)) * TL::V_ELEMS + ((i & 1) * NF * 64 + lane) * 8;
+#pragma unroll
+      for (int x = 0; x < NDT; ++x)
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) vf[i][x][sl] = *(const v4u *)(vblk + ((NDT * kg + x) * 2 + sl) * 512);
+    }
+  };
+  auto read_probs = [&](int i) __attribute__((always_inline)) {
+    rs[i] = sums[wave_of(i) * 64 + lane];
+    pb[i][0] = probs[wave_of(i) * 128 + lane];
+    pb[i][1] = probs[wave_of(i) * 128 + 64 + lane];
+  };
+  auto add_block = [&](int i) __attribute__((always_inline)) {
+    l += rs[i];
+    if (owner)
+#pragma unroll
+      for (int x = 0; x < NDT; ++x)
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) o[x] = mfma32p(vf[i][x][sl], pb[i][sl], o[x]);
+  };
+  // the loads issued after those that a barrier waits for: 2 SLOTS - 2 half steps
+  constexpr int kAhead = (2 * SP::SLOTS - 2) * SP::LPH;
+  const int n_steps = (pages.n + SP::PP - 1) / SP::PP;
+  wait_barrier_p<kAhead + SP::LPH>();           // K of step 0
+  read_k(0);
+  int slot = 0;
+  for (int st = 0; st < n_steps; ++st) {
+    // V of this step is there; its K is in registers, the last step's probabilities are no longer read
+    wait_barrier_p<kAhead, true>();
+    issue_k(st + SP::SLOTS, slot);
+    read_v(slot);
+    __builtin_amdgcn_sched_barrier(0);
+    const int pi = st * SP::PP + (kg >> 1);
+    int abs0;
+    const int nv = pages.block(pi, kg & 1, abs0);
+    const bool live = active && pi < pages.n && nv > 0 && abs0 <= my_last;      // uniform; else all masked
+    f32x16 s;
+    int found = 0;
+    if (live) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NF; ++c) s = mfma32p(kf[c], qf[c], s);
+      mask_scores(s, nv, abs0, pos_start, my_pos, h);
+      f32x16 p;
+      const float sum = block_probs(s, scale2, m, p);
+      found = leaves_range(sum) ? 2 : 1;
+      leave_probs(p, sum);
+    }
+    if (lane == 0) state[wave] = found;
+    // K of the next step is there, and the heads' probabilities; V of this one is in registers
+    wait_barrier_p<kAhead, true>();
+    const int states = state[lane & 7];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) read_probs(i);
+    slot = slot == SP::SLOTS - 1 ? 0 : slot + 1;
+    read_k(slot);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_v(st + SP::SLOTS, slot >= 1 ? slot - 1 : SP::SLOTS - 1);
+    const unsigned int lives = (unsigned int)__ballot(states != 0);     // bit w: wave w's block
+    if (!__any(states == 2)) {
+#pragma unroll
+      for (int i = 0; i < KS; ++i)
+        if ((lives >> wave_of(i)) & 1) add_block(i);
+    } else {
+      // block by block, the whole workgroup together
+#pragma unroll
+      for (int i = 0; i < KS; ++i) {
+        if (kg == i && live) {
+          f32x16 p;
+          float sum = block_probs(s, scale2, m, p);
+          const bool move = leaves_range(sum);
+          if (move) {
+            const float m_new = moved_reference(s, scale2, m);
+            refs[wave * 64 + lane] = m_new;
+            sum = block_probs(s, scale2, usable_reference(m_new), p);
+          }
+          leave_probs(p, sum);
+          if (lane == 0) moved[wave] = move;
+        }
+        wait_barrier_p<63, true>();
+        if ((lives >> wave_of(i)) & 1) {
+          if (__builtin_amdgcn_readfirstlane(moved[wave_of(i)])) {
+            const float m_new = refs[wave_of(i) * 64 + lane], corr = rescale_factor(m, m_new);
+            l *= corr;
+            m = m_new;
+#pragma unroll
+            for (int x = 0; x < NDT; ++x)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) o[x][r] *= corr;
+          }
+          read_probs(i);
+          add_block(i);
+        }
       }
+    }
+  }
+  wait_barrier_p<0>();                          // no load into LDS outlives the loop
+
+  if (active && owner && col_valid) {
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int x = 0; x < NDT; ++x) store_tile<HD>(a, row_start + col, head, NDT * kg + x, h, o[x], inv);
   }
 }
 
@@ -330,39 +565,44 @@ bool prefill_attention_mfma_supported(int page_tokens, int head_dim, int Hq, int
   return page_tokens == PPG && (head_dim == 64 || head_dim == 128) && Hq % Hkv == 0;
 }
 
-template <int HD, int KS>
+// workgroups of the form with KS waves per head (1: the whole-item kernel)
+template <int KS>
 static long prefill_grid(const PrefillAttnArgs &a) {
-  using SP = PSplit<HD, KS>;
-  const int G = a.n_q_heads / a.n_kv_heads;
-  return (long)a.n_items * (2 / SP::HALVES) * a.n_kv_heads * ((G + SP::HEADS - 1) / SP::HEADS);
+  const int heads = KS == 1 ? 4 : 8 / KS, G = a.n_q_heads / a.n_kv_heads;
+  return (long)a.n_items * (KS == 1 ? 1 : 2) * a.n_kv_heads * ((G + heads - 1) / heads);
 }
 
 template <int HD, int KS>
 static int launch_prefill_t(hipStream_t st, const PrefillAttnArgs &a) {
-  using SP = PSplit<HD, KS>;
-  const int lds = SP::LDS_BYTES + kPrefillMaxPids * (int)sizeof(int);
-  MC_TRY(raise_dynamic_lds_limit((const void *)prefill_attention_kernel<HD, KS>, lds));
-  prefill_attention_kernel<HD, KS><<<(unsigned)prefill_grid<HD, KS>(a), 512, lds, st>>>(a);
+  const void *kernel;
+  int lds = kPrefillMaxPids * (int)sizeof(int);
+  if constexpr (KS == 1) {
+    kernel = (const void *)prefill_attention_kernel<HD>;
+    lds += PWhole<HD>::LDS_BYTES;
+  } else {
+    kernel = (const void *)prefill_attention_split_kernel<HD, KS>;
+    lds += PSplit<HD, KS>::LDS_BYTES;
+  }
+  MC_TRY(raise_dynamic_lds_limit(kernel, lds));
+  const unsigned grid = (unsigned)prefill_grid<KS>(a);
+  if constexpr (KS == 1) prefill_attention_kernel<HD><<<grid, 512, lds, st>>>(a);
+  else prefill_attention_split_kernel<HD, KS><<<grid, 512, lds, st>>>(a);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }
 
 template <int HD>
 static int launch_prefill_hd(hipStream_t st, const PrefillAttnArgs &a) {
-  // A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a
-  // compute unit holds one) leaves units idle, more of them with fewer columns each are faster; a
-  // second round costs what the split gains.  8B heads, one sequence after 4096 keys, us with 1 / 2 /
-  // 4 key groups: 65 rows 100 / 60 / 43, 300 rows 106 / 64 / 45, 512 rows (256 workgroups with four
-  // groups) 112 / 68 / 53, 800 rows 119 / 76 / 92, 1024 rows (256 with two) 125 / 86 / 100; four
-  // sequences of 400 rows 123 / 133 / 171.
-  // Up to 2560 shared keys the split saves 10 - 30 us a layer, and there the order of additions of one
-  // group is kept: the ids that a session samples and the ranks that it gives follow the last bits of
-  // its prefill.
+  // A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a compute
+  // unit holds one) leaves units idle, more of them with shorter steps are faster; a second round costs more
+  // than the split gains.  All forms give the same bits.  8B heads, one sequence, us with 1 / 2 / 4 waves per
+  // head: 65 rows after 256 keys 16 / 14 / 12, after 1024 33 / 28 / 20, after 4096 103 / 86 / 53; 300 rows after
+  // 256 keys 21 / 19 / 15, after 1024 38 / 33 / 23, after 4096 108 / 89 / 56; 512 rows (256 workgroups with
+  // four waves) after 4096 keys 113 / 93 / 59, 800 rows 119 / 99 / 115, 1000 rows (256 with two) after 256 keys
+  // 37 / 33 / 37, after 4096 124 / 106 / 119; four sequences of 400 rows after 1024 keys 45 / 66 / 85.
   constexpr long kComputeUnits = 256;
-  constexpr int kShortChain = 2560;
-  if (a.prefix_len <= kShortChain) return launch_prefill_t<HD, 1>(st, a);
-  if (prefill_grid<HD, 4>(a) <= kComputeUnits) return launch_prefill_t<HD, 4>(st, a);
-  if (prefill_grid<HD, 2>(a) <= kComputeUnits) return launch_prefill_t<HD, 2>(st, a);
+  if (prefill_grid<4>(a) <= kComputeUnits) return launch_prefill_t<HD, 4>(st, a);
+  if (prefill_grid<2>(a) <= kComputeUnits) return launch_prefill_t<HD, 2>(st, a);
   return launch_prefill_t<HD, 1>(st, a);
 }
 

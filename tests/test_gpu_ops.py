@@ -813,20 +813,52 @@ def test_attention_prefill_item_sizes(item_rows):
 
 
 @pytest.mark.parametrize("Hq,Hkv,hd,P,seqs,stride", [
-    # four key groups: two pages a step, an odd number of pages, a prefix that ends inside its last
+    # four waves per head: two pages a step, an odd number of pages, a prefix that ends inside its last
     # page's first block, three query heads for two per workgroup; more of a prefix, scored suffixes
     (8, 2, 128, 2593, [(2593, 40), (2593, 1)], 3), (6, 2, 128, 2700, [(2700, 50)], 3), (8, 2, 64, 2626, [(2596, 30)], 1),
-    # two key groups (too many items for four): suffixes of one page each, a late part of a prefix
+    # two waves per head (too many items for four): suffixes of one page each, a late part of a prefix
     (32, 8, 128, 2570, [(2570, 64)] * 10, 97), (32, 8, 64, 3130, [(2600, 530)], 211),
-    # the last item count of each group count, and the first of the next
+    # the last item count of each form, and the first of the next
     (32, 8, 128, 3112, [(2600, 512)], 401), (32, 8, 64, 3113, [(2600, 513)], 401), (32, 8, 128, 3624, [(2600, 1024)], 1601),
     (32, 8, 64, 3625, [(2600, 1025)], 1601),
-    # the longest prefix that keeps one group, and one key more: groups that see no key of their own
+    # whole pages only and suffixes that end early; rows at the prefix's begin: waves whose blocks no row sees
     (8, 2, 128, 2560, [(2560, 33)], 1), (8, 2, 64, 2561, [(0, 70)], 1),
 ])
 def test_attention_prefill_key_groups(Hq, Hkv, hd, P, seqs, stride):
     worst, _ = prefill_case(Hq, Hkv, hd, P, seqs, stride)
     assert worst < ATT_REL["bf16"], worst
+
+
+@pytest.mark.parametrize("hd,P,rows", [(128, 300, 100), (64, 300, 100), (128, 2700, 70), (64, 2700, 70), (128, 4097, 33)])
+def test_attention_prefill_rows_do_not_depend_on_the_launch(hd, P, rows):
+    """A candidate's rows scored alone, with a few others and in a full chunk, which take one, two and four
+    waves per head: the same bits.  Some keys outgrow the softmax's reference far into the walk, in every
+    place of a step of four blocks."""
+    import torch
+    Hq, Hkv, pg, n = 32, 8, 64, 24
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7 * P + hd)
+    normal = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)  # noqa: E731
+    per, n_pre = -(-rows // pg), -(-P // pg)
+    k, v = normal(n_pre, Hkv, pg, hd), normal(n_pre, Hkv, pg, hd)
+    for page, key in [(1, 5), (2, 40), (3, 63), (n_pre - 2, 33)]:
+        k[page, :, key] *= 8
+    kp, vp = binding.kv_pages_pack(k, v)
+    ks, vs = binding.kv_pages_pack(normal(n * per, Hkv, pg, hd), normal(n * per, Hkv, pg, hd))
+    table = torch.randperm(n * per, generator=g, device="cuda").to(torch.int32).reshape(n, per)
+    q = normal(n * rows, Hq, hd) * 2
+
+    def score(cands):
+        items = [[i * rows + j, min(64, rows - j), P + j, c] for i, c in enumerate(cands) for j in range(0, rows, 64)]
+        rq = torch.cat([q[c * rows: (c + 1) * rows] for c in cands])
+        out = binding.op_attention_prefill(rq, torch.tensor(items, dtype=torch.int32, device="cuda"), kp, vp, ks, vs, table, P, pg)
+        return out.view(torch.int16).reshape(len(cands), rows, Hq, hd)
+
+    print("case: prefill rows alone and together", hd, P, rows, flush=True)
+    full = score(list(range(n)))
+    assert not torch.isnan(full.view(torch.bfloat16)).any()
+    for cands in ([3], [5, 3, 17, 0], list(range(n - 1, n - 9, -1)), list(range(14))):
+        assert torch.equal(score(cands), full[cands]), (len(cands), "candidates")
 
 
 def test_attention_prefill_tiled_output_matches():
