@@ -135,6 +135,29 @@ def test_decode_attention_plan_covers_every_block_and_fits_its_workspace(lib):
         assert p["n_parts"] * B * Hq * (hd + 2) * 4 <= ws, (B, Hq, Hkv, hd, P, t, S, p, ws)
 
 
+@pytest.mark.parametrize("rows,K,calls", [(1, 64, 1), (32, 2048, 1), (33, 4096, 1), (55, 5120, 1), (64, 128, 1), (300, 4096, 1),
+                                          (300, 14336, 3)])
+def test_tiled_outputs_cost_one_torch_call_and_have_zero_padding(rows, K, calls):
+    """The buffer of a tiled output: its size, zeros in the padding rows, and no more torch calls than a
+    plain zeroed tensor takes unless it is large."""
+    import torch
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Count(TorchDispatchMode):
+        seen = 0
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            Count.seen += 1
+            return func(*args, **(kwargs or {}))
+
+    with Count():
+        out = binding._tiled_out(rows, K, torch.bfloat16, "cpu")
+    assert Count.seen == calls
+    assert out.dtype == torch.bfloat16 and out.numel() * 2 == binding.load_library().mc_op_tiled_bytes(rows, K)
+    if rows % 32:
+        assert not binding.tiled_to_rowmajor(out, (rows + 31) // 32 * 32, K)[rows:].any()
+
+
 def test_bench_refuses_more_than_one_gpu_and_bad_step_counts():
     """bench.py is a one-GPU program: --gpus N > 1 ends with a message and a non-zero status before
     anything touches a device; so do step counts outside the workload."""
