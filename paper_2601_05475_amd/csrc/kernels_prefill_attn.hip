@@ -180,8 +180,11 @@ __device__ inline void store_tile(const PrefillAttnArgs &a, int row, int head, i
   }
 }
 
+// Waves per SIMD: two at head_dim 128 (190 registers); at head_dim 64 (125 registers, 52 KB of LDS) two workgroups
+// share a compute unit.  (With an upper bound of two there the second stays out: 8 x 1024 rows after 4096
+// keys, 32 / 8 heads of 64, 339 -> 390 us.)
 template <int HD>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, HD == 64 ? 4 : 2)))
 void prefill_attention_kernel(PrefillAttnArgs a) {
   using TL = PTile<HD>;
   using SP = PWhole<HD>;
@@ -319,9 +322,10 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
 #pragma unroll
   for (int st = 0; st + 1 < SP::STEPS; ++st) issue_next(st, st);
   int buf = 0;
-  // The loop's place in the 64-byte lines of the instruction cache is fixed (13 s_nop, past once): by it the same
-  // code took 586 or 599 us at 8 x 1024 rows after 4096 keys, whichever the code before it left.
-  asm volatile(".p2align 6\n.fill 13, 4, 0xbf800000");
+  // The loop's place among the 32-byte lines of the instruction fetch is fixed here (by s_nop, passed once): left to
+  // the code before it, the same loop took 586 or 599 us at 8 x 1024 rows after 4096 keys, and at head_dim 64
+  // 76 or 78 us at 2 x 607 rows after 3418.
+  asm volatile(".p2align 5\n.fill %0, 4, 0xbf800000" ::"i"(HD == 128 ? 3 : 0));
   for (int pi = 0; pi < n_pages; ++pi) {
     // page pi has landed once at most the loads of the later ones that were issued are outstanding;
     // past the barrier that holds for every wave, and page pi - 1 is no longer read

@@ -3,6 +3,7 @@ sizing / validation code behaves (no GPU work is launched here)."""
 import ctypes as C
 import os
 import re
+import struct
 
 import pytest
 
@@ -156,6 +157,35 @@ def test_tiled_outputs_cost_one_torch_call_and_have_zero_padding(rows, K, calls)
     assert out.dtype == torch.bfloat16 and out.numel() * 2 == binding.load_library().mc_op_tiled_bytes(rows, K)
     if rows % 32:
         assert not binding.tiled_to_rowmajor(out, (rows + 31) // 32 * 32, K)[rows:].any()
+
+
+def _vgprs_allocated():
+    """{kernel name: vector registers that a wave of it is given}, from the kernel descriptors of the library."""
+    blob, out, at = open(binding.LIB_PATH, "rb").read(), {}, 0
+    while (at := blob.find(b"\x7fELF\x02\x01\x01\x40", at + 1)) > 0:           # the device code objects inside
+        shoff, = struct.unpack_from("<Q", blob, at + 40)
+        shsize, shnum = struct.unpack_from("<HH", blob, at + 58)
+        heads = [struct.unpack_from("<IIQQQQIIQQ", blob, at + shoff + i * shsize) for i in range(shnum)]
+        for _, kind, _, _, off, size, link, _, _, entry in heads:
+            if kind != 11:                                                          # dynamic symbols
+                continue
+            names = at + heads[link][4]
+            for sym in range(at + off, at + off + size, entry):
+                name, _, _, sec, value, _ = struct.unpack_from("<IBBHQQ", blob, sym)
+                text = blob[names + name: blob.index(b"\0", names + name)].decode()
+                if text.endswith(".kd") and sec < shnum:
+                    kd = at + heads[sec][4] + value - heads[sec][3]
+                    out[text[:-3]] = ((struct.unpack_from("<I", blob, kd + 48)[0] & 63) + 1) * 8
+    return out
+
+
+def test_prefill_attention_leaves_room_for_a_second_workgroup(lib):
+    """512 registers per lane and SIMD: at head_dim 64 two workgroups of eight waves share a compute unit, and
+    a bound on the waves per SIMD must not take that from them."""
+    regs = {k: v for k, v in _vgprs_allocated().items() if "prefill_attention_kernelILi64E" in k}
+    assert regs
+    for name, n in regs.items():
+        assert 512 // n >= 4, (name, n)
 
 
 def test_bench_refuses_more_than_one_gpu_and_bad_step_counts():
