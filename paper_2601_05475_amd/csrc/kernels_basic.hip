@@ -2,6 +2,8 @@
 // tiled linear layer, a generic attention kernel, sampling, reward scoring.
 // They serve every dtype and shape; the bf16 MFMA kernels in kernels_mfma.hip take over
 // the large contractions when the shape allows.
+#include <stddef.h>
+
 #include "common.h"
 
 namespace mc {
@@ -718,11 +720,13 @@ __device__ inline void scan_row(const float *row, int V, F f) {
 struct SampleShared {
   unsigned long long sel[MC_MAX_TOP_K];
   float ev[MC_MAX_TOP_K];
-  unsigned int hist[2048];
+  alignas(16) unsigned int hist[2048];
   unsigned long long scratch64[16];
   unsigned int scratch32[16];
   unsigned int s_bin, s_above, s_cnt, s_cnt2;
 };
+// group_select reads the groups' maxima four at a time
+static_assert(alignof(SampleShared) >= 16 && offsetof(SampleShared, hist) % 16 == 0, "hist is read by 16-byte loads");
 
 // Threshold selection of the k largest keys of the elements `scan` walks (224 < k <= 1024, at least
 // 4096 elements, every thread sees some and no two threads see the same): pass 1 takes every
