@@ -1100,7 +1100,7 @@ __device__ inline const unsigned long long *group_select(Scan scan, float temper
 // and LDS round trips and barriers, so the steps of that chain were taken out: a second pass over
 // the row, a histogram, a bitonic sort, two serial walks over LDS by one thread.  Top 50 of 8 x 32000:
 // 25.6 -> 10.1 us, 4 x 4096: 20 -> 8.2 us, 32 x 128256 from lists: 24 -> 10 us, from whole rows (wall
-// time) 39 -> 17 us; top 200 of 64 x 152064: 87 -> 41 us; arg max of 64 x 152064: 54 -> 24 us.
+// time) 39 -> 17 us; top 200 of 64 x 152064: 87 -> 41 us; arg max of 64 x 152064: 54 -> 16 us.
 constexpr int kTopListLen = 4, kTopListMaxK = 64;
 __global__ __launch_bounds__(1024) void sample_kernel(
     int V, const float *__restrict__ logits, size_t row_stride, const uint2 *__restrict__ top,
@@ -1121,10 +1121,30 @@ __global__ __launch_bounds__(1024) void sample_kernel(
         best = key > best ? key : best;
       }
     } else {
-      scan_row(row, V, [&](bool ok, float z, int v) {
-        const unsigned long long key = ok ? sample_key(z, v) : 0ull;
+      // 16-byte loads, eight in flight, past the end the last vector again (the same keys); single loads for the
+      // rest and for rows that are not 16-byte aligned, where scan_row's would go one at a time
+      constexpr int NB = 8;
+      const int V4 = (((uintptr_t)row & 15) == 0) ? V / 4 : 0;
+      auto take = [&](float z, int v) {
+        const unsigned long long key = sample_key(z, v);
         best = key > best ? key : best;
-      });
+      };
+      for (int g0 = 0; g0 < V4; g0 += NB * 1024) {
+        float4 z[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          if (g0 + j * 1024 < V4) z[j] = ((const float4 *)row)[min(g0 + j * 1024 + tid, V4 - 1)];
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          if (g0 + j * 1024 < V4) {
+            const int v = 4 * min(g0 + j * 1024 + tid, V4 - 1);
+            take(z[j].x, v);
+            take(z[j].y, v + 1);
+            take(z[j].z, v + 2);
+            take(z[j].w, v + 3);
+          }
+      }
+      for (int v = 4 * V4 + tid; v < V; v += 1024) take(row[v], v);
     }
     best = block_max_u64(best, sh.scratch64);
     if (tid == 0) {
