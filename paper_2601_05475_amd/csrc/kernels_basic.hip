@@ -1013,6 +1013,46 @@ struct ListScan {
   }
 };
 
+// Cuts a list of n keys (256 <= n <= MC_MAX_TOP_K) down to those that can be among the k <= 224 largest: the first
+// step of group_select once more, on the list, where the k-th largest of the maxima of 256 groups bounds the
+// k-th largest key from below.  Rows whose largest values lie together (in neighbouring threads, so in few
+// groups) leave up to 4096 keys here, and sorting them is what that would cost: top 50 of 8 x 32000 rising
+// values 36 us sorted, 12.7 cut; top 200 of 64 x 32000 random ones, 389 keys on average, 23.7 either way.
+// Returns how many are left in sh.sel.
+__device__ inline int cut_list(int n, int k, SampleShared &sh) {
+  const int tid = threadIdx.x;
+  constexpr int PER = MC_MAX_TOP_K / 1024;
+  unsigned long long mine[PER];
+  unsigned int top = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    mine[j] = tid + 1024 * j < n ? sh.sel[tid + 1024 * j] : 0ull;
+    top = max(top, (unsigned int)(mine[j] >> 32));
+  }
+  sh.hist[tid] = top;
+  if (tid == 0) { sh.s_cnt = 0; sh.s_bin = 0xFFFFFFFFu; }
+  __syncthreads();
+  // neighbours in the list, which may be neighbours in the row, fall into different groups
+  if (tid < 256) sh.hist[1024 + tid] = max(max(sh.hist[tid], sh.hist[tid + 256]), max(sh.hist[tid + 512], sh.hist[tid + 768]));
+  __syncthreads();
+  const unsigned int v = sh.hist[1024 + (tid >> 2)];
+  int gt = 0;
+#pragma unroll 4
+  for (int j = 0; j < 16; ++j) {
+    const uint4 u = *(const uint4 *)&sh.hist[1024 + (4 * j + (tid & 3)) * 4];
+    gt += (u.x > v) + (u.y > v) + (u.z > v) + (u.w > v);
+  }
+  gt += __shfl_xor(gt, 1, 64);
+  gt += __shfl_xor(gt, 2, 64);
+  if ((tid & 3) == 0 && gt < k) atomicMin(&sh.s_bin, v);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (mine[j] != 0 && (unsigned int)(mine[j] >> 32) >= sh.s_bin) sh.sel[atomicAdd(&sh.s_cnt, 1u)] = mine[j];
+  __syncthreads();
+  return (int)sh.s_cnt;
+}
+
 // Selection of the k <= kGroupSelectMaxK largest keys, in order: the threads form n_g = 128 groups of
 // eight (k <= 64) or 256 of four, and the k-th largest of the groups' maxima, L, is a lower bound of
 // the k-th largest value (k distinct elements are >= L), a tight one: with the largest values spread at
@@ -1056,7 +1096,7 @@ __device__ inline const unsigned long long *group_select(Scan scan, float temper
   // a value below this cannot reach L after the division, as in threshold_select
   scan.above(z_l - fabsf(z_l) * 3.8147e-06f - 1e-30f, sh);
   __syncthreads();
-  const int n = (int)sh.s_cnt;
+  int n = (int)sh.s_cnt;
   if (n < k || n > MC_MAX_TOP_K) return nullptr;
   last_ob = 0;
   for (int i = tid; i < n; i += 1024) {            // listed values become keys
@@ -1067,6 +1107,7 @@ __device__ inline const unsigned long long *group_select(Scan scan, float temper
     sh.sel[i] = key;
   }
   __syncthreads();
+  if (n > kRankMax) n = cut_list(n, k, sh);
   if (n > kRankMax) {
     sort_selected(n, sh);
     return sh.sel;

@@ -427,6 +427,26 @@ def test_sample_group_selection(V, k):
         check_sampler_on_logits(lg[b], T, k, us[b], toks[b], topk[b])
 
 
+@pytest.mark.parametrize("k,c", [(2, 385), (50, 384), (50, 385), (50, 1024), (200, 1500), (224, 385), (224, 4096)])
+def test_sample_clustered_rows(k, c):
+    """The candidate list cut down a second time: c large values side by side in falling, rising and random
+    order, and in two values only (more ties than the cut can part).  Ids bit-exact."""
+    import torch
+    V, T = 32000, 0.7
+    lg = np.full((5, V), -50.0, np.float32) + rnd(540, (5, V), 0.1)
+    big = np.linspace(1.0, 4.0, c, dtype=np.float32)
+    for b, x in enumerate((big, big[::-1], np.random.default_rng(k + c).permutation(big), np.where(np.arange(c) % 3 == 0, 2.0, 1.5))):
+        at = 4096 * b + 8
+        lg[b, at: at + c] = x
+    lg[4, 17: 17 + 6 * c: 6] = big                      # spread out: every sixth place
+    us = synth.uniforms(541, 1, (5,))
+    print("case: sample clustered", k, c, flush=True)
+    toks, topk = binding.op_sample(torch.from_numpy(lg).cuda(), T, k, torch.from_numpy(us).cuda(), want_topk=True)
+    toks, topk = toks.cpu().numpy(), topk.cpu().numpy()
+    for b in range(5):
+        check_sampler_on_logits(lg[b], T, k, us[b], toks[b], topk[b])
+
+
 def _top4_per_group(row):
     """Reference for the LM head's lists: ids of the four largest of every 64 consecutive logits
     under (value descending, id ascending)."""
