@@ -502,9 +502,16 @@ template <> __device__ inline float4 load4<bf16_t>(const bf16_t *p) {
 
 constexpr int kAttnWaves = 4;
 
-// V4: head_dim and page_tokens are multiples of 4 and the pools are aligned for loads of four
-// elements (K in both layouts, V in quads of keys)
-template <typename T, bool V4>
+// x of lane t, t uniform: by way of scalar registers, no trip through LDS
+__device__ inline uint32_t of_lane(uint32_t x, int t) { return __builtin_amdgcn_readlane(x, t); }
+__device__ inline unsigned long long of_lane(unsigned long long x, int t) {
+  return ((unsigned long long)of_lane((uint32_t)(x >> 32), t) << 32) | of_lane((uint32_t)x, t);
+}
+
+// K4: head_dim is a multiple of 4 and the pools are aligned for loads of four elements (a key's coordinates lie
+// together by fours in both layouts); V4: page_tokens is one as well (quads of keys).  With K by single
+// loads, 64 rows x 16 heads of 64, 220 keys in pages of 2 took 53 us, by fours 28.
+template <typename T, bool K4, bool V4>
 __global__ __launch_bounds__(64 * kAttnWaves) void attention_generic_kernel(AttnArgs a) {
   constexpr int MAXD = 4;   // head_dim <= 256
   __shared__ __attribute__((aligned(16))) float qs[256];
@@ -540,12 +547,15 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attention_generic_kernel(Attn
     const T *kp = (const T *)(in_prefix ? a.k_prefix : a.k_suffix) + base;
     const T *vpool = (const T *)(in_prefix ? a.v_prefix : a.v_suffix);
     float dot = 0.f;
-    if (V4) {
+    if (K4) {
 #pragma unroll 4
       for (int i = 0; i < hd; i += 4) {
         const float4 k4 = load4<T>(kp + k_elem_offset(off, i, pg, hd)), q4 = *(const float4 *)(qs + i);
         dot += q4.x * k4.x; dot += q4.y * k4.y; dot += q4.z * k4.z; dot += q4.w * k4.w;
       }
+    } else if (!kv_fragment_layout(pg, hd)) {
+      const T *kr = kp + (size_t)off * hd;
+      for (int i = 0; i < hd; ++i) dot += qs[i] * Cvt<T>::to_f32(kr[i]);
     } else {
       for (int i = 0; i < hd; ++i) dot += qs[i] * Cvt<T>::to_f32(kp[k_elem_offset(off, i, pg, hd)]);
     }
@@ -567,8 +577,8 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attention_generic_kernel(Attn
         // not taken
 #pragma unroll 4
         for (int t = 0; t < nblk; t += 4) {
-          const size_t vb = __shfl((unsigned long long)base, t, 64);
-          const int vo = __shfl(off, t, 64);
+          const size_t vb = of_lane((unsigned long long)base, t);
+          const int vo = of_lane((uint32_t)off, t);
           const float4 w4 = *(const float4 *)(&ps[wave][t]);
           if (d < hd) {
             const float4 v4 = load4<T>(vpool + vb + v_elem_offset(vo, d, pg, hd));
@@ -579,9 +589,10 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attention_generic_kernel(Attn
           }
         }
       } else {
+#pragma unroll 4
         for (int t = 0; t < nblk; ++t) {
-          const size_t vb = __shfl((unsigned long long)base, t, 64);
-          const int vo = __shfl(off, t, 64);
+          const size_t vb = of_lane((unsigned long long)base, t);
+          const int vo = of_lane((uint32_t)off, t);
           if (d < hd) acc += ps[wave][t] * Cvt<T>::to_f32(vpool[vb + v_elem_offset(vo, d, pg, hd)]);
         }
       }
@@ -614,10 +625,11 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attention_generic_kernel(Attn
 template <typename T>
 static void launch_attention_generic_t(hipStream_t st, const AttnArgs &a) {
   const uintptr_t pools = (uintptr_t)a.k_prefix | (uintptr_t)a.v_prefix | (uintptr_t)a.k_suffix | (uintptr_t)a.v_suffix;
-  const bool v4 = a.head_dim % 4 == 0 && a.page_tokens % 4 == 0 && pools % (4 * sizeof(T)) == 0;
+  const bool k4 = a.head_dim % 4 == 0 && pools % (4 * sizeof(T)) == 0;
   const dim3 grid(a.rows, a.n_q_heads);
-  if (v4) attention_generic_kernel<T, true><<<grid, 64 * kAttnWaves, 0, st>>>(a);
-  else attention_generic_kernel<T, false><<<grid, 64 * kAttnWaves, 0, st>>>(a);
+  if (k4 && a.page_tokens % 4 == 0) attention_generic_kernel<T, true, true><<<grid, 64 * kAttnWaves, 0, st>>>(a);
+  else if (k4) attention_generic_kernel<T, true, false><<<grid, 64 * kAttnWaves, 0, st>>>(a);
+  else attention_generic_kernel<T, false, false><<<grid, 64 * kAttnWaves, 0, st>>>(a);
 }
 
 int launch_attention_generic(hipStream_t st, int dtype, const AttnArgs &a) {
