@@ -4,6 +4,8 @@
 // the large contractions when the shape allows.
 #include <stddef.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace mc {
@@ -333,9 +335,24 @@ __global__ __launch_bounds__(256) void linear_few_rows_kernel(
     }
 }
 
-// Up to 32 rows, K in whole 16-byte pieces and pointers that allow them.
-static bool few_rows_ok(int dtype, int M, int K, const void *a, const void *w, const void *w2) {
-  return M <= 32 && K % (dtype == MC_F32 ? 4 : 8) == 0 && (((uintptr_t)a | (uintptr_t)w | (uintptr_t)w2) & 15) == 0;
+// Up to 32 rows, K in whole 16-byte pieces and pointers that allow them, and where it is the faster of the two
+// by these estimates (us).  Here a wave pays for its start, for its sums' way across the lanes and for every
+// 64 pieces of K it passes, full or not; the tiled kernel walks slabs of 16, 1.6 us each up to one workgroup per
+// compute unit and more as they pile up.  Many rows, wide N and short or split K go to the tiles.  Fitted (what it
+// chooses is at most 15 % off the better one) to
+// fp32 and bf16, 4 to 32 rows, N 256 to 65536, K 256 to 4096, 1 to 16 splits; us tiles / here:
+//   fp32:  4 x 256 x 688 34 / 3.2; 32 x 4096 x 4096 418 / 83, in 4 splits 110 / 77, in 16 57 / 128;
+//          32 x 4096 x 256 in 4 splits 9 / 36; 16 x 14336 x 4096 403 / 140; 24 x 32000 x 1024 134 / 116, 32 rows 140 / 155
+//   bf16:  32 x 32000 x 4096 548 / 401, in 4 splits of K 2048 175 / 264; SwiGLU 32 x 14336 x 4096 801 / 241,
+//          32 x 65536 x 512 174 / 262
+static bool few_rows_ok(int dtype, int M, int N, int K, int kps, int n_splits, const void *a, const void *w, const void *w2) {
+  const int v = dtype == MC_F32 ? 4 : 8;
+  if (M > 32 || K % v || (((uintptr_t)a | (uintptr_t)w | (uintptr_t)w2) & 15)) return false;
+  const bool swiglu = w2 != nullptr;
+  const double waves = (double)((M + 7) / 8) * N * n_splits * (M <= 4 ? 0.6 : 1.0), passes = (kps + 64 * v - 1) / (64 * v);
+  const double here = waves * (swiglu ? 4.0e-4 + 4.0e-4 * passes : 2.3e-4 + 3.0e-4 * passes);
+  const double slab = std::max(1.6, 0.95 + 0.0024 * ((N + 63) / 64) * n_splits) * (swiglu ? 1.9 : 1.0);
+  return here <= kps / 16.0 * slab;
 }
 
 template <typename T, bool SWIGLU>
@@ -353,7 +370,7 @@ int launch_linear_generic(hipStream_t st, int dtype, int M, int N, int K, const 
   if (M <= 0 || N <= 0) return MC_OK;
   int kps = (K + n_splits - 1) / n_splits;
   kps = (kps + 15) / 16 * 16;
-  if (few_rows_ok(dtype, M, K, a, w, nullptr)) {
+  if (few_rows_ok(dtype, M, N, K, kps, n_splits, a, w, nullptr)) {
     if (dtype == MC_F32) launch_few_rows<float, false>(st, M, N, K, kps, n_splits, a, w, nullptr, out, nullptr);
     else launch_few_rows<bf16_t, false>(st, M, N, K, kps, n_splits, a, w, nullptr, out, nullptr);
     MC_HIP(hipGetLastError());
@@ -373,7 +390,7 @@ int launch_linear_generic(hipStream_t st, int dtype, int M, int N, int K, const 
 int launch_linear_swiglu_generic(hipStream_t st, int dtype, int M, int N, int K, const void *a,
                                  const void *wg, const void *wu, void *out) {
   if (M <= 0 || N <= 0) return MC_OK;
-  if (few_rows_ok(dtype, M, K, a, wg, wu)) {
+  if (few_rows_ok(dtype, M, N, K, K, 1, a, wg, wu)) {
     if (dtype == MC_F32) launch_few_rows<float, true>(st, M, N, K, K, 1, a, wg, wu, nullptr, out);
     else launch_few_rows<bf16_t, true>(st, M, N, K, K, 1, a, wg, wu, nullptr, out);
     MC_HIP(hipGetLastError());

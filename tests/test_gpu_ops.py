@@ -62,6 +62,8 @@ def test_linear(dtype, M, N, K, S):
 @pytest.mark.parametrize("dtype,M,N,K,S", [
     ("f32", 1, 5, 4, 1), ("f32", 4, 256, 688, 2), ("f32", 5, 66, 260, 1), ("f32", 9, 7, 1028, 3), ("f32", 32, 130, 512, 4),
     ("bf16", 3, 9, 8, 1), ("bf16", 8, 33, 520, 1), ("bf16", 17, 64, 1032, 2), ("f32", 2, 6, 20, 3),
+    # few rows that go to the tiles: many waves with little of K each
+    ("f32", 32, 4096, 256, 4), ("bf16", 16, 4100, 264, 4), ("f32", 9, 4096, 1024, 16),
 ])
 def test_linear_few_rows_generic(dtype, M, N, K, S):
     test_linear(dtype, M, N, K, S)
