@@ -674,6 +674,39 @@ def test_linear_qkv_rope_few_hundred_rows(rows, Hq, Hkv, hd, K):
     test_linear_qkv_rope_fused(rows, Hq, Hkv, hd, K)
 
 
+def test_many_row_gemm_forms_give_the_same_bits():
+    """Rows alone (128 x 32 tiles), with more rows (128 x 64 and 128 x 128) and in a chunk (256 x 128): the
+    same bits in every output form, and every form twice."""
+    import torch
+    N, K, rows = 4096, 768, (100, 300, 600, 3000)
+    w = binding.op_pack_tiled(to_dev(rnd(550, (N, K), 0.05), "bf16")[0])
+    w2 = binding.op_pack_tiled(to_dev(rnd(551, (N, K), 0.05), "bf16")[0])
+    Hq, Hkv, hd, pg = 16, 8, 128, 64                    # (Hq + 2 Hkv) hd = N
+    a = to_dev(rnd(552, (rows[-1], K)), "bf16")[0]
+    x0 = to_dev(rnd(553, (rows[-1], N)), "f32")[0]
+
+    def outputs(M):
+        am = binding.op_pack_tiled(a[:M].contiguous())
+        at = torch.arange(M, dtype=torch.int32, device="cuda")
+        kp = torch.zeros((-(-M // pg), Hkv, pg * hd), dtype=torch.bfloat16, device="cuda")
+        vp = torch.zeros_like(kp)
+        q = binding.op_linear_qkv_rope(am, w, M, K, at, at // pg, at % pg, Hq, Hkv, hd, pg, 1.0e4, M, kp, vp)
+        act = binding.op_linear_swiglu(am, w, w2, tiled_shape=(M, N, K))
+        out = [binding.op_linear(am, w, 1, tiled_shape=(M, N, K))[0], binding.op_linear_accumulate(am, w, x0[:M].clone(), (M, N, K)),
+               binding.tiled_to_rowmajor(act, M, N), q] + list(binding.kv_pages_unpack(kp, vp, pg, hd))
+        out[4:] = [t.transpose(1, 2).reshape(-1, Hkv, hd)[:M] for t in out[4:]]
+        return out
+
+    names = ("sums", "residual", "swiglu", "queries", "keys", "values")
+    full = outputs(rows[-1])
+    for M in rows:
+        print("case: GEMM forms", M, flush=True)
+        one, two = outputs(M), outputs(M)
+        for name, x, y, z in zip(names, one, two, full):
+            assert torch.equal(x, y), (name, M, "run to run")
+            assert torch.equal(x, z[:M]), (name, M)
+
+
 def test_scoring_size_gemms_on_sampled_rows():
     """The many-row GEMMs at the sizes one scoring chunk of the 8B shape launches (8192 rows):
     gate/up + SwiGLU 8192 x 14336 x 4096, down with the residual update 8192 x 4096 x 14336, QKV
@@ -878,8 +911,10 @@ def test_attention_prefill_rows_do_not_depend_on_the_launch(hd, P, rows):
 
     print("case: prefill rows alone and together", hd, P, rows, flush=True)
     full = score(list(range(n)))
+    assert torch.equal(score(list(range(n))), full)
     assert not torch.isnan(full.view(torch.bfloat16)).any()
     for cands in ([3], [5, 3, 17, 0], list(range(n - 1, n - 9, -1)), list(range(14))):
+        assert torch.equal(score(cands), score(cands))
         assert torch.equal(score(cands), full[cands]), (len(cands), "candidates")
 
 
