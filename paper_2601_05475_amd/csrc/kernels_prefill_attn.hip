@@ -9,7 +9,7 @@
 // columns of a head (prefill_attention_split_kernel): they score different key blocks and add different
 // coordinates of the result, so that a row's sum runs over its keys in the same order as with one wave
 // and has the same bits whatever else is in the launch (300 positions of the 8B shape after 1024 / 4096
-// keys: 38 -> 23 / 108 -> 56 us).
+// keys: 38 -> 22 / 108 -> 55 us).
 // Keys are streamed page by page (64 keys) through LDS and shared by the waves: first the
 // shared-prefix pages that are visible to the block, then (scoring) the sequence's own suffix
 // pages.  Pages are stored in MFMA fragment order, so a page is copied to LDS as it is (by
@@ -349,10 +349,10 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
 // The same with KS waves for the 32 columns of a head: a workgroup has one half of an item's rows and
 // 8 / KS heads, and a step is KS blocks of 32 keys.  In a step wave kg of a head scores block kg and leaves
 // its probabilities and their sums in LDS, all against the reference that stood when the step began;
-// past a barrier every wave adds the KS blocks, in order, to the result coordinates it owns.  Where a
-// block's sums leave the range (in the first step, and seldom later) the blocks are done again one by one,
-// the reference moving in between.  So a row's additions and references are those of one wave that walks
-// all keys.  (States of separate key groups merged at the end take 44 instead of 56 us for 300 rows
+// past a barrier every wave adds the KS blocks, in order, to the result coordinates it owns.  The first step
+// waits for block 0's maximum instead; where a block's sums leave the range later, which is seldom, the blocks
+// are done again one by one, the reference moving in between.  So a row's additions and references are those
+// of one wave that walks all keys.  (States of separate key groups merged at the end take 44 instead of 55 us for 300 rows
 // after 4096 keys, but then a row's last bits change with the number of groups, that is with the launch.)
 // Two barriers a step and the probabilities' way through LDS bound it: 1.35 us per step of four blocks, 0.9 us
 // of it LDS traffic (272 KB).  Fragments are read half a step ahead of their use: K of the next step
@@ -503,6 +503,14 @@ void prefill_attention_split_kernel(PrefillAttnArgs a) {
 #pragma unroll
       for (int c = 0; c < NF; ++c) s = mfma32p(kf[c], qf[c], s);
       mask_scores(s, nv, abs0, pos_start, my_pos, h);
+    }
+    if (st == 0) {
+      // the first reference is block 0's maximum, as any block finds it that comes first
+      if (kg == 0 && live) refs[wave * 64 + lane] = moved_reference(s, scale2, m);
+      wait_barrier_p<63, true>();
+      m = refs[wave_of(0) * 64 + lane];
+    }
+    if (live) {
       f32x16 p;
       const float sum = block_probs(s, scale2, m, p);
       found = leaves_range(sum) ? 2 : 1;
@@ -600,10 +608,10 @@ static int launch_prefill_hd(hipStream_t st, const PrefillAttnArgs &a) {
   // A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a compute
   // unit holds one) leaves units idle, more of them with shorter steps are faster; a second round costs more
   // than the split gains.  All forms give the same bits.  8B heads, one sequence, us with 1 / 2 / 4 waves per
-  // head: 65 rows after 256 keys 16 / 14 / 12, after 1024 33 / 28 / 20, after 4096 103 / 86 / 53; 300 rows after
-  // 256 keys 21 / 19 / 15, after 1024 38 / 33 / 23, after 4096 108 / 89 / 56; 512 rows (256 workgroups with
-  // four waves) after 4096 keys 113 / 93 / 59, 800 rows 119 / 99 / 115, 1000 rows (256 with two) after 256 keys
-  // 37 / 33 / 37, after 4096 124 / 106 / 119; four sequences of 400 rows after 1024 keys 45 / 66 / 85.
+  // head: 65 rows after 256 keys 16 / 13 / 10.5, after 1024 33 / 27 / 19, after 4096 103 / 87 / 52; 300 rows after
+  // 256 keys 21 / 18 / 13.4, after 1024 38 / 33 / 22, after 4096 108 / 91 / 55; 512 rows (256 workgroups with
+  // four waves) after 4096 keys 113 / 96 / 60, 800 rows 119 / 103 / 114, 1000 rows (256 with two) after 256 keys
+  // 37 / 33 / 34, after 4096 124 / 111 / 122; four sequences of 400 rows after 1024 keys 45 / 67 / 80.
   constexpr long kComputeUnits = 256;
   if (prefill_grid<4>(a) <= kComputeUnits) return launch_prefill_t<HD, 4>(st, a);
   if (prefill_grid<2>(a) <= kComputeUnits) return launch_prefill_t<HD, 2>(st, a);
