@@ -410,7 +410,8 @@ int mc_op_attention_decode_plan(int32_t n_cands, int32_t n_q_heads, int32_t n_kv
  * position of the first row, page-table row or -1): up to 64 consecutive positions of one sequence.
  * A row at position p attends to keys 0..p: positions < prefix_len from the prefix pages (in
  * order), later ones from pages page_table[row][.] of the suffix pool.  q: [rows][Hq][hd];
- * out: [rows][Hq*hd], row-major or tiled (out_tiled = 1). */
+ * out: [rows][Hq*hd], row-major or tiled (out_tiled = 1).  A row's bits do not depend on which other
+ * sequences are in the call, as long as its sequence is cut into the same items. */
 int mc_op_attention_prefill(void *stream, int32_t n_items, const int32_t *items,
                             int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
                             int32_t page_tokens, int32_t prefix_len, const void *q,

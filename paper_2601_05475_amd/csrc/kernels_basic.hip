@@ -1086,8 +1086,9 @@ __device__ inline int cut_list(int n, int k, SampleShared &sh) {
 // eight (k <= 64) or 256 of four, and the k-th largest of the groups' maxima, L, is a lower bound of
 // the k-th largest value (k distinct elements are >= L), a tight one: with the largest values spread at
 // random n_g ln(n_g / (n_g - k)) elements of a row are >= L, 63 for k = 50 and 389 for k = 200.  Those go to a
-// list in LDS, and every one's rank is the number of larger keys in it (keys are distinct, the id is
-// part of them), counted by 16 lanes per key.  One pass over memory and five barriers.  Returns
+// list in LDS (more than 384 are cut down by cut_list), and every one's rank is the number of larger keys in it
+// (keys are distinct, the id is part of them), counted by 16 lanes per key.  Five barriers, and one pass over
+// memory for rows of up to 32768 values; longer ones are read a second time.  Returns
 // where the k sorted keys lie, or nullptr where L is no bound (fewer than k groups with a
 // value) or the list overflowed (thousands of equal values).  NaN is passed over, as by the
 // threshold selection.
@@ -1168,9 +1169,9 @@ __device__ inline const unsigned long long *group_select(Scan scan, float temper
 // (two passes over the row), radix selection for the rest and where those two give up.  A launch has as
 // many blocks as rows, a few of the 256 CUs, and what bounds it is one block's chain of launch, memory
 // and LDS round trips and barriers, so the steps of that chain were taken out: a second pass over
-// the row, a histogram, a bitonic sort, two serial walks over LDS by one thread.  Top 50 of 8 x 32000:
+// a short row, a histogram, a bitonic sort, two serial walks over LDS by one thread.  Top 50 of 8 x 32000:
 // 25.6 -> 10.1 us, 4 x 4096: 20 -> 8.2 us, 32 x 128256 from lists: 24 -> 10 us, from whole rows (wall
-// time) 39 -> 17 us; top 200 of 64 x 152064: 87 -> 41 us; arg max of 64 x 152064: 54 -> 16 us.
+// time) 39 -> 17 us; top 200 of 64 x 152064: 87 -> 37 us; arg max of 64 x 152064: 54 -> 16 us.
 constexpr int kTopListLen = 4, kTopListMaxK = 64;
 __global__ __launch_bounds__(1024) void sample_kernel(
     int V, const float *__restrict__ logits, size_t row_stride, const uint2 *__restrict__ top,

@@ -6,7 +6,7 @@
 // form); a wave keeps 8 accumulator tiles of 32 x 32 (its own 64 rows of a x all 128 rows of w).  Few
 // tiles take narrower ones: 128 rows of a and 128, 64 or 32 rows of w (see gemm_form); an output's
 // sum runs over K in the same order in all of them, so they give the same bits.
-// Two workgroups share a CU (two waves per SIMD, 215 registers each): they run out of step, so
+// Two workgroups share a CU (two waves per SIMD, 232 registers each): they run out of step, so
 // the barrier, prologue and epilogue of one are covered by the matrix work of the other.
 // The two operands reach the matrix cores by different roads, which splits the traffic between
 // LDS and the vector memory path instead of loading one of them with everything:
@@ -332,7 +332,9 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
 // 128 x 32 tiles, N x K = 4096 x 14336: 128 rows 139 / 127 / 84 / 66, 256 rows 161 / 125 / 83 / 68, 300
 // rows 135 / 102 / 70 / 102, 512 rows 160 / 124 / 84 / 130, 1024 rows 161 / 128 / 168 / 240, 1500 rows
 // 167 / 207 / 225 / 328; 6144 x 4096: 300 rows 47 / 33 / 39 / 44; SwiGLU 14336 x 4096 (2 x 64, 2 x 32 wide): 128 rows
-// 77 / 49 / 62, 256 rows 61 / 77 / 105.
+// 77 / 49 / 62, 256 rows 61 / 77 / 105.  The rule looks at idle units only, not at rows that a 256-row tile computes
+// for nothing: SwiGLU at 300 rows 98 / 83 / 99 and 384 rows 98 / 83 / 103 would be better by the second form, 400 rows
+// 100 / 109 / 125, 512 98 / 109 / 126, 600 145 / 136 / 153, 1000 195 / 209 / 301.
 struct GemmForm { int tm, tn; };
 static GemmForm gemm_form(int M, int N, bool swiglu) {
   constexpr long kComputeUnits = 256;

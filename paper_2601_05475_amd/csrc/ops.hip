@@ -54,7 +54,8 @@ static bool use_gemm256(int M, int N, int K, bool swiglu) { return M > 64 && gem
 int linear_auto_splits(int dtype, int M, int N, int K, int tiled) {
   if (tiled) return (dtype == MC_BF16 && M <= 64) ? skinny_linear_splits(M, N, K) : 1;
   if (M > 64) return 1;
-  // generic kernel, few rows: aim at >= 256 workgroups while keeping >= 256 of K per split
+  // generic kernels, few rows: aim at >= 256 workgroups of 64 columns while keeping >= 256 of K per split (the
+  // column-per-wave kernel, which has a workgroup per four columns, would fill the chip with fewer)
   const int tiles = (N + 63) / 64;
   int s = 1;
   while (tiles * s < 256 && K / (s * 2) >= 256 && s < 16) s *= 2;
@@ -118,6 +119,8 @@ int launch_attention_decode(hipStream_t st, int dtype, const DecodeAttnArgs &a) 
   if (a.n_cands <= 0) return MC_OK;
   if (dtype == MC_BF16 && decode_attention_mfma_supported(a))
     return launch_attention_decode_mfma(st, a);
+  // The generic kernel needs no scratch; a workspace below the size that mc_op_attention_decode_ws names is
+  // refused as on the other path.
   if (a.workspace_bytes < (size_t)a.n_cands * 2 * sizeof(int32_t))
     MC_FAIL(MC_ERR_INVALID, "attention workspace too small");
   AttnArgs g;
