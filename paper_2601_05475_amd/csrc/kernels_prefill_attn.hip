@@ -9,7 +9,7 @@
 // columns of a head (prefill_attention_split_kernel): they score different key blocks and add different
 // coordinates of the result, so that a row's sum runs over its keys in the same order as with one wave
 // and has the same bits whatever else is in the launch (300 positions of the 8B shape after 1024 / 4096
-// keys: 38 -> 22 / 108 -> 55 us).
+// keys: 38 -> 21 / 108 -> 51 us).
 // Keys are streamed page by page (64 keys) through LDS and shared by the waves: first the
 // shared-prefix pages that are visible to the block, then (scoring) the sequence's own suffix
 // pages.  Pages are stored in MFMA fragment order, so a page is copied to LDS as it is (by
@@ -81,28 +81,18 @@ __device__ inline void wait_barrier_p() {
 struct PPages {
   int nA, nB, nPA, n, prefix_len;
   const int32_t *table;
-  lds_int *ids;
-  bool ids_in_lds;
-  __device__ inline PPages(const PrefillAttnArgs &a, int tab, int last_pos, lds_int *lds_ids) {
+  __device__ inline PPages(const PrefillAttnArgs &a, int tab, int last_pos) {
     prefix_len = a.prefix_len;
     nA = min(a.prefix_len, last_pos + 1);
     nB = (tab >= 0 && last_pos >= a.prefix_len) ? last_pos - a.prefix_len + 1 : 0;
-    const int nPB = (nB + PPG - 1) / PPG;
     nPA = (nA + PPG - 1) / PPG;
-    n = nPA + nPB;
-    table = (nPB > 0) ? a.page_table + (size_t)tab * a.table_stride : nullptr;
-    ids = lds_ids;
-    ids_in_lds = nPB <= kPrefillMaxPids;
-    if (nPB > 0 && ids_in_lds) {
-      for (int i = threadIdx.x; i < nPB; i += 512) ids[i] = table[i];
-      __syncthreads();
-    }
+    n = nPA + (nB + PPG - 1) / PPG;
+    table = n > nPA ? a.page_table + (size_t)tab * a.table_stride : nullptr;
   }
-  __device__ inline int id(int pi) const {
-    if (pi >= n) return 0;
-    if (pi < nPA) return pi;
-    if (ids_in_lds) return __builtin_amdgcn_readfirstlane(ids[pi - nPA]);
-    return __builtin_amdgcn_readfirstlane(table[pi - nPA]);
+  // ids of pages p0 .. p0 + 63, one per lane (0 past the end)
+  __device__ inline int ids(int p0) const {
+    const int p = p0 + (int)(threadIdx.x & 63);
+    return p < nPA ? p : p < n ? table[p - nPA] : 0;
   }
   // 32-key block blk of page pi: the position of its key 0; returns how many of its keys exist
   __device__ inline int block(int pi, int blk, int &abs0) const {
@@ -352,11 +342,13 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
 // past a barrier every wave adds the KS blocks, in order, to the result coordinates it owns.  The first step
 // waits for block 0's maximum instead; where a block's sums leave the range later, which is seldom, the blocks
 // are done again one by one, the reference moving in between.  So a row's additions and references are those
-// of one wave that walks all keys.  (States of separate key groups merged at the end take 44 instead of 55 us for 300 rows
+// of one wave that walks all keys.  (States of separate key groups merged at the end take 44 instead of 51 us for 300 rows
 // after 4096 keys, but then a row's last bits change with the number of groups, that is with the launch.)
-// Two barriers a step and the probabilities' way through LDS bound it: 1.35 us per step of four blocks, 0.9 us
-// of it LDS traffic (272 KB).  Fragments are read half a step ahead of their use: K of the next step
-// beside the value products, V under the scores; K's and V's slots are refilled at the barrier behind that, which
+// A wave's chain bounds it, 1.2 us per step of four blocks: scores, exponentials, the probabilities' way through
+// LDS (272 KB a step in all), value products, two barriers, and what scalar work stands between: with page
+// ids looked up and block limits worked out anew in every step 1.35 us.  Fragments are read half a step ahead of
+// their use: K of the next step beside the value products, V under the scores; K's and V's slots are refilled at the
+// barrier behind that, which
 // gives a load 2 SLOTS - 1 half steps to land.
 template <int HD, int KS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -386,7 +378,7 @@ void prefill_attention_split_kernel(PrefillAttnArgs a) {
   const int head = kvh * G + (active ? g : 0);
   const bool col_valid = col < my_rows;
   const int my_pos = pos_start + (col_valid ? col : 0), my_last = pos_start + my_rows - 1;
-  const PPages pages(a, item.w, my_last, (lds_int *)(plds_raw + SP::LDS_BYTES));
+  const PPages pages(a, item.w, my_last);
 
   v4u qf[NF];
   {
@@ -404,34 +396,37 @@ void prefill_attention_split_kernel(PrefillAttnArgs a) {
     for (int r = 0; r < 16; ++r) o[x][r] = 0.f;
   float m = -INFINITY, l = 0.f;
 
-  const size_t page_stride = (size_t)Hkv * PPG * HD, head_off = (size_t)kvh * PPG * HD;
-  const bf16_t *kA = (const bf16_t *)a.k_prefix, *vA = (const bf16_t *)a.v_prefix;
-  const bf16_t *kB = (const bf16_t *)a.k_suffix, *vB = (const bf16_t *)a.v_suffix;
-  int k_ids[SP::PP], v_ids[SP::PP];
+  // K of a step, then, half a step later, V of the same step.  A wave's scalar work stands between the barrier and
+  // its products, so there is little of it: page ids come out of a register of 64, addresses by one multiplication.
+  const uint32_t page_bytes = (uint32_t)Hkv * PPG * HD * 2;
+  const size_t head_off = (size_t)kvh * PPG * HD * 2;
+  const char *kA = (const char *)a.k_prefix + head_off, *vA = (const char *)a.v_prefix + head_off;
+  const char *kB = (const char *)a.k_suffix + head_off, *vB = (const char *)a.v_suffix + head_off;
+  int ids = pages.ids(0), ids_next = pages.ids(64);
+  uint64_t offs[SP::PP];
   auto issue_k = [&](int step, int slot) __attribute__((always_inline)) {
+    const int p0 = step * SP::PP;
+    if ((p0 & 63) == 0 && p0 > 0) {
+      ids = ids_next;
+      ids_next = pages.ids(p0 + 64);
+    }
 #pragma unroll
     for (int i = 0; i < SP::PP; ++i) {
-      const int pi = step * SP::PP + i;
-      const __amdgpu_buffer_rsrc_t kr =
-          page_range((pi < pages.nPA ? kA : kB) + (size_t)k_ids[i] * page_stride + head_off, pi < pages.n, HD);
+      offs[i] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, (p0 + i) & 63) * page_bytes;
+      const __amdgpu_buffer_rsrc_t kr = page_range((const bf16_t *)((p0 + i < pages.nPA ? kA : kB) + offs[i]), p0 + i < pages.n, HD);
 #pragma unroll
       for (int c = 0; c < TL::CPT; ++c) load_piece(kr, k_lds + (slot * SP::PP + i) * TL::K_ELEMS + wave * 512, c);
-      v_ids[i] = k_ids[i];
-      k_ids[i] = pages.id(pi + SP::PP);
     }
   };
   auto issue_v = [&](int step, int slot) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < SP::PP; ++i) {
       const int pi = step * SP::PP + i;
-      const __amdgpu_buffer_rsrc_t vr =
-          page_range((pi < pages.nPA ? vA : vB) + (size_t)v_ids[i] * page_stride + head_off, pi < pages.n, HD);
+      const __amdgpu_buffer_rsrc_t vr = page_range((const bf16_t *)((pi < pages.nPA ? vA : vB) + offs[i]), pi < pages.n, HD);
 #pragma unroll
       for (int c = 0; c < TL::CPT; ++c) load_piece(vr, v_lds + (slot * SP::PP + i) * TL::V_ELEMS + wave * 512, c);
     }
   };
-#pragma unroll
-  for (int i = 0; i < SP::PP; ++i) k_ids[i] = pages.id(i);
 #pragma unroll
   for (int st = 0; st < SP::SLOTS; ++st) {
     issue_k(st, st);
@@ -482,6 +477,8 @@ void prefill_attention_split_kernel(PrefillAttnArgs a) {
   // the loads issued after those that a barrier waits for: 2 SLOTS - 2 half steps
   constexpr int kAhead = (2 * SP::SLOTS - 2) * SP::LPH;
   const int n_steps = (pages.n + SP::PP - 1) / SP::PP;
+  // steps whose keys all exist and lie before every row, in the prefix
+  const int n_plain = min(pages.nA, pos_start + 1) / (32 * KS);
   wait_barrier_p<kAhead + SP::LPH>();           // K of step 0
   read_k(0);
   int slot = 0;
@@ -491,10 +488,14 @@ void prefill_attention_split_kernel(PrefillAttnArgs a) {
     issue_k(st + SP::SLOTS, slot);
     read_v(slot);
     __builtin_amdgcn_sched_barrier(0);
-    const int pi = st * SP::PP + (kg >> 1);
-    int abs0;
-    const int nv = pages.block(pi, kg & 1, abs0);
-    const bool live = active && pi < pages.n && nv > 0 && abs0 <= my_last;      // uniform; else all masked
+    const bool plain = st < n_plain;
+    int abs0 = 0, nv = 32;
+    bool live = active;                         // uniform; else all masked
+    if (!plain) {
+      const int pi = st * SP::PP + (kg >> 1);
+      nv = pages.block(pi, kg & 1, abs0);
+      live = active && pi < pages.n && nv > 0 && abs0 <= my_last;
+    }
     f32x16 s;
     int found = 0;
     if (live) {
@@ -502,7 +503,7 @@ void prefill_attention_split_kernel(PrefillAttnArgs a) {
       for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
       for (int c = 0; c < NF; ++c) s = mfma32p(kf[c], qf[c], s);
-      mask_scores(s, nv, abs0, pos_start, my_pos, h);
+      if (!plain) mask_scores(s, nv, abs0, pos_start, my_pos, h);
     }
     if (st == 0) {
       // the first reference is block 0's maximum, as any block finds it that comes first
@@ -528,9 +529,15 @@ void prefill_attention_split_kernel(PrefillAttnArgs a) {
     issue_v(st + SP::SLOTS, slot >= 1 ? slot - 1 : SP::SLOTS - 1);
     const unsigned int lives = (unsigned int)__ballot(states != 0);     // bit w: wave w's block
     if (!__any(states == 2)) {
+      if (plain) {
+        if (active)
 #pragma unroll
-      for (int i = 0; i < KS; ++i)
-        if ((lives >> wave_of(i)) & 1) add_block(i);
+          for (int i = 0; i < KS; ++i) add_block(i);
+      } else {
+#pragma unroll
+        for (int i = 0; i < KS; ++i)
+          if ((lives >> wave_of(i)) & 1) add_block(i);
+      }
     } else {
       // block by block, the whole workgroup together
 #pragma unroll
@@ -587,13 +594,13 @@ static long prefill_grid(const PrefillAttnArgs &a) {
 template <int HD, int KS>
 static int launch_prefill_t(hipStream_t st, const PrefillAttnArgs &a) {
   const void *kernel;
-  int lds = kPrefillMaxPids * (int)sizeof(int);
+  int lds;
   if constexpr (KS == 1) {
     kernel = (const void *)prefill_attention_kernel<HD>;
-    lds += PWhole<HD>::LDS_BYTES;
+    lds = PWhole<HD>::LDS_BYTES + kPrefillMaxPids * (int)sizeof(int);
   } else {
     kernel = (const void *)prefill_attention_split_kernel<HD, KS>;
-    lds += PSplit<HD, KS>::LDS_BYTES;
+    lds = PSplit<HD, KS>::LDS_BYTES;
   }
   MC_TRY(raise_dynamic_lds_limit(kernel, lds));
   const unsigned grid = (unsigned)prefill_grid<KS>(a);
@@ -608,10 +615,10 @@ static int launch_prefill_hd(hipStream_t st, const PrefillAttnArgs &a) {
   // A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a compute
   // unit holds one) leaves units idle, more of them with shorter steps are faster; a second round costs more
   // than the split gains.  All forms give the same bits.  8B heads, one sequence, us with 1 / 2 / 4 waves per
-  // head: 65 rows after 256 keys 16 / 13 / 10.5, after 1024 33 / 27 / 19, after 4096 103 / 87 / 52; 300 rows after
-  // 256 keys 21 / 18 / 13.4, after 1024 38 / 33 / 22, after 4096 108 / 91 / 55; 512 rows (256 workgroups with
-  // four waves) after 4096 keys 113 / 96 / 60, 800 rows 119 / 103 / 114, 1000 rows (256 with two) after 256 keys
-  // 37 / 33 / 34, after 4096 124 / 111 / 122; four sequences of 400 rows after 1024 keys 45 / 67 / 80.
+  // head: 65 rows after 256 keys 16 / 12.7 / 10.3, after 1024 33 / 26 / 18, after 4096 103 / 83 / 48; 300 rows after
+  // 256 keys 21 / 17.5 / 13, after 1024 38 / 31 / 21, after 4096 108 / 86 / 51; 512 rows (256 workgroups with
+  // four waves) after 4096 keys 113 / 91 / 55, 800 rows 119 / 97 / 106, 1000 rows (256 with two) after 256 keys
+  // 37 / 32 / 33, after 4096 124 / 103 / 112; four sequences of 400 rows after 1024 keys 45 / 63 / 73.
   constexpr long kComputeUnits = 256;
   if (prefill_grid<4>(a) <= kComputeUnits) return launch_prefill_t<HD, 4>(st, a);
   if (prefill_grid<2>(a) <= kComputeUnits) return launch_prefill_t<HD, 2>(st, a);
