@@ -878,13 +878,15 @@ def test_attention_prefill_item_sizes(item_rows):
     (32, 8, 64, 3625, [(2600, 1025)], 1601),
     # whole pages only and suffixes that end early; rows at the prefix's begin: waves whose blocks no row sees
     (8, 2, 128, 2560, [(2560, 33)], 1), (8, 2, 64, 2561, [(0, 70)], 1),
+    # page ids in registers of 64: a suffix that goes through two of them, a prefix that goes through three
+    (2, 1, 128, 100, [(100, 4300)], 97), (2, 1, 64, 4032, [(4032, 130)], 7), (4, 2, 128, 8250, [(8250, 20)], 1),
 ])
 def test_attention_prefill_key_groups(Hq, Hkv, hd, P, seqs, stride):
     worst, _ = prefill_case(Hq, Hkv, hd, P, seqs, stride)
     assert worst < ATT_REL["bf16"], worst
 
 
-@pytest.mark.parametrize("hd,P,rows", [(128, 300, 100), (64, 300, 100), (128, 2700, 70), (64, 2700, 70), (128, 4097, 33)])
+@pytest.mark.parametrize("hd,P,rows", [(128, 300, 100), (64, 300, 100), (128, 2700, 70), (64, 2700, 70), (128, 4097, 33), (128, 8200, 40)])
 def test_attention_prefill_rows_do_not_depend_on_the_launch(hd, P, rows):
     """A candidate's rows scored alone, with a few others and in a full chunk, which take one, two and four
     waves per head: the same bits.  Some keys outgrow the softmax's reference far into the walk, in every
