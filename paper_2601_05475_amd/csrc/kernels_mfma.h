@@ -106,7 +106,7 @@ __device__ inline void rope_store_quad(const RopeOut &ro, int m, int n, float4 s
 
 // Many-row GEMM (more than 64 rows): fp32 out, or the SwiGLU form with bf16 tiled out.  N % 128
 // == 0, K % 256 == 0.  256 x 128 output tile per workgroup (256 x 64 of each weight matrix in the
-// SwiGLU form; narrower where few tiles would leave compute units idle), XCD-aware tile order.
+// SwiGLU form; other shapes where few tiles would leave compute units idle), XCD-aware tile order.
 bool gemm256_supported(int M, int N, int K, bool swiglu);
 // rope != nullptr: the fused QKV layer as in launch_linear_skinny (N = (Hq + 2 Hkv) hd, hd % 4 == 0).
 // accumulate: out[m][n] += the product (the residual stream updated in place) instead of a store.

@@ -707,6 +707,29 @@ def test_many_row_gemm_forms_give_the_same_bits():
             assert torch.equal(x, z[:M]), (name, M)
 
 
+@pytest.mark.parametrize("M,N,K", [(128, 8192, 256), (129, 4096, 512), (65, 5120, 256), (129, 5120, 768), (192, 5120, 256), (193, 5120, 256)])
+def test_linear_64_row_workgroups(M, N, K):
+    """GEMM workgroups of two waves (64 rows x 32 or 64 columns): full and ragged last workgroups, the last row
+    count that takes the form and the first past it."""
+    test_linear_tiled(M, N, K, 1)
+    test_linear_accumulate_tiled(M, N, K)
+
+
+@pytest.mark.parametrize("M,K", [(100, 256), (257, 256), (320, 768), (321, 512), (384, 256), (385, 256)])
+def test_linear_swiglu_wide_workgroups(M, K):
+    """The SwiGLU form with a wave per row tile (10 and 12 waves; waves past the last row tile), its neighbours, and
+    the single row tile whose weights bypass L2: against the oracle, and a row has the bits that it has in any
+    other launch."""
+    import torch
+    N = 14336
+    test_linear_swiglu_tiled(M, N, K)
+    a = to_dev(rnd(62, (M, K)), "bf16")[0]
+    wg, wu = (binding.op_pack_tiled(to_dev(rnd(s, (N, K), 0.05), "bf16")[0]) for s in (63, 64))
+    run = lambda m: binding.tiled_to_rowmajor(binding.op_linear_swiglu(binding.op_pack_tiled(a[:m].contiguous()), wg, wu, tiled_shape=(m, N, K)), m, N)  # noqa: E731
+    full = run(M)
+    assert torch.equal(full, run(M)) and torch.equal(full[:70], run(70)) and torch.equal(full[:130], run(min(M, 130))[:130])
+
+
 def test_scoring_size_gemms_on_sampled_rows():
     """The many-row GEMMs at the sizes one scoring chunk of the 8B shape launches (8192 rows):
     gate/up + SwiGLU 8192 x 14336 x 4096, down with the residual update 8192 x 4096 x 14336, QKV
