@@ -141,10 +141,14 @@ struct DecodeAttnArgs {
 
 int launch_embed(hipStream_t st, int dtype, int rows, int d, const int32_t *tokens,
                  const void *table, float *x);
+// like_rows > 0: a row's sum runs in the order that a launch of that many rows takes (its bits do not tell the two apart)
 int launch_add_rmsnorm(hipStream_t st, int dtype, int rows, int d, float *x, const float *partials,
-                       int n_partials, const void *gain, float eps, void *h_out, int h_tiled);
+                       int n_partials, const void *gain, float eps, void *h_out, int h_tiled, int like_rows = 0);
 int launch_gather_rows(hipStream_t st, int rows, int d, const float *x, const int32_t *idx,
                        float *out);
+// rows idx[0 .. rows - 1] of x (fp32, row-major) and of t (bf16, tiled, K columns) to the first rows of x_out and t_out
+int launch_gather_last(hipStream_t st, int rows, int d, int K, const float *x, const void *t, const int32_t *idx,
+                       float *x_out, void *t_out);
 // tiled != 0: a, w (and the SwiGLU output) are in the tiled layout; bf16 only
 // top_out != nullptr (tiled few-row layers with >= 2048 weight tiles only, see
 // linear_top_lists_supported): also leave per-group top lists of every output row

@@ -158,12 +158,12 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_vec_kernel(
 
 template <typename T>
 static void launch_add_rmsnorm_t(hipStream_t st, int rows, int d, float *x, const float *partials,
-                                 int n_partials, size_t ps, const T *gain, float eps, T *h, int h_tiled) {
+                                 int n_partials, size_t ps, const T *gain, float eps, T *h, int h_tiled, int like_rows) {
   if (d % 4 == 0 && d <= 16384) {
     // enough threads for one float4 each where possible; at least one wave
     const int quads = d / 4;
     // many rows: 512 threads with two loads each in flight were measured faster than 1024 x 1
-    const int nt_max = (rows >= 2048 && quads <= 4 * 512) ? 512 : 1024;
+    const int nt_max = (like_rows >= 2048 && quads <= 4 * 512) ? 512 : 1024;
     int nt = 64;
     while (nt < nt_max && nt < quads) nt *= 2;
     const int vec = (quads + nt - 1) / nt;
@@ -179,13 +179,14 @@ static void launch_add_rmsnorm_t(hipStream_t st, int rows, int d, float *x, cons
 }
 
 int launch_add_rmsnorm(hipStream_t st, int dtype, int rows, int d, float *x, const float *partials,
-                       int n_partials, const void *gain, float eps, void *h_out, int h_tiled) {
+                       int n_partials, const void *gain, float eps, void *h_out, int h_tiled, int like_rows) {
   if (rows <= 0) return MC_OK;
+  if (like_rows <= 0) like_rows = rows;
   const size_t ps = (size_t)rows * d;
   if (dtype == MC_F32)
-    launch_add_rmsnorm_t<float>(st, rows, d, x, partials, n_partials, ps, (const float *)gain, eps, (float *)h_out, h_tiled);
+    launch_add_rmsnorm_t<float>(st, rows, d, x, partials, n_partials, ps, (const float *)gain, eps, (float *)h_out, h_tiled, like_rows);
   else
-    launch_add_rmsnorm_t<bf16_t>(st, rows, d, x, partials, n_partials, ps, (const bf16_t *)gain, eps, (bf16_t *)h_out, h_tiled);
+    launch_add_rmsnorm_t<bf16_t>(st, rows, d, x, partials, n_partials, ps, (const bf16_t *)gain, eps, (bf16_t *)h_out, h_tiled, like_rows);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }
@@ -201,6 +202,23 @@ int launch_gather_rows(hipStream_t st, int rows, int d, const float *x, const in
                        float *out) {
   if (rows <= 0) return MC_OK;
   gather_rows_kernel<<<rows, 256, 0, st>>>(d, x, idx, out);
+  MC_HIP(hipGetLastError());
+  return MC_OK;
+}
+
+// 4 to 10 KB of x and as much of t per row, one workgroup each: the launch is what it costs
+__global__ __launch_bounds__(256) void gather_last_kernel(int d, int K, const float *__restrict__ x, const bf16_t *__restrict__ t,
+                                                          const int32_t *__restrict__ idx, float *__restrict__ x_out,
+                                                          bf16_t *__restrict__ t_out) {
+  const int r = blockIdx.x, from = idx[r];
+  for (int i = 4 * threadIdx.x; i < d; i += 4 * 256) *(float4 *)(x_out + (size_t)r * d + i) = *(const float4 *)(x + (size_t)from * d + i);
+  for (int k = 8 * threadIdx.x; k < K; k += 8 * 256) *(uint4 *)(t_out + tiled_offset(r, k, K)) = *(const uint4 *)(t + tiled_offset(from, k, K));
+}
+
+int launch_gather_last(hipStream_t st, int rows, int d, int K, const float *x, const void *t, const int32_t *idx, float *x_out, void *t_out) {
+  if (rows <= 0) return MC_OK;
+  if (d % 4 || K % 64) MC_FAIL(MC_ERR_UNSUPPORTED, "gathered rows: d %% 4 == 0 and K %% 64 == 0 (d = %d, K = %d)", d, K);
+  gather_last_kernel<<<rows, 256, 0, st>>>(d, K, x, (const bf16_t *)t, idx, x_out, (bf16_t *)t_out);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }

@@ -966,3 +966,36 @@ def test_oversample_then_filter_by_reward_score():
     for i, tok in enumerate([1, 2, 3]):
         ref = otf.forward(cfg, w, np.array([tok]), want.copy())[0][0]
         assert_logits_close(got[i][None], ref[None], "f32", "new round on the promoted prefix")
+
+
+@pytest.mark.parametrize("chunk_rows", [0, 128])
+def test_last_layer_for_the_last_rows_gives_the_bits_of_all_rows(chunk_rows):
+    """Many-row passes finish their last layer for the rows whose logits are read.  A further layer that adds
+    exactly nothing (zero output and down projections) makes the layer before it one that is computed for
+    every row: logits and scores must keep their bits.  Prefix and extension in one and several chunks, candidates
+    that end on and beside tile and item edges, scored and written."""
+    d, F = 256, 512
+    s = synth.Shape("two layers", 2, d, 4, 2, 64, F, 1024, 1.0e4, "bf16")
+    w = synth.make_weights(s, 901)
+    zero = dict(w["layers"][1], wo=np.zeros_like(w["layers"][1]["wo"]), w_down=np.zeros_like(w["layers"][1]["w_down"]))
+    s3 = synth.Shape("and one that adds nothing", 3, d, 4, 2, 64, F, 1024, 1.0e4, "bf16")
+    w3 = dict(w, layers=list(w["layers"]) + [zero])
+    prefix, more = synth.tokens(902, 1, (300,), s.vocab), synth.tokens(902, 2, (131,), s.vocab)
+    lens = np.array([64, 65, 1, 127, 128, 33], np.int32)
+    suffix = synth.tokens(902, 3, (len(lens), 128), s.vocab)
+    out = []
+    for shape, weights in ((s, w), (s3, w3)):
+        model = binding.Model(shape, weights)
+        sess = binding.Session(model, 512, len(lens), 192, 64, chunk_rows=chunk_rows)
+        sess.prefill_shared(prefix)
+        got = [sess.logits(1)]
+        sess.extend_shared(more)
+        got.append(sess.logits(1))
+        lp, score, _ = sess.score_candidates(suffix, lens, np.arange(8, dtype=np.int32), np.arange(8, dtype=np.float32))
+        sess.prefill_suffix_ragged(suffix, lens)
+        got += [lp, score, sess.logits(len(lens))]
+        sess.decode_step(np.arange(len(lens), dtype=np.int32))
+        got.append(sess.logits(len(lens)))
+        out.append(got)
+    for name, a, b in zip(("prefix", "extension", "reward log-probabilities", "scores", "written candidates", "next step"), *out):
+        np.testing.assert_array_equal(a, b, err_msg=name)
