@@ -293,7 +293,8 @@ int mc_profile_end(mc_session *s, int32_t *n_timed, double *total_ms);
  * ((row / 32) * (K / 64) + k / 64) * 4096, and inside it the 16-byte chunk c = (k % 32) / 8 of
  * lane l = row % 32 + 32 * ((k % 64) / 32), at byte (c * 64 + l) * 16, holds the 8 elements
  * k - k % 8 .. +7 of that row.  mc_op_tiled_bytes gives the buffer size (0 if K is unsuitable);
- * mc_op_pack_tiled converts a row-major bf16 matrix (padding rows are zero-filled). */
+ * mc_op_pack_tiled converts a row-major bf16 matrix (padding rows are zero-filled).  The operations
+ * below that store a tiled output write its padding rows as zeros too, unless they say otherwise. */
 size_t mc_op_tiled_bytes(int32_t rows, int32_t K);
 int mc_op_pack_tiled(void *stream, int32_t rows, int32_t K, const void *src, void *dst);
 
@@ -410,14 +411,22 @@ int mc_op_attention_decode_plan(int32_t n_cands, int32_t n_q_heads, int32_t n_kv
  * position of the first row, page-table row or -1): up to 64 consecutive positions of one sequence.
  * A row at position p attends to keys 0..p: positions < prefix_len from the prefix pages (in
  * order), later ones from pages page_table[row][.] of the suffix pool.  q: [rows][Hq][hd];
- * out: [rows][Hq*hd], row-major or tiled (out_tiled = 1).  A row's bits do not depend on which other
- * sequences are in the call, as long as its sequence is cut into the same items. */
+ * out: [rows][Hq*hd], row-major or tiled (out_tiled = 1); rows that no item covers, padding rows among
+ * them, are left alone.  A row's bits do not depend on which other sequences are in the call, as long as
+ * its sequence is cut into the same items.  mc_op_attention_prefill_tiled: the same into a tiled output of
+ * `rows` rows (>= 1, n_items >= 1), of which those that no item covers become zero. */
 int mc_op_attention_prefill(void *stream, int32_t n_items, const int32_t *items,
                             int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
                             int32_t page_tokens, int32_t prefix_len, const void *q,
                             const void *k_prefix, const void *v_prefix, const void *k_suffix,
                             const void *v_suffix, const int32_t *page_table,
                             int32_t table_stride, void *out, int32_t out_tiled);
+int mc_op_attention_prefill_tiled(void *stream, int32_t rows, int32_t n_items, const int32_t *items,
+                                  int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                  int32_t page_tokens, int32_t prefix_len, const void *q,
+                                  const void *k_prefix, const void *v_prefix, const void *k_suffix,
+                                  const void *v_suffix, const int32_t *page_table,
+                                  int32_t table_stride, void *out);
 
 /* HBM read-rate probe (a measurement aid): reads `bytes` of device memory once (a multiple of
  * 64 MiB; larger than the 256 MB memory-side cache for an HBM figure) with 16-byte streaming

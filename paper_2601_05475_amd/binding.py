@@ -107,6 +107,7 @@ SIGNATURES = {
     "mc_op_read_probe": (C.c_int, [_vp, _vp, _sz, _vp]),
     "mc_op_mfma_probe": (C.c_int, [_vp, _vp, _vp, _i32, _i32]),
     "mc_op_attention_prefill": (C.c_int, [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp, _i32]),
+    "mc_op_attention_prefill_tiled": (C.c_int, [_vp, _i32, _i32, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp]),
     "mc_op_top_list_bytes": (_sz, [_i32, _i32]),
     "mc_op_lm_head": (C.c_int, [_vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp]),
     "mc_op_sample_lists": (C.c_int, [_vp, _i32, _i32, _vp, _sz, _vp, _f32, _i32, _vp, _vp, _vp]),
@@ -472,10 +473,8 @@ def kv_pages_unpack(kp, vp, page_tokens: int, head_dim: int):
 
 
 def _tiled_out(rows: int, K: int, dtype, device):
-    """A tiled [rows, K] buffer for a kernel that writes every row: the padding rows, which lie in the last
-    tile of 32, are zero-filled.  Calls of few rows are bound by the host, which takes 5 us for a zeroed
-    tensor, 6.7 us for an empty one and a fill of its last tile, 1.4 us for an empty one; from 4 MB on
-    filling the whole would add a microsecond and more to kernels that hide the host's work."""
+    """A tiled [rows, K] buffer with zeros in its padding rows, for a program that writes the rows itself
+    (the library's own operations write the padding rows of their outputs)."""
     import torch
     n = max(0, (rows + 31) // 32 * 32 * K)
     if rows % 32 and n < 1 << 21:
@@ -486,13 +485,19 @@ def _tiled_out(rows: int, K: int, dtype, device):
     return out
 
 
+def _tiled_empty(rows: int, K: int, dtype, device):
+    """A tiled [rows, K] buffer that a kernel writes whole, padding rows and all."""
+    import torch
+    return torch.empty((max(0, rows) + 31) // 32 * 32 * K, dtype=dtype, device=device)
+
+
 def op_add_rmsnorm(x, partials, gain, eps: float, tiled: bool = False):
     """x: fp32 [rows, d] (updated in place); partials: fp32 [S, rows, d] or None.  Returns h
     ([rows, d], or the flat tiled buffer when tiled)."""
     import torch
     rows, d = x.shape
     if tiled:
-        h = _tiled_out(rows, d, gain.dtype, x.device)
+        h = _tiled_empty(rows, d, gain.dtype, x.device)
     else:
         h = torch.empty((rows, d), dtype=gain.dtype, device=x.device)
     S = 0 if partials is None else partials.shape[0]
@@ -562,7 +567,7 @@ def op_linear_swiglu(a, w_gate, w_up, tiled_shape=None):
         out = torch.empty((M, N), dtype=a.dtype, device=a.device)
     else:
         M, N, K = tiled_shape
-        out = _tiled_out(M, N, a.dtype, a.device)
+        out = _tiled_empty(M, N, a.dtype, a.device)
     _check(load_library().mc_op_linear_swiglu(_stream(), _code_of(a), M, N, K, a.data_ptr(),
                                               w_gate.data_ptr(), w_up.data_ptr(), out.data_ptr(),
                                               int(tiled_shape is not None)))
@@ -597,7 +602,7 @@ def op_attention_decode(q, k_prefix, v_prefix, k_suffix, v_suffix, page_table, p
     Hkv = (k_prefix if k_prefix is not None else k_suffix).shape[1]
     if out is None:
         if out_tiled:
-            out = _tiled_out(B, Hq * hd, q.dtype, q.device)
+            out = _tiled_empty(B, Hq * hd, q.dtype, q.device)
         else:
             out = torch.empty_like(q)
     p = lambda t: None if t is None else t.data_ptr()
@@ -652,16 +657,23 @@ def op_attention_prefill(q, items, k_prefix, v_prefix, k_suffix, v_suffix, page_
     lib = load_library()
     rows, Hq, hd = q.shape
     Hkv = k_prefix.shape[1]
+    p = lambda t: None if t is None else t.data_ptr()
+    stride = 0 if page_table is None else page_table.shape[1]
+    if out_tiled and items.shape[0]:
+        out = torch.empty(lib.mc_op_tiled_bytes(rows, Hq * hd) // 2, dtype=q.dtype, device=q.device)
+        _check(lib.mc_op_attention_prefill_tiled(
+            _stream(), rows, items.shape[0], items.data_ptr(), Hq, Hkv, hd, page_tokens, prefix_len,
+            q.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(), p(k_suffix), p(v_suffix),
+            p(page_table), stride, out.data_ptr()))
+        return out
     if out_tiled:
         out = torch.zeros(lib.mc_op_tiled_bytes(rows, Hq * hd) // 2, dtype=q.dtype, device=q.device)
     else:
         out = torch.empty_like(q)
-    p = lambda t: None if t is None else t.data_ptr()
     _check(lib.mc_op_attention_prefill(
         _stream(), items.shape[0], items.data_ptr(), Hq, Hkv, hd, page_tokens, prefix_len,
         q.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(), p(k_suffix), p(v_suffix),
-        p(page_table), 0 if page_table is None else page_table.shape[1], out.data_ptr(),
-        int(out_tiled)))
+        p(page_table), stride, out.data_ptr(), int(out_tiled)))
     return out
 
 

@@ -102,6 +102,12 @@ __host__ __device__ inline size_t tiled_offset(int row, int k, int K) {
          (size_t)(((k & 31) >> 3) * 64 + (row & 31) + 32 * ((k & 63) >> 5)) * 8 + (k & 7);
 }
 
+// How a launcher's output is laid out.  TILED leaves the padding rows of the last 32-row tile alone (a product computes
+// nothing from them); TILED_ZERO writes them as zeros, for outputs that leave the library: the kernel has the tile
+// open already, where a fill of the buffer ahead of it is a launch of its own (2 to 5 us, and as much on the host).
+enum { ROW_MAJOR = 0, TILED = 1, TILED_ZERO = 2 };
+__host__ __device__ inline int padded_rows(int rows) { return (rows + 31) & ~31; }
+
 // ---- kernel launchers (defined in kernels_*.hip) -----------------------------------
 // Every launcher validates nothing: callers (runtime.cpp, ops.cpp) check shapes first.
 

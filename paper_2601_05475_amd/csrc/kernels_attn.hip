@@ -51,6 +51,15 @@ __device__ inline uint32_t pack2_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
+// TILED_ZERO: candidate b answers for the padding rows B + b, 2 B + b, ..., at coordinate k (of K) and the N elements from there
+template <int N>
+__device__ inline void zero_padding(bf16_t *out, int B, int b, int k, int K) {
+  for (int z = B + b; z < padded_rows(B); z += B) {
+    if constexpr (N == 4) *(uint2 *)(out + tiled_offset(z, k, K)) = make_uint2(0u, 0u);
+    else out[tiled_offset(z, k, K)] = 0;
+  }
+}
+
 constexpr int PG = 64;                       // keys per page (the only page size of this kernel)
 constexpr int kMaxSuffixSplits = 8;
 
@@ -371,6 +380,7 @@ void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__
         pk.x = pack2_bf16(v.x / lg, v.y / lg);
         pk.y = pack2_bf16(v.z / lg, v.w / lg);
         *(uint2 *)((bf16_t *)a.out + at) = pk;
+        if (a.out_tiled == TILED_ZERO) zero_padding<4>((bf16_t *)a.out, B, bc, hq * HD + d, Hq * HD);
         continue;
       }
       const size_t row = ((size_t)part * B + bc) * Hq + hq;
@@ -435,6 +445,7 @@ void decode_attention_kernel(DecodeAttnArgs a, AttnItems it, float *__restrict__
       pk.x = pack2_bf16(v.x / lg, v.y / lg);
       pk.y = pack2_bf16(v.z / lg, v.w / lg);
       *(uint2 *)((bf16_t *)a.out + at) = pk;
+      if (a.out_tiled == TILED_ZERO) zero_padding<4>((bf16_t *)a.out, B, bc, hq * HD + d, Hq * HD);
       continue;
     }
     const size_t row = ((size_t)part * B + bc) * Hq + hq;
@@ -484,6 +495,7 @@ __global__ __launch_bounds__(HD) void decode_attention_merge_kernel(
     const int b = bh / Hq, head = bh % Hq;
     const size_t at = out_tiled ? tiled_offset(b, head * HD + d, Hq * HD) : (size_t)bh * HD + d;
     out[at] = f32_to_bf16(num / den);
+    if (out_tiled == TILED_ZERO) zero_padding<1>(out, B, b, head * HD + d, Hq * HD);
     return;
   }
   for (int p = d; p < n_parts; p += HD) {
@@ -513,6 +525,7 @@ __global__ __launch_bounds__(HD) void decode_attention_merge_kernel(
   const int b = bh / Hq, head = bh % Hq;
   const size_t at = out_tiled ? tiled_offset(b, head * HD + d, Hq * HD) : (size_t)bh * HD + d;
   out[at] = f32_to_bf16(num / den);
+  if (out_tiled == TILED_ZERO) zero_padding<1>(out, B, b, head * HD + d, Hq * HD);
 }
 
 static AttnItems plan_items(const DecodeAttnArgs &a) {

@@ -83,10 +83,14 @@ int launch_embed(hipStream_t st, int dtype, int rows, int d, const int32_t *toke
 // x[r] += sum_s partials[s][r];  h[r] = x[r] * gain / sqrt(mean(x[r]^2) + eps)
 template <typename T>
 __global__ __launch_bounds__(256) void add_rmsnorm_kernel(
-    int d, float *__restrict__ x, const float *__restrict__ partials, int n_partials,
+    int rows, int d, float *__restrict__ x, const float *__restrict__ partials, int n_partials,
     size_t pstride, const T *__restrict__ gain, float eps, T *__restrict__ h, int h_tiled) {
   __shared__ float scratch[16];
   const int r = blockIdx.x;
+  if (r >= rows) {                              // TILED_ZERO: a padding row
+    for (int i = threadIdx.x; i < d; i += 256) h[tiled_offset(r, i, d)] = Cvt<T>::from_f32(0.f);
+    return;
+  }
   const size_t row = (size_t)blockIdx.x * d;
   float ss = 0.f;
   for (int i = threadIdx.x; i < d; i += 256) {
@@ -117,7 +121,11 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_vec_kernel(
   __shared__ float scratch[16];
   const int nt = blockDim.x;
   const int r = rows_per_xcd > 0 ? (int)(blockIdx.x & 7) * rows_per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-  if (r >= rows) return;
+  if (r >= rows) {
+    if (h_tiled == TILED_ZERO && r < padded_rows(rows))
+      for (int i = 4 * threadIdx.x; i < d; i += 4 * nt) *(uint2 *)(h + tiled_offset(r, i, d)) = make_uint2(0u, 0u);    // tiled: bf16
+    return;
+  }
   const size_t row = (size_t)r * d;
   float4 v[VEC];
   float ss = 0.f;
@@ -159,6 +167,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_vec_kernel(
 template <typename T>
 static void launch_add_rmsnorm_t(hipStream_t st, int rows, int d, float *x, const float *partials,
                                  int n_partials, size_t ps, const T *gain, float eps, T *h, int h_tiled, int like_rows) {
+  const int all_rows = h_tiled == TILED_ZERO ? padded_rows(rows) : rows;
   if (d % 4 == 0 && d <= 16384) {
     // enough threads for one float4 each where possible; at least one wave
     const int quads = d / 4;
@@ -168,13 +177,13 @@ static void launch_add_rmsnorm_t(hipStream_t st, int rows, int d, float *x, cons
     while (nt < nt_max && nt < quads) nt *= 2;
     const int vec = (quads + nt - 1) / nt;
     // many rows into the tiled layout: a contiguous range of rows per XCD
-    const int rpx = (h_tiled && rows >= 256) ? ((rows + 7) / 8 + 7) / 8 * 8 : 0;
-    const int grid = rpx > 0 ? 8 * rpx : rows;
+    const int rpx = (h_tiled && rows >= 256) ? ((all_rows + 7) / 8 + 7) / 8 * 8 : 0;
+    const int grid = rpx > 0 ? 8 * rpx : all_rows;
     if (vec <= 1) add_rmsnorm_vec_kernel<T, 1><<<grid, nt, 0, st>>>(rows, rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
     else if (vec <= 2) add_rmsnorm_vec_kernel<T, 2><<<grid, nt, 0, st>>>(rows, rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
     else add_rmsnorm_vec_kernel<T, 4><<<grid, nt, 0, st>>>(rows, rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
   } else {
-    add_rmsnorm_kernel<T><<<rows, 256, 0, st>>>(d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
+    add_rmsnorm_kernel<T><<<all_rows, 256, 0, st>>>(rows, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
   }
 }
 
@@ -654,6 +663,8 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attention_generic_kernel(Attn
     const size_t at = a.out_tiled ? tiled_offset(r, qh * hd + d, a.n_q_heads * hd)
                                   : ((size_t)r * a.n_q_heads + qh) * hd + d;
     out[at] = Cvt<T>::from_f32(num / den);
+    if (a.out_tiled == TILED_ZERO)               // row r answers for padding rows rows + r, 2 rows + r, ...
+      for (int z = a.rows + r; z < padded_rows(a.rows); z += a.rows) out[tiled_offset(z, qh * hd + d, a.n_q_heads * hd)] = Cvt<T>::from_f32(0.f);
   }
 }
 

@@ -101,7 +101,7 @@ __device__ inline void wait_barrier() {
 // the operands run ahead; WV: waves; NT: w's lines are read by this workgroup only and need not stay in L2.
 template <int MODE, int TM, int TN, int D, int WV, bool NT>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(WV > 8 ? 3 : 2, WV > 8 ? 3 : 2)))
-void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
+void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
                     const bf16_t *__restrict__ w, const bf16_t *__restrict__ w2,
                     float *__restrict__ out, bf16_t *__restrict__ out_t, RopeOut ro) {
   constexpr bool SWIGLU = MODE == GEMM_SWIGLU;
@@ -273,7 +273,7 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
 #pragma unroll
   for (int y = 0; y < TM; ++y) {
     const int m = 32 * (mt0 + TM * wm + y) + j;
-    if (m >= M) continue;
+    if (m >= (SWIGLU ? Mw : M)) continue;                  // Mw > M: the padding rows too, as zeros
 #pragma unroll
     for (int x = 0; x < TN; ++x)
 #pragma unroll
@@ -285,6 +285,7 @@ void gemm256_kernel(int M, int N, int K, int tiles_m, int tiles_n, const bf16_t 
           uint2 pk;
           pk.x = pack2g_bf16(silu_g(g[4 * r4]) * uu[4 * r4], silu_g(g[4 * r4 + 1]) * uu[4 * r4 + 1]);
           pk.y = pack2g_bf16(silu_g(g[4 * r4 + 2]) * uu[4 * r4 + 2], silu_g(g[4 * r4 + 3]) * uu[4 * r4 + 3]);
+          if (m >= M) pk = make_uint2(0u, 0u);
           *(uint2 *)(out_t + tiled_offset(m, n, N)) = pk;
         } else if (MODE == GEMM_ACCUM) {
           float4 *p = (float4 *)(out + (size_t)m * N + n);
@@ -388,7 +389,7 @@ static GemmForm swiglu_form(int M, int N) {
 }
 
 template <int MODE, int TM, int TN, int D, int WV, bool NT = false>
-static int launch_gemm256_t(hipStream_t st, int M, int N, int K, const bf16_t *a, const bf16_t *w,
+static int launch_gemm256_t(hipStream_t st, int M, int Mw, int N, int K, const bf16_t *a, const bf16_t *w,
                             const bf16_t *w2, float *out, bf16_t *out_t, const RopeOut &ro) {
   const int tiles_m = (M + 32 * WV * TM - 1) / (32 * WV * TM), tiles_n = N / (32 * TN);
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
@@ -396,14 +397,15 @@ static int launch_gemm256_t(hipStream_t st, int M, int N, int K, const bf16_t *a
   const int lds = std::max<int>((D + 2) * TN * (MODE == GEMM_SWIGLU ? 2 : 1) * 4096 + (WV > 8 ? 1024 : 0),
                                 MODE == GEMM_ROPE ? WV * 32 * kParkStride * (int)sizeof(float) : 0);
   MC_TRY(raise_dynamic_lds_limit((const void *)gemm256_kernel<MODE, TM, TN, D, WV, NT>, lds));
-  gemm256_kernel<MODE, TM, TN, D, WV, NT><<<8 * per_xcd, 64 * WV, lds, st>>>(M, N, K, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
+  gemm256_kernel<MODE, TM, TN, D, WV, NT><<<8 * per_xcd, 64 * WV, lds, st>>>(M, Mw, N, K, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }
 
 int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const void *w,
-                   const void *w2, float *out, void *out_t, const RopeOut *rope, int accumulate) {
+                   const void *w2, float *out, void *out_t, const RopeOut *rope, int accumulate, bool zero_pad) {
   const bool swiglu = w2 != nullptr;
+  const int Mw = zero_pad ? padded_rows(M) : M;
   if (!gemm256_supported(M, N, K, swiglu)) MC_FAIL(MC_ERR_UNSUPPORTED, "GEMM: M=%d N=%d K=%d not covered", M, N, K);
   if ((swiglu && (rope || accumulate)) || (rope && accumulate))
     MC_FAIL(MC_ERR_INVALID, "GEMM: one output form at a time");
@@ -416,20 +418,20 @@ int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const voi
     constexpr int MODE = decltype(mode)::value;
     const RopeOut ro = rope ? *rope : RopeOut{};
     if constexpr (MODE == GEMM_SWIGLU) {
-      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 2, 2, 4>(st, M, N, K, A, W, W2, out, OT, ro);
-      if (f.waves == 10) return launch_gemm256_t<MODE, 1, 2, 2, 10>(st, M, N, K, A, W, W2, out, OT, ro);
-      if (f.waves == 12) return launch_gemm256_t<MODE, 1, 2, 2, 12>(st, M, N, K, A, W, W2, out, OT, ro);
+      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 2, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.waves == 10) return launch_gemm256_t<MODE, 1, 2, 2, 10>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.waves == 12) return launch_gemm256_t<MODE, 1, 2, 2, 12>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       // one row tile: every weight is read once (14336 x 4096, 100 rows: 49.4 -> 45.7 us)
-      if (f.tn == 2 && M <= 128) return launch_gemm256_t<MODE, 1, 2, 2, 4, true>(st, M, N, K, A, W, W2, out, OT, ro);
-      if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 2, 4>(st, M, N, K, A, W, W2, out, OT, ro);
-      return launch_gemm256_t<MODE, 1, 1, 2, 4>(st, M, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 2 && M <= 128) return launch_gemm256_t<MODE, 1, 2, 2, 4, true>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      return launch_gemm256_t<MODE, 1, 1, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
     } else {
-      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 4, 2, 4>(st, M, N, K, A, W, W2, out, OT, ro);
-      if (f.tn == 4) return launch_gemm256_t<MODE, 1, 4, 2, 4>(st, M, N, K, A, W, W2, out, OT, ro);
-      if (f.waves == 2 && f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4, 2>(st, M, N, K, A, W, W2, out, OT, ro);
-      if (f.waves == 2) return launch_gemm256_t<MODE, 1, 1, 4, 2>(st, M, N, K, A, W, W2, out, OT, ro);
-      if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4, 4>(st, M, N, K, A, W, W2, out, OT, ro);
-      return launch_gemm256_t<MODE, 1, 1, 4, 4>(st, M, N, K, A, W, W2, out, OT, ro);
+      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 4, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 4) return launch_gemm256_t<MODE, 1, 4, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.waves == 2 && f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4, 2>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.waves == 2) return launch_gemm256_t<MODE, 1, 1, 4, 2>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      return launch_gemm256_t<MODE, 1, 1, 4, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
     }
   };
   if (swiglu) return run(std::integral_constant<int, GEMM_SWIGLU>{});

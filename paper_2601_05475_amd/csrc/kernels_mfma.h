@@ -35,7 +35,8 @@ __device__ inline float other_half(float x) {
 
 // All operands of these linear kernels are in the tiled layout (see tiled_offset).
 // Few-row linear layer (M <= 64): out = a w^T streamed once over the weights.
-// w2 != nullptr selects the SwiGLU form (out_t = silu(a wg^T) * (a wu^T), bf16, tiled).
+// w2 != nullptr selects the SwiGLU form (out_t = silu(a wg^T) * (a wu^T), bf16, tiled; zero_pad: its padding
+// rows are written as zeros).
 bool skinny_linear_supported(int M, int N, int K);
 int skinny_linear_splits(int M, int N, int K);
 // rope != nullptr: the fused QKV layer (one K split): w has the rows of every query / key head
@@ -48,7 +49,7 @@ constexpr int kTopPerGroup = 4;
 bool skinny_top_lists_supported(int M, int N, int K);
 int launch_linear_skinny(hipStream_t st, int M, int N, int K, const void *a, const void *w,
                          const void *w2, float *out, void *out_t, int n_splits,
-                         const RopeOut *rope = nullptr, void *top_out = nullptr);
+                         const RopeOut *rope = nullptr, void *top_out = nullptr, bool zero_pad = false);
 
 // Epilogue of the fused QKV layer for one row m and four consecutive outputs n .. n + 3 of the
 // interleaved weight layout, i.e. coordinates (i, i + hd/2, i + 1, i + 1 + hd/2) of one query or
@@ -112,7 +113,7 @@ bool gemm256_supported(int M, int N, int K, bool swiglu);
 // accumulate: out[m][n] += the product (the residual stream updated in place) instead of a store.
 int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const void *w,
                    const void *w2, float *out, void *out_t, const RopeOut *rope = nullptr,
-                   int accumulate = 0);
+                   int accumulate = 0, bool zero_pad = false);
 
 // Streaming-read probe over `bytes` of device memory (a multiple of 64 MiB); out: one word.
 int launch_read_probe(hipStream_t st, const void *buf, size_t bytes, uint32_t *out);
@@ -132,7 +133,8 @@ struct PrefillAttnArgs {
   int32_t table_stride;
   int32_t n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len;
   void *out;                     // bf16 [rows][Hq*hd], row-major or tiled
-  int32_t out_tiled;
+  int32_t out_tiled;             // TILED_ZERO: rows of the `rows` tiled ones that no item covers, padding rows among them, become zero
+  int32_t rows = 0;
 };
 bool prefill_attention_mfma_supported(int page_tokens, int head_dim, int Hq, int Hkv);
 int launch_attention_prefill_mfma(hipStream_t st, const PrefillAttnArgs &a);

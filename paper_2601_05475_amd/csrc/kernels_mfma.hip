@@ -149,7 +149,7 @@ struct Top4 {
 enum { SKINNY_PLAIN = 0, SKINNY_SWIGLU = 1, SKINNY_PAIR = 2 };
 template <int MB, int MODE, bool ROPE>
 __global__ __launch_bounds__(256) void skinny_linear_kernel(
-    int M, int N, int K, int units_per_wave, const bf16_t *__restrict__ a,
+    int M, int Mw, int N, int K, int units_per_wave, const bf16_t *__restrict__ a,
     const bf16_t *__restrict__ w, const bf16_t *__restrict__ w2, float *__restrict__ out,
     bf16_t *__restrict__ out_t, RopeOut ro, uint2 *__restrict__ top_out) {
   constexpr bool SWIGLU = MODE == SKINNY_SWIGLU, PAIR = MODE == SKINNY_PAIR;
@@ -285,10 +285,10 @@ __global__ __launch_bounds__(256) void skinny_linear_kernel(
         s[i].x += t.x; s[i].y += t.y; s[i].z += t.z; s[i].w += t.w;
       }
     }
-    if (m < M) {
+    if (m < (SWIGLU ? Mw : M)) {
       if (SWIGLU) {
         // the product feeds the next linear layer: store it tiled, as a [*][N] activation
-        *(uint2 *)(out_t + tiled_offset(m, n, N)) =
+        *(uint2 *)(out_t + tiled_offset(m, n, N)) = m >= M ? make_uint2(0u, 0u) :
             pack4_bf16(silu_f(s[0].x) * s[NW - 1].x, silu_f(s[0].y) * s[NW - 1].y,
                        silu_f(s[0].z) * s[NW - 1].z, silu_f(s[0].w) * s[NW - 1].w);
       } else if (ROPE) {
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(256) void skinny_linear_kernel(
 // =====================================================================================
 template <int NB, int MODE, bool ROPE>
 __global__ __launch_bounds__(256) void skinny_rows_kernel(
-    int M, int N, int K, int rows_per_wg, const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
+    int M, int Mw, int N, int K, int rows_per_wg, const bf16_t *__restrict__ a, const bf16_t *__restrict__ w,
     const bf16_t *__restrict__ w2, bf16_t *__restrict__ out_t, RopeOut ro) {
   constexpr bool SWIGLU = MODE == SKINNY_SWIGLU;
   constexpr int NW = SWIGLU ? 2 : 1;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256) void skinny_rows_kernel(
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int n = r0 + 32 * b + 8 * r4 + 4 * h;
-    if (n >= r1 || m >= M) continue;
+    if (n >= r1 || m >= (SWIGLU ? Mw : M)) continue;
     float4 s[NW];
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(256) void skinny_rows_kernel(
       }
     }
     if (SWIGLU) {
-      *(uint2 *)(out_t + tiled_offset(m, n, N)) =
+      *(uint2 *)(out_t + tiled_offset(m, n, N)) = m >= M ? make_uint2(0u, 0u) :
           pack4_bf16(silu_f(s[0].x) * s[NW - 1].x, silu_f(s[0].y) * s[NW - 1].y,
                      silu_f(s[0].z) * s[NW - 1].z, silu_f(s[0].w) * s[NW - 1].w);
     } else if (ROPE) {
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(256) void skinny_rows_kernel(
 // =====================================================================================
 template <bool SWIGLU>
 __global__ __launch_bounds__(256) void skinny_shared_kernel(
-    int M, int N, int K, int units_per_split, const bf16_t *__restrict__ a,
+    int M, int Mw, int N, int K, int units_per_split, const bf16_t *__restrict__ a,
     const bf16_t *__restrict__ w, const bf16_t *__restrict__ w2, float *__restrict__ out,
     bf16_t *__restrict__ out_t) {
   constexpr int MB = 2, NW = SWIGLU ? 2 : 1, CH = 4;
@@ -507,14 +507,14 @@ __global__ __launch_bounds__(256) void skinny_shared_kernel(
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int m = mb * 32 + nl;
-    if (m >= M) continue;
+    if (m >= (SWIGLU ? Mw : M)) continue;
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
       const int n = 32 * wt + 8 * r4 + 4 * h;
       const f32x16 &g = acc[0][mb];
       if (SWIGLU) {
         const f32x16 &v = acc[NW - 1][mb];
-        *(uint2 *)(out_t + tiled_offset(m, n, N)) =
+        *(uint2 *)(out_t + tiled_offset(m, n, N)) = m >= M ? make_uint2(0u, 0u) :
             pack4_bf16(silu_f(g[4 * r4]) * v[4 * r4], silu_f(g[4 * r4 + 1]) * v[4 * r4 + 1],
                        silu_f(g[4 * r4 + 2]) * v[4 * r4 + 2], silu_f(g[4 * r4 + 3]) * v[4 * r4 + 3]);
       } else {
@@ -581,8 +581,8 @@ bool skinny_top_lists_supported(int M, int N, int K) {
 
 int launch_linear_skinny(hipStream_t st, int M, int N, int K, const void *a, const void *w,
                          const void *w2, float *out, void *out_t, int n_splits, const RopeOut *rope,
-                         void *top_out) {
-  const int units = K / 64;
+                         void *top_out, bool zero_pad) {
+  const int units = K / 64, Mw = zero_pad ? padded_rows(M) : M;      // Mw: rows of the SwiGLU output that are written
   if (!skinny_linear_supported(M, N, K) || n_splits < 1 || units % (4 * n_splits))
     MC_FAIL(MC_ERR_UNSUPPORTED, "few-row linear: M=%d N=%d K=%d splits=%d not covered", M, N, K, n_splits);
   if (w2 && n_splits != 1) MC_FAIL(MC_ERR_INVALID, "the SwiGLU form cannot be split over K");
@@ -598,10 +598,10 @@ int launch_linear_skinny(hipStream_t st, int M, int N, int K, const void *a, con
       const int lds = 4 * n_blocks * n_w * 4 * 64 * (int)sizeof(float4);
       MC_TRY(raise_dynamic_lds_limit((const void *)kernel, lds));
       if (ev3.start || ev3.stop)
-        hipExtLaunchKernelGGL(kernel, dim3(N / R), dim3(256), lds, st, ev3.start, ev3.stop, 0, M, N, K, R,
+        hipExtLaunchKernelGGL(kernel, dim3(N / R), dim3(256), lds, st, ev3.start, ev3.stop, 0, M, Mw, N, K, R,
                               (const bf16_t *)a, (const bf16_t *)w, (const bf16_t *)w2, (bf16_t *)out_t, ro);
       else
-        kernel<<<dim3(N / R), 256, lds, st>>>(M, N, K, R, (const bf16_t *)a, (const bf16_t *)w,
+        kernel<<<dim3(N / R), 256, lds, st>>>(M, Mw, N, K, R, (const bf16_t *)a, (const bf16_t *)w,
                                               (const bf16_t *)w2, (bf16_t *)out_t, ro);
       return MC_OK;
     };
@@ -618,10 +618,10 @@ int launch_linear_skinny(hipStream_t st, int M, int N, int K, const void *a, con
     const LaunchEvents ev2 = take_launch_events();
     auto go2 = [&](auto kernel) {
       if (ev2.start || ev2.stop)
-        hipExtLaunchKernelGGL(kernel, grid2, dim3(256), 0, st, ev2.start, ev2.stop, 0, M, N, K, units / n_splits,
+        hipExtLaunchKernelGGL(kernel, grid2, dim3(256), 0, st, ev2.start, ev2.stop, 0, M, Mw, N, K, units / n_splits,
                               (const bf16_t *)a, (const bf16_t *)w, (const bf16_t *)w2, out, (bf16_t *)out_t);
       else
-        kernel<<<grid2, 256, 0, st>>>(M, N, K, units / n_splits, (const bf16_t *)a, (const bf16_t *)w,
+        kernel<<<grid2, 256, 0, st>>>(M, Mw, N, K, units / n_splits, (const bf16_t *)a, (const bf16_t *)w,
                                       (const bf16_t *)w2, out, (bf16_t *)out_t);
     };
     if (w2) go2(skinny_shared_kernel<true>);
@@ -642,9 +642,9 @@ int launch_linear_skinny(hipStream_t st, int M, int N, int K, const void *a, con
   const LaunchEvents ev = take_launch_events();
   auto go = [&](auto kernel, const RopeOut &ro) {
     if (ev.start || ev.stop)
-      hipExtLaunchKernelGGL(kernel, grid, dim3(256), 0, st, ev.start, ev.stop, 0, M, N, K, upw, A, W, W2, out, OT, ro, (uint2 *)top_out);
+      hipExtLaunchKernelGGL(kernel, grid, dim3(256), 0, st, ev.start, ev.stop, 0, M, Mw, N, K, upw, A, W, W2, out, OT, ro, (uint2 *)top_out);
     else
-      kernel<<<grid, 256, 0, st>>>(M, N, K, upw, A, W, W2, out, OT, ro, (uint2 *)top_out);
+      kernel<<<grid, 256, 0, st>>>(M, Mw, N, K, upw, A, W, W2, out, OT, ro, (uint2 *)top_out);
   };
   if (M <= 32) {
     if (rope) go(skinny_linear_kernel<1, SKINNY_PLAIN, true>, *rope);

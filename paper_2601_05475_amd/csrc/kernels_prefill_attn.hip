@@ -170,6 +170,46 @@ __device__ inline void store_tile(const PrefillAttnArgs &a, int row, int head, i
   }
 }
 
+// TILED_ZERO: block b takes eight 32-row tiles, marks the rows that the items cover (a thread per item: one round trip) and
+// writes zeros to the others, where a fill of the whole output takes 5 us (300 rows of 4096) to 11 us
+// (8192 rows).  The split kernel has such blocks behind those of its items, and they run beside them.  In the
+// whole-item kernel the added code moved the loop's registers and its place (two sequences of 831 rows after 1940 keys,
+// heads of 64: 57 -> 61 us), so there something is launched ahead of it: the same for an output that outgrows the L2s (8 x 1024
+// rows of 4096: 600 -> 592 us for the call), a fill of the whole for a smaller one, whose lines the stores then find in L2
+// (5 sequences of 350 to 700 rows: 63.8 us by the fill, 66.2 by the uncovered rows alone).
+__device__ inline void zero_uncovered_rows(const PrefillAttnArgs &a, int b, int K) {
+  __shared__ uint32_t cover[8];
+  const int tid = threadIdx.x, row0 = 256 * b;
+  if (tid < 8) cover[tid] = 0;
+  __syncthreads();
+  for (int i = tid; i < a.n_items; i += 512) {
+    const int4 item = a.items[i];
+    const int from = max(item.x, row0), to = min(item.x + item.y, row0 + 256);         // rows [from, to) of this block's
+    for (int r = from; r < to; r = (r | 31) + 1) {
+      const uint32_t upto = to > (r | 31) ? ~0u : (1u << (to & 31)) - 1;
+      atomicOr(&cover[(r - row0) >> 5], upto & (~0u << (r & 31)));
+    }
+  }
+  __syncthreads();
+  for (int t = 0; t < 8 && row0 + 32 * t < a.rows; ++t) {
+    const uint32_t bare = __builtin_amdgcn_readfirstlane(~cover[t]);
+    if (bare == 0) continue;
+    for (int k = 8 * tid; k < K; k += 8 * 512)
+      for (uint32_t left = bare; left; left &= left - 1)
+        *(v4u *)((bf16_t *)a.out + tiled_offset(row0 + 32 * t + __builtin_ctz(left), k, K)) = v4u{0, 0, 0, 0};
+  }
+}
+
+__global__ __launch_bounds__(512) void zero_uncovered_rows_kernel(PrefillAttnArgs a) {
+  zero_uncovered_rows(a, blockIdx.x, a.n_q_heads * a.head_dim);
+}
+
+__global__ __launch_bounds__(256) void zero_rows_kernel(v4u *out, size_t pieces) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < pieces) out[i] = v4u{0, 0, 0, 0};
+}
+constexpr size_t kL2Bytes = 32u << 20;         // of the eight XCDs together
+
 // Waves per SIMD: two at head_dim 128 (190 registers); at head_dim 64 (125 registers, 52 KB of LDS) two workgroups
 // share a compute unit.  (With an upper bound of two there the second stays out: 8 x 1024 rows after 4096
 // keys, 32 / 8 heads of 64, 339 -> 390 us.)
@@ -352,7 +392,8 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
 // gives a load 2 SLOTS - 1 half steps to land.
 template <int HD, int KS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void prefill_attention_split_kernel(PrefillAttnArgs a) {
+void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
+  if ((int)blockIdx.x >= n_main) return zero_uncovered_rows(a, (int)blockIdx.x - n_main, a.n_q_heads * HD);
   using TL = PTile<HD>;
   using SP = PSplit<HD, KS>;
   constexpr int NF = TL::NF, NDT = SP::NDT;
@@ -603,9 +644,15 @@ static int launch_prefill_t(hipStream_t st, const PrefillAttnArgs &a) {
     lds = PSplit<HD, KS>::LDS_BYTES;
   }
   MC_TRY(raise_dynamic_lds_limit(kernel, lds));
-  const unsigned grid = (unsigned)prefill_grid<KS>(a);
-  if constexpr (KS == 1) prefill_attention_kernel<HD><<<grid, 512, lds, st>>>(a);
-  else prefill_attention_split_kernel<HD, KS><<<grid, 512, lds, st>>>(a);
+  const unsigned n_main = (unsigned)prefill_grid<KS>(a), n_zero = a.out_tiled == TILED_ZERO ? (a.rows + 255) / 256 : 0;
+  if constexpr (KS == 1) {
+    const size_t pieces = (size_t)padded_rows(a.rows) * a.n_q_heads * HD / 8;
+    if (n_zero && pieces * 16 <= kL2Bytes) zero_rows_kernel<<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((v4u *)a.out, pieces);
+    else if (n_zero) zero_uncovered_rows_kernel<<<n_zero, 512, 0, st>>>(a);
+    prefill_attention_kernel<HD><<<n_main, 512, lds, st>>>(a);
+  } else {
+    prefill_attention_split_kernel<HD, KS><<<n_main + n_zero, 512, lds, st>>>(a, (int)n_main);
+  }
   MC_HIP(hipGetLastError());
   return MC_OK;
 }

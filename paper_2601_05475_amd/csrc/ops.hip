@@ -103,8 +103,9 @@ int launch_linear_swiglu(hipStream_t st, int dtype, int M, int N, int K, const v
   if (!tiled) return launch_linear_swiglu_generic(st, dtype, M, N, K, a, wg, wu, out);
   if (dtype != MC_BF16 || !tiled_shapes_ok(M, N, K))
     MC_FAIL(MC_ERR_UNSUPPORTED, "tiled linear layer: bf16 with N %% 128 == 0 and K %% 256 == 0 only");
-  if (M <= 64) return launch_linear_skinny(st, M, N, K, a, wg, wu, nullptr, out, 1);
-  return launch_gemm256(st, M, N, K, a, wg, wu, nullptr, out);
+  const bool zero_pad = tiled == TILED_ZERO;
+  if (M <= 64) return launch_linear_skinny(st, M, N, K, a, wg, wu, nullptr, out, 1, nullptr, nullptr, zero_pad);
+  return launch_gemm256(st, M, N, K, a, wg, wu, nullptr, out, nullptr, 0, zero_pad);
 }
 
 // ---- decode attention: MFMA split-K kernel when the shape allows, else the generic kernel ---
@@ -166,7 +167,7 @@ extern "C" int mc_op_add_rmsnorm(void *stream, int32_t dtype, int32_t rows, int3
   if (rows < 0 || d < 1 || n_partials < 0) MC_FAIL(MC_ERR_INVALID, "bad sizes");
   if (!x || !gain || !h_out || (n_partials && !partials)) MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
   MC_TRY(check_tiled(dtype, h_tiled, d));
-  return launch_add_rmsnorm((hipStream_t)stream, dtype, rows, d, x, partials, n_partials, gain, eps, h_out, h_tiled);
+  return launch_add_rmsnorm((hipStream_t)stream, dtype, rows, d, x, partials, n_partials, gain, eps, h_out, h_tiled ? TILED_ZERO : ROW_MAJOR);
 }
 
 extern "C" int mc_op_linear(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K,
@@ -218,7 +219,7 @@ extern "C" int mc_op_linear_swiglu(void *stream, int32_t dtype, int32_t M, int32
   if (M < 0 || N < 1 || K < 1) MC_FAIL(MC_ERR_INVALID, "bad sizes");
   if (!a || !w_gate || !w_up || !out) MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
   MC_TRY(check_tiled(dtype, tiled, K));
-  return launch_linear_swiglu((hipStream_t)stream, dtype, M, N, K, a, w_gate, w_up, out, tiled);
+  return launch_linear_swiglu((hipStream_t)stream, dtype, M, N, K, a, w_gate, w_up, out, tiled ? TILED_ZERO : ROW_MAJOR);
 }
 
 extern "C" int mc_op_rope_kv_write(void *stream, int32_t dtype, int32_t rows, int32_t n_q_heads,
@@ -275,7 +276,7 @@ extern "C" int mc_op_attention_decode(void *stream, int32_t dtype, int32_t n_can
   a.page_tokens = page_tokens; a.prefix_len = prefix_len; a.suffix_len = suffix_len;
   a.row_len = suffix_len ? row_len : nullptr;
   a.prefix_splits = prefix_splits; a.workspace = workspace; a.workspace_bytes = workspace_bytes;
-  a.out = out; a.out_tiled = out_tiled;
+  a.out = out; a.out_tiled = out_tiled ? TILED_ZERO : ROW_MAJOR;
   return launch_attention_decode((hipStream_t)stream, dtype, a);
 }
 
@@ -354,17 +355,14 @@ extern "C" int mc_op_mfma_probe(void *stream, const void *operands, float *out, 
   return launch_mfma_probe((hipStream_t)stream, operands, out, n_workgroups, iters);
 }
 
-extern "C" int mc_op_attention_prefill(void *stream, int32_t n_items, const int32_t *items,
-                                       int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
-                                       int32_t page_tokens, int32_t prefix_len, const void *q,
-                                       const void *k_prefix, const void *v_prefix,
-                                       const void *k_suffix, const void *v_suffix,
-                                       const int32_t *page_table, int32_t table_stride, void *out,
-                                       int32_t out_tiled) {
+static int op_attention_prefill(void *stream, int32_t rows, int32_t n_items, const int32_t *items, int32_t n_q_heads,
+                                int32_t n_kv_heads, int32_t head_dim, int32_t page_tokens, int32_t prefix_len, const void *q,
+                                const void *k_prefix, const void *v_prefix, const void *k_suffix, const void *v_suffix,
+                                const int32_t *page_table, int32_t table_stride, void *out, int32_t layout) {
   if (n_items < 0 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads || prefix_len < 1)
     MC_FAIL(MC_ERR_INVALID, "bad sizes");
   if (!items || !q || !k_prefix || !v_prefix || !out) MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
-  MC_TRY(check_tiled(MC_BF16, out_tiled, n_q_heads * head_dim));
+  MC_TRY(check_tiled(MC_BF16, layout != ROW_MAJOR, n_q_heads * head_dim));
   if (!prefill_attention_mfma_supported(page_tokens, head_dim, n_q_heads, n_kv_heads))
     MC_FAIL(MC_ERR_UNSUPPORTED, "prefill attention: bf16, 64-token pages, head_dim 64 or 128 only");
   PrefillAttnArgs a;
@@ -372,8 +370,32 @@ extern "C" int mc_op_attention_prefill(void *stream, int32_t n_items, const int3
   a.items = (const int4 *)items; a.n_items = n_items; a.page_table = page_table;
   a.table_stride = table_stride; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads;
   a.head_dim = head_dim; a.page_tokens = page_tokens; a.prefix_len = prefix_len; a.out = out;
-  a.out_tiled = out_tiled;
+  a.out_tiled = layout; a.rows = rows;
   return launch_attention_prefill_mfma((hipStream_t)stream, a);
+}
+
+extern "C" int mc_op_attention_prefill(void *stream, int32_t n_items, const int32_t *items,
+                                       int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                       int32_t page_tokens, int32_t prefix_len, const void *q,
+                                       const void *k_prefix, const void *v_prefix,
+                                       const void *k_suffix, const void *v_suffix,
+                                       const int32_t *page_table, int32_t table_stride, void *out,
+                                       int32_t out_tiled) {
+  if (out_tiled != 0 && out_tiled != 1) MC_FAIL(MC_ERR_INVALID, "tiled must be 0 or 1");
+  return op_attention_prefill(stream, 0, n_items, items, n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len, q, k_prefix,
+                              v_prefix, k_suffix, v_suffix, page_table, table_stride, out, out_tiled ? TILED : ROW_MAJOR);
+}
+
+extern "C" int mc_op_attention_prefill_tiled(void *stream, int32_t rows, int32_t n_items, const int32_t *items,
+                                       int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                       int32_t page_tokens, int32_t prefix_len, const void *q,
+                                       const void *k_prefix, const void *v_prefix,
+                                       const void *k_suffix, const void *v_suffix,
+                                       const int32_t *page_table, int32_t table_stride, void *out) {
+  if (rows < 1) MC_FAIL(MC_ERR_INVALID, "bad sizes");
+  if (n_items == 0) MC_FAIL(MC_ERR_INVALID, "no items");
+  return op_attention_prefill(stream, rows, n_items, items, n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len, q, k_prefix,
+                              v_prefix, k_suffix, v_suffix, page_table, table_stride, out, TILED_ZERO);
 }
 
 extern "C" size_t mc_op_top_list_bytes(int32_t rows, int32_t N) {

@@ -973,3 +973,79 @@ def test_mfma_probe_counts_what_it_claims():
     torch.cuda.synchronize()
     assert torch.all(out == 8 * 16 * 16 * iters)
     assert binding.op_mfma_probe(ops, n_wg, iters) == n_wg * 4 * iters * 8 * 32768.0
+
+
+def _poison(n):
+    """Leave NaN where the next buffer of n bf16 values is allocated from."""
+    import torch
+    t = torch.full((n,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    del t
+
+
+def _padding_of(flat, rows, K):
+    return binding.tiled_to_rowmajor(flat, (rows + 31) // 32 * 32, K)[rows:]
+
+
+@pytest.mark.parametrize("rows,d", [(1, 64), (31, 256), (33, 4096), (300, 2048), (2050, 1024), (5, 16448)])
+def test_norm_writes_its_padding_rows(rows, d):
+    import torch
+    x = to_dev(rnd(920, (rows, d)), "f32")[0]
+    _poison((rows + 31) // 32 * 32 * d)
+    h = binding.op_add_rmsnorm(x, None, torch.ones(d, dtype=torch.bfloat16, device="cuda"), 1e-6, tiled=True)
+    assert not h.isnan().any() and not _padding_of(h, rows, d).any()
+    want = x.double() / torch.sqrt((x.double() ** 2).mean(-1, keepdim=True) + 1e-6)
+    assert rel_l2(binding.tiled_to_rowmajor(h, rows, d).double().cpu().numpy(), want.cpu().numpy()) < TOL["bf16"]
+
+
+# the tile per workgroup, the row ranges, shared activations, two row tiles, and the GEMM's forms
+@pytest.mark.parametrize("M,N,K", [(5, 256, 512), (17, 6144, 256), (50, 20480, 256), (40, 256, 256), (70, 14336, 256), (100, 2048, 256),
+                                   (150, 8192, 256), (270, 14336, 256), (330, 14336, 256), (601, 14336, 256)])
+def test_swiglu_writes_its_padding_rows(M, N, K):
+    a, wg, wu = (binding.op_pack_tiled(to_dev(rnd(s, (n, K), 0.1), "bf16")[0]) for s, n in ((921, M), (922, N), (923, N)))
+    _poison((M + 31) // 32 * 32 * N)
+    out = binding.op_linear_swiglu(a, wg, wu, tiled_shape=(M, N, K))
+    assert not out.isnan().any() and not _padding_of(out, M, N).any()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,hd,pg,P,t,splits", [
+    (8, 32, 8, 64, 64, 777, 37, 0), (1, 8, 2, 128, 64, 300, 5, 0), (33, 8, 2, 128, 64, 300, 5, 0),     # merged partial states
+    (3, 8, 2, 64, 64, 3000, 1, 64),                                                                    # more of them than one batch
+    (5, 8, 2, 128, 64, 20, 0, 0), (9, 8, 4, 64, 64, 0, 30, 0), (57, 32, 8, 128, 64, 100, 0, 0),        # one: the items write
+    (5, 8, 2, 96, 64, 100, 9, 0), (7, 4, 2, 64, 16, 33, 4, 0)])                                        # the generic kernel
+def test_decode_attention_writes_its_padding_rows(B, Hq, Hkv, hd, pg, P, t, splits):
+    import torch
+    kp, vp, _, _ = make_pools("bf16", max(1, -(-P // pg)), Hkv, pg, hd, 924)
+    per = max(1, -(-t // pg))
+    ks, vs, _, _ = make_pools("bf16", B * per, Hkv, pg, hd, 925)
+    table = torch.arange(B * per, dtype=torch.int32, device="cuda").reshape(B, per)
+    q = to_dev(rnd(926, (B, Hq, hd)), "bf16")[0]
+    run = lambda tiled: binding.op_attention_decode(q, kp if P else None, vp if P else None, ks, vs, table, P, t, pg, splits, out_tiled=tiled)  # noqa: E731
+    _poison((B + 31) // 32 * 32 * Hq * hd)
+    out = run(True)
+    assert not out.isnan().any() and not _padding_of(out, B, Hq * hd).any()
+    assert torch.equal(binding.tiled_to_rowmajor(out, B, Hq * hd).reshape(B, Hq, hd), run(False))
+
+
+@pytest.mark.parametrize("Hq,hd,lens", [(8, 128, (300,)), (8, 64, (33,)), (8, 128, (1000, 70, 40)), (8, 64, (1000, 1000, 71)),
+                                        (64, 128, (1000, 65, 1000, 30))])
+def test_prefill_attention_zeroes_the_rows_that_no_item_covers(Hq, hd, lens):
+    """Padding rows, and rows between the items: in all forms (few and many workgroups, the last with an output
+    larger than the L2s)."""
+    import torch
+    Hkv, pg, P = 2, 64, 200
+    items, row, holes = [], 0, []
+    for n in lens:
+        items += [[row + r, min(64, n - r), P - n % 100 + r, -1] for r in range(0, n, 64)]
+        holes += list(range(row + n, row + n + 7))
+        row += n + 7                                    # seven rows that nobody computes
+    rows = row
+    kp, vp, _, _ = make_pools("bf16", -(-(P + max(lens)) // pg), Hkv, pg, hd, 927)
+    q = to_dev(rnd(928, (rows, Hq, hd)), "bf16")[0]
+    it = torch.tensor(items, dtype=torch.int32, device="cuda")
+    run = lambda tiled: binding.op_attention_prefill(q, it, kp, vp, None, None, None, P + max(lens), pg, out_tiled=tiled)  # noqa: E731
+    _poison((rows + 31) // 32 * 32 * Hq * hd)
+    out = run(True)
+    plain = binding.tiled_to_rowmajor(out, rows, Hq * hd)
+    assert not out.isnan().any() and not _padding_of(out, rows, Hq * hd).any() and not plain[holes].any()
+    keep = [r for r in range(rows) if r not in set(holes)]
+    assert torch.equal(plain[keep], run(False).reshape(rows, -1)[keep])
