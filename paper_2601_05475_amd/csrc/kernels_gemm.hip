@@ -97,6 +97,118 @@ __device__ inline void wait_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// The two ways of a wave's 32 x 32 TN sums, parked in LDS, to queries, keys and values.
+// Quad by quad, any head_dim and page: consecutive lanes take consecutive quads of one row.
+template <int TN>
+__device__ inline void rope_store_quads(const RopeOut &ro, int M, int m0, int n0, const float *park, int lane) {
+  constexpr int kBatch = 4;                  // quads per lane whose loads go out together
+#pragma unroll 1
+  for (int it0 = 0; it0 < 32 * TN * 8 / 64; it0 += kBatch) {
+    float4 s[kBatch];
+    RopeQuad rq[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int e = (it0 + u) * 64 + lane, row = e / (TN * 8), quad = e % (TN * 8);
+      s[u] = *(const float4 *)(park + row * kParkStride + 4 * quad);
+      rq[u] = rope_load_quad(ro, min(m0 + row, M - 1), n0 + 4 * quad);
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int e = (it0 + u) * 64 + lane, row = e / (TN * 8), quad = e % (TN * 8);
+      if (m0 + row < M) rope_store_quad(ro, m0 + row, n0 + 4 * quad, s[u], rq[u]);
+    }
+  }
+}
+
+// In pieces of 16 bytes, 32 columns (half of them a head's first coordinates, half their partners, or 32 coordinates of
+// a value head) at a time: a lane rotates eight pairs of one row and stores two pieces; for the keys the lanes of a store are
+// 32 rows, which is a fragment of the page, and a value piece is eight rows of one coordinate, as a fragment has
+// them.  By quads a key took 4-byte stores 16 bytes apart and a value 2-byte stores 64 bytes apart, and the
+// launch waited for the workgroups that had those: 1000 x 6144 x 4096 75 -> 67 us in a search depth (the plain product
+// 57), with the angle table's launch 2048 rows 136 -> 122, 4096 203 -> 186, 8192 375 -> 359.
+// Needs whole 32-column blocks inside a head, fragment-order pages and aligned bases.
+__device__ inline bool rope_pieces_ok(const RopeOut &ro) {
+  return kv_fragment_layout(ro.pg, ro.hd) && (((uintptr_t)ro.q_out | (uintptr_t)ro.k_pages | (uintptr_t)ro.v_pages) & 15) == 0;
+}
+struct RopeRow {
+  int pos, off, page;
+};
+__device__ inline RopeRow rope_row(const RopeOut &ro, int M, int m) {
+  m = min(m, M - 1);
+  return RopeRow{ro.row_pos[m], ro.row_off[m], ro.row_page[m]};
+}
+__device__ inline void rope_store_pieces(const RopeOut &ro, int M, int m0, int n0, int blocks, const RopeRow &mine, const float *park, int lane) {
+  const int hd = ro.hd, half = hd >> 1, j = lane & 31, h = lane >> 5;
+  const size_t pelems = (size_t)ro.Hkv * hd * ro.pg;
+  const int off = mine.off, page = mine.page, rows = min(32, M - m0);
+  // The rows fill consecutive slots, of one page between two slots that are multiples of 16: then 16 slots that the values'
+  // pieces span have one page.  (The session's passes; a caller's slots may be any.)
+  const int off0 = __builtin_amdgcn_readfirstlane(off), before = __shfl_up(page, 1, 32);
+  const bool in_line = j >= rows || (off == (off0 + j) % ro.pg && (j == 0 || off % 16 == 0 || page == before));
+  const bool regular = __all(in_line);
+  // Queries are rows of memory: a store's lanes share a row as far as the columns of one head at hand go (4 blocks of a
+  // 128-wide head: eight lanes, whole lines).
+  const int span = hd % (32 * blocks) == 0 ? blocks : 32 * blocks % hd == 0 ? hd / 32 : 1;
+#pragma unroll 1
+  for (int x = 0; x < blocks; ++x) {
+    const int n = n0 + 32 * x, head = n / hd;
+    if (head < ro.Hq + ro.Hkv) {
+      const bool query = head < ro.Hq;
+      const int per_row = query ? 2 * span : 1, x0 = query ? x - x % span : x;              // lanes of a row; first block at hand
+      const int row = query ? (x - x0) * (64 / per_row) + lane / per_row : j, g = query ? lane % per_row : h;
+      const int i = ((n0 + 32 * x0) % hd >> 1) + 8 * g;                                        // this lane's pairs: i .. i + 7
+      const int p = query ? __shfl(mine.pos, row) : mine.pos;
+      const float4 *src = (const float4 *)(park + 32 * x0 + row * kParkStride + 16 * g);
+      const double2 *tp = ro.table + (size_t)p * half + i;
+      v4u lo, hi;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float4 s = src[e];
+        const double2 t0 = tp[2 * e], t1 = tp[2 * e + 1];
+        const double lo0 = s.x, hi0 = s.y, lo1 = s.z, hi1 = s.w;
+        lo[e] = (uint32_t)f32_to_bf16((float)(lo0 * t0.x - hi0 * t0.y)) | ((uint32_t)f32_to_bf16((float)(lo1 * t1.x - hi1 * t1.y)) << 16);
+        hi[e] = (uint32_t)f32_to_bf16((float)(hi0 * t0.x + lo0 * t0.y)) | ((uint32_t)f32_to_bf16((float)(hi1 * t1.x + lo1 * t1.y)) << 16);
+      }
+      if (row < rows) {
+        bf16_t *dst = query ? (bf16_t *)ro.q_out + ((size_t)(m0 + row) * ro.Hq + head) * hd
+                            : (bf16_t *)ro.k_pages + (size_t)page * pelems + (size_t)(head - ro.Hq) * ro.pg * hd;
+        *(v4u *)(dst + (query ? i : k_elem_offset(off, i, ro.pg, hd))) = lo;
+        *(v4u *)(dst + (query ? i + half : k_elem_offset(off, i + half, ro.pg, hd))) = hi;
+      }
+      continue;
+    }
+    const int jp = n % hd;
+    const float *blk = park + 32 * x;
+    bf16_t *vh = (bf16_t *)ro.v_pages + (size_t)(head - ro.Hq - ro.Hkv) * ro.pg * hd;
+    if (regular) {
+      // lane: coordinate jp + j; slots 16 g + 4 h + {0..3, 8..11} of the 16-slot groups that the rows reach into
+      for (int r0 = -(off0 & 15); r0 < rows; r0 += 16) {
+        const int pg_of = __shfl(page, max(0, r0)), slot = (off0 + r0) % ro.pg;
+        bf16_t *dst = vh + (size_t)pg_of * pelems + v_elem_offset(slot + 4 * h, jp + j, ro.pg, hd);
+        const int ra = r0 + 4 * h, rb = ra + 8;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = blk[min(max((e < 4 ? ra : rb - 4) + e, 0), 31) * kParkStride + j];
+        if (ra >= 0 && rb + 3 < rows) {
+          v4u w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = (uint32_t)f32_to_bf16(v[2 * e]) | ((uint32_t)f32_to_bf16(v[2 * e + 1]) << 16);
+          *(v4u *)dst = w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int r = (e < 4 ? ra : rb - 4) + e;
+            if (r >= 0 && r < rows) dst[e] = f32_to_bf16(v[e]);
+          }
+        }
+      }
+    } else {
+      for (int c = h; c < 32; c += 2)
+        if (j < rows) (vh + (size_t)page * pelems)[v_elem_offset(off, jp + c, ro.pg, hd)] = f32_to_bf16(blk[j * kParkStride + c]);
+    }
+  }
+}
+
 // TM: 32-row tiles of a per wave; TN: 32-row tiles of each weight matrix per workgroup; D: units by which
 // the operands run ahead; WV: waves; NT: w's lines are read by this workgroup only and need not stay in L2.
 template <int MODE, int TM, int TN, int D, int WV, bool NT>
@@ -234,11 +346,13 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
   // weight rows are the A operand: a lane holds column m = j of the tile and, per register quad,
   // four consecutive n
   if (MODE == GEMM_ROPE) {
-    // The rotation epilogue is long; it runs as a rolled loop over quads that the wave first
-    // parks in its own slice of LDS (free after the last barrier above).  The loop hands
-    // consecutive lanes consecutive quads of one row, so table reads and query stores coalesce.
+    // The rotation epilogue is long; it runs as a rolled loop over what the wave first parks in its own
+    // slice of LDS (free after the last barrier above).
     float *park = (float *)gemm_lds + wave * (32 * kParkStride);
-    const int n_wave = 32 * nt0;
+    const bool pieces = rope_pieces_ok(ro);
+    RopeRow mine[TM];
+#pragma unroll
+    for (int y = 0; y < TM; ++y) mine[y] = rope_row(ro, M, 32 * (mt0 + TM * wm + y) + j);
 #pragma unroll
     for (int y = 0; y < TM; ++y) {
       const int m0 = 32 * (mt0 + TM * wm + y);
@@ -250,23 +364,9 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
           *(float4 *)(park + j * kParkStride + 32 * x + 8 * r4 + 4 * h) =
               make_float4(g[4 * r4], g[4 * r4 + 1], g[4 * r4 + 2], g[4 * r4 + 3]);
         }
-      constexpr int kBatch = 4;        // quads per lane whose loads go out together
-#pragma unroll 1
-      for (int it0 = 0; it0 < 32 * TN * 8 / 64; it0 += kBatch) {
-        float4 s[kBatch];
-        RopeQuad rq[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const int e = (it0 + u) * 64 + lane, row = e / (TN * 8), quad = e % (TN * 8);
-          s[u] = *(const float4 *)(park + row * kParkStride + 4 * quad);
-          rq[u] = rope_load_quad(ro, min(m0 + row, M - 1), n_wave + 4 * quad);
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const int e = (it0 + u) * 64 + lane, row = e / (TN * 8), quad = e % (TN * 8);
-          if (m0 + row < M) rope_store_quad(ro, m0 + row, n_wave + 4 * quad, s[u], rq[u]);
-        }
-      }
+      if (m0 >= M) continue;
+      if (pieces) rope_store_pieces(ro, M, m0, 32 * nt0, TN, mine[y], park, lane);
+      else rope_store_quads<TN>(ro, M, m0, 32 * nt0, park, lane);
     }
     return;
   }

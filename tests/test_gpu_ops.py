@@ -637,6 +637,39 @@ def test_linear_qkv_rope_fused(rows, Hq, Hkv, hd, K):
     assert np.all(kh.transpose(0, 2, 1, 3)[~written] == 0) and np.all(vh.transpose(0, 2, 1, 3)[~written] == 0)
 
 
+@pytest.mark.parametrize("rows,Hq,Hkv,hd,pg,start", [(200, 4, 2, 64, 64, 0), (333, 4, 2, 128, 64, 37), (300, 8, 2, 64, 32, 17), (97, 6, 1, 128, 96, 90),
+                                                     (1030, 8, 4, 128, 64, 1), (70, 4, 4, 32, 64, 50), (2100, 12, 2, 128, 64, 13)])
+def test_linear_qkv_rope_consecutive_slots(rows, Hq, Hkv, hd, pg, start):
+    """Keys and values of consecutive positions, as the session's passes write them (pages of any id, a first slot inside a
+    16-slot group, page ends inside a tile): every slot has the bits of the same product with its slots shuffled
+    (which goes by single values), and the others stay zero."""
+    import torch
+    K, base = 256, 1.0e4
+    nq = (Hq + 2 * Hkv) * hd
+    a = binding.op_pack_tiled(to_dev(rnd(940, (rows, K)), "bf16")[0])
+    w = binding.op_pack_tiled(to_dev(rnd(941, (nq, K), 0.05), "bf16")[0])
+    n_pages = -(-(start + rows) // pg)
+    rng = np.random.default_rng(942)
+    ids = rng.permutation(n_pages)
+    at = start + np.arange(rows)
+    lines = ids[at // pg] * pg + at % pg
+    mixed = rng.permutation(n_pages * pg)[:rows]
+
+    def run(slots):
+        t = lambda x: torch.from_numpy(x.astype(np.int32)).cuda()  # noqa: E731
+        kp = torch.zeros((n_pages, Hkv, pg * hd), dtype=torch.bfloat16, device="cuda")
+        vp = torch.zeros_like(kp)
+        q = binding.op_linear_qkv_rope(a, w, rows, K, t(at), t(slots // pg), t(slots % pg), Hq, Hkv, hd, pg, base, start + rows, kp, vp)
+        k, v = (x.transpose(1, 2).reshape(-1, Hkv, hd) for x in binding.kv_pages_unpack(kp, vp, pg, hd))
+        rest = np.setdiff1d(np.arange(n_pages * pg), slots)
+        assert not k[rest].any() and not v[rest].any()
+        return q, k[slots], v[slots]
+
+    print("case: qkv rope, consecutive slots", rows, Hq, Hkv, hd, pg, start, flush=True)
+    for name, x, y in zip(("queries", "keys", "values"), run(lines), run(mixed)):
+        assert x.any() and torch.equal(x, y), name
+
+
 @pytest.mark.parametrize("M,N,K", [(32, 256, 512), (7, 14336, 4096), (64, 128, 256), (150, 256, 512),
                                    (3000, 2048, 512), (2070, 2944, 256), (65, 384, 256),
                                    (50, 27648, 512), (64, 20480, 256),
