@@ -145,8 +145,31 @@ struct DecodeAttnArgs {
   int32_t out_tiled;
 };
 
+// Rows of a decode step: row r is the next token of candidate alive[r] (nullptr: of candidate r).  Its position and KV
+// slot follow from the candidate's length; they go to the row arrays that the layers read.
+struct StepRows {
+  const int32_t *tok;                                       // [rows]
+  const int32_t *alive, *page_table, *cand_len;             // cand_len: by candidate, nullptr: every candidate has length t
+  int32_t *row_pos, *row_page, *row_off, *row_tab, *row_len;    // row_len: written where lengths differ
+  int table_stride, page_tokens, prefix_len, t;
+  __device__ void publish(int r) const {
+    const int cand = alive ? alive[r] : r, n = cand_len ? cand_len[cand] : t;
+    row_pos[r] = prefix_len + n;
+    row_page[r] = page_table[(size_t)cand * table_stride + n / page_tokens];
+    row_off[r] = n % page_tokens;
+    row_tab[r] = cand;
+    if (cand_len) row_len[r] = n + 1;
+  }
+};
+
 int launch_embed(hipStream_t st, int dtype, int rows, int d, const int32_t *tokens,
                  const void *table, float *x);
+// x = table[token], h = x * gain / rms(x): the gather and the first norm of a pass in one launch; step: a decode step,
+// whose row arrays are written as well (tokens is not read then)
+bool norm_vec_ok(int d);                                    // the widths that it takes
+int launch_embed_rmsnorm(hipStream_t st, int dtype, int rows, int d, const int32_t *tokens, const StepRows *step, const void *table,
+                         float *x, const void *gain, float eps, void *h_out, int h_tiled);
+int launch_decode_rows(hipStream_t st, int rows, const StepRows &src, int32_t *tok);    // the other widths: tokens and row arrays alone
 // like_rows > 0: a row's sum runs in the order that a launch of that many rows takes (its bits do not tell the two apart)
 int launch_add_rmsnorm(hipStream_t st, int dtype, int rows, int d, float *x, const float *partials,
                        int n_partials, const void *gain, float eps, void *h_out, int h_tiled, int like_rows = 0);

@@ -5,6 +5,7 @@
 #include <stddef.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -114,35 +115,29 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(
 // on row (b % 8) * rows_per_xcd + b / 8 and every XCD gets a contiguous range of rows.  In the
 // tiled layout the 16-byte pieces of 8 consecutive rows share a 128-byte line; written from one
 // L2 they leave as whole lines instead of eight partial ones.
+// Written out, so that a row's sum has the same bits in every kernel that takes it (VEC fixes the order of the first two)
+template <int VEC>
+__device__ __forceinline__ float sum_squares(const float4 &v) {
+  const float a = VEC == 1 ? v.x : v.y, b = VEC == 1 ? v.y : v.x;
+  return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(b, b, a * a)));
+}
+
+// false: a padding row (zeroed here where asked for) or no row at all
+template <typename T>
+__device__ __forceinline__ bool norm_row(int rows, int rows_per_xcd, int d, T *__restrict__ h, int h_tiled, int &r) {
+  r = rows_per_xcd > 0 ? (int)(blockIdx.x & 7) * rows_per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  if (r < rows) return true;
+  if (h_tiled == TILED_ZERO && r < padded_rows(rows))
+    for (int i = 4 * threadIdx.x; i < d; i += 4 * blockDim.x) *(uint2 *)(h + tiled_offset(r, i, d)) = make_uint2(0u, 0u);    // tiled: bf16
+  return false;
+}
+
+// v: the row's quads, ss: this thread's sum of their squares
 template <typename T, int VEC>
-__global__ __launch_bounds__(1024) void add_rmsnorm_vec_kernel(
-    int rows, int rows_per_xcd, int d, float *__restrict__ x, const float *__restrict__ partials, int n_partials,
-    size_t pstride, const T *__restrict__ gain, float eps, T *__restrict__ h, int h_tiled) {
-  __shared__ float scratch[16];
+__device__ __forceinline__ void norm_store(const float4 (&v)[VEC], float ss, int r, int d, const T *__restrict__ gain, float eps,
+                                           T *__restrict__ h, int h_tiled, float *scratch) {
   const int nt = blockDim.x;
-  const int r = rows_per_xcd > 0 ? (int)(blockIdx.x & 7) * rows_per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-  if (r >= rows) {
-    if (h_tiled == TILED_ZERO && r < padded_rows(rows))
-      for (int i = 4 * threadIdx.x; i < d; i += 4 * nt) *(uint2 *)(h + tiled_offset(r, i, d)) = make_uint2(0u, 0u);    // tiled: bf16
-    return;
-  }
   const size_t row = (size_t)r * d;
-  float4 v[VEC];
-  float ss = 0.f;
-#pragma unroll
-  for (int j = 0; j < VEC; ++j) {
-    const int i = 4 * (threadIdx.x + j * nt);
-    v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < d) {
-      v[j] = *(const float4 *)(x + row + i);
-      for (int s = 0; s < n_partials; ++s) {
-        const float4 p = *(const float4 *)(partials + s * pstride + row + i);
-        v[j].x += p.x; v[j].y += p.y; v[j].z += p.z; v[j].w += p.w;
-      }
-      if (n_partials) *(float4 *)(x + row + i) = v[j];
-      ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
-    }
-  }
   ss = block_sum<float>(ss, scratch);
   const float inv = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
@@ -164,27 +159,147 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_vec_kernel(
   }
 }
 
+template <typename T, int VEC>
+__global__ __launch_bounds__(1024) void add_rmsnorm_vec_kernel(
+    int rows, int rows_per_xcd, int d, float *__restrict__ x, const float *__restrict__ partials, int n_partials,
+    size_t pstride, const T *__restrict__ gain, float eps, T *__restrict__ h, int h_tiled) {
+  __shared__ float scratch[16];
+  const int nt = blockDim.x;
+  int r;
+  if (!norm_row(rows, rows_per_xcd, d, h, h_tiled, r)) return;
+  const size_t row = (size_t)r * d;
+  float4 v[VEC];
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < VEC; ++j) {
+    const int i = 4 * (threadIdx.x + j * nt);
+    v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < d) {
+      v[j] = *(const float4 *)(x + row + i);
+      for (int s = 0; s < n_partials; ++s) {
+        const float4 p = *(const float4 *)(partials + s * pstride + row + i);
+        v[j].x += p.x; v[j].y += p.y; v[j].z += p.z; v[j].w += p.w;
+      }
+      if (n_partials) *(float4 *)(x + row + i) = v[j];
+      ss += sum_squares<VEC>(v[j]);
+    }
+  }
+  norm_store<T, VEC>(v, ss, r, d, gain, eps, h, h_tiled, scratch);
+}
+
+// Rows of a pass whose tokens, positions and KV slots are on the device
+struct TokenRows {
+  const int32_t *tok;
+  __device__ void publish(int) const {}
+};
+
+// The first normalisation of a pass with the embedding gather in front of it, and for a decode step the rows' metadata
+// beside it: a workgroup past the rows stores that, so no row waits for it.  Each of these is a few KB per row, so a decode
+// step pays for the launches alone: metadata, gather and norm took 1.6 + 2.6 + 4.0 us at 8 rows of 2048.
+template <typename T, int VEC, typename ROWS>
+__global__ __launch_bounds__(1024) void embed_rmsnorm_kernel(int rows, int rows_per_xcd, int n_row_blocks, int d, ROWS src, const T *__restrict__ table,
+                                                             float *__restrict__ x, const T *__restrict__ gain, float eps,
+                                                             T *__restrict__ h, int h_tiled) {
+  __shared__ float scratch[16];
+  const int nt = blockDim.x;
+  if ((int)blockIdx.x == n_row_blocks) {
+    for (int i = threadIdx.x; i < rows; i += nt) src.publish(i);
+    return;
+  }
+  int r;
+  if (!norm_row(rows, rows_per_xcd, d, h, h_tiled, r)) return;
+  const T *e = table + (size_t)src.tok[r] * d;
+  float *xr = x + (size_t)r * d;
+  float4 v[VEC];
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < VEC; ++j) {
+    const int i = 4 * (threadIdx.x + j * nt);
+    v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < d) {
+      if (sizeof(T) == 2) {
+        const uint2 p = *(const uint2 *)(e + i);
+        v[j] = make_float4(bf16_to_f32((bf16_t)(p.x & 0xFFFF)), bf16_to_f32((bf16_t)(p.x >> 16)),
+                           bf16_to_f32((bf16_t)(p.y & 0xFFFF)), bf16_to_f32((bf16_t)(p.y >> 16)));
+      } else {
+        v[j] = *(const float4 *)(e + i);
+      }
+      *(float4 *)(xr + i) = v[j];
+      ss += sum_squares<VEC>(v[j]);
+    }
+  }
+  norm_store<T, VEC>(v, ss, r, d, gain, eps, h, h_tiled, scratch);
+}
+
+__global__ void decode_rows_kernel(int rows, StepRows src, int32_t *__restrict__ tok) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= rows) return;
+  src.publish(r);
+  tok[r] = src.tok[r];
+}
+
+int launch_decode_rows(hipStream_t st, int rows, const StepRows &src, int32_t *tok) {
+  decode_rows_kernel<<<(rows + 63) / 64, 64, 0, st>>>(rows, src, tok);
+  MC_HIP(hipGetLastError());
+  return MC_OK;
+}
+
+// Launch shape of the norms that take four elements per thread (norm_vec_ok)
+struct NormShape {
+  int nt, vec, rpx, grid;
+};
+bool norm_vec_ok(int d) { return d % 4 == 0 && d <= 16384; }
+static NormShape norm_shape(int rows, int d, int h_tiled, int like_rows) {
+  // enough threads for one float4 each where possible; at least one wave
+  const int quads = d / 4, all_rows = h_tiled == TILED_ZERO ? padded_rows(rows) : rows;
+  // many rows: 512 threads with two loads each in flight were measured faster than 1024 x 1
+  const int nt_max = (like_rows >= 2048 && quads <= 4 * 512) ? 512 : 1024;
+  NormShape n;
+  n.nt = 64;
+  while (n.nt < nt_max && n.nt < quads) n.nt *= 2;
+  n.vec = (quads + n.nt - 1) / n.nt;
+  // many rows into the tiled layout: a contiguous range of rows per XCD
+  n.rpx = (h_tiled && rows >= 256) ? ((all_rows + 7) / 8 + 7) / 8 * 8 : 0;
+  n.grid = n.rpx > 0 ? 8 * n.rpx : all_rows;
+  return n;
+}
+
 template <typename T>
 static void launch_add_rmsnorm_t(hipStream_t st, int rows, int d, float *x, const float *partials,
                                  int n_partials, size_t ps, const T *gain, float eps, T *h, int h_tiled, int like_rows) {
-  const int all_rows = h_tiled == TILED_ZERO ? padded_rows(rows) : rows;
-  if (d % 4 == 0 && d <= 16384) {
-    // enough threads for one float4 each where possible; at least one wave
-    const int quads = d / 4;
-    // many rows: 512 threads with two loads each in flight were measured faster than 1024 x 1
-    const int nt_max = (like_rows >= 2048 && quads <= 4 * 512) ? 512 : 1024;
-    int nt = 64;
-    while (nt < nt_max && nt < quads) nt *= 2;
-    const int vec = (quads + nt - 1) / nt;
-    // many rows into the tiled layout: a contiguous range of rows per XCD
-    const int rpx = (h_tiled && rows >= 256) ? ((all_rows + 7) / 8 + 7) / 8 * 8 : 0;
-    const int grid = rpx > 0 ? 8 * rpx : all_rows;
-    if (vec <= 1) add_rmsnorm_vec_kernel<T, 1><<<grid, nt, 0, st>>>(rows, rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
-    else if (vec <= 2) add_rmsnorm_vec_kernel<T, 2><<<grid, nt, 0, st>>>(rows, rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
-    else add_rmsnorm_vec_kernel<T, 4><<<grid, nt, 0, st>>>(rows, rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
+  if (norm_vec_ok(d)) {
+    const NormShape n = norm_shape(rows, d, h_tiled, like_rows);
+    if (n.vec <= 1) add_rmsnorm_vec_kernel<T, 1><<<n.grid, n.nt, 0, st>>>(rows, n.rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
+    else if (n.vec <= 2) add_rmsnorm_vec_kernel<T, 2><<<n.grid, n.nt, 0, st>>>(rows, n.rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
+    else add_rmsnorm_vec_kernel<T, 4><<<n.grid, n.nt, 0, st>>>(rows, n.rpx, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
   } else {
+    const int all_rows = h_tiled == TILED_ZERO ? padded_rows(rows) : rows;
     add_rmsnorm_kernel<T><<<all_rows, 256, 0, st>>>(rows, d, x, partials, n_partials, ps, gain, eps, h, h_tiled);
   }
+}
+
+template <typename T, typename ROWS>
+static void launch_embed_rmsnorm_t(hipStream_t st, int rows, int d, const ROWS &src, const T *table, float *x, const T *gain, float eps,
+                                   T *h, int h_tiled) {
+  const NormShape n = norm_shape(rows, d, h_tiled, rows);
+  const int grid = n.grid + (std::is_same<ROWS, StepRows>::value ? 1 : 0);
+  if (n.vec <= 1) embed_rmsnorm_kernel<T, 1, ROWS><<<grid, n.nt, 0, st>>>(rows, n.rpx, n.grid, d, src, table, x, gain, eps, h, h_tiled);
+  else if (n.vec <= 2) embed_rmsnorm_kernel<T, 2, ROWS><<<grid, n.nt, 0, st>>>(rows, n.rpx, n.grid, d, src, table, x, gain, eps, h, h_tiled);
+  else embed_rmsnorm_kernel<T, 4, ROWS><<<grid, n.nt, 0, st>>>(rows, n.rpx, n.grid, d, src, table, x, gain, eps, h, h_tiled);
+}
+
+int launch_embed_rmsnorm(hipStream_t st, int dtype, int rows, int d, const int32_t *tokens, const StepRows *step, const void *table,
+                         float *x, const void *gain, float eps, void *h_out, int h_tiled) {
+  if (rows <= 0) return MC_OK;
+  if (!norm_vec_ok(d)) MC_FAIL(MC_ERR_UNSUPPORTED, "embedding with norm: d %% 4 == 0 and d <= 16384 (d = %d)", d);
+  auto go = [&](const auto &src) {
+    if (dtype == MC_F32) launch_embed_rmsnorm_t<float>(st, rows, d, src, (const float *)table, x, (const float *)gain, eps, (float *)h_out, h_tiled);
+    else launch_embed_rmsnorm_t<bf16_t>(st, rows, d, src, (const bf16_t *)table, x, (const bf16_t *)gain, eps, (bf16_t *)h_out, h_tiled);
+  };
+  if (step) go(*step);
+  else go(TokenRows{tokens});
+  MC_HIP(hipGetLastError());
+  return MC_OK;
 }
 
 int launch_add_rmsnorm(hipStream_t st, int dtype, int rows, int d, float *x, const float *partials,

@@ -432,21 +432,6 @@ static int download(mc_session *s, void *dst_host, const void *src_dev, size_t b
   return MC_OK;
 }
 
-// tok_src != nullptr: the tokens drawn on the device become the rows' tokens here as well
-__global__ void decode_rows_kernel(int B, int pos, int page_slot, int off, int table_stride,
-                                   const int32_t *__restrict__ table, const int32_t *__restrict__ alive,
-                                   int32_t *row_pos, int32_t *row_page, int32_t *row_off, int32_t *row_tab,
-                                   const int32_t *__restrict__ tok_src, int32_t *row_tok) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  if (tok_src) row_tok[b] = tok_src[b];
-  const int cand = alive ? alive[b] : b;
-  row_pos[b] = pos;
-  row_page[b] = table[(size_t)cand * table_stride + page_slot];
-  row_off[b] = off;
-  row_tab[b] = cand;
-}
-
 // dst[r] = src[idx[r]] for r < n (idx ascending, so in place is safe when done by one thread each
 // after all reads: the kernel reads everything first)
 __global__ void compact_i32_kernel(int n, const int32_t *__restrict__ idx, int32_t *data) {
@@ -478,7 +463,7 @@ struct LastRows {
 // kernels and the same sums, on fewer rows.  One search depth of the two-layer 8B model (1000 + 211 + 900 rows): 2850 ->
 // 2190 us; a pass of a model of n layers loses about 0.8 / n of its work.
 static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int n_items, int *tail_splits,
-                      const LastRows *last = nullptr, bool *compact = nullptr) {
+                      const LastRows *last = nullptr, bool *compact = nullptr, const StepRows *step = nullptr) {
   const mc_model *m = s->m;
   const mc_config &c = m->cfg;
   const SessionLayout &L = s->lay;
@@ -490,11 +475,13 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
        *act = s->ptr<void>(L.act);
   const int32_t *row_pos = s->ptr<int32_t>(L.row_pos), *row_page = s->ptr<int32_t>(L.row_page),
                 *row_off = s->ptr<int32_t>(L.row_off), *row_tab = s->ptr<int32_t>(L.row_tab);
-  {
+  const int tl = m->tiled;
+  const bool embed_norm = norm_vec_ok(d);
+  if (!embed_norm) {
     ProfScope ps(s, MC_K_EMBED);
+    if (step) MC_TRY(launch_decode_rows(st, rows, *step, s->ptr<int32_t>(L.row_tok)));
     MC_TRY(launch_embed(st, dt, rows, d, s->ptr<int32_t>(L.row_tok), m->embed, x));
   }
-  const int tl = m->tiled;
   auto splits_for = [&](int N, int K) {
     int sp = linear_auto_splits(dt, rows, N, K, tl);
     sp = std::min(sp, kMaxSplits);
@@ -510,7 +497,10 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
   const size_t prefix_bytes = (size_t)L.n_prefix_pages * L.page_bytes;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW &W = m->layers[l];
-    {
+    if (l == 0 && embed_norm) {
+      ProfScope pe(s, MC_K_EMBED), ps(s, MC_K_ADD_RMSNORM);          // one launch is both
+      MC_TRY(launch_embed_rmsnorm(st, dt, rows, d, s->ptr<int32_t>(L.row_tok), step, m->embed, x, W.attn_norm, c.rms_eps, h, tl));
+    } else {
       ProfScope ps(s, MC_K_ADD_RMSNORM);
       MC_TRY(launch_add_rmsnorm(st, dt, rows, d, x, part, pending, W.attn_norm, c.rms_eps, h, tl));
     }
@@ -984,25 +974,6 @@ static void commit_pages(mc_session *s, const std::vector<int32_t> &idx, const s
   }
 }
 
-// rows of a decode step whose candidates differ in length: everything per row comes from the
-// candidate's own length (cand_len, by candidate id)
-__global__ void decode_rows_ragged_kernel(int B, int prefix_len, int pg, int table_stride,
-                                          const int32_t *__restrict__ table, const int32_t *__restrict__ alive,
-                                          const int32_t *__restrict__ cand_len, int32_t *row_pos,
-                                          int32_t *row_page, int32_t *row_off, int32_t *row_tab, int32_t *row_len,
-                                          const int32_t *__restrict__ tok_src, int32_t *row_tok) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  if (tok_src) row_tok[b] = tok_src[b];
-  const int cand = alive ? alive[b] : b;
-  const int t = cand_len[cand];
-  row_pos[b] = prefix_len + t;
-  row_page[b] = table[(size_t)cand * table_stride + t / pg];
-  row_off[b] = t % pg;
-  row_tab[b] = cand;
-  row_len[b] = t + 1;
-}
-
 extern "C" int mc_decode_step(mc_session *s, const int32_t *tokens, int32_t n_cands) {
   if (!s) MC_FAIL(MC_ERR_INVALID, "session is NULL");
   if (s->prefix_len <= 0) MC_FAIL(MC_ERR_STATE, "mc_decode_step before mc_prefill_shared");
@@ -1027,26 +998,16 @@ extern "C" int mc_decode_step(mc_session *s, const int32_t *tokens, int32_t n_ca
   if (tokens) {
     if (int rc1 = upload(s, s->ptr<void>(L.row_tok), tokens, (size_t)n_cands * 4)) return fail(rc1);
   }
-  const int32_t *tok_src = tokens ? nullptr : s->ptr<int32_t>(L.samp_tok);      // copied by the row kernel below
   if (s->ragged) {
     if (int rc1 = upload(s, s->ptr<void>(L.cand_len), s->cand_len.data(), (size_t)s->n_cands * 4)) return fail(rc1);
-    decode_rows_ragged_kernel<<<(n_cands + 63) / 64, 64, 0, s->stream>>>(
-        n_cands, s->prefix_len, pg, L.pages_per_cand, s->ptr<int32_t>(L.page_table),
-        s->dropped_any ? s->ptr<int32_t>(L.alive) : nullptr, s->ptr<int32_t>(L.cand_len), s->ptr<int32_t>(L.row_pos),
-        s->ptr<int32_t>(L.row_page), s->ptr<int32_t>(L.row_off), s->ptr<int32_t>(L.row_tab), s->ptr<int32_t>(L.row_len),
-        tok_src, s->ptr<int32_t>(L.row_tok));
-  } else {
-    decode_rows_kernel<<<(n_cands + 63) / 64, 64, 0, s->stream>>>(
-        n_cands, s->prefix_len + t, t / pg, t % pg, L.pages_per_cand, s->ptr<int32_t>(L.page_table),
-        s->dropped_any ? s->ptr<int32_t>(L.alive) : nullptr, s->ptr<int32_t>(L.row_pos), s->ptr<int32_t>(L.row_page), s->ptr<int32_t>(L.row_off),
-        s->ptr<int32_t>(L.row_tab), tok_src, s->ptr<int32_t>(L.row_tok));
   }
-  if (hipGetLastError() != hipSuccess) {
-    set_error("launch of the decode-row kernel failed");
-    return fail(MC_ERR_DEVICE);
-  }
+  const StepRows step = {tokens ? s->ptr<int32_t>(L.row_tok) : s->ptr<int32_t>(L.samp_tok),
+                         s->dropped_any ? s->ptr<int32_t>(L.alive) : nullptr, s->ptr<int32_t>(L.page_table),
+                         s->ragged ? s->ptr<int32_t>(L.cand_len) : nullptr, s->ptr<int32_t>(L.row_pos), s->ptr<int32_t>(L.row_page),
+                         s->ptr<int32_t>(L.row_off), s->ptr<int32_t>(L.row_tab), s->ptr<int32_t>(L.row_len),
+                         L.pages_per_cand, pg, s->prefix_len, t};
   int tail = 0;
-  int rc = run_layers(s, n_cands, PASS_DECODE, s->prefix_len, 0, &tail);
+  int rc = run_layers(s, n_cands, PASS_DECODE, s->prefix_len, 0, &tail, nullptr, nullptr, &step);
   bool lists = false;
   s->lists_cands = false;
   if (rc == MC_OK) rc = lm_head(s, n_cands, tail, n_cands, false, false, s->ptr<float>(L.logits), s->ptr<void>(L.top_lists), &lists);

@@ -207,6 +207,21 @@ def test_odd_shapes_both_dtypes(kw, dtype):
     check_against_oracle(s, w, prefix, suffix, pl, steps)
 
 
+@pytest.mark.parametrize("d", [60, 130, 1028, 5120, 8200, 16388])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_widths_of_the_first_norm(d, dtype):
+    """The first norm of a pass gathers the embedding and, in a decode step, writes the rows' slots: a part of a wave,
+    one, two and four quads per thread, and the widths (not of whole quads, too wide) that take launches of their own."""
+    # the mean of V rounding errors has a deviation of 1 / sqrt(V) of their RMS: 0.018 at 3000 logits, where the check
+    # allows 0.10 (48 logits gave 0.101, with the errors of the bf16 rounding itself)
+    s = small_shape("width", 1, d, 2, 1, 16, 24, 3000, dtype=dtype)
+    w = synth.make_weights(s, 78)
+    prefix, suffix = synth.tokens(6, 1, (37,), s.vocab), synth.tokens(6, 2, (5, 6), s.vocab)
+    print("case: width", d, dtype, flush=True)
+    pl, steps, _, _ = teacher_forced_gpu(s, w, prefix, suffix, 4, chunk_rows=32)
+    check_against_oracle(s, w, prefix, suffix, pl, steps)
+
+
 def test_1b_shape_two_layer_twin():
     """The 1B shape at full width (2048 wide, 32/8 heads of 64, FFN 8192, vocabulary 32000) with
     2 of its 16 layers: 16 candidates, 64-token pages crossed by a 70-step suffix is too slow for
