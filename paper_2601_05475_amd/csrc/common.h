@@ -145,13 +145,22 @@ struct DecodeAttnArgs {
   int32_t out_tiled;
 };
 
+// A word per row in a kernel's arguments: what the host gives for a decode step or a draw, without a copy ahead of the
+// kernel.  64 rows are 256 bytes of the argument block; more rows go through the staging ring and a copy.
+constexpr int kInlineRows = 64;
+struct RowWords {
+  uint32_t v[kInlineRows];
+};
+
 // Rows of a decode step: row r is the next token of candidate alive[r] (nullptr: of candidate r).  Its position and KV
 // slot follow from the candidate's length; they go to the row arrays that the layers read.
 struct StepRows {
-  const int32_t *tok;                                       // [rows]
+  const int32_t *tok;                                       // [rows], or nullptr: the tokens are in `words`
   const int32_t *alive, *page_table, *cand_len;             // cand_len: by candidate, nullptr: every candidate has length t
   int32_t *row_pos, *row_page, *row_off, *row_tab, *row_len;    // row_len: written where lengths differ
   int table_stride, page_tokens, prefix_len, t;
+  RowWords words;
+  __device__ int token(int r) const { return tok ? tok[r] : (int)words.v[r]; }
   __device__ void publish(int r) const {
     const int cand = alive ? alive[r] : r, n = cand_len ? cand_len[cand] : t;
     row_pos[r] = prefix_len + n;
@@ -230,10 +239,11 @@ int launch_attention_decode(hipStream_t st, int dtype, const DecodeAttnArgs &a);
 // top_lists != nullptr: the LM head's per-group top lists of the same rows ([row][n_groups][4]
 // pairs of {float bits, id}, row stride top_stride pairs; 0 = every candidate reads row 0), which
 // the selection uses instead of the rows where that is conclusive (see sample_kernel)
+// host_uniforms: the uniforms' bits, taken instead of `uniforms`; host_tokens: pinned host memory that gets the tokens too
 int launch_sample(hipStream_t st, int n_cands, int vocab, const float *logits, size_t row_stride,
                   float temperature, int top_k, const float *uniforms, int32_t *out_tokens,
                   int32_t *out_topk, const void *top_lists = nullptr, size_t top_stride = 0,
-                  int n_groups = 0);
+                  int n_groups = 0, const RowWords *host_uniforms = nullptr, int32_t *host_tokens = nullptr);
 int launch_reward_score(hipStream_t st, int n_cands, int vocab, const float *logits,
                         const int32_t *reward_ids, const float *reward_values, int n_reward,
                         float score_temperature, float *out_logprobs, float *out_scores,

@@ -190,12 +190,14 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_vec_kernel(
 // Rows of a pass whose tokens, positions and KV slots are on the device
 struct TokenRows {
   const int32_t *tok;
+  __device__ int token(int r) const { return tok[r]; }
   __device__ void publish(int) const {}
 };
 
 // The first normalisation of a pass with the embedding gather in front of it, and for a decode step the rows' metadata
-// beside it: a workgroup past the rows stores that, so no row waits for it.  Each of these is a few KB per row, so a decode
-// step pays for the launches alone: metadata, gather and norm took 1.6 + 2.6 + 4.0 us at 8 rows of 2048.
+// beside it: a workgroup past the rows stores that, so no row waits for it.  Each of these is a few KB per row, so a
+// decode step pays for the launches alone: metadata, gather and norm took 1.6 + 2.6 + 4.0 us at 8 rows of 2048.  The
+// steps of a two-layer model of that width took 151 us so, 147 us with one launch.
 template <typename T, int VEC, typename ROWS>
 __global__ __launch_bounds__(1024) void embed_rmsnorm_kernel(int rows, int rows_per_xcd, int n_row_blocks, int d, ROWS src, const T *__restrict__ table,
                                                              float *__restrict__ x, const T *__restrict__ gain, float eps,
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(1024) void embed_rmsnorm_kernel(int rows, int rows_
   }
   int r;
   if (!norm_row(rows, rows_per_xcd, d, h, h_tiled, r)) return;
-  const T *e = table + (size_t)src.tok[r] * d;
+  const T *e = table + (size_t)src.token(r) * d;
   float *xr = x + (size_t)r * d;
   float4 v[VEC];
   float ss = 0.f;
@@ -235,7 +237,7 @@ __global__ void decode_rows_kernel(int rows, StepRows src, int32_t *__restrict__
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= rows) return;
   src.publish(r);
-  tok[r] = src.tok[r];
+  tok[r] = src.token(r);
 }
 
 int launch_decode_rows(hipStream_t st, int rows, const StepRows &src, int32_t *tok) {
@@ -1320,8 +1322,8 @@ constexpr int kTopListLen = 4, kTopListMaxK = 64;
 __global__ __launch_bounds__(1024) void sample_kernel(
     int V, const float *__restrict__ logits, size_t row_stride, const uint2 *__restrict__ top,
     size_t top_stride, int n_groups, float temperature, int top_k,
-    const float *__restrict__ uniforms, int32_t *__restrict__ out_tokens,
-    int32_t *__restrict__ out_topk) {
+    const float *__restrict__ uniforms, RowWords host_uniforms, int32_t *__restrict__ out_tokens,
+    int32_t *__restrict__ host_tokens, int32_t *__restrict__ out_topk) {
   __shared__ SampleShared sh;
   const int b = blockIdx.x, tid = threadIdx.x;
   const float *row = logits + (size_t)b * row_stride;
@@ -1365,12 +1367,13 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     if (tid == 0) {
       const int tok = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));
       out_tokens[b] = tok;
+      if (host_tokens) host_tokens[b] = tok;
       if (out_topk) out_topk[b] = tok;
     }
     return;
   }
   const int k = (top_k <= 0 || top_k >= V) ? V : top_k;
-  const float u = uniforms[b];
+  const float u = uniforms ? uniforms[b] : __uint_as_float(host_uniforms.v[b]);
   const unsigned long long *sorted = nullptr;      // the top k keys in order, in LDS
   unsigned int last_ob = 0;
 
@@ -1426,15 +1429,20 @@ __global__ __launch_bounds__(1024) void sample_kernel(
       break;
     }
   }
-  if (tid == 0) out_tokens[b] = (int)(0xFFFFFFFFu - (uint32_t)(sorted[pick] & 0xFFFFFFFFull));
+  if (tid == 0) {
+    const int tok = (int)(0xFFFFFFFFu - (uint32_t)(sorted[pick] & 0xFFFFFFFFull));
+    out_tokens[b] = tok;
+    if (host_tokens) host_tokens[b] = tok;
+  }
 }
 
 int launch_sample(hipStream_t st, int n_cands, int vocab, const float *logits, size_t row_stride,
                   float temperature, int top_k, const float *uniforms, int32_t *out_tokens,
-                  int32_t *out_topk, const void *top_lists, size_t top_stride, int n_groups) {
+                  int32_t *out_topk, const void *top_lists, size_t top_stride, int n_groups, const RowWords *host_uniforms, int32_t *host_tokens) {
   if (n_cands <= 0) return MC_OK;
   sample_kernel<<<n_cands, 1024, 0, st>>>(vocab, logits, row_stride, (const uint2 *)top_lists, top_stride, n_groups,
-                                          temperature, top_k, uniforms, out_tokens, out_topk);
+                                          temperature, top_k, host_uniforms ? nullptr : uniforms, host_uniforms ? *host_uniforms : RowWords{}, out_tokens,
+                                          host_tokens, out_topk);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }

@@ -222,6 +222,37 @@ def test_widths_of_the_first_norm(d, dtype):
     check_against_oracle(s, w, prefix, suffix, pl, steps)
 
 
+@pytest.mark.parametrize("B", [1, 64, 65, 130])
+def test_tokens_and_uniforms_up_to_and_past_what_a_launch_carries(B):
+    """Up to 64 candidates the uniforms and the given tokens are kernel arguments, beyond that copies; the tokens read
+    back, the tokens left on the device and the same tokens given by the host lead to the same bits."""
+    s = small_shape("words", 1, 64, 2, 1, 32, 64, 256)
+    w = synth.make_weights(s, 79)
+    sess = binding.Session(binding.Model(s, w), 16, B, 8, 4)
+    prefix = synth.tokens(7, 1, (9,), s.vocab)
+    us = np.random.default_rng(5).random((2, B), dtype=np.float32)
+    runs = []
+    for given in (True, False):
+        sess.prefill_shared(prefix)
+        first = sess.logits(1)[0]
+        toks, topk = sess.sample(B, 0.9, 20, us[0], want_topk=True)
+        for b in range(B):
+            check_sampler_on_logits(first, 0.9, 20, us[0, b], toks[b], topk[b])
+        if not given:
+            assert sess.sample(B, 0.9, 20, us[0], want_tokens=False) is None
+        sess.decode_step(toks if given else None, B)
+        logits = sess.logits(B)
+        second = sess.sample(B, 0.9, 20, us[1])
+        greedy = sess.sample(B, 0.0, 0, us[1])
+        np.testing.assert_array_equal(greedy, logits.argmax(1))
+        runs.append((toks, logits, second))
+    for x, y in zip(*runs):
+        np.testing.assert_array_equal(x, y)
+    for b in (0, B - 1):
+        ref = otf.forward(oracle_config(s), w, np.append(prefix, runs[0][0][b]))[0][-1]
+        assert_logits_close(runs[0][1][b][None], ref[None], "f32", "token of the first and last candidate")
+
+
 def test_1b_shape_two_layer_twin():
     """The 1B shape at full width (2048 wide, 32/8 heads of 64, FFN 8192, vocabulary 32000) with
     2 of its 16 layers: 16 candidates, 64-token pages crossed by a 70-step suffix is too slow for
