@@ -4,8 +4,8 @@
 //
 // A workgroup of 4 waves owns 256 rows of a and 128 rows of w (64 of wg and of wu in the SwiGLU
 // form); a wave keeps 8 accumulator tiles of 32 x 32 (its own 64 rows of a x all 128 rows of w).  Few
-// tiles take other shapes, a wave then owning 32 rows of a: 64 or 128 rows of a (2 or 4 waves) and 128, 64
-// or 32 rows of w, or 320 and 384 rows (10 and 12 waves) and 64 of wg and of wu (see gemm_form and swiglu_form);
+// tiles take other shapes, a wave then owning 32 rows of a: 64, 96 or 128 rows of a (2 to 4 waves) and 128, 64
+// or 32 rows of w, or 320 and 384 rows (10 and 12 waves) and 64 of wg and of wu (see plain_form and swiglu_form);
 // an output's sum runs over K in the same order in all of them, so they give the same bits.
 // Two workgroups share a CU (two waves per SIMD, 232 registers each): they run out of step, so
 // the barrier, prologue and epilogue of one are covered by the matrix work of the other.
@@ -209,6 +209,13 @@ __device__ inline void rope_store_pieces(const RopeOut &ro, int M, int m0, int n
   }
 }
 
+// 1 KB pieces that a wave brings of a unit of `blocks` weight blocks, which divide over as many of the waves as they can
+constexpr int weight_pieces(int blocks, int waves) {
+  int per = (4 * blocks + waves - 1) / waves;
+  while (4 * blocks % per) ++per;
+  return per;
+}
+
 // TM: 32-row tiles of a per wave; TN: 32-row tiles of each weight matrix per workgroup; D: units by which
 // the operands run ahead; WV: waves; NT: w's lines are read by this workgroup only and need not stay in L2.
 template <int MODE, int TM, int TN, int D, int WV, bool NT>
@@ -222,8 +229,8 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
   constexpr int AB = WV * TM;              // 32-row tiles of a per workgroup
   constexpr int WB = TN;                   // blocks of each weight matrix per unit (workgroup)
   constexpr int NBW = NW * WB;             // weight blocks of 256 chunks per unit
-  constexpr int PW = (4 * NBW + WV - 1) / WV, LW = 4 * NBW / PW;   // 1 KB pieces of w per unit and wave, waves that bring them
-  static_assert(LW * PW == 4 * NBW, "a unit's weights divide over the waves");
+  constexpr int PW = weight_pieces(NBW, WV), LW = 4 * NBW / PW;    // 1 KB pieces of w per unit and wave, waves that bring them
+  constexpr bool kEven = 4 % WV == 0;      // a load's waves bring neighbouring pieces of a block that is known here
   constexpr int S = D + 2;                 // LDS stages of one unit each
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_lds[];
   v4u *lds = (v4u *)gemm_lds;              // [S][NBW][256], then 1 KB where waves that bring no weights let their empty loads land
@@ -243,7 +250,7 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
       __builtin_amdgcn_make_buffer_rsrc((void *)(w + (size_t)nt0 * U * 2048), 0, w_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t w2src =
       SWIGLU ? __builtin_amdgcn_make_buffer_rsrc((void *)(w2 + (size_t)nt0 * U * 2048), 0, w_bytes, 0x00020000) : wsrc;
-  const uint32_t w_off = (WV <= 4 ? tid : lane) * 16u;
+  const uint32_t w_off = (kEven ? tid : lane) * 16u;
   // the rows of a come straight from memory in operand order: a chunk of a tile is 1 KB, 16 bytes per lane
   const char *asrc[TM];
 #pragma unroll
@@ -265,10 +272,9 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
     const uint32_t at = (uint32_t)min(u, U - 1) * 4096u;
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
-      // up to 4 waves: a load's waves bring neighbouring pieces of a block that is known here
-      constexpr int kPer = WV <= 4 ? 4 / WV : 1;
-      const int b = WV <= 4 ? i / kPer : (wave * PW + i) >> 2, c0 = WV <= 4 ? WV * (i % kPer) : (wave * PW + i) & 3;
-      v4u *dst = lds + (LW == WV || wave < LW ? stage * NBW * 256 + b * 256 + c0 * 64 + (WV <= 4 ? wave * 64 : 0) : S * NBW * 256);
+      constexpr int kPer = kEven ? 4 / WV : 1;
+      const int b = kEven ? i / kPer : (wave * PW + i) >> 2, c0 = kEven ? WV * (i % kPer) : (wave * PW + i) & 3;
+      v4u *dst = lds + (LW == WV || wave < LW ? stage * NBW * 256 + b * 256 + c0 * 64 + (kEven ? wave * 64 : 0) : S * NBW * 256);
       const uint32_t from = LW == WV || wave < LW ? at + (uint32_t)((b < WB ? b : b - WB) * U) * 4096u + (uint32_t)c0 * 1024u : 0u;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(b < WB ? wsrc : w2src, (__attribute__((address_space(3))) void *)dst,
                                                16, w_off, from, 0, NT ? 2 : 0);
@@ -451,12 +457,19 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
 // (150), 1024 rows - / 240 / - / 168 / 126 (158), 1500 rows 327 / 227 / 205 (162) by 128 x 32 / 64 / 128; 4096 x 4096: 100
 // rows 15 / 21 / 20 / 25 / 35; 2048 x 8192: 100 rows 25 / 36 / 36 / 45 / 66, 256 rows 26 / 36 / 36 / 45 / 65, 300 rows 43 / 31 / 37 / 39 /
 // 56; 6144 x 4096: 100 rows 25 / 21 / 20 / 26 / 36; 5120 x 27648: 100 rows 157 / 125 / 122 / 159, 160 rows 64 x 64 101, 128 x 64 161.
+// Over a long K three waves (96 x 64) take the place of 128 x 64 where that is more workgroups and still one round: the load of a
+// unit that has four row tiles sets the pace of all.  us, 128 x 64 and 96 x 64: 4096 x 14336, 300 rows 69 / 66, 330 rows 76 / 70, 384 rows
+// 83 / 76; 5120 x 27648, 211 rows 144 / 124, 256 rows 159 / 133.  Not with as many workgroups (4096 x 14336, 288 rows 66 / 75) or a
+// short K (2048 x 8192, 768 rows 35 / 36; 4096 x 4096, 384 rows 20 / 21).
 struct GemmForm { int waves, tm, tn; };
 constexpr long kComputeUnits = 256;
-static GemmForm plain_form(int M, int N) {
+static GemmForm plain_form(int M, int N, int K) {
   for (const GemmForm f : {GemmForm{2, 1, 1}, GemmForm{4, 1, 1}, GemmForm{2, 1, 2}, GemmForm{4, 1, 2}, GemmForm{4, 1, 4}}) {
     const long row_tiles = (M + 32 * f.waves - 1) / (32 * f.waves);
-    if (row_tiles * (N / 32) / f.tn <= kComputeUnits) return f;
+    if (row_tiles * (N / 32) / f.tn > kComputeUnits) continue;
+    const long by_96 = (M + 95) / 96;
+    if (f.waves == 4 && f.tn == 2 && K >= 12288 && by_96 > row_tiles && by_96 * (N / 64) <= kComputeUnits) return GemmForm{3, 1, 2};
+    return f;
   }
   return GemmForm{4, M <= 128 ? 1 : 2, 4};
 }
@@ -494,7 +507,8 @@ static int launch_gemm256_t(hipStream_t st, int M, int Mw, int N, int K, const b
   const int tiles_m = (M + 32 * WV * TM - 1) / (32 * WV * TM), tiles_n = N / (32 * TN);
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
   // D + 2 stages of the unit's weight blocks and a place for empty loads; the parking areas of the rotation epilogue may need more
-  const int lds = std::max<int>((D + 2) * TN * (MODE == GEMM_SWIGLU ? 2 : 1) * 4096 + (WV > 8 ? 1024 : 0),
+  constexpr int NBW = TN * (MODE == GEMM_SWIGLU ? 2 : 1);
+  const int lds = std::max<int>((D + 2) * NBW * 4096 + (weight_pieces(NBW, WV) * WV > 4 * NBW ? 1024 : 0),
                                 MODE == GEMM_ROPE ? WV * 32 * kParkStride * (int)sizeof(float) : 0);
   MC_TRY(raise_dynamic_lds_limit((const void *)gemm256_kernel<MODE, TM, TN, D, WV, NT>, lds));
   gemm256_kernel<MODE, TM, TN, D, WV, NT><<<8 * per_xcd, 64 * WV, lds, st>>>(M, Mw, N, K, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
@@ -513,7 +527,7 @@ int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const voi
     MC_FAIL(MC_ERR_INVALID, "fused QKV output: N = (Hq + 2 Hkv) hd, hd %% 4 == 0");
   const bf16_t *A = (const bf16_t *)a, *W = (const bf16_t *)w, *W2 = (const bf16_t *)w2;
   bf16_t *OT = (bf16_t *)out_t;
-  const GemmForm f = swiglu ? swiglu_form(M, N) : plain_form(M, N);
+  const GemmForm f = swiglu ? swiglu_form(M, N) : plain_form(M, N, K);
   auto run = [&](auto mode) -> int {
     constexpr int MODE = decltype(mode)::value;
     const RopeOut ro = rope ? *rope : RopeOut{};
@@ -527,6 +541,7 @@ int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const voi
       return launch_gemm256_t<MODE, 1, 1, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
     } else {
       if (f.tm == 2) return launch_gemm256_t<MODE, 2, 4, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.waves == 3) return launch_gemm256_t<MODE, 1, 2, 4, 3>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.tn == 4) return launch_gemm256_t<MODE, 1, 4, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.waves == 2 && f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4, 2>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.waves == 2) return launch_gemm256_t<MODE, 1, 1, 4, 2>(st, M, Mw, N, K, A, W, W2, out, OT, ro);

@@ -748,6 +748,16 @@ def test_linear_64_row_workgroups(M, N, K):
     test_linear_accumulate_tiled(M, N, K)
 
 
+@pytest.mark.parametrize("M,N", [(289, 4096), (384, 4096), (193, 5120)])
+def test_gemm_96_row_workgroups(M, N):
+    """GEMM workgroups of three waves (96 rows x 64 columns; one wave brings no weights), over a K that takes them: a ragged
+    and a full last workgroup, in the three plain output forms."""
+    K = 12288
+    test_linear_tiled(M, N, K, 1)
+    test_linear_accumulate_tiled(M, N, K)
+    test_linear_qkv_rope_fused(M, N // 256, N // 512, 128, K)
+
+
 @pytest.mark.parametrize("M,K", [(100, 256), (257, 256), (320, 768), (321, 512), (384, 256), (385, 256)])
 def test_linear_swiglu_wide_workgroups(M, K):
     """The SwiGLU form with a wave per row tile (10 and 12 waves; waves past the last row tile), its neighbours, and
