@@ -297,7 +297,9 @@ int mc_profile_end(mc_session *s, int32_t *n_timed, double *total_ms);
  * lane l = row % 32 + 32 * ((k % 64) / 32), at byte (c * 64 + l) * 16, holds the 8 elements
  * k - k % 8 .. +7 of that row.  mc_op_tiled_bytes gives the buffer size (0 if K is unsuitable);
  * mc_op_pack_tiled converts a row-major bf16 matrix (padding rows are zero-filled).  The operations
- * below that store a tiled output write its padding rows as zeros too, unless they say otherwise. */
+ * below leave the padding rows of a tiled output alone: rows of one 32-row tile may come from several calls (a call for
+ * rows r0.. of a tile takes its output pointer 16 r0 bytes further).  Those whose name ends in _tiled take the same
+ * arguments, store the whole tiles and write the padding rows as zeros. */
 size_t mc_op_tiled_bytes(int32_t rows, int32_t K);
 int mc_op_pack_tiled(void *stream, int32_t rows, int32_t K, const void *src, void *dst);
 
@@ -307,6 +309,9 @@ int mc_op_pack_tiled(void *stream, int32_t rows, int32_t K, const void *src, voi
 int mc_op_add_rmsnorm(void *stream, int32_t dtype, int32_t rows, int32_t d, float *x,
                       const float *partials, int32_t n_partials, const void *gain /*(T)[d]*/,
                       float eps, void *h_out /*(T)[rows][d]*/, int32_t h_tiled);
+int mc_op_add_rmsnorm_tiled(void *stream, int32_t dtype, int32_t rows, int32_t d, float *x,
+                            const float *partials, int32_t n_partials, const void *gain,
+                            float eps, void *h_out);
 
 /* out[s][m][n] = sum over the s-th K range of a[m][k] * w[n][k]; n_splits partial sums
  * (fp32, row-major) that add up to a * w^T.  a: (T)[M][K], w: (T)[N][K], out: fp32
@@ -345,6 +350,8 @@ int mc_op_linear_qkv_rope(void *stream, int32_t rows, int32_t n_q_heads, int32_t
 int mc_op_linear_swiglu(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K,
                         const void *a, const void *w_gate, const void *w_up, void *out,
                         int32_t tiled);
+int mc_op_linear_swiglu_tiled(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K,
+                              const void *a, const void *w_gate, const void *w_up, void *out);
 
 /* Sum the n_splits partial QKV rows, rotate q and k of row r by position row_pos[r],
  * store q as (T)[rows][Hq][hd] and write k, v of row r into KV page row_page[r] at
@@ -382,6 +389,13 @@ int mc_op_attention_decode(void *stream, int32_t dtype, int32_t n_cands, int32_t
                            const void *v_suffix, const int32_t *page_table,
                            int32_t table_stride, const int32_t *row_len, int32_t prefix_splits,
                            void *workspace, size_t workspace_bytes, void *out, int32_t out_tiled);
+int mc_op_attention_decode_tiled(void *stream, int32_t dtype, int32_t n_cands, int32_t n_q_heads,
+                                 int32_t n_kv_heads, int32_t head_dim, int32_t page_tokens,
+                                 int32_t prefix_len, int32_t suffix_len, const void *q,
+                                 const void *k_prefix, const void *v_prefix, const void *k_suffix,
+                                 const void *v_suffix, const int32_t *page_table,
+                                 int32_t table_stride, const int32_t *row_len, int32_t prefix_splits,
+                                 void *workspace, size_t workspace_bytes, void *out);
 
 /* mc_op_attention_decode for callers that cannot allocate device memory or bring a workspace
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same

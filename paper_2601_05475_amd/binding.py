@@ -94,14 +94,17 @@ SIGNATURES = {
     "mc_op_tiled_bytes": (_sz, [_i32, _i32]),
     "mc_op_pack_tiled": (C.c_int, [_vp, _i32, _i32, _vp, _vp]),
     "mc_op_add_rmsnorm": (C.c_int, [_vp, _i32, _i32, _i32, _vp, _vp, _i32, _vp, _f32, _vp, _i32]),
+    "mc_op_add_rmsnorm_tiled": (C.c_int, [_vp, _i32, _i32, _i32, _vp, _vp, _i32, _vp, _f32, _vp]),
     "mc_op_linear": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _i32, _i32]),
     "mc_op_linear_splits": (_i32, [_i32] * 5),
     "mc_op_linear_accumulate": (C.c_int, [_vp, _i32, _i32, _i32, _vp, _vp, _vp]),
     "mc_op_linear_qkv_rope": (C.c_int, [_vp] + [_i32] * 6 + [_f32, _i32] + [_vp] * 9),
     "mc_op_linear_swiglu": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _i32]),
+    "mc_op_linear_swiglu_tiled": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp]),
     "mc_op_rope_kv_write": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _i32, _i32, _f32, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp]),
     "mc_op_attention_decode_ws": (_sz, [_i32] * 7),
     "mc_op_attention_decode": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp, _i32, _vp, _sz, _vp, _i32]),
+    "mc_op_attention_decode_tiled": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp, _i32, _vp, _sz, _vp]),
     "mc_op_attention_decode_static": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp, _i32, _vp, _i32]),
     "mc_op_attention_decode_plan": (C.c_int, [_i32] * 8 + [_vp]),
     "mc_op_read_probe": (C.c_int, [_vp, _vp, _sz, _vp]),
@@ -473,8 +476,8 @@ def kv_pages_unpack(kp, vp, page_tokens: int, head_dim: int):
 
 
 def _tiled_out(rows: int, K: int, dtype, device):
-    """A tiled [rows, K] buffer with zeros in its padding rows, for a program that writes the rows itself
-    (the library's own operations write the padding rows of their outputs)."""
+    """A tiled [rows, K] buffer with zeros in its padding rows, for an operation that writes only the rows: one
+    torch call unless it is large, where filling the whole would cost more than filling its last tile."""
     import torch
     n = max(0, (rows + 31) // 32 * 32 * K)
     if rows % 32 and n < 1 << 21:
@@ -496,14 +499,16 @@ def op_add_rmsnorm(x, partials, gain, eps: float, tiled: bool = False):
     ([rows, d], or the flat tiled buffer when tiled)."""
     import torch
     rows, d = x.shape
+    S = 0 if partials is None else partials.shape[0]
+    part = None if partials is None else partials.data_ptr()
     if tiled:
         h = _tiled_empty(rows, d, gain.dtype, x.device)
-    else:
-        h = torch.empty((rows, d), dtype=gain.dtype, device=x.device)
-    S = 0 if partials is None else partials.shape[0]
-    _check(load_library().mc_op_add_rmsnorm(_stream(), _code_of(gain), rows, d, x.data_ptr(),
-                                            None if partials is None else partials.data_ptr(), S,
-                                            gain.data_ptr(), eps, h.data_ptr(), int(tiled)))
+        _check(load_library().mc_op_add_rmsnorm_tiled(_stream(), _code_of(gain), rows, d, x.data_ptr(), part, S,
+                                                      gain.data_ptr(), eps, h.data_ptr()))
+        return h
+    h = torch.empty((rows, d), dtype=gain.dtype, device=x.device)
+    _check(load_library().mc_op_add_rmsnorm(_stream(), _code_of(gain), rows, d, x.data_ptr(), part, S,
+                                            gain.data_ptr(), eps, h.data_ptr(), 0))
     return h
 
 
@@ -565,12 +570,13 @@ def op_linear_swiglu(a, w_gate, w_up, tiled_shape=None):
         M, K = a.shape
         N = w_gate.shape[0]
         out = torch.empty((M, N), dtype=a.dtype, device=a.device)
-    else:
-        M, N, K = tiled_shape
-        out = _tiled_empty(M, N, a.dtype, a.device)
-    _check(load_library().mc_op_linear_swiglu(_stream(), _code_of(a), M, N, K, a.data_ptr(),
-                                              w_gate.data_ptr(), w_up.data_ptr(), out.data_ptr(),
-                                              int(tiled_shape is not None)))
+        _check(load_library().mc_op_linear_swiglu(_stream(), _code_of(a), M, N, K, a.data_ptr(),
+                                                  w_gate.data_ptr(), w_up.data_ptr(), out.data_ptr(), 0))
+        return out
+    M, N, K = tiled_shape
+    out = _tiled_empty(M, N, a.dtype, a.device)
+    _check(load_library().mc_op_linear_swiglu_tiled(_stream(), _code_of(a), M, N, K, a.data_ptr(),
+                                                    w_gate.data_ptr(), w_up.data_ptr(), out.data_ptr()))
     return out
 
 
@@ -593,33 +599,32 @@ def op_attention_decode(q, k_prefix, v_prefix, k_suffix, v_suffix, page_table, p
                         row_len=None, out=None, static_scratch: bool = False):
     """q: [B, Hq, hd]; pools: [n_pages, Hkv, pg * hd] in the page layout (kv_pages_pack);
     page_table: int32 [B, stride]; row_len: optional int32 [B] device tensor of per-candidate
-    suffix lengths.  Returns out [B, Hq, hd] (or the flat tiled [B, Hq*hd]); `out` may be passed
-    in.  static_scratch: call mc_op_attention_decode_static (the library's own scratch buffer; with
+    suffix lengths.  Returns out [B, Hq, hd] (or the flat tiled [B, Hq*hd], zeros in its padding
+    rows); `out` may be passed in (the padding rows of a tiled one stay as they are).
+    static_scratch: call mc_op_attention_decode_static (the library's own scratch buffer; with
     `out` given the call allocates nothing)."""
     import torch
     lib = load_library()
     B, Hq, hd = q.shape
     Hkv = (k_prefix if k_prefix is not None else k_suffix).shape[1]
-    if out is None:
-        if out_tiled:
-            out = _tiled_empty(B, Hq * hd, q.dtype, q.device)
-        else:
-            out = torch.empty_like(q)
+    whole = out is None and out_tiled and not static_scratch         # padding rows by the kernel
+    if whole:
+        out = _tiled_empty(B, Hq * hd, q.dtype, q.device)
+    elif out is None:
+        out = _tiled_out(B, Hq * hd, q.dtype, q.device) if out_tiled else torch.empty_like(q)
     p = lambda t: None if t is None else t.data_ptr()
-    if static_scratch:
-        _check(lib.mc_op_attention_decode_static(
-            _stream(), _code_of(q), B, Hq, Hkv, hd, page_tokens, prefix_len, suffix_len, q.data_ptr(),
+    args = (_stream(), _code_of(q), B, Hq, Hkv, hd, page_tokens, prefix_len, suffix_len, q.data_ptr(),
             p(k_prefix), p(v_prefix), p(k_suffix), p(v_suffix), p(page_table),
-            0 if page_table is None else page_table.shape[1], p(row_len), prefix_splits,
-            out.data_ptr(), int(out_tiled)))
+            0 if page_table is None else page_table.shape[1], p(row_len), prefix_splits)
+    if static_scratch:
+        _check(lib.mc_op_attention_decode_static(*args, out.data_ptr(), int(out_tiled)))
         return out
     ws_bytes = lib.mc_op_attention_decode_ws(B, Hq, Hkv, hd, prefix_len, suffix_len, page_tokens)
     ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=q.device)
-    _check(lib.mc_op_attention_decode(
-        _stream(), _code_of(q), B, Hq, Hkv, hd, page_tokens, prefix_len, suffix_len, q.data_ptr(),
-        p(k_prefix), p(v_prefix), p(k_suffix), p(v_suffix), p(page_table),
-        0 if page_table is None else page_table.shape[1], p(row_len), prefix_splits, ws.data_ptr(), ws.numel(),
-        out.data_ptr(), int(out_tiled)))
+    if whole:
+        _check(lib.mc_op_attention_decode_tiled(*args, ws.data_ptr(), ws.numel(), out.data_ptr()))
+    else:
+        _check(lib.mc_op_attention_decode(*args, ws.data_ptr(), ws.numel(), out.data_ptr(), int(out_tiled)))
     return out
 
 

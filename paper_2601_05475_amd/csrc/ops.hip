@@ -139,9 +139,14 @@ static int check_dtype(int dtype) {
   return MC_OK;
 }
 
-static int check_tiled(int dtype, int tiled, int K) {
+// A caller's flag selects ROW_MAJOR or TILED; TILED_ZERO has entry points of its own
+static int check_tiled_flag(int tiled) {
   if (tiled != 0 && tiled != 1) MC_FAIL(MC_ERR_INVALID, "tiled must be 0 or 1");
-  if (tiled && (dtype != MC_BF16 || K % 64)) MC_FAIL(MC_ERR_UNSUPPORTED, "the tiled layout is bf16 with K %% 64 == 0");
+  return MC_OK;
+}
+
+static int check_tiled(int dtype, int layout, int K) {
+  if (layout != ROW_MAJOR && (dtype != MC_BF16 || K % 64)) MC_FAIL(MC_ERR_UNSUPPORTED, "the tiled layout is bf16 with K %% 64 == 0");
   return MC_OK;
 }
 
@@ -160,14 +165,26 @@ extern "C" int mc_op_pack_tiled(void *stream, int32_t rows, int32_t K, const voi
   return launch_pack_tiled((hipStream_t)stream, rows, K, src, dst);
 }
 
-extern "C" int mc_op_add_rmsnorm(void *stream, int32_t dtype, int32_t rows, int32_t d, float *x,
-                                 const float *partials, int32_t n_partials, const void *gain,
-                                 float eps, void *h_out, int32_t h_tiled) {
+static int op_add_rmsnorm(void *stream, int32_t dtype, int32_t rows, int32_t d, float *x, const float *partials, int32_t n_partials,
+                          const void *gain, float eps, void *h_out, int32_t layout) {
   MC_TRY(check_dtype(dtype));
   if (rows < 0 || d < 1 || n_partials < 0) MC_FAIL(MC_ERR_INVALID, "bad sizes");
   if (!x || !gain || !h_out || (n_partials && !partials)) MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
-  MC_TRY(check_tiled(dtype, h_tiled, d));
-  return launch_add_rmsnorm((hipStream_t)stream, dtype, rows, d, x, partials, n_partials, gain, eps, h_out, h_tiled ? TILED_ZERO : ROW_MAJOR);
+  MC_TRY(check_tiled(dtype, layout, d));
+  return launch_add_rmsnorm((hipStream_t)stream, dtype, rows, d, x, partials, n_partials, gain, eps, h_out, layout);
+}
+
+extern "C" int mc_op_add_rmsnorm(void *stream, int32_t dtype, int32_t rows, int32_t d, float *x,
+                                 const float *partials, int32_t n_partials, const void *gain,
+                                 float eps, void *h_out, int32_t h_tiled) {
+  MC_TRY(check_tiled_flag(h_tiled));
+  return op_add_rmsnorm(stream, dtype, rows, d, x, partials, n_partials, gain, eps, h_out, h_tiled ? TILED : ROW_MAJOR);
+}
+
+extern "C" int mc_op_add_rmsnorm_tiled(void *stream, int32_t dtype, int32_t rows, int32_t d, float *x,
+                                       const float *partials, int32_t n_partials, const void *gain,
+                                       float eps, void *h_out) {
+  return op_add_rmsnorm(stream, dtype, rows, d, x, partials, n_partials, gain, eps, h_out, TILED_ZERO);
 }
 
 extern "C" int mc_op_linear(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K,
@@ -176,6 +193,7 @@ extern "C" int mc_op_linear(void *stream, int32_t dtype, int32_t M, int32_t N, i
   MC_TRY(check_dtype(dtype));
   if (M < 0 || N < 1 || K < 1 || n_splits < 1 || n_splits > K) MC_FAIL(MC_ERR_INVALID, "bad sizes");
   if (!a || !w || !out) MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
+  MC_TRY(check_tiled_flag(tiled));
   MC_TRY(check_tiled(dtype, tiled, K));
   return launch_linear((hipStream_t)stream, dtype, M, N, K, a, w, out, n_splits, tiled);
 }
@@ -212,14 +230,25 @@ extern "C" int32_t mc_op_linear_splits(int32_t dtype, int32_t M, int32_t N, int3
   return linear_auto_splits(dtype, M, N, K, tiled);
 }
 
-extern "C" int mc_op_linear_swiglu(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K,
-                                   const void *a, const void *w_gate, const void *w_up, void *out,
-                                   int32_t tiled) {
+static int op_linear_swiglu(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void *a, const void *w_gate,
+                            const void *w_up, void *out, int32_t layout) {
   MC_TRY(check_dtype(dtype));
   if (M < 0 || N < 1 || K < 1) MC_FAIL(MC_ERR_INVALID, "bad sizes");
   if (!a || !w_gate || !w_up || !out) MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
-  MC_TRY(check_tiled(dtype, tiled, K));
-  return launch_linear_swiglu((hipStream_t)stream, dtype, M, N, K, a, w_gate, w_up, out, tiled ? TILED_ZERO : ROW_MAJOR);
+  MC_TRY(check_tiled(dtype, layout, K));
+  return launch_linear_swiglu((hipStream_t)stream, dtype, M, N, K, a, w_gate, w_up, out, layout);
+}
+
+extern "C" int mc_op_linear_swiglu(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K,
+                                   const void *a, const void *w_gate, const void *w_up, void *out,
+                                   int32_t tiled) {
+  MC_TRY(check_tiled_flag(tiled));
+  return op_linear_swiglu(stream, dtype, M, N, K, a, w_gate, w_up, out, tiled ? TILED : ROW_MAJOR);
+}
+
+extern "C" int mc_op_linear_swiglu_tiled(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K,
+                                         const void *a, const void *w_gate, const void *w_up, void *out) {
+  return op_linear_swiglu(stream, dtype, M, N, K, a, w_gate, w_up, out, TILED_ZERO);
 }
 
 extern "C" int mc_op_rope_kv_write(void *stream, int32_t dtype, int32_t rows, int32_t n_q_heads,
@@ -248,14 +277,11 @@ extern "C" size_t mc_op_attention_decode_ws(int32_t n_cands, int32_t n_q_heads, 
   return decode_attention_ws_bytes(n_cands, n_q_heads, n_kv_heads, head_dim, prefix_len, suffix_len, page_tokens);
 }
 
-extern "C" int mc_op_attention_decode(void *stream, int32_t dtype, int32_t n_cands,
-                                      int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
-                                      int32_t page_tokens, int32_t prefix_len, int32_t suffix_len,
-                                      const void *q, const void *k_prefix, const void *v_prefix,
-                                      const void *k_suffix, const void *v_suffix,
-                                      const int32_t *page_table, int32_t table_stride,
-                                      const int32_t *row_len, int32_t prefix_splits, void *workspace,
-                                      size_t workspace_bytes, void *out, int32_t out_tiled) {
+static int op_attention_decode(void *stream, int32_t dtype, int32_t n_cands, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                               int32_t page_tokens, int32_t prefix_len, int32_t suffix_len, const void *q, const void *k_prefix,
+                               const void *v_prefix, const void *k_suffix, const void *v_suffix, const int32_t *page_table,
+                               int32_t table_stride, const int32_t *row_len, int32_t prefix_splits, void *workspace,
+                               size_t workspace_bytes, void *out, int32_t layout) {
   MC_TRY(check_dtype(dtype));
   if (n_cands < 1 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads || head_dim < 2 ||
       head_dim > 256 || page_tokens < 1 || (page_tokens & (page_tokens - 1)) || prefix_len < 0 ||
@@ -264,7 +290,7 @@ extern "C" int mc_op_attention_decode(void *stream, int32_t dtype, int32_t n_can
   if (!q || !out || !workspace || (prefix_len && (!k_prefix || !v_prefix)) ||
       (suffix_len && (!k_suffix || !v_suffix || !page_table)))
     MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
-  MC_TRY(check_tiled(dtype, out_tiled, n_q_heads * head_dim));
+  MC_TRY(check_tiled(dtype, layout, n_q_heads * head_dim));
   if (suffix_len && table_stride < (suffix_len + page_tokens - 1) / page_tokens)
     MC_FAIL(MC_ERR_INVALID, "table_stride %d too small for %d suffix tokens", table_stride, suffix_len);
   const size_t need = decode_attention_ws_bytes(n_cands, n_q_heads, n_kv_heads, head_dim, prefix_len, suffix_len, page_tokens);
@@ -276,8 +302,35 @@ extern "C" int mc_op_attention_decode(void *stream, int32_t dtype, int32_t n_can
   a.page_tokens = page_tokens; a.prefix_len = prefix_len; a.suffix_len = suffix_len;
   a.row_len = suffix_len ? row_len : nullptr;
   a.prefix_splits = prefix_splits; a.workspace = workspace; a.workspace_bytes = workspace_bytes;
-  a.out = out; a.out_tiled = out_tiled ? TILED_ZERO : ROW_MAJOR;
+  a.out = out; a.out_tiled = layout;
   return launch_attention_decode((hipStream_t)stream, dtype, a);
+}
+
+extern "C" int mc_op_attention_decode(void *stream, int32_t dtype, int32_t n_cands,
+                                      int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                      int32_t page_tokens, int32_t prefix_len, int32_t suffix_len,
+                                      const void *q, const void *k_prefix, const void *v_prefix,
+                                      const void *k_suffix, const void *v_suffix,
+                                      const int32_t *page_table, int32_t table_stride,
+                                      const int32_t *row_len, int32_t prefix_splits, void *workspace,
+                                      size_t workspace_bytes, void *out, int32_t out_tiled) {
+  MC_TRY(check_tiled_flag(out_tiled));
+  return op_attention_decode(stream, dtype, n_cands, n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len, suffix_len, q, k_prefix,
+                             v_prefix, k_suffix, v_suffix, page_table, table_stride, row_len, prefix_splits, workspace,
+                             workspace_bytes, out, out_tiled ? TILED : ROW_MAJOR);
+}
+
+extern "C" int mc_op_attention_decode_tiled(void *stream, int32_t dtype, int32_t n_cands,
+                                            int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                            int32_t page_tokens, int32_t prefix_len, int32_t suffix_len,
+                                            const void *q, const void *k_prefix, const void *v_prefix,
+                                            const void *k_suffix, const void *v_suffix,
+                                            const int32_t *page_table, int32_t table_stride,
+                                            const int32_t *row_len, int32_t prefix_splits, void *workspace,
+                                            size_t workspace_bytes, void *out) {
+  return op_attention_decode(stream, dtype, n_cands, n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len, suffix_len, q, k_prefix,
+                             v_prefix, k_suffix, v_suffix, page_table, table_stride, row_len, prefix_splits, workspace,
+                             workspace_bytes, out, TILED_ZERO);
 }
 
 // ---- decode attention for callers that cannot allocate ---------------------------------------
@@ -362,7 +415,7 @@ static int op_attention_prefill(void *stream, int32_t rows, int32_t n_items, con
   if (n_items < 0 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads || prefix_len < 1)
     MC_FAIL(MC_ERR_INVALID, "bad sizes");
   if (!items || !q || !k_prefix || !v_prefix || !out) MC_FAIL(MC_ERR_INVALID, "a pointer is NULL");
-  MC_TRY(check_tiled(MC_BF16, layout != ROW_MAJOR, n_q_heads * head_dim));
+  MC_TRY(check_tiled(MC_BF16, layout, n_q_heads * head_dim));
   if (!prefill_attention_mfma_supported(page_tokens, head_dim, n_q_heads, n_kv_heads))
     MC_FAIL(MC_ERR_UNSUPPORTED, "prefill attention: bf16, 64-token pages, head_dim 64 or 128 only");
   PrefillAttnArgs a;
@@ -381,7 +434,7 @@ extern "C" int mc_op_attention_prefill(void *stream, int32_t n_items, const int3
                                        const void *k_suffix, const void *v_suffix,
                                        const int32_t *page_table, int32_t table_stride, void *out,
                                        int32_t out_tiled) {
-  if (out_tiled != 0 && out_tiled != 1) MC_FAIL(MC_ERR_INVALID, "tiled must be 0 or 1");
+  MC_TRY(check_tiled_flag(out_tiled));
   return op_attention_prefill(stream, 0, n_items, items, n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len, q, k_prefix,
                               v_prefix, k_suffix, v_suffix, page_table, table_stride, out, out_tiled ? TILED : ROW_MAJOR);
 }

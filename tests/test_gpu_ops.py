@@ -1069,6 +1069,66 @@ def test_decode_attention_writes_its_padding_rows(B, Hq, Hkv, hd, pg, P, t, spli
     assert torch.equal(binding.tiled_to_rowmajor(out, B, Hq * hd).reshape(B, Hq, hd), run(False))
 
 
+def _tile_calls(n):
+    """Row ranges of one tile that several calls fill, 16 bytes a row further each: (first row, rows)."""
+    return [(0, n), (n, 3), (n + 3, 32 - n - 3 - 2)]
+
+
+def _assert_tile(out, want, K, written):
+    """The rows written hold `want`, the others of the two tiles and everything past them their old values."""
+    got = binding.tiled_to_rowmajor(out, 64, K)
+    import torch
+    assert torch.equal(got[:written], want[:written]) and torch.all(got[written:] == -7)
+
+
+def test_tiled_outputs_leave_rows_that_are_not_theirs():
+    """The entry points without _tiled in their name store their rows and nothing else: the padding rows of a caller's
+    buffer stay, and one 32-row tile may be filled by several calls."""
+    import torch
+    lib = binding.load_library()
+    d, n = 512, 11
+    dev = lambda seed, shape, scale=1.0: to_dev(rnd(seed, shape, scale), "bf16")[0]  # noqa: E731
+    print("case: tiled outputs of several calls", flush=True)
+    for width in (d, 16448):                                            # norm: by quads, one row after another
+        x, gain = to_dev(rnd(960, (30, width)), "f32")[0], dev(961, (width,))
+        want = binding.op_add_rmsnorm(x, None, gain, 1e-6)
+        out = torch.full((64 * width,), -7.0, dtype=torch.bfloat16, device="cuda")
+        for r0, rows in _tile_calls(n):
+            assert lib.mc_op_add_rmsnorm(None, 1, rows, width, x[r0:].data_ptr(), None, 0, gain.data_ptr(), 1e-6, out.data_ptr() + 16 * r0, 1) == 0
+        _assert_tile(out, want, width, 30)
+    a = dev(962, (30, 256))
+    for N in (128, 14336):                                             # SwiGLU: a tile and a range of rows per workgroup
+        wg, wu = (binding.op_pack_tiled(dev(s, (N, 256), 0.1)) for s in (963, 964))
+        want = binding.tiled_to_rowmajor(binding.op_linear_swiglu(binding.op_pack_tiled(a), wg, wu, tiled_shape=(30, N, 256)), 30, N)
+        out = torch.full((64 * N,), -7.0, dtype=torch.bfloat16, device="cuda")
+        for r0, rows in _tile_calls(n):
+            at = binding.op_pack_tiled(a[r0:r0 + rows].contiguous())
+            assert lib.mc_op_linear_swiglu(None, 1, rows, N, 256, at.data_ptr(), wg.data_ptr(), wu.data_ptr(), out.data_ptr() + 16 * r0, 1) == 0
+        _assert_tile(out, want, N, 30)
+    M, N = 70, 256                                                     # many rows: padding only
+    wg, wu = (binding.op_pack_tiled(dev(s, (N, 256), 0.1)) for s in (963, 964))
+    am = binding.op_pack_tiled(dev(965, (M, 256)))
+    out = torch.full((96 * N,), -7.0, dtype=torch.bfloat16, device="cuda")
+    assert lib.mc_op_linear_swiglu(None, 1, M, N, 256, am.data_ptr(), wg.data_ptr(), wu.data_ptr(), out.data_ptr(), 1) == 0
+    got = binding.tiled_to_rowmajor(out, 96, N)
+    want = binding.tiled_to_rowmajor(binding.op_linear_swiglu(am, wg, wu, tiled_shape=(M, N, 256)), M, N)
+    assert torch.equal(got[:M], want) and torch.all(got[M:] == -7)
+    Hq, Hkv, pg = 8, 2, 64
+    for hd, P, t in ((64, 300, 20), (128, 20, 0), (96, 50, 9)):          # merged states, one state, the generic kernel
+        for static in (False, True):
+            kp, vp, _, _ = make_pools("bf16", -(-P // pg), Hkv, pg, hd, 966)
+            ks, vs, _, _ = make_pools("bf16", 30, Hkv, pg, hd, 968)
+            table = torch.arange(30, dtype=torch.int32, device="cuda").reshape(30, 1)
+            q = dev(970, (30, Hq, hd))
+            out = torch.full((64 * Hq * hd,), -7.0, dtype=torch.bfloat16, device="cuda")
+            want = torch.full((30, Hq * hd), -7.0, dtype=torch.bfloat16, device="cuda")
+            for r0, rows in _tile_calls(n):
+                part = (q[r0:r0 + rows].contiguous(), kp, vp, ks, vs, table[r0:r0 + rows].contiguous(), P, t, pg)
+                binding.op_attention_decode(*part, out_tiled=True, out=out[8 * r0:], static_scratch=static)
+                want[r0:r0 + rows] = binding.op_attention_decode(*part).reshape(rows, -1)
+            _assert_tile(out, want, Hq * hd, 30)
+
+
 @pytest.mark.parametrize("Hq,hd,lens", [(8, 128, (300,)), (8, 64, (33,)), (8, 128, (1000, 70, 40)), (8, 64, (1000, 1000, 71)),
                                         (64, 128, (1000, 65, 1000, 30))])
 def test_prefill_attention_zeroes_the_rows_that_no_item_covers(Hq, hd, lens):
