@@ -323,6 +323,11 @@ int mc_op_linear(void *stream, int32_t dtype, int32_t M, int32_t N, int32_t K, c
                  const void *w, float *out, int32_t n_splits, int32_t tiled);
 int32_t mc_op_linear_splits(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t tiled);
 
+/* Host-only: the workgroups that a many-row (M > 64) layer on tiled operands is launched as.  swiglu = 1:
+ * mc_op_linear_swiglu, 0: the others.  out3 (host): rows and columns (of each weight matrix) per workgroup, number of
+ * workgroups.  MC_ERR_UNSUPPORTED for shapes that the many-row kernel does not cover. */
+int mc_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t swiglu, int32_t *out3);
+
 /* bf16 tiled operands, many rows: x[m][n] += sum_k a[m][k] w[n][k] in the epilogue of the
  * 256-row-tile matrix-core GEMM (the residual update of the O and down projections in prefill and
  * scoring).  x: fp32 [M][N] row-major, device, updated in

@@ -97,6 +97,7 @@ SIGNATURES = {
     "mc_op_add_rmsnorm_tiled": (C.c_int, [_vp, _i32, _i32, _i32, _vp, _vp, _i32, _vp, _f32, _vp]),
     "mc_op_linear": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _i32, _i32]),
     "mc_op_linear_splits": (_i32, [_i32] * 5),
+    "mc_op_gemm_plan": (C.c_int, [_i32] * 4 + [_vp]),
     "mc_op_linear_accumulate": (C.c_int, [_vp, _i32, _i32, _i32, _vp, _vp, _vp]),
     "mc_op_linear_qkv_rope": (C.c_int, [_vp] + [_i32] * 6 + [_f32, _i32] + [_vp] * 9),
     "mc_op_linear_swiglu": (C.c_int, [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _i32]),
@@ -562,6 +563,13 @@ def op_linear_qkv_rope(a, wqkv, rows, K, row_pos, row_page, row_off, n_q_heads, 
 
 def op_linear_splits(dtype: str, M: int, N: int, K: int, tiled: bool) -> int:
     return load_library().mc_op_linear_splits(_dtype_code(dtype), M, N, K, int(tiled))
+
+
+def op_gemm_plan(M: int, N: int, K: int, swiglu: bool = False):
+    """Host-only: (rows, columns per workgroup, workgroups) of a many-row layer on tiled operands."""
+    out = np.zeros(3, np.int32)
+    _check(load_library().mc_op_gemm_plan(M, N, K, int(swiglu), out.ctypes.data))
+    return tuple(int(v) for v in out)
 
 
 def op_linear_swiglu(a, w_gate, w_up, tiled_shape=None):

@@ -457,10 +457,13 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
 // (150), 1024 rows - / 240 / - / 168 / 126 (158), 1500 rows 327 / 227 / 205 (162) by 128 x 32 / 64 / 128; 4096 x 4096: 100
 // rows 15 / 21 / 20 / 25 / 35; 2048 x 8192: 100 rows 25 / 36 / 36 / 45 / 66, 256 rows 26 / 36 / 36 / 45 / 65, 300 rows 43 / 31 / 37 / 39 /
 // 56; 6144 x 4096: 100 rows 25 / 21 / 20 / 26 / 36; 5120 x 27648: 100 rows 157 / 125 / 122 / 159, 160 rows 64 x 64 101, 128 x 64 161.
-// Over a long K three waves (96 x 64) take the place of 128 x 64 where that is more workgroups and still one round: the load of a
-// unit that has four row tiles sets the pace of all.  us, 128 x 64 and 96 x 64: 4096 x 14336, 300 rows 69 / 66, 330 rows 76 / 70, 384 rows
-// 83 / 76; 5120 x 27648, 211 rows 144 / 124, 256 rows 159 / 133.  Not with as many workgroups (4096 x 14336, 288 rows 66 / 75) or a
-// short K (2048 x 8192, 768 rows 35 / 36; 4096 x 4096, 384 rows 20 / 21).
+// Over a long K three waves (96 x 64) take the place of 128 x 64 where that is at least 4/3 of the workgroups and still one round: the
+// load of a unit that has four row tiles sets the pace of all.  us, 128 x 64 and 96 x 64: 4096 x 14336 (192 and 256 workgroups), 300 rows
+// 69 / 67, 330 rows 75 / 71, 384 rows 81 / 75; 4096 x 12288, 300 rows 59 / 58, 384 rows 69 / 64; 5120 x 27648 (160 and 240), 211 rows
+// 144 / 126, 256 rows 159 / 133; 3072 x 16384 (144 and 192), 384 rows 87 / 80; 2048 x 12288 (160 and 224), 600 rows 61 / 54.  With fewer
+// more it is slower: 2048 x 12288, 576 rows (160 and 192) 57 / 61, 641 rows (192 and 224) 55 / 61; 3072 x 16384, 448 rows (192 and 240)
+// 78 / 78; 4096 x 14336, 288 rows (192 both) 66 / 75.  So it is over a short K (2048 x 8192, 768 rows 35 / 36; 4096 x 4096, 384 rows
+// 20 / 21); between 8192 and 12288 nothing was measured.
 struct GemmForm { int waves, tm, tn; };
 constexpr long kComputeUnits = 256;
 static GemmForm plain_form(int M, int N, int K) {
@@ -468,7 +471,7 @@ static GemmForm plain_form(int M, int N, int K) {
     const long row_tiles = (M + 32 * f.waves - 1) / (32 * f.waves);
     if (row_tiles * (N / 32) / f.tn > kComputeUnits) continue;
     const long by_96 = (M + 95) / 96;
-    if (f.waves == 4 && f.tn == 2 && K >= 12288 && by_96 > row_tiles && by_96 * (N / 64) <= kComputeUnits) return GemmForm{3, 1, 2};
+    if (f.waves == 4 && f.tn == 2 && K >= 12288 && 3 * by_96 >= 4 * row_tiles && by_96 * (N / 64) <= kComputeUnits) return GemmForm{3, 1, 2};
     return f;
   }
   return GemmForm{4, M <= 128 ? 1 : 2, 4};
@@ -499,6 +502,13 @@ static GemmForm swiglu_form(int M, int N) {
     }
   }
   return best;
+}
+
+void gemm256_plan(int M, int N, int K, bool swiglu, int32_t *out3) {
+  const GemmForm f = swiglu ? swiglu_form(M, N) : plain_form(M, N, K);
+  out3[0] = 32 * f.waves * f.tm;
+  out3[1] = 32 * f.tn;
+  out3[2] = (M + out3[0] - 1) / out3[0] * (N / out3[1]);
 }
 
 template <int MODE, int TM, int TN, int D, int WV, bool NT = false>

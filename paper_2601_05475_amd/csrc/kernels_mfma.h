@@ -109,6 +109,7 @@ __device__ inline void rope_store_quad(const RopeOut &ro, int m, int n, float4 s
 // == 0, K % 256 == 0.  256 x 128 output tile per workgroup (256 x 64 of each weight matrix in the
 // SwiGLU form; other shapes where few tiles would leave compute units idle), XCD-aware tile order.
 bool gemm256_supported(int M, int N, int K, bool swiglu);
+void gemm256_plan(int M, int N, int K, bool swiglu, int32_t *out3);        // see mc_op_gemm_plan
 // rope != nullptr: the fused QKV layer as in launch_linear_skinny (N = (Hq + 2 Hkv) hd, hd % 4 == 0).
 // accumulate: out[m][n] += the product (the residual stream updated in place) instead of a store.
 int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const void *w,

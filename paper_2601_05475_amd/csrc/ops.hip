@@ -198,6 +198,13 @@ extern "C" int mc_op_linear(void *stream, int32_t dtype, int32_t M, int32_t N, i
   return launch_linear((hipStream_t)stream, dtype, M, N, K, a, w, out, n_splits, tiled);
 }
 
+extern "C" int mc_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t swiglu, int32_t *out3) {
+  if (M < 1 || N < 1 || K < 1 || !out3 || (swiglu != 0 && swiglu != 1)) MC_FAIL(MC_ERR_INVALID, "bad sizes");
+  if (!tiled_shapes_ok(M, N, K) || !use_gemm256(M, N, K, swiglu)) MC_FAIL(MC_ERR_UNSUPPORTED, "GEMM: M=%d N=%d K=%d not covered", M, N, K);
+  gemm256_plan(M, N, K, swiglu, out3);
+  return MC_OK;
+}
+
 extern "C" int mc_op_linear_accumulate(void *stream, int32_t M, int32_t N, int32_t K, const void *a,
                                        const void *w, float *x) {
   if (M < 1 || N < 1 || K < 1) MC_FAIL(MC_ERR_INVALID, "bad sizes");

@@ -136,6 +136,29 @@ def test_decode_attention_plan_covers_every_block_and_fits_its_workspace(lib):
         assert p["n_parts"] * B * Hq * (hd + 2) * 4 <= ws, (B, Hq, Hkv, hd, P, t, S, p, ws)
 
 
+def test_gemm_plan_takes_96_rows_only_for_a_third_more_workgroups(lib):
+    """Host logic of the many-row GEMM: one round of workgroups where a listed shape can have it, and the 96-row form in
+    place of 128 x 64 only over a long K and where it has at least 4/3 of the workgroups (with 1.17 and 1.20 of
+    them it was slower)."""
+    for N, K in ((2048, 12288), (3072, 16384), (4096, 14336), (4096, 4096), (5120, 27648), (2048, 8192)):
+        taken = 0
+        for M in range(65, 1200):
+            rows, cols, groups = binding.op_gemm_plan(M, N, K)
+            assert groups == -(-M // rows) * (N // cols)
+            by_128 = -(-M // 128) * (N // 64)
+            if rows == 96:
+                taken += 1
+                assert cols == 64 and K >= 12288 and 3 * groups >= 4 * by_128 and groups <= 256, (M, N, K)
+            assert groups <= 256 or -(-M // 128) * (N // 128) > 256, (M, N, K)
+        assert (taken > 0) == (K >= 12288), (N, K)
+    assert binding.op_gemm_plan(641, 2048, 12288) == (128, 64, 192)
+    assert binding.op_gemm_plan(600, 2048, 12288) == (96, 64, 224)
+    out = (C.c_int32 * 3)()
+    assert lib.mc_op_gemm_plan(64, 4096, 4096, 0, out) == -5 and lib.mc_op_gemm_plan(65, 4000, 4096, 0, out) == -5
+    assert lib.mc_op_gemm_plan(65, 4096, 4000, 1, out) == -5 and lib.mc_op_gemm_plan(0, 4096, 4096, 0, out) == -1
+    assert lib.mc_op_gemm_plan(65, 4096, 4096, 2, out) == -1 and lib.mc_op_gemm_plan(65, 4096, 4096, 0, None) == -1
+
+
 @pytest.mark.parametrize("rows,K,calls", [(1, 64, 1), (32, 2048, 1), (33, 4096, 1), (55, 5120, 1), (64, 128, 1), (300, 4096, 1),
                                           (300, 14336, 3)])
 def test_tiled_outputs_cost_one_torch_call_and_have_zero_padding(rows, K, calls):
