@@ -302,7 +302,9 @@ def bench_rerank(args, torch, binding, synth):
     rows = B * Ls
     n_chunks = -(-rows // (chunk // Ls * Ls))
     m_chunk = rows / n_chunks
-    gu_flops = 2.0 * m_chunk * (2 * s.d_ffn) * s.d_model
+    # the mean over the timed launches; the last layer's have the rows of a chunk whose logits are read
+    gu_rows = (m_chunk * (s.n_layers - 1) + m_chunk / Ls) / s.n_layers
+    gu_flops = 2.0 * gu_rows * (2 * s.d_ffn) * s.d_model
     gu_us = ms_gu * 1e3 / max(n_gu, 1)
     layer_flops = 2.0 * rows * s.d_model * ((s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim + s.n_q_heads * s.head_dim + 3 * s.d_ffn)
     attn_flops = 4.0 * s.n_q_heads * s.head_dim * B * Ls * (P + Ls / 2.0)          # per layer, causal
@@ -310,9 +312,8 @@ def bench_rerank(args, torch, binding, synth):
     # 64 rows) that holds each of them
     qkv_flops = 2.0 * rows * s.d_model * (s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim
     linear_flops = layer_flops * (s.n_layers - 1) + qkv_flops + (layer_flops - qkv_flops) / Ls
-    attn_timed = attn_flops * (s.n_layers - 1)                                     # launches that the profile times
-    gu_tflops = gu_flops / gu_us / 1e6 if n_gu else 0.0                             # (none of a single layer's)
-    attn_total = attn_timed + 4.0 * s.n_q_heads * s.head_dim * B * min(64, Ls) * (P + Ls)
+    gu_tflops = gu_flops / gu_us / 1e6
+    attn_total = attn_flops * (s.n_layers - 1) + 4.0 * s.n_q_heads * s.head_dim * B * min(64, Ls) * (P + Ls)
     out = {
         "metric": "scored candidates/s (8B-shape reranking: expected categorical reward at each suffix end)",
         "value": B * K / elapsed, "unit": "candidates/s", "n_gpus": 1, "steps": K, "warmup": W,
@@ -324,11 +325,11 @@ def bench_rerank(args, torch, binding, synth):
         "roofline": {"bound": "mfma", "kernel": "gemm256_kernel<GEMM_SWIGLU> (gate/up + SwiGLU)",
                      "achieved": gu_tflops, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": gu_tflops / MFMA_PEAK_TFLOPS, "traffic": None,
-                     "launches_timed": n_gu, "avg_us": gu_us, "rows_per_launch": m_chunk,
+                     "launches_timed": n_gu, "avg_us": gu_us, "rows_per_launch": gu_rows,
                      "peak_measured": mfma_meas, "frac_of_measured": gu_tflops / mfma_meas},
         "whole_pass": {"linear_flops": linear_flops, "attention_flops": attn_total,
                        "achieved_tflops": (linear_flops + attn_total) / (elapsed / K) / 1e12,
-                       "attention_ms_per_pass": ms_at, "attention_tflops": attn_timed / (ms_at * 1e-3) / 1e12 if n_at else 0.0},
+                       "attention_ms_per_pass": ms_at, "attention_tflops": attn_total / (ms_at * 1e-3) / 1e12},
         "prefill_s": t_prefill, "setup_s": {"generate_weights": t_gen},
         "yardsticks": {"hbm_copy_gbs": measured_copy_gbs(torch), "mfma_matmul_tflops": matmul_yardstick_tflops(torch),
                        "mfma_probe_tflops": mfma_meas,

@@ -281,8 +281,8 @@ typedef enum {
  * themselves and carry the kernels' own begin and end times; for the other classes they are
  * recorded on the stream before and after the launch, which adds a few microseconds.  Where the last
  * layer of a many-row pass goes on with the rows alone whose logits are read, its launches past the
- * keys and values are not of the pass's size and are not timed; the embedding gather and the first
- * norm of a pass are one launch, which counts in both classes. */
+ * keys and values count like the others, though they are not of the pass's size; the embedding gather
+ * and the first norm of a pass are one launch, which counts in both classes. */
 int mc_profile_begin(mc_session *s, int32_t kernel_class, int32_t stride);
 /* Synchronise, then report how many launches were timed and their total duration. */
 int mc_profile_end(mc_session *s, int32_t *n_timed, double *total_ms);

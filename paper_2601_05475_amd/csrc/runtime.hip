@@ -554,12 +554,25 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
       *compact = true;
       *tail_splits = 0;
       if (last->n == 0) return MC_OK;                         // a chunk before the last: its keys and values are all
-      MC_TRY(launch_prefill(last->n_items));
       float *xl = s->ptr<float>(L.xlast);
+      {
+        ProfScope ps(s, MC_K_ATTN_PREFILL);
+        MC_TRY(launch_prefill(last->n_items));
+      }
       MC_TRY(launch_gather_last(st, last->n, d, qd, x, ao, s->ptr<int32_t>(L.last_idx), xl, act));
-      MC_TRY(launch_gemm256(st, last->n, d, qd, act, W.wo, nullptr, xl, nullptr, nullptr, 1));
-      MC_TRY(launch_add_rmsnorm(st, dt, last->n, d, xl, nullptr, 0, W.ffn_norm, c.rms_eps, h, tl, rows));
-      MC_TRY(launch_gemm256(st, last->n, c.d_ffn, d, h, W.w_gate, W.w_up, nullptr, act));
+      {
+        ProfScope ps(s, MC_K_LINEAR_O);
+        MC_TRY(launch_gemm256(st, last->n, d, qd, act, W.wo, nullptr, xl, nullptr, nullptr, 1));
+      }
+      {
+        ProfScope ps(s, MC_K_ADD_RMSNORM);
+        MC_TRY(launch_add_rmsnorm(st, dt, last->n, d, xl, nullptr, 0, W.ffn_norm, c.rms_eps, h, tl, rows));
+      }
+      {
+        ProfScope ps(s, MC_K_LINEAR_GATE_UP);
+        MC_TRY(launch_gemm256(st, last->n, c.d_ffn, d, h, W.w_gate, W.w_up, nullptr, act));
+      }
+      ProfScope ps(s, MC_K_LINEAR_DOWN);
       return launch_gemm256(st, last->n, d, c.d_ffn, act, W.w_down, nullptr, xl, nullptr, nullptr, 1);
     }
     if (pass == PASS_DECODE) {

@@ -1014,6 +1014,27 @@ def test_oversample_then_filter_by_reward_score():
         assert_logits_close(got[i][None], ref[None], "f32", "new round on the promoted prefix")
 
 
+@pytest.mark.parametrize("layers", [1, 2])
+def test_profile_counts_the_launches_of_a_shortened_last_layer(layers):
+    """A many-row pass that finishes its last layer for a few rows reports one launch of each class per layer, that
+    layer's among them, and a prefix in two chunks those of the second chunk's last layer only."""
+    s = synth.Shape("profiled", layers, 256, 4, 2, 64, 512, 1024, 1.0e4, "bf16")
+    model = binding.Model(s, synth.make_weights(s, 905))
+    sess = binding.Session(model, 256, 4, 64, 64, chunk_rows=128)
+    prefix, suffix = synth.tokens(906, 1, (256,), s.vocab), synth.tokens(906, 2, (4, 32), s.vocab)
+    sess.prefill_shared(prefix)
+    print("case: profile of the last layer", layers, flush=True)
+    for cls, score, prefill in [("linear_qkv", layers, 2 * layers), ("attn_prefill", layers, 2 * layers - 1), ("linear_o", layers, 2 * layers - 1),
+                                ("add_rmsnorm", 2 * layers, 4 * layers - 1), ("linear_gate_up", layers, 2 * layers - 1),
+                                ("linear_down", layers, 2 * layers - 1)]:
+        for run, want in ((lambda: sess.score_candidates(suffix, [32] * 4, np.arange(8, dtype=np.int32), np.arange(8, dtype=np.float32)), score),
+                          (lambda: sess.prefill_shared(prefix), prefill)):
+            sess.profile_begin(cls, 1)
+            run()
+            n, ms = sess.profile_end()
+            assert n == want and ms > 0, (cls, n, want, ms)
+
+
 @pytest.mark.parametrize("chunk_rows", [0, 128])
 def test_last_layer_for_the_last_rows_gives_the_bits_of_all_rows(chunk_rows):
     """Many-row passes finish their last layer for the rows whose logits are read.  A further layer that adds
