@@ -162,8 +162,8 @@ def test_gemm_plan_takes_96_rows_only_for_a_third_more_workgroups(lib):
 @pytest.mark.parametrize("rows,K,calls", [(1, 64, 1), (32, 2048, 1), (33, 4096, 1), (55, 5120, 1), (64, 128, 1), (300, 4096, 1),
                                           (300, 14336, 3)])
 def test_tiled_outputs_cost_one_torch_call_and_have_zero_padding(rows, K, calls):
-    """The buffer of a tiled output: its size, zeros in the padding rows, and no more torch calls than a
-    plain zeroed tensor takes unless it is large."""
+    """The buffer of a tiled output: its size, zeros in the padding rows where the operation does not write them, and
+    then no more torch calls than a plain zeroed tensor takes unless it is large; one call where it does."""
     import torch
     from torch.utils._python_dispatch import TorchDispatchMode
 
@@ -177,6 +177,9 @@ def test_tiled_outputs_cost_one_torch_call_and_have_zero_padding(rows, K, calls)
     with Count():
         out = binding._tiled_out(rows, K, torch.bfloat16, "cpu")
     assert Count.seen == calls
+    with Count():
+        whole = binding._tiled_empty(rows, K, torch.bfloat16, "cpu")
+    assert Count.seen == calls + 1 and whole.dtype == out.dtype and whole.shape == out.shape
     assert out.dtype == torch.bfloat16 and out.numel() * 2 == binding.load_library().mc_op_tiled_bytes(rows, K)
     if rows % 32:
         assert not binding.tiled_to_rowmajor(out, (rows + 31) // 32 * 32, K)[rows:].any()

@@ -707,14 +707,18 @@ def test_linear_qkv_rope_few_hundred_rows(rows, Hq, Hkv, hd, K):
     test_linear_qkv_rope_fused(rows, Hq, Hkv, hd, K)
 
 
-def test_many_row_gemm_forms_give_the_same_bits():
-    """Rows alone (128 x 32 tiles), with more rows (128 x 64 and 128 x 128) and in a chunk (256 x 128): the
-    same bits in every output form, and every form twice."""
+@pytest.mark.parametrize("N,K,Hq,Hkv,rows,forms", [
+    (4096, 768, 16, 8, (100, 200, 300, 600, 3000), ((64, 32), (128, 32), (128, 64), (128, 128), (256, 128))),
+    (5120, 768, 20, 10, (192, 3000), ((64, 64), (256, 128))),
+    (4096, 12288, 16, 8, (300, 3000), ((96, 64), (256, 128)))])
+def test_many_row_gemm_forms_give_the_same_bits(N, K, Hq, Hkv, rows, forms):
+    """Rows alone, with more rows and in a chunk, which are workgroups of every shape (rows x columns) that the plain and
+    the rotary products take: the same bits in every output form, and every form twice."""
     import torch
-    N, K, rows = 4096, 768, (100, 300, 600, 3000)
+    assert tuple(binding.op_gemm_plan(M, N, K)[:2] for M in rows) == forms
     w = binding.op_pack_tiled(to_dev(rnd(550, (N, K), 0.05), "bf16")[0])
     w2 = binding.op_pack_tiled(to_dev(rnd(551, (N, K), 0.05), "bf16")[0])
-    Hq, Hkv, hd, pg = 16, 8, 128, 64                    # (Hq + 2 Hkv) hd = N
+    hd, pg = 128, 64                                    # (Hq + 2 Hkv) hd = N
     a = to_dev(rnd(552, (rows[-1], K)), "bf16")[0]
     x0 = to_dev(rnd(553, (rows[-1], N)), "f32")[0]
 
@@ -733,7 +737,7 @@ def test_many_row_gemm_forms_give_the_same_bits():
     names = ("sums", "residual", "swiglu", "queries", "keys", "values")
     full = outputs(rows[-1])
     for M in rows:
-        print("case: GEMM forms", M, flush=True)
+        print("case: GEMM forms", N, K, M, flush=True)
         one, two = outputs(M), outputs(M)
         for name, x, y, z in zip(names, one, two, full):
             assert torch.equal(x, y), (name, M, "run to run")
@@ -1127,6 +1131,8 @@ def test_tiled_outputs_leave_rows_that_are_not_theirs():
                 binding.op_attention_decode(*part, out_tiled=True, out=out[8 * r0:], static_scratch=static)
                 want[r0:r0 + rows] = binding.op_attention_decode(*part).reshape(rows, -1)
             _assert_tile(out, want, Hq * hd, 30)
+            whole = binding.op_attention_decode(*part, out_tiled=True, static_scratch=static)
+            assert not _padding_of(whole, rows, Hq * hd).any()
 
 
 @pytest.mark.parametrize("Hq,hd,lens", [(8, 128, (300,)), (8, 64, (33,)), (8, 128, (1000, 70, 40)), (8, 64, (1000, 1000, 71)),

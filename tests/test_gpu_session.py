@@ -1041,19 +1041,40 @@ def test_last_layer_for_the_last_rows_gives_the_bits_of_all_rows(chunk_rows):
     exactly nothing (zero output and down projections) makes the layer before it one that is computed for
     every row: logits and scores must keep their bits.  Prefix and extension in one and several chunks, candidates
     that end on and beside tile and item edges, scored and written."""
-    d, F = 256, 512
-    s = synth.Shape("two layers", 2, d, 4, 2, 64, F, 1024, 1.0e4, "bf16")
+    _last_layer_keeps_its_bits(256, 4, 2, 64, 512, 300, 131, (64, 65, 1, 127, 128, 33), chunk_rows)
+
+
+@pytest.mark.parametrize("d,hd,F", [(4096, 128, 1024), (2560, 64, 1536)])
+def test_last_layer_for_the_last_rows_of_a_large_pass(d, hd, F):
+    """The same where the pass and its last rows take different kernels: 256-row workgroups and 64-row ones in the
+    products, whole items and four waves per head in the attention, 512 and 1024 threads in the norm.  A norm whose sum
+    runs in another order changes an output's bf16 in about 2^-16 of the elements and shows in few rows (3 and 1 of 64 by the
+    scores here), so there are 64 last rows."""
+    Hq, Hkv, prefix = 4, 1, 8300
+    lens = (1, 64, 65, 128, 1000) + tuple(119 + i % 7 for i in range(59))
+    for M in (sum(lens), prefix):
+        assert M >= 2048 and d > 4 * 512                                           # the norm's threads, by rows
+        assert all(binding.op_gemm_plan(M, *nk)[:2] == (256, 128) for nk in ((d, Hq * hd), (d, F)))
+        assert binding.op_gemm_plan(M, F, d, True)[:2] == (256, 64)
+    items = min(sum(-(-n // 64) for n in lens), -(-prefix // 64))
+    assert items * 2 > 256 >= len(lens) * 4                                        # workgroups with two and four waves per head
+    _last_layer_keeps_its_bits(d, Hq, Hkv, hd, F, prefix, 131, lens, 8704)
+
+
+def _last_layer_keeps_its_bits(d, Hq, Hkv, hd, F, n_prefix, n_more, lens, chunk_rows):
+    s = synth.Shape("two layers", 2, d, Hq, Hkv, hd, F, 1024, 1.0e4, "bf16")
     w = synth.make_weights(s, 901)
     zero = dict(w["layers"][1], wo=np.zeros_like(w["layers"][1]["wo"]), w_down=np.zeros_like(w["layers"][1]["w_down"]))
-    s3 = synth.Shape("and one that adds nothing", 3, d, 4, 2, 64, F, 1024, 1.0e4, "bf16")
+    s3 = synth.Shape("and one that adds nothing", 3, d, Hq, Hkv, hd, F, 1024, 1.0e4, "bf16")
     w3 = dict(w, layers=list(w["layers"]) + [zero])
-    prefix, more = synth.tokens(902, 1, (300,), s.vocab), synth.tokens(902, 2, (131,), s.vocab)
-    lens = np.array([64, 65, 1, 127, 128, 33], np.int32)
-    suffix = synth.tokens(902, 3, (len(lens), 128), s.vocab)
+    prefix, more = synth.tokens(902, 1, (n_prefix,), s.vocab), synth.tokens(902, 2, (n_more,), s.vocab)
+    lens = np.array(lens, np.int32)
+    suffix = synth.tokens(902, 3, (len(lens), int(lens.max())), s.vocab)
+    print("case: last layer", d, hd, n_prefix, lens, chunk_rows, flush=True)
     out = []
     for shape, weights in ((s, w), (s3, w3)):
         model = binding.Model(shape, weights)
-        sess = binding.Session(model, 512, len(lens), 192, 64, chunk_rows=chunk_rows)
+        sess = binding.Session(model, n_prefix + n_more + 64, len(lens), int(lens.max()) + 64, 64, chunk_rows=chunk_rows)
         sess.prefill_shared(prefix)
         got = [sess.logits(1)]
         sess.extend_shared(more)
