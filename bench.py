@@ -33,17 +33,17 @@ MFMA_PEAK_TFLOPS = 2500.0    # MI355X dense bf16 MFMA, published
 # HBM traffic of one gate/up launch from the FETCH_SIZE / WRITE_SIZE counter runs (KiB per
 # dispatch, scaled by what the same counters read for a plain copy of known size; see
 # profiles/decode_8b_traffic_counters.md).  Valid for the kernel source with this hash only.
-TRAFFIC_GATE_UP = {"fetch_kib": 115760.5, "fetch_scale": 2.0, "write_kib": 896.0, "write_scale": 1.0,
+TRAFFIC_GATE_UP = {"fetch_kib": 115761.0, "fetch_scale": 2.0, "write_kib": 896.0, "write_scale": 1.0,
                    "source": "paper_2601_05475_amd/csrc/kernels_mfma.hip",
-                   "sha256": "195b3cd0cc63be24d006182355f7596e3582871f57e80ab923bcf591f9c5ba36"}
+                   "sha256": "2e04089189f7d9df1f5d72002e61c7cffd29c8b631b143d45c95a72d54eaccdb"}
 
 
 # Decode attention + merge at suffix lengths 255..258 (the same two counter runs: four timed steps
 # sit at the middle of the 512-step workload, whose average suffix length is 256.5).
-TRAFFIC_ATTN = {"fetch_kib": 26427.5, "merge_fetch_kib": 2922.0, "write_kib": 4680.0, "merge_write_kib": 256.0,
+TRAFFIC_ATTN = {"fetch_kib": 26452.4, "merge_fetch_kib": 2922.5, "write_kib": 4680.0, "merge_write_kib": 256.0,
                 "fetch_scale": 2.0, "write_scale": 1.0, "suffix_len": 256.5,
                 "source": "paper_2601_05475_amd/csrc/kernels_attn.hip",
-                "sha256": "0ab99c8fa2d8bfba6214bf19266d40b3861557b3f9ebbff542f3b9bf4a2434f7"}
+                "sha256": "1e9c6f88b01320a65d5cc1bf00a7729b759aca73f76702fc86ae045c52b5d7fe"}
 
 
 def measured_attention_traffic_bytes(workload, mean_suffix_len):

@@ -450,9 +450,10 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
 // Plain products: rows per workgroup (64: two waves, 128: four, 256: four with two row tiles each) and weight tiles per
 // workgroup.  The first form of this list with which one round (a workgroup to each of the 256 compute units) covers
 // the product, else the 256 x 128 tile, which moves the fewest operand bytes per flop; up to 128 rows at least not its
-// empty half.  A workgroup is a serial chain over K whose pace is set by its loads, so the list is in the order of the
-// operand bytes per unit: 64 x 32, 128 x 32, 64 x 64, 128 x 64, 128 x 128 (128 x 32 before 64 x 64: its rows are read
-// from L2 by more workgroups).  us, N x K = 4096 x 14336: 100 rows 43 / 62 / 61 / 78 / 115 (256 x 128: 130), 200 rows
+// empty half.  A workgroup is a serial chain over K whose pace is set by its loads, so the list goes by the
+// operand bytes per unit: 64 x 32, 128 x 32, 64 x 64, 128 x 64, 128 x 128.  But for one place: 128 x 32 takes five blocks of 4 KB and
+// comes before 64 x 64, which takes four.  That gains where 64 x 64 has fewer workgroups (2048 x 8192, 300 rows) and costs
+// where it has as many (4096 x 14336, 200 rows).  us, N x K = 4096 x 14336: 100 rows 43 / 62 / 61 / 78 / 115 (256 x 128: 130), 200 rows
 // 78 / 60 / 52 / 72 / 105, 256 rows 78 / 64 / 64 / 79 / 125, 300 rows - / 96 / 95 / 67 / 96 (128), 512 rows - / 119 / 122 / 80 / 115
 // (150), 1024 rows - / 240 / - / 168 / 126 (158), 1500 rows 327 / 227 / 205 (162) by 128 x 32 / 64 / 128; 4096 x 4096: 100
 // rows 15 / 21 / 20 / 25 / 35; 2048 x 8192: 100 rows 25 / 36 / 36 / 45 / 66, 256 rows 26 / 36 / 36 / 45 / 65, 300 rows 43 / 31 / 37 / 39 /
