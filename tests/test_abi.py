@@ -136,6 +136,25 @@ def test_decode_attention_plan_covers_every_block_and_fits_its_workspace(lib):
         assert p["n_parts"] * B * Hq * (hd + 2) * 4 <= ws, (B, Hq, Hkv, hd, P, t, S, p, ws)
 
 
+def test_tiled_entry_points_refuse_what_the_plain_ones_refuse(lib):
+    """Host checks, pointers never followed: NULL pointers, fp32 and widths without the layout, a workspace too small."""
+    p = C.c_void_p(256)
+    assert lib.mc_op_add_rmsnorm_tiled(None, 1, 3, 64, None, None, 0, p, 1e-6, p) == -1
+    assert lib.mc_op_add_rmsnorm_tiled(None, 0, 3, 64, p, None, 0, p, 1e-6, p) == -5
+    assert lib.mc_op_add_rmsnorm_tiled(None, 1, 3, 96, p, None, 0, p, 1e-6, p) == -5
+    assert lib.mc_op_add_rmsnorm(None, 1, 3, 64, p, None, 0, p, 1e-6, p, 2) == -1
+    assert lib.mc_op_linear_swiglu_tiled(None, 1, 3, 128, 256, p, p, None, p) == -1
+    assert lib.mc_op_linear_swiglu_tiled(None, 0, 3, 128, 256, p, p, p, p) == -5
+    assert lib.mc_op_linear_swiglu_tiled(None, 1, 3, 100, 256, p, p, p, p) == -5
+    assert lib.mc_op_linear_swiglu(None, 1, 3, 128, 256, p, p, p, p, 2) == -1
+    sizes = (4, 8, 2, 64, 64, 100, 0)
+    tail = (p, p, p, None, None, None, 0, None, 0)
+    assert lib.mc_op_attention_decode_tiled(None, 1, *sizes, *tail, p, 16, p) == -1
+    assert lib.mc_op_attention_decode_tiled(None, 0, *sizes, *tail, p, 1 << 30, p) == -5
+    assert lib.mc_op_attention_decode_tiled(None, 1, *sizes, *tail, p, 1 << 30, None) == -1
+    assert lib.mc_op_attention_decode(None, 1, *sizes, *tail, p, 1 << 30, p, 2) == -1
+
+
 def test_gemm_plan_takes_96_rows_only_for_a_third_more_workgroups(lib):
     """Host logic of the many-row GEMM: one round of workgroups where a listed shape can have it, and the 96-row form in
     place of 128 x 64 only over a long K and where it has at least 4/3 of the workgroups (with 1.17 and 1.20 of
