@@ -5,11 +5,12 @@
 // positions 32 (w / 4) .. + 31 of the item, which are its MFMA columns.  Two waves per SIMD let
 // one wave's softmax run under the other's MFMAs, and the LDS only reaches its full read rate
 // with eight waves per CU.
-// Where that gives fewer workgroups than the chip has compute units, two or four waves share the 32
-// columns of a head (prefill_attention_split_kernel): they score different key blocks and add different
+// Where that gives fewer workgroups than the chip has compute units, two waves share the 32
+// columns of a head (prefill_attention_split_kernel), or four that score and four that add take two heads' (prefill_attention_pair_kernel): they
+// score different key blocks and add different
 // coordinates of the result, so that a row's sum runs over its keys in the same order as with one wave
 // and has the same bits whatever else is in the launch (300 positions of the 8B shape after 1024 / 4096
-// keys: 38 -> 21 / 108 -> 51 us).
+// keys: 38 -> 19 / 108 -> 45 us).
 // Keys are streamed page by page (64 keys) through LDS and shared by the waves: first the
 // shared-prefix pages that are visible to the block, then (scoring) the sequence's own suffix
 // pages.  Pages are stored in MFMA fragment order, so a page is copied to LDS as it is (by
@@ -21,6 +22,7 @@
 #include "kernels_mfma.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mc {
 
@@ -52,17 +54,18 @@ template <int HD> struct PWhole {              // pages of K and V together, thr
   static constexpr int STEPS = 3, LPS = 2 * PTile<HD>::CPT;   // LPS: loads into LDS per wave and step
   static constexpr int LDS_BYTES = STEPS * PTile<HD>::PAGE_ELEMS * 2;
 };
-template <int HD, int KS> struct PSplit {      // KS waves per head: a step is KS blocks, KS / 2 pages
-  static constexpr int PP = KS / 2, HEADS = 8 / KS;
-  static constexpr int SLOTS = KS == 4 && HD == 128 ? 2 : 3;  // steps of K, and of V, held in LDS
-  static constexpr int LPH = PTile<HD>::CPT * PP;             // loads into LDS per wave and step of K (of V)
-  static constexpr int NDT = HD / 32 / KS ? HD / 32 / KS : 1; // 32-coordinate tiles of the result per wave
-  static constexpr int K_BYTES = SLOTS * PP * PTile<HD>::K_ELEMS * 2;
+template <int HD> struct PSplit {              // two waves per head: a step is two blocks, one page
+  static constexpr int KS = 2, HEADS = 8 / KS;
+  static constexpr int SLOTS = 3;                            // steps of K, and of V, held in LDS
+  static constexpr int LPH = PTile<HD>::CPT;                 // loads into LDS per wave and step of K (of V)
+  static constexpr int NDT = HD / 32 / KS;                   // 32-coordinate tiles of the result per wave
+  static constexpr int K_BYTES = SLOTS * PTile<HD>::K_ELEMS * 2;
   // K slots, V slots, the probabilities of eight blocks, their sums and references, flags
   static constexpr int LDS_BYTES = 2 * K_BYTES + 8 * (2048 + 256 + 256) + 64;
 };
 
 constexpr int kPrefillMaxPids = 1024;
+constexpr int kPairSharedKeys = 2048;          // see prefill_form
 typedef __attribute__((address_space(3))) int lds_int;
 
 // All but the newest N vector memory operations of this wave have landed, loads into LDS among them,
@@ -376,27 +379,26 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   }
 }
 
-// The same with KS waves for the 32 columns of a head: a workgroup has one half of an item's rows and
-// 8 / KS heads, and a step is KS blocks of 32 keys.  In a step wave kg of a head scores block kg and leaves
+// The same with two waves for the 32 columns of a head: a workgroup has one half of an item's rows and
+// four heads, and a step is a page, two blocks of 32 keys.  In a step wave kg of a head scores block kg and leaves
 // its probabilities and their sums in LDS, all against the reference that stood when the step began;
-// past a barrier every wave adds the KS blocks, in order, to the result coordinates it owns.  The first step
+// past a barrier every wave adds both blocks, in order, to the result coordinates it owns.  The first step
 // waits for block 0's maximum instead; where a block's sums leave the range later, which is seldom, the blocks
 // are done again one by one, the reference moving in between.  So a row's additions and references are those
-// of one wave that walks all keys.  (States of separate key groups merged at the end take 44 instead of 51 us for 300 rows
-// after 4096 keys, but then a row's last bits change with the number of groups, that is with the launch.)
-// A wave's chain bounds it, 1.2 us per step of four blocks: scores, exponentials, the probabilities' way through
-// LDS (272 KB a step in all), value products, two barriers, and what scalar work stands between: with page
-// ids looked up and block limits worked out anew in every step 1.35 us.  Fragments are read half a step ahead of
+// of one wave that walks all keys.  (States of separate key groups merged at the end are faster for few rows, but then a row's
+// last bits change with the number of groups, that is with the launch.)
+// A wave's chain bounds it: scores, exponentials, the probabilities' way through
+// LDS, value products, two barriers, and what scalar work stands between.  Fragments are read half a step ahead of
 // their use: K of the next step beside the value products, V under the scores; K's and V's slots are refilled at the
 // barrier behind that, which
 // gives a load 2 SLOTS - 1 half steps to land.
-template <int HD, int KS>
+template <int HD>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
   if ((int)blockIdx.x >= n_main) return zero_uncovered_rows(a, (int)blockIdx.x - n_main, a.n_q_heads * HD);
   using TL = PTile<HD>;
-  using SP = PSplit<HD, KS>;
-  constexpr int NF = TL::NF, NDT = SP::NDT;
+  using SP = PSplit<HD>;
+  constexpr int NF = TL::NF, NDT = SP::NDT, KS = SP::KS;
   extern __shared__ __attribute__((aligned(16))) unsigned char plds_raw[];
   bf16_t *k_lds = (bf16_t *)plds_raw, *v_lds = (bf16_t *)(plds_raw + SP::K_BYTES);
   v4u *probs = (v4u *)(plds_raw + 2 * SP::K_BYTES);             // [8 waves][2][64]
@@ -428,8 +430,7 @@ void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
     for (int c = 0; c < NF; ++c) qf[c] = *(const v4u *)(qrow + 16 * c);
   }
   const float scale2 = 1.4426950408889634f / sqrtf((float)HD);
-  // this wave's coordinate tiles: NDT * kg .. + NDT - 1 (head_dim 64 and four waves: the last two own none)
-  const bool owner = NDT * KS <= HD / 32 || NDT * kg < HD / 32;
+  // this wave's coordinate tiles: NDT * kg .. + NDT - 1
   f32x16 o[NDT];
 #pragma unroll
   for (int x = 0; x < NDT; ++x)
@@ -444,29 +445,21 @@ void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
   const char *kA = (const char *)a.k_prefix + head_off, *vA = (const char *)a.v_prefix + head_off;
   const char *kB = (const char *)a.k_suffix + head_off, *vB = (const char *)a.v_suffix + head_off;
   int ids = pages.ids(0), ids_next = pages.ids(64);
-  uint64_t offs[SP::PP];
-  auto issue_k = [&](int step, int slot) __attribute__((always_inline)) {
-    const int p0 = step * SP::PP;
-    if ((p0 & 63) == 0 && p0 > 0) {
+  uint64_t off;
+  auto issue_k = [&](int pi, int slot) __attribute__((always_inline)) {          // a step is a page
+    if ((pi & 63) == 0 && pi > 0) {
       ids = ids_next;
-      ids_next = pages.ids(p0 + 64);
+      ids_next = pages.ids(pi + 64);
     }
+    off = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, pi & 63) * page_bytes;
+    const __amdgpu_buffer_rsrc_t kr = page_range((const bf16_t *)((pi < pages.nPA ? kA : kB) + off), pi < pages.n, HD);
 #pragma unroll
-    for (int i = 0; i < SP::PP; ++i) {
-      offs[i] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, (p0 + i) & 63) * page_bytes;
-      const __amdgpu_buffer_rsrc_t kr = page_range((const bf16_t *)((p0 + i < pages.nPA ? kA : kB) + offs[i]), p0 + i < pages.n, HD);
-#pragma unroll
-      for (int c = 0; c < TL::CPT; ++c) load_piece(kr, k_lds + (slot * SP::PP + i) * TL::K_ELEMS + wave * 512, c);
-    }
+    for (int c = 0; c < TL::CPT; ++c) load_piece(kr, k_lds + slot * TL::K_ELEMS + wave * 512, c);
   };
-  auto issue_v = [&](int step, int slot) __attribute__((always_inline)) {
+  auto issue_v = [&](int pi, int slot) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t vr = page_range((const bf16_t *)((pi < pages.nPA ? vA : vB) + off), pi < pages.n, HD);
 #pragma unroll
-    for (int i = 0; i < SP::PP; ++i) {
-      const int pi = step * SP::PP + i;
-      const __amdgpu_buffer_rsrc_t vr = page_range((const bf16_t *)((pi < pages.nPA ? vA : vB) + offs[i]), pi < pages.n, HD);
-#pragma unroll
-      for (int c = 0; c < TL::CPT; ++c) load_piece(vr, v_lds + (slot * SP::PP + i) * TL::V_ELEMS + wave * 512, c);
-    }
+    for (int c = 0; c < TL::CPT; ++c) load_piece(vr, v_lds + slot * TL::V_ELEMS + wave * 512, c);
   };
 #pragma unroll
   for (int st = 0; st < SP::SLOTS; ++st) {
@@ -487,15 +480,14 @@ void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
   v4u kf[NF], vf[KS][NDT][2], pb[KS][2];
   float rs[KS];
   auto read_k = [&](int slot) __attribute__((always_inline)) {
-    const bf16_t *kblk = k_lds + (slot * SP::PP + (kg >> 1)) * TL::K_ELEMS + ((kg & 1) * NF * 64 + lane) * 8;
+    const bf16_t *kblk = k_lds + slot * TL::K_ELEMS + (kg * NF * 64 + lane) * 8;
 #pragma unroll
     for (int c = 0; c < NF; ++c) kf[c] = *(const v4u *)(kblk + c * 512);
   };
   auto read_v = [&](int slot) __attribute__((always_inline)) {
-    if (!owner) return;
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const bf16_t *vblk = v_lds + (slot * SP::PP + (i >> 1)) * TL::V_ELEMS + ((i & 1) * NF * 64 + lane) * 8;
+      const bf16_t *vblk = v_lds + slot * TL::V_ELEMS + (i * NF * 64 + lane) * 8;
 #pragma unroll
       for (int x = 0; x < NDT; ++x)
 #pragma unroll
@@ -509,15 +501,14 @@ void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
   };
   auto add_block = [&](int i) __attribute__((always_inline)) {
     l += rs[i];
-    if (owner)
 #pragma unroll
-      for (int x = 0; x < NDT; ++x)
+    for (int x = 0; x < NDT; ++x)
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl) o[x] = mfma32p(vf[i][x][sl], pb[i][sl], o[x]);
+      for (int sl = 0; sl < 2; ++sl) o[x] = mfma32p(vf[i][x][sl], pb[i][sl], o[x]);
   };
   // the loads issued after those that a barrier waits for: 2 SLOTS - 2 half steps
   constexpr int kAhead = (2 * SP::SLOTS - 2) * SP::LPH;
-  const int n_steps = (pages.n + SP::PP - 1) / SP::PP;
+  const int n_steps = pages.n;
   // steps whose keys all exist and lie before every row, in the prefix
   const int n_plain = min(pages.nA, pos_start + 1) / (32 * KS);
   wait_barrier_p<kAhead + SP::LPH>();           // K of step 0
@@ -533,9 +524,8 @@ void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
     int abs0 = 0, nv = 32;
     bool live = active;                         // uniform; else all masked
     if (!plain) {
-      const int pi = st * SP::PP + (kg >> 1);
-      nv = pages.block(pi, kg & 1, abs0);
-      live = active && pi < pages.n && nv > 0 && abs0 <= my_last;
+      nv = pages.block(st, kg, abs0);
+      live = active && nv > 0 && abs0 <= my_last;
     }
     f32x16 s;
     int found = 0;
@@ -614,10 +604,326 @@ void prefill_attention_split_kernel(PrefillAttnArgs a, int n_main) {
   }
   wait_barrier_p<0>();                          // no load into LDS outlives the loop
 
-  if (active && owner && col_valid) {
+  if (active && col_valid) {
     const float inv = 1.0f / l;
 #pragma unroll
     for (int x = 0; x < NDT; ++x) store_tile<HD>(a, row_start + col, head, NDT * kg + x, h, o[x], inv);
+  }
+}
+
+// The same with the work of 32 columns split by kind, for few workgroups: a workgroup has two heads, and a step is four
+// blocks of 32 keys.  Four waves score, each one block for both heads, and leave probabilities and sums in LDS; beside them
+// four waves add the step before, each 32 coordinates for both heads (head_dim 64: of one head).  A scoring and an adding
+// wave share a SIMD, so value products run under exponentials, and there is one barrier per step.  A block's keys are read by one wave
+// only, and so is a tile of its values, so both go from memory to registers and LDS holds the probabilities alone.  References
+// move as in the kernel above: all four blocks are scored against the one that stood when the step began, and where
+// a sum leaves the range the scoring waves do the step again block by block while the adding waves wait.  So the bits are the same, too.
+// Bound by a scoring wave's chain, 2300 cycles per step at head_dim 128 (8B heads, 300 rows after 4096 keys, by the cycle counter): eight
+// loads to ask for 400 (32 KB of keys and 32 of values per step at 64 bytes per cycle: 1024 in all), products and exponentials of the
+// first head 700 to 950, exponentials of the second 700 (a wave alone on the vector unit issues an instruction every 6 to
+// 12 cycles), barrier and flags 300.  Two scoring waves per SIMD, the next step's products under this one's exponentials, keys
+// by LDS, and loads spread among the exponentials were measured and are no faster.
+// us, one wave kind doing all four blocks' work in turn (two barriers, keys and values by LDS) -> this: 8B heads, 300 rows after 256 /
+// 1024 / 4096 keys 13.5 -> 12.1 / 21.7 -> 19.0 / 52.6 -> 45.4, heads of 64 after 1024 / 4096 17.6 -> 13.0 / 44.0 -> 30.5.
+template <int HD> struct PPair {
+  static constexpr int NF = HD / 16, KB = 4, HEADS = 2;         // blocks per step, heads per workgroup
+  static constexpr int ADD_HEADS = HD == 128 ? 2 : 1;           // heads per adding wave
+  // probabilities of eight (block, head) pairs, twice; their sums, twice; references; flags
+  static constexpr int PROBS = 0, SUMS = 2 * 8 * 2048, REFS = SUMS + 2 * 8 * 256, FLAGS = REFS + 8 * 256, LDS_BYTES = FLAGS + 128;
+};
+
+template <int HD>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, HD == 64 ? 4 : 2)))
+void prefill_attention_pair_kernel(PrefillAttnArgs a, int n_main) {
+  if ((int)blockIdx.x >= n_main) return zero_uncovered_rows(a, (int)blockIdx.x - n_main, a.n_q_heads * HD);
+  using SP = PPair<HD>;
+  constexpr int NF = SP::NF, KB = SP::KB, NH = SP::HEADS;
+  extern __shared__ __attribute__((aligned(16))) unsigned char plds_raw[];
+  v4u *probs = (v4u *)(plds_raw + SP::PROBS);                   // [2][8][2][64]
+  float *sums = (float *)(plds_raw + SP::SUMS), *refs = (float *)(plds_raw + SP::REFS);   // [2][8][64], [8][64]
+  int *state = (int *)(plds_raw + SP::FLAGS), *moved = state + 16;   // [2][8]: 0 no visible key, 1 scored, 2 out of range; [8]
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave & 3;
+  const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, HG = (G + NH - 1) / NH;
+
+  int id = blockIdx.x;
+  const int kvh = id % Hkv; id /= Hkv;
+  const int hg = id % HG; id /= HG;
+  const int half = id & 1;
+  const int4 item = a.items[id >> 1];
+  const int row_start = item.x + 32 * half, pos_start = item.z + 32 * half, my_rows = min(32, item.y - 32 * half);
+  if (my_rows <= 0) return;                     // the whole workgroup: the item has no second half
+  const bool both = NH * hg + 1 < G;            // the second head exists
+  const int head0 = kvh * G + NH * hg;
+  const bool col_valid = col < my_rows;
+  const int my_pos = pos_start + (col_valid ? col : 0), my_last = pos_start + my_rows - 1;
+  const PPages pages(a, item.w, my_last);
+  const float scale2 = 1.4426950408889634f / sqrtf((float)HD);
+  const uint32_t page_bytes = (uint32_t)Hkv * PPG * HD * 2;
+  const size_t head_off = (size_t)kvh * PPG * HD * 2;
+  int ids = pages.ids(0), ids_next = pages.ids(64);
+  const int n_steps = (pages.n + 1) / 2;
+  // steps whose keys all exist and lie before every row, in the prefix
+  const int n_plain = min(pages.nA, pos_start + 1) / (32 * KB);
+
+  if (wave < 4) {
+    // ---- scores: block kg of every step, for both heads
+    v4u qf[NH][NF], kf[2][NF];
+#pragma unroll
+    for (int x = 0; x < NH; ++x) {
+      const bf16_t *qrow = (const bf16_t *)a.q + ((size_t)(row_start + (col_valid ? col : 0)) * Hq + head0 + (both ? x : 0)) * HD + 8 * h;
+#pragma unroll
+      for (int c = 0; c < NF; ++c) qf[x][c] = *(const v4u *)(qrow + 16 * c);
+    }
+    const char *kA = (const char *)a.k_prefix + head_off + (kg & 1) * NF * 1024 + lane * 16;
+    const char *kB = (const char *)a.k_suffix + head_off + (kg & 1) * NF * 1024 + lane * 16;
+    auto load_k = [&](int step, v4u (&f)[NF]) __attribute__((always_inline)) {
+      const int p0 = 2 * step, pi = p0 + (kg >> 1);
+      if ((p0 & 63) == 0 && p0 > 0) {
+        ids = ids_next;
+        ids_next = pages.ids(p0 + 64);
+      }
+      // a page past the end: the first one again, never used
+      const uint64_t off = (uint64_t)(uint32_t)(pi < pages.n ? __builtin_amdgcn_readlane(ids, pi & 63) : 0) * page_bytes;
+      const char *k = (pi < pages.nPA || pi >= pages.n ? kA : kB) + off;
+#pragma unroll
+      for (int c = 0; c < NF; ++c) f[c] = *(const v4u *)(k + c * 1024);
+    };
+    load_k(0, kf[0]);
+    float m[NH] = {-INFINITY, -INFINITY};
+    auto leave_probs = [&](int buf, int x, const f32x16 &p, float rs) __attribute__((always_inline)) {
+      v4u pb[2];
+      pack_probs(p, pb);
+      v4u *mine = probs + (buf * 8 + kg * NH + x) * 128 + lane;
+      mine[0] = pb[0];
+      mine[64] = pb[1];
+      sums[(buf * 8 + kg * NH + x) * 64 + lane] = rs + other_half(rs);
+    };
+    auto score = [&](const v4u (&f)[NF], int x, f32x16 &s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NF; ++c) s = mfma32p(f[c], qf[x][c], s);
+    };
+    auto step = [&](int st, auto parity) __attribute__((always_inline)) {
+      constexpr int U = decltype(parity)::value;
+      const bool plain = st < n_plain;
+      f32x16 s[NH];
+      int found[NH] = {0, 0};
+      load_k(st + 1, kf[U ^ 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (plain && both && st > 0) {
+        score(kf[U], 0, s[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        score(kf[U], 1, s[1]);
+        float sum[NH];
+        f32x16 p;
+        sum[0] = block_probs(s[0], scale2, m[0], p);
+        leave_probs(U, 0, p, sum[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        sum[1] = block_probs(s[1], scale2, m[1], p);
+        leave_probs(U, 1, p, sum[1]);
+#pragma unroll
+        for (int x = 0; x < NH; ++x) found[x] = leaves_range(sum[x]) ? 2 : 1;
+      } else {
+        int abs0 = 0, nv = 32;
+        bool live = true;
+        if (!plain) {
+          const int pi = 2 * st + (kg >> 1);
+          nv = pages.block(pi, kg & 1, abs0);
+          live = pi < pages.n && nv > 0 && abs0 <= my_last;
+        }
+        if (live) {
+#pragma unroll
+          for (int x = 0; x < NH; ++x) {
+            score(kf[U], x, s[x]);
+            if (!plain) mask_scores(s[x], nv, abs0, pos_start, my_pos, h);
+          }
+        }
+        if (st == 0) {
+          // the first reference is block 0's maximum, as any block finds it that comes first
+          if (kg == 0)
+#pragma unroll
+            for (int x = 0; x < NH; ++x) refs[x * 64 + lane] = moved_reference(s[x], scale2, m[x]);
+          wait_barrier_p<63, true>();
+#pragma unroll
+          for (int x = 0; x < NH; ++x) m[x] = refs[x * 64 + lane];
+        }
+        if (live) {
+#pragma unroll
+          for (int x = 0; x < NH; ++x) {
+            if (x == 1 && !both) break;
+            f32x16 p;
+            const float sum = block_probs(s[x], scale2, m[x], p);
+            found[x] = leaves_range(sum) ? 2 : 1;
+            leave_probs(U, x, p, sum);
+          }
+        }
+      }
+      if (lane < NH) state[U * 8 + kg * NH + lane] = lane ? found[1] : found[0];
+      wait_barrier_p<63, true>();
+      if (__any(state[U * 8 + (lane & 7)] == 2)) {
+        // block by block, the whole workgroup together
+#pragma unroll 1
+        for (int i = 0; i < KB; ++i) {
+          if (kg == i) {
+#pragma unroll
+            for (int x = 0; x < NH; ++x) {
+              if (!found[x]) continue;
+              f32x16 p;
+              float sum = block_probs(s[x], scale2, m[x], p);
+              const bool move = leaves_range(sum);
+              if (move) {
+                const float m_new = moved_reference(s[x], scale2, m[x]);
+                refs[(i * NH + x) * 64 + lane] = m_new;
+                sum = block_probs(s[x], scale2, usable_reference(m_new), p);
+              }
+              leave_probs(U, x, p, sum);
+              if (lane == 0) moved[i * NH + x] = move;
+            }
+          }
+          wait_barrier_p<63, true>();
+#pragma unroll
+          for (int x = 0; x < NH; ++x)
+            if (__builtin_amdgcn_readfirstlane(state[U * 8 + i * NH + x]) && __builtin_amdgcn_readfirstlane(moved[i * NH + x]))
+              m[x] = refs[(i * NH + x) * 64 + lane];
+        }
+      }
+    };
+    for (int st = 0; st < n_steps; st += 2) {
+      step(st, std::integral_constant<int, 0>{});
+      if (st + 1 < n_steps) step(st + 1, std::integral_constant<int, 1>{});
+    }
+    return;
+  }
+
+  // ---- sums: 32 coordinates of both heads (head_dim 64: of one head)
+  constexpr int AH = SP::ADD_HEADS;
+  const int dt = AH == 2 ? kg : kg & 1, x0 = AH == 2 ? 0 : kg >> 1;
+  const char *vA = (const char *)a.v_prefix + head_off + dt * 2048 + lane * 16;
+  const char *vB = (const char *)a.v_suffix + head_off + dt * 2048 + lane * 16;
+  v4u vf[2][KB][2];
+  auto load_v = [&](int step, v4u (&f)[KB][2]) __attribute__((always_inline)) {
+    const int p0 = 2 * step;
+    if ((p0 & 63) == 0 && p0 > 0) {
+      ids = ids_next;
+      ids_next = pages.ids(p0 + 64);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int pi = p0 + i;
+      const uint64_t off = (uint64_t)(uint32_t)(pi < pages.n ? __builtin_amdgcn_readlane(ids, pi & 63) : 0) * page_bytes;
+      const char *v = (pi < pages.nPA || pi >= pages.n ? vA : vB) + off;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) f[2 * i + b][sl] = *(const v4u *)(v + (b * NF + sl) * 1024);
+    }
+  };
+  load_v(0, vf[0]);
+  load_v(1, vf[1]);
+  f32x16 o[AH];
+  float m[AH], l[AH];
+#pragma unroll
+  for (int x = 0; x < AH; ++x) {
+    l[x] = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[x][r] = 0.f;
+  }
+  auto add_block = [&](int buf, int i, int x, const v4u (&f)[2]) __attribute__((always_inline)) {
+    const int at = buf * 8 + i * NH + x0 + x;
+    const v4u p0 = probs[at * 128 + lane], p1 = probs[at * 128 + 64 + lane];
+    l[x] += sums[at * 64 + lane];
+    o[x] = mfma32p(f[0], p0, o[x]);
+    o[x] = mfma32p(f[1], p1, o[x]);
+  };
+  unsigned int lives = 0;                       // of the step to be added; 0: nothing is left of it
+  auto add_step = [&](auto parity) __attribute__((always_inline)) {
+    constexpr int U = decltype(parity)::value;
+    v4u pb[KB][AH][2];
+    float rs[KB][AH];
+#pragma unroll
+    for (int i = 0; i < KB; ++i)
+#pragma unroll
+      for (int x = 0; x < AH; ++x) {
+        const int at = U * 8 + i * NH + x0 + x;
+        pb[i][x][0] = probs[at * 128 + lane];
+        pb[i][x][1] = probs[at * 128 + 64 + lane];
+      }
+#pragma unroll
+    for (int i = 0; i < KB; ++i)
+#pragma unroll
+      for (int x = 0; x < AH; ++x) rs[i][x] = sums[(U * 8 + i * NH + x0 + x) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+    if (lives == 0xFFu) {
+#pragma unroll
+      for (int i = 0; i < KB; ++i)
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+          for (int x = 0; x < AH; ++x) o[x] = mfma32p(vf[U][i][sl], pb[i][x][sl], o[x]);
+#pragma unroll
+      for (int i = 0; i < KB; ++i)
+#pragma unroll
+        for (int x = 0; x < AH; ++x) l[x] += rs[i][x];
+    } else {
+#pragma unroll
+      for (int i = 0; i < KB; ++i)
+#pragma unroll
+        for (int x = 0; x < AH; ++x)
+          if ((lives >> (i * NH + x0 + x)) & 1) {
+            l[x] += rs[i][x];
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl) o[x] = mfma32p(vf[U][i][sl], pb[i][x][sl], o[x]);
+          }
+    }
+  };
+  auto step = [&](int st, auto parity) __attribute__((always_inline)) {
+    constexpr int U = decltype(parity)::value;
+    if (st > 0) {
+      add_step(std::integral_constant<int, U ^ 1>{});
+      load_v(st + 1, vf[U ^ 1]);
+    } else {
+      wait_barrier_p<63, true>();
+#pragma unroll
+      for (int x = 0; x < AH; ++x) m[x] = refs[(x0 + x) * 64 + lane];
+    }
+    wait_barrier_p<63, true>();
+    const int states = state[U * 8 + (lane & 7)];
+    lives = (unsigned int)__ballot(states != 0) & 0xFFu;
+    if (__any(states == 2)) {
+#pragma unroll
+      for (int i = 0; i < KB; ++i) {
+        wait_barrier_p<63, true>();
+#pragma unroll
+        for (int x = 0; x < AH; ++x) {
+          const int e = i * NH + x0 + x;
+          if (!((lives >> e) & 1)) continue;
+          if (__builtin_amdgcn_readfirstlane(moved[e])) {
+            const float m_new = refs[e * 64 + lane], corr = rescale_factor(m[x], m_new);
+            l[x] *= corr;
+            m[x] = m_new;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[x][r] *= corr;
+          }
+          add_block(U, i, x, vf[U][i]);
+        }
+      }
+      lives = 0;
+    }
+  };
+  for (int st = 0; st < n_steps; st += 2) {
+    step(st, std::integral_constant<int, 0>{});
+    if (st + 1 < n_steps) step(st + 1, std::integral_constant<int, 1>{});
+  }
+  if (n_steps & 1) add_step(std::integral_constant<int, 0>{});
+  else add_step(std::integral_constant<int, 1>{});
+  if (col_valid) {
+#pragma unroll
+    for (int x = 0; x < AH; ++x) {
+      if (x0 + x == 1 && !both) break;
+      store_tile<HD>(a, row_start + col, head0 + x0 + x, dt, h, o[x], 1.0f / l[x]);
+    }
   }
 }
 
@@ -625,51 +931,52 @@ bool prefill_attention_mfma_supported(int page_tokens, int head_dim, int Hq, int
   return page_tokens == PPG && (head_dim == 64 || head_dim == 128) && Hq % Hkv == 0;
 }
 
-// workgroups of the form with KS waves per head (1: the whole-item kernel)
-template <int KS>
-static long prefill_grid(const PrefillAttnArgs &a) {
-  const int heads = KS == 1 ? 4 : 8 / KS, G = a.n_q_heads / a.n_kv_heads;
-  return (long)a.n_items * (KS == 1 ? 1 : 2) * a.n_kv_heads * ((G + heads - 1) / heads);
+enum { PREFILL_WHOLE, PREFILL_SPLIT, PREFILL_PAIR };
+
+// workgroups of a form
+template <int HD>
+static long prefill_grid(const PrefillAttnArgs &a, int form) {
+  const int heads = form == PREFILL_PAIR ? PPair<HD>::HEADS : 4, G = a.n_q_heads / a.n_kv_heads;
+  return (long)a.n_items * (form == PREFILL_WHOLE ? 1 : 2) * a.n_kv_heads * ((G + heads - 1) / heads);
 }
 
-template <int HD, int KS>
-static int launch_prefill_t(hipStream_t st, const PrefillAttnArgs &a) {
-  const void *kernel;
-  int lds;
-  if constexpr (KS == 1) {
-    kernel = (const void *)prefill_attention_kernel<HD>;
-    lds = PWhole<HD>::LDS_BYTES + kPrefillMaxPids * (int)sizeof(int);
-  } else {
-    kernel = (const void *)prefill_attention_split_kernel<HD, KS>;
-    lds = PSplit<HD, KS>::LDS_BYTES;
-  }
-  MC_TRY(raise_dynamic_lds_limit(kernel, lds));
-  const unsigned n_main = (unsigned)prefill_grid<KS>(a), n_zero = a.out_tiled == TILED_ZERO ? (a.rows + 255) / 256 : 0;
-  if constexpr (KS == 1) {
-    const size_t pieces = (size_t)padded_rows(a.rows) * a.n_q_heads * HD / 8;
-    if (n_zero && pieces * 16 <= kL2Bytes) zero_rows_kernel<<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((v4u *)a.out, pieces);
-    else if (n_zero) zero_uncovered_rows_kernel<<<n_zero, 512, 0, st>>>(a);
-    prefill_attention_kernel<HD><<<n_main, 512, lds, st>>>(a);
-  } else {
-    prefill_attention_split_kernel<HD, KS><<<n_main + n_zero, 512, lds, st>>>(a, (int)n_main);
-  }
-  MC_HIP(hipGetLastError());
-  return MC_OK;
+// A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a compute
+// unit holds one) leaves units idle, more of them with shorter steps are faster.  All forms give the same bits.  A second round
+// of the pair form, whose step is the shortest for its work, still gains for one sequence, which all its workgroups walk together, and for several
+// behind a long prefix; behind a short one the suffix pages and the fixed part of a workgroup weigh more, and two waves per head or
+// whole items are better.  us, whole items or two waves per head / pairs: one sequence, 8B heads, 560 rows after 512 / 4096 keys 29 / 24, 95 / 86,
+// 800 after 256 27.8 / 23.1, 1000 after 256 / 1024 / 4096 (512 workgroups) 31 / 26, 46 / 38, 103 / 92, heads of 64 24 / 18 after 256, 79 / 62 after 4096;
+// 40 heads, 600 after 4096 117 / 84; several sequences, 5 of 100 after 300 16.0 / 19.5, heads of 64 11.8 / 13.7, 8 of 112 after 1211 33.7 / 36.9, 5 of 150 after
+// 3000 66 / 65, heads of 64 52 / 46; 4 of 400 after 1024 keys (896 workgroups) 50 / 73.
+template <int HD>
+static int prefill_form(const PrefillAttnArgs &a) {
+  constexpr long kComputeUnits = 256;
+  const long pairs = prefill_grid<HD>(a, PREFILL_PAIR);
+  const bool shared = a.page_table == nullptr || a.prefix_len >= kPairSharedKeys;
+  if (pairs <= (shared ? 2 : 1) * kComputeUnits) return PREFILL_PAIR;
+  return prefill_grid<HD>(a, PREFILL_SPLIT) <= kComputeUnits ? PREFILL_SPLIT : PREFILL_WHOLE;
 }
 
 template <int HD>
 static int launch_prefill_hd(hipStream_t st, const PrefillAttnArgs &a) {
-  // A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a compute
-  // unit holds one) leaves units idle, more of them with shorter steps are faster; a second round costs more
-  // than the split gains.  All forms give the same bits.  8B heads, one sequence, us with 1 / 2 / 4 waves per
-  // head: 65 rows after 256 keys 16 / 12.7 / 10.3, after 1024 33 / 26 / 18, after 4096 103 / 83 / 48; 300 rows after
-  // 256 keys 21 / 17.5 / 13, after 1024 38 / 31 / 21, after 4096 108 / 86 / 51; 512 rows (256 workgroups with
-  // four waves) after 4096 keys 113 / 91 / 55, 800 rows 119 / 97 / 106, 1000 rows (256 with two) after 256 keys
-  // 37 / 32 / 33, after 4096 124 / 103 / 112; four sequences of 400 rows after 1024 keys 45 / 63 / 73.
-  constexpr long kComputeUnits = 256;
-  if (prefill_grid<4>(a) <= kComputeUnits) return launch_prefill_t<HD, 4>(st, a);
-  if (prefill_grid<2>(a) <= kComputeUnits) return launch_prefill_t<HD, 2>(st, a);
-  return launch_prefill_t<HD, 1>(st, a);
+  const int form = prefill_form<HD>(a);
+  const unsigned n_main = (unsigned)prefill_grid<HD>(a, form), n_zero = a.out_tiled == TILED_ZERO ? (a.rows + 255) / 256 : 0;
+  if (form == PREFILL_PAIR) {
+    MC_TRY(raise_dynamic_lds_limit((const void *)prefill_attention_pair_kernel<HD>, PPair<HD>::LDS_BYTES));
+    prefill_attention_pair_kernel<HD><<<n_main + n_zero, 512, PPair<HD>::LDS_BYTES, st>>>(a, (int)n_main);
+  } else if (form == PREFILL_SPLIT) {
+    MC_TRY(raise_dynamic_lds_limit((const void *)prefill_attention_split_kernel<HD>, PSplit<HD>::LDS_BYTES));
+    prefill_attention_split_kernel<HD><<<n_main + n_zero, 512, PSplit<HD>::LDS_BYTES, st>>>(a, (int)n_main);
+  } else {
+    const int lds = PWhole<HD>::LDS_BYTES + kPrefillMaxPids * (int)sizeof(int);
+    MC_TRY(raise_dynamic_lds_limit((const void *)prefill_attention_kernel<HD>, lds));
+    const size_t pieces = (size_t)padded_rows(a.rows) * a.n_q_heads * HD / 8;
+    if (n_zero && pieces * 16 <= kL2Bytes) zero_rows_kernel<<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((v4u *)a.out, pieces);
+    else if (n_zero) zero_uncovered_rows_kernel<<<n_zero, 512, 0, st>>>(a);
+    prefill_attention_kernel<HD><<<n_main, 512, lds, st>>>(a);
+  }
+  MC_HIP(hipGetLastError());
+  return MC_OK;
 }
 
 int launch_attention_prefill_mfma(hipStream_t st, const PrefillAttnArgs &a) {

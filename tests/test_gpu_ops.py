@@ -1158,3 +1158,35 @@ def test_prefill_attention_zeroes_the_rows_that_no_item_covers(Hq, hd, lens):
     assert not out.isnan().any() and not _padding_of(out, rows, Hq * hd).any() and not plain[holes].any()
     keep = [r for r in range(rows) if r not in set(holes)]
     assert torch.equal(plain[keep], run(False).reshape(rows, -1)[keep])
+
+
+@pytest.mark.parametrize("Hq,Hkv,hd,P,rows", [(5, 1, 128, 64, 33), (40, 8, 128, 129, 70), (2, 2, 64, 1, 40), (3, 1, 64, 191, 64), (8, 2, 128, 2049, 5),
+                                              (32, 8, 64, 2113, 64)])
+def test_attention_prefill_pairs_of_heads(Hq, Hkv, hd, P, rows):
+    """Workgroups of two heads with scoring and adding waves: odd and single heads per group, one page, odd and even page counts,
+    steps that end among masked blocks.  A sequence alone (those workgroups) has the bits that it has among many (whole
+    items), where a key that outgrows the reference stands in its suffix."""
+    import torch
+    n = -(-1100 // (2 * -(-Hq // Hkv // 2) * Hkv))
+    pg, per, n_pre = 64, -(-rows // 64), -(-P // 64)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31 * P + Hq)
+    normal = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)  # noqa: E731
+    kp, vp = binding.kv_pages_pack(normal(n_pre, Hkv, pg, hd), normal(n_pre, Hkv, pg, hd))
+    k = normal(n * per, Hkv, pg, hd)
+    k[:, :, 3] *= 8
+    ks, vs = binding.kv_pages_pack(k, normal(n * per, Hkv, pg, hd))
+    table = torch.randperm(n * per, generator=g, device="cuda").to(torch.int32).reshape(n, per)
+    q = normal(n * rows, Hq, hd) * 2
+
+    def score(seqs):
+        items = [[i * rows + j, min(64, rows - j), P + j, c] for i, c in enumerate(seqs) for j in range(0, rows, 64)]
+        rq = torch.cat([q[c * rows: (c + 1) * rows] for c in seqs])
+        out = binding.op_attention_prefill(rq, torch.tensor(items, dtype=torch.int32, device="cuda"), kp, vp, ks, vs, table, P, pg)
+        return out.view(torch.int16).reshape(len(seqs), rows, Hq, hd)
+
+    print("case: prefill pairs of heads", Hq, Hkv, hd, P, rows, n, flush=True)
+    full = score(list(range(n)))
+    assert not torch.isnan(full.view(torch.bfloat16)).any()
+    for seqs in ([n // 2], [0, n - 1]):
+        assert torch.equal(score(seqs), score(seqs)) and torch.equal(score(seqs), full[seqs])
