@@ -4,7 +4,7 @@
 //
 // A workgroup of 4 waves owns 256 rows of a and 128 rows of w (64 of wg and of wu in the SwiGLU
 // form); a wave keeps 8 accumulator tiles of 32 x 32 (its own 64 rows of a x all 128 rows of w).  Few
-// tiles take other shapes, a wave then owning 32 rows of a: 64, 96 or 128 rows of a (2 to 4 waves) and 128, 64
+// tiles take other shapes, a wave then mostly owning 32 rows of a: 64, 96, 128, 192 or 256 rows of a (2 to 6 waves) and 128, 64
 // or 32 rows of w, or 320 and 384 rows (10 and 12 waves) and 64 of wg and of wu (see plain_form and swiglu_form);
 // an output's sum runs over K in the same order in all of them, so they give the same bits.
 // Two workgroups share a CU (two waves per SIMD, 232 registers each): they run out of step, so
@@ -34,7 +34,7 @@
 // HBM and activations from L2 (110 to 130 GB/s where L2 has everything).  A unit of a tile of RT x CT blocks costs
 // 4 KB (RT + CT) of that, whatever there is to multiply: taking the MFMAs, the barriers or the LDS look-ahead out
 // changes nothing, nor do operands four or eight units ahead, so the rules below look for few operand bytes
-// per compute unit, not for deep pipelines.
+// per compute unit, not for deep pipelines; asking for the weights of four units at once (B) does help.
 // At 8192 rows the part is at its power limit (the matrix pipes are 81 % busy at a lowered clock),
 // and variants that differ in barrier scope or fragment look-ahead land on the same rate.
 //
@@ -217,8 +217,13 @@ constexpr int weight_pieces(int blocks, int waves) {
 }
 
 // TM: 32-row tiles of a per wave; TN: 32-row tiles of each weight matrix per workgroup; D: units by which
-// the operands run ahead; WV: waves; NT: w's lines are read by this workgroup only and need not stay in L2.
-template <int MODE, int TM, int TN, int D, int WV, bool NT>
+// the operands run ahead; WV: waves; NT: w's lines are read by this workgroup only and need not stay in L2; B: 0, or the
+// units (a multiple of D) whose weights are asked for at once, at the start of the B units before them, where otherwise every unit
+// asks for one.  A wave's loads return in order, so an activation fragment that L2 has waits for every weight load
+// from HBM before it; in bursts that wait comes once per B units.  Gains where the compute units' load path is full: 500 x
+// 4096 x 14336 by 128 x 64 85 -> 76 us, 300 x 5120 x 27648 165 -> 140, 1000 x 4096 x 14336 by 256 x 64 142 -> 119; eight units at once are no better, and
+// the SwiGLU form loses (300 x 14336 x 4096 by 320 rows 75 -> 88).
+template <int MODE, int TM, int TN, int D, int WV, bool NT, int B>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(WV > 8 ? 3 : 2, WV > 8 ? 3 : 2)))
 void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const bf16_t *__restrict__ a,
                     const bf16_t *__restrict__ w, const bf16_t *__restrict__ w2,
@@ -231,7 +236,7 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
   constexpr int NBW = NW * WB;             // weight blocks of 256 chunks per unit
   constexpr int PW = weight_pieces(NBW, WV), LW = 4 * NBW / PW;    // 1 KB pieces of w per unit and wave, waves that bring them
   constexpr bool kEven = 4 % WV == 0;      // a load's waves bring neighbouring pieces of a block that is known here
-  constexpr int S = D + 2;                 // LDS stages of one unit each
+  constexpr int S = B ? 2 * B : D + 2;     // LDS stages of one unit each
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_lds[];
   v4u *lds = (v4u *)gemm_lds;              // [S][NBW][256], then 1 KB where waves that bring no weights let their empty loads land
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
@@ -303,7 +308,7 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
 
   v4u fw[2][WT];
 #pragma unroll
-  for (int d = 0; d <= D; ++d) load_w(d, d);
+  for (int d = 0; d < (B ? B : D + 1); ++d) load_w(d, d);
 #pragma unroll
   for (int d = 0; d < D; ++d)
 #pragma unroll
@@ -317,10 +322,15 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
   // which every wave left before the barrier that ended it.  At the barrier that ends unit u
   // everything older than the fragments of a for unit u + 1 has landed: the weights of unit u + 2,
   // issued just before them, among it.
+  // In bursts: the stages that take units u + B .. u + 2 B - 1, u a multiple of B, were last read in the B units before u, and the
+  // burst has to have landed at the barrier that ends unit u + B - 2, the loads of a since then not.
   int cur = 0;
-  auto unit = [&](int u, int slot) __attribute__((always_inline)) {
+  auto unit = [&](int u, int slot, int b) __attribute__((always_inline)) {
     const int nxt = cur == S - 1 ? 0 : cur + 1;
-    load_w(u + D + 1, cur == 0 ? S - 1 : cur - 1);
+    if (B == 0) load_w(u + D + 1, cur == 0 ? S - 1 : cur - 1);
+    else if (b == 0)
+#pragma unroll
+      for (int i = 0; i < B; ++i) load_w(u + B + i, (cur + B + i) % S);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -338,14 +348,17 @@ void gemm256_kernel(int M, int Mw, int N, int K, int tiles_m, int tiles_n, const
       __builtin_amdgcn_sched_group_barrier(0x020, TM, 0);     // the loads of a
       __builtin_amdgcn_sched_barrier(0);
     }
-    wait_barrier<4 * TM + (D - 1) * (PW + 4 * TM)>();
+    if (B == 0) wait_barrier<4 * TM + (D - 1) * (PW + 4 * TM)>();
+    else if (b == B - 2) wait_barrier<B ? (B - 1) * 4 * TM : 0>();
+    else wait_barrier<63>();
     cur = nxt;
   };
   int u = 0;
-  do {                                     // U is a multiple of D
+  constexpr int kGroup = B ? B : D;
+  do {                                     // U is a multiple of kGroup
 #pragma unroll
-    for (int d = 0; d < D; ++d) unit(u + d, d);
-    u += D;
+    for (int d = 0; d < kGroup; ++d) unit(u + d, d % D, d);
+    u += kGroup;
   } while (u < U);
   wait_barrier<0>();                         // no load into LDS outlives the loop
 
@@ -448,7 +461,7 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
 }
 
 // Plain products: rows per workgroup (64: two waves, 128: four, 256: four with two row tiles each) and weight tiles per
-// workgroup.  The first form of this list with which one round (a workgroup to each of the 256 compute units) covers
+// workgroup.  The first form of the list with which one round (a workgroup to each of the 256 compute units) covers
 // the product, else the 256 x 128 tile, which moves the fewest operand bytes per flop; up to 128 rows at least not its
 // empty half.  A workgroup is a serial chain over K whose pace is set by its loads, so the list goes by the
 // operand bytes per unit: 64 x 32, 128 x 32, 64 x 64, 128 x 64, 128 x 128.  But for one place: 128 x 32 takes five blocks of 4 KB and
@@ -465,14 +478,26 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
 // more it is slower: 2048 x 12288, 576 rows (160 and 192) 57 / 61, 641 rows (192 and 224) 55 / 61; 3072 x 16384, 448 rows (192 and 240)
 // 78 / 78; 4096 x 14336, 288 rows (192 both) 66 / 75.  So it is over a short K (2048 x 8192, 768 rows 35 / 36; 4096 x 4096, 384 rows
 // 20 / 21); between 8192 and 12288 nothing was measured.
-struct GemmForm { int waves, tm, tn; };
+// Weights in bursts (see the kernel): 128 x 64 from K = 2048 on where the row tiles are full to seven eighths, and from K = 4096 on two more forms ahead of 128 x 128,
+// 192 x 64 and 256 x 64, the latter where it has no more rows to spare than 128 x 128.  us, 128 x 64 unit by unit / in bursts: 4096 x 14336, 450 rows 80 / 72, 512 rows
+// 87 / 77, 300 rows 70 / 72; 6144 x 4096 with the rotary epilogue, 300 rows (three row tiles of 96 columns) 40 / 38 and 384 rows 45 / 38 by 192 x 64 (128 x 128 before);
+// 2048 x 2048, 1000 rows 16.5 / 15.5; 400 of 512 rows x 2048 x 8192 39 / 40; K = 256, 512 rows x 4096 7.3 / 7.6.  128 x 128 / 192 x 64: 4096 x 14336, 600 rows 115 / 100, 768 rows 126 / 105;
+// 2048 x 8192, 1100 rows 68 / 58, 1500 rows 69 / 62; 5120 x 5120, 500 rows 49 / 41; K = 2048, 600 rows x 4096 17.9 / 19.8, 1500 rows x 2048 21 / 22.  128 x 128 / 256 x 64:
+// 4096 x 14336, 1000 rows 130 / 119, 800 rows (seven row tiles or four) 102 / 111; 4096 x 4096, 1000 rows 43 / 40; 3072 x 2048, 1000 rows 26 / 27.
+struct GemmForm { int waves, tm, tn; bool burst = false; };
 constexpr long kComputeUnits = 256;
 static GemmForm plain_form(int M, int N, int K) {
-  for (const GemmForm f : {GemmForm{2, 1, 1}, GemmForm{4, 1, 1}, GemmForm{2, 1, 2}, GemmForm{4, 1, 2}, GemmForm{4, 1, 4}}) {
-    const long row_tiles = (M + 32 * f.waves - 1) / (32 * f.waves);
+  for (const GemmForm f : {GemmForm{2, 1, 1}, GemmForm{4, 1, 1}, GemmForm{2, 1, 2}, GemmForm{4, 1, 2}, GemmForm{6, 1, 2, true}, GemmForm{4, 2, 2, true},
+                           GemmForm{4, 1, 4}}) {
+    const int rows = 32 * f.waves * f.tm;
+    const long row_tiles = (M + rows - 1) / rows;
     if (row_tiles * (N / 32) / f.tn > kComputeUnits) continue;
-    const long by_96 = (M + 95) / 96;
-    if (f.waves == 4 && f.tn == 2 && K >= 12288 && 3 * by_96 >= 4 * row_tiles && by_96 * (N / 64) <= kComputeUnits) return GemmForm{3, 1, 2};
+    if (f.burst && (K < 4096 || (f.tm == 2 && 2 * row_tiles > (M + 127) / 128))) continue;
+    if (f.waves == 4 && f.tm == 1 && f.tn == 2) {
+      const long by_96 = (M + 95) / 96;
+      if (K >= 12288 && 3 * by_96 >= 4 * row_tiles && by_96 * (N / 64) <= kComputeUnits) return GemmForm{3, 1, 2};
+      return GemmForm{4, 1, 2, K >= 2048 && 8L * M > 7L * 128 * row_tiles};
+    }
     return f;
   }
   return GemmForm{4, M <= 128 ? 1 : 2, 4};
@@ -512,17 +537,17 @@ void gemm256_plan(int M, int N, int K, bool swiglu, int32_t *out3) {
   out3[2] = (M + out3[0] - 1) / out3[0] * (N / out3[1]);
 }
 
-template <int MODE, int TM, int TN, int D, int WV, bool NT = false>
+template <int MODE, int TM, int TN, int D, int WV, bool NT = false, int B = 0>
 static int launch_gemm256_t(hipStream_t st, int M, int Mw, int N, int K, const bf16_t *a, const bf16_t *w,
                             const bf16_t *w2, float *out, bf16_t *out_t, const RopeOut &ro) {
   const int tiles_m = (M + 32 * WV * TM - 1) / (32 * WV * TM), tiles_n = N / (32 * TN);
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  // D + 2 stages of the unit's weight blocks and a place for empty loads; the parking areas of the rotation epilogue may need more
+  // the stages of the unit's weight blocks and a place for empty loads; the parking areas of the rotation epilogue may need more
   constexpr int NBW = TN * (MODE == GEMM_SWIGLU ? 2 : 1);
-  const int lds = std::max<int>((D + 2) * NBW * 4096 + (weight_pieces(NBW, WV) * WV > 4 * NBW ? 1024 : 0),
+  const int lds = std::max<int>((B ? 2 * B : D + 2) * NBW * 4096 + (weight_pieces(NBW, WV) * WV > 4 * NBW ? 1024 : 0),
                                 MODE == GEMM_ROPE ? WV * 32 * kParkStride * (int)sizeof(float) : 0);
-  MC_TRY(raise_dynamic_lds_limit((const void *)gemm256_kernel<MODE, TM, TN, D, WV, NT>, lds));
-  gemm256_kernel<MODE, TM, TN, D, WV, NT><<<8 * per_xcd, 64 * WV, lds, st>>>(M, Mw, N, K, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
+  MC_TRY(raise_dynamic_lds_limit((const void *)gemm256_kernel<MODE, TM, TN, D, WV, NT, B>, lds));
+  gemm256_kernel<MODE, TM, TN, D, WV, NT, B><<<8 * per_xcd, 64 * WV, lds, st>>>(M, Mw, N, K, tiles_m, tiles_n, a, w, w2, out, out_t, ro);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }
@@ -551,11 +576,14 @@ int launch_gemm256(hipStream_t st, int M, int N, int K, const void *a, const voi
       if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       return launch_gemm256_t<MODE, 1, 1, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
     } else {
-      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 4, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.tm == 2 && f.tn == 4) return launch_gemm256_t<MODE, 2, 4, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.tm == 2) return launch_gemm256_t<MODE, 2, 2, 2, 4, false, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.waves == 6) return launch_gemm256_t<MODE, 1, 2, 4, 6, false, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.waves == 3) return launch_gemm256_t<MODE, 1, 2, 4, 3>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.tn == 4) return launch_gemm256_t<MODE, 1, 4, 2, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.waves == 2 && f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4, 2>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.waves == 2) return launch_gemm256_t<MODE, 1, 1, 4, 2>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
+      if (f.tn == 2 && f.burst) return launch_gemm256_t<MODE, 1, 2, 4, 4, false, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       if (f.tn == 2) return launch_gemm256_t<MODE, 1, 2, 4, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
       return launch_gemm256_t<MODE, 1, 1, 4, 4>(st, M, Mw, N, K, A, W, W2, out, OT, ro);
     }

@@ -744,6 +744,14 @@ def test_many_row_gemm_forms_give_the_same_bits(N, K, Hq, Hkv, rows, forms):
             assert torch.equal(x, z[:M]), (name, M)
 
 
+def test_gemm_weights_in_bursts():
+    """The forms that ask for the weights of four units at once (128, 192 and 256 rows x 64 columns), full and ragged, and the ones beside
+    them: the bits of the 256 x 128 workgroups in every output form, over a K that is several bursts and over one that is just long enough."""
+    test_many_row_gemm_forms_give_the_same_bits(4096, 4096, 16, 8, (449, 512, 520, 768, 1000, 3000),
+                                                ((128, 64), (128, 64), (192, 64), (192, 64), (256, 64), (256, 128)))
+    test_many_row_gemm_forms_give_the_same_bits(2048, 2304, 8, 4, (1000, 1100, 5000), ((128, 64), (128, 128), (256, 128)))
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 8192, 256), (129, 4096, 512), (65, 5120, 256), (129, 5120, 768), (192, 5120, 256), (193, 5120, 256)])
 def test_linear_64_row_workgroups(M, N, K):
     """GEMM workgroups of two waves (64 rows x 32 or 64 columns): full and ragged last workgroups, the last row
