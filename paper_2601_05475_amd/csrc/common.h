@@ -203,8 +203,7 @@ int launch_pack_tiled(hipStream_t st, int rows, int K, const void *src, void *ds
 // cos / sin of pos * base^(-2i/hd) in double for pos < n_pos, i < hd / 2: table[pos * hd/2 + i]
 int launch_rope_table(hipStream_t st, int n_pos, int hd, double rope_base, double2 *table);
 
-// Where the fused QKV layer puts its result (few-row bf16 path): rotated queries, and keys /
-// values straight into their page slots.
+// Where a fused QKV layer puts its result: rotated queries, and keys / values straight into their page slots.
 struct RopeOut {
   const int32_t *row_pos, *row_page, *row_off;   // device, per row
   void *q_out, *k_pages, *v_pages;
@@ -232,6 +231,13 @@ int launch_rope_kv(hipStream_t st, int dtype, int rows, int Hq, int Hkv, int hd,
                    double rope_base, const float *qkv, int n_splits, const int32_t *row_pos,
                    const int32_t *row_page, const int32_t *row_off, void *q_out, void *k_pages,
                    void *v_pages, const double2 *table = nullptr, int qk_interleaved = 0);
+// Few rows of models that are not tiled: the norm inside the layer behind it (x: the fp32 residual stream, not changed), the
+// QKV layer with the rotation and the stores, products that add to x.  few_rows_fused_ok: the shapes that all of them take.
+bool few_rows_fused_ok(int dtype, int rows, int d, int n_qkv, int qd, int F, int vocab, int head_dim);
+int launch_norm_qkv_rope_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *w, const RopeOut &ro);
+int launch_norm_swiglu_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *wg, const void *wu, void *out);
+int launch_norm_linear_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *w, float *out);
+int launch_accumulate_few(hipStream_t st, int dtype, int M, int N, int K, const void *a, const void *w, float *x);
 int launch_attention_generic(hipStream_t st, int dtype, const AttnArgs &a);
 size_t decode_attention_ws_bytes(int n_cands, int Hq, int Hkv, int hd, int prefix_len,
                                  int suffix_len, int page_tokens);

@@ -509,6 +509,165 @@ static void launch_few_rows(hipStream_t st, int M, int N, int K, int kps, int n_
   else linear_few_rows_kernel<T, SWIGLU, 8><<<grid, 256, 0, st>>>(M, N, K, kps, A, W, W2, out, (T *)out_t);
 }
 
+// Whole layers of few rows: the norm inside the product behind it, the QKV layer with rotation and stores, products that add to the
+// residual stream.  A layer is then five launches (norm + QKV + rotary, attention, output projection, norm + SwiGLU, down projection) where it was
+// eight.  As above a wave takes an output column (two for SwiGLU and for a rotary pair), with P pieces of 16 bytes of K per lane, all asked for at
+// once.  NORM: a is fp32 x, and the operand is x * gain / sqrt(mean(x^2) + eps) rounded to the model's type; every wave takes the mean itself:
+// rows of this path are a few KB, whose sum is a wave's shuffles away, where a norm launch takes 2.5 us and the gap before it.  What bounds the
+// kernels is the launch and one trip to memory.
+// 16 steps of the two-layer fp32 model (4 candidates, d 256, F 688, vocabulary 4096, pages of 4, every token read by the host): 19 launches a step -> 13,
+// 73 -> 67 us in kernels, 1745 -> 1460 us in all.  Two loads deep over K in place of all at once: 1480.
+// FEW_ROPE: a wave takes the members i and i + hd / 2 of a query or key head, or two coordinates of a value head.
+enum { FEW_STORE = 0, FEW_SWIGLU = 1, FEW_ROPE = 2, FEW_ACCUM = 3 };
+template <typename T, int MODE, bool NORM, int MR, int P>
+__global__ __launch_bounds__(256) void few_rows_fused_kernel(int M, int N, int K, const void *__restrict__ a, const T *__restrict__ gain, float eps,
+                                                             const T *__restrict__ w, const T *__restrict__ w2, float *__restrict__ out,
+                                                             T *__restrict__ out_t, RopeOut ro) {
+  constexpr int V = Vec16<T>::N;
+  constexpr bool TWO = MODE == FEW_SWIGLU || MODE == FEW_ROPE;           // two weight rows per wave
+  const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6), m0 = blockIdx.y * MR;
+  if (n >= (MODE == FEW_ROPE ? N / 2 : N)) return;
+  const T *wr = w + (size_t)n * K, *ur = TWO ? w2 + (size_t)n * K : nullptr;
+  int head = 0, i = 0, slot = 0, page = 0;
+  double2 turn = {1.0, 0.0};
+  if (MODE == FEW_ROPE) {
+    const int half = ro.hd >> 1, row = min(m0 + (lane & (MR - 1)), M - 1);      // the row that this lane will store
+    head = n / half;
+    i = n % half;
+    const bool turned = head < ro.Hq + ro.Hkv;
+    wr = w + ((size_t)head * ro.hd + (turned ? i : 2 * i)) * K;
+    ur = wr + (size_t)(turned ? half : 1) * K;
+    slot = ro.row_off[row];
+    page = ro.row_page[row];
+    if (turned) turn = ro.table[(size_t)ro.row_pos[row] * half + i];
+  }
+  // pieces past K: the last one again, with weights of zero
+  float av[MR][P][V], wv[P][V], uv[P][V], gv[P][V];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int k = min((p * 64 + lane) * V, K - V);
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      const size_t at = (size_t)min(m0 + m, M - 1) * K + k;
+      if (NORM) {
+#pragma unroll
+        for (int j = 0; j < V; j += 4) Vec16<float>::load((const float *)a + at + j, av[m][p] + j);
+      } else {
+        Vec16<T>::load((const T *)a + at, av[m][p]);
+      }
+    }
+    Vec16<T>::load(wr + k, wv[p]);
+    if (TWO) Vec16<T>::load(ur + k, uv[p]);
+    if (NORM) Vec16<T>::load(gain + k, gv[p]);
+  }
+  if (NORM) {
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      float ss = 0.f;
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int j = 0; j < V; ++j) ss = (p * 64 + lane) * V < K ? fmaf(av[m][p][j], av[m][p][j], ss) : ss;
+      const float inv = 1.0f / sqrtf(wave_sum(ss) / (float)K + eps);
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int j = 0; j < V; ++j) av[m][p][j] = Cvt<T>::to_f32(Cvt<T>::from_f32(av[m][p][j] * inv * gv[p][j]));
+    }
+  }
+  float acc[MR] = {}, acc2[MR] = {};
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if ((p * 64 + lane) * V < K)
+#pragma unroll
+      for (int m = 0; m < MR; ++m)
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+          acc[m] += av[m][p][j] * wv[p][j];
+          if (TWO) acc2[m] += av[m][p][j] * uv[p][j];
+        }
+#pragma unroll
+  for (int m = 0; m < MR; ++m) {
+    acc[m] = wave_sum(acc[m]);
+    if (TWO) acc2[m] = wave_sum(acc2[m]);
+  }
+#pragma unroll
+  for (int m = 0; m < MR; ++m) {
+    if (lane != m || m0 + m >= M) continue;
+    const float g = acc[m];
+    if (MODE == FEW_SWIGLU) {
+      out_t[(size_t)(m0 + m) * N + n] = Cvt<T>::from_f32(g / (1.0f + expf(-g)) * acc2[m]);
+    } else if (MODE == FEW_ACCUM) {
+      out[(size_t)(m0 + m) * N + n] += g;
+    } else if (MODE == FEW_STORE) {
+      out[(size_t)(m0 + m) * N + n] = g;
+    } else {
+      const int hd = ro.hd, half = hd >> 1;
+      const size_t at = (size_t)page * ro.Hkv * hd * ro.pg;
+      const double lo = g, hi = acc2[m];
+      if (head < ro.Hq + ro.Hkv) {
+        const bool query = head < ro.Hq;
+        T *dst = query ? (T *)ro.q_out + ((size_t)(m0 + m) * ro.Hq + head) * hd : (T *)ro.k_pages + at + (size_t)(head - ro.Hq) * ro.pg * hd;
+        dst[query ? (size_t)i : k_elem_offset(slot, i, ro.pg, hd)] = Cvt<T>::from_f32((float)(lo * turn.x - hi * turn.y));
+        dst[query ? (size_t)(i + half) : k_elem_offset(slot, i + half, ro.pg, hd)] = Cvt<T>::from_f32((float)(hi * turn.x + lo * turn.y));
+      } else {
+        T *dst = (T *)ro.v_pages + at + (size_t)(head - ro.Hq - ro.Hkv) * ro.pg * hd;
+        dst[v_elem_offset(slot, 2 * i, ro.pg, hd)] = Cvt<T>::from_f32(g);
+        dst[v_elem_offset(slot, 2 * i + 1, ro.pg, hd)] = Cvt<T>::from_f32(acc2[m]);
+      }
+    }
+  }
+}
+
+// Where every product of the model goes by columns as it stands and K is at most 1024: above, the mean that each wave takes and a K that is
+// not split over workgroups cost more.
+constexpr int kFusedMostK = 1024;
+bool few_rows_fused_ok(int dtype, int rows, int d, int n_qkv, int qd, int F, int vocab, int head_dim) {
+  if (head_dim % 2 || std::max(d, std::max(qd, F)) > kFusedMostK) return false;
+  // (the operands are rows of the model's and the session's arenas, aligned for 16-byte loads)
+  auto ok = [&](int N, int K, bool swiglu) { return few_rows_ok(dtype, rows, N, K, K, 1, nullptr, nullptr, swiglu ? (const void *)16 : nullptr); };
+  return ok(n_qkv, d, false) && ok(d, qd, false) && ok(F, d, true) && ok(d, F, false) && ok(vocab, d, false);
+}
+
+template <typename T, int MODE, bool NORM>
+static void launch_few_fused_t(hipStream_t st, int M, int N, int K, const void *a, const void *gain, float eps, const void *w, const void *w2,
+                               float *out, void *out_t, const RopeOut &ro) {
+  const int mr = M <= 4 ? 4 : 8, columns = MODE == FEW_ROPE ? N / 2 : N, pieces = (K + 64 * Vec16<T>::N - 1) / (64 * Vec16<T>::N);
+  const dim3 grid((columns + 3) / 4, (M + mr - 1) / mr);
+  auto go = [&](auto p) {
+    constexpr int P = decltype(p)::value;
+    if (mr == 4)
+      few_rows_fused_kernel<T, MODE, NORM, 4, P><<<grid, 256, 0, st>>>(M, N, K, a, (const T *)gain, eps, (const T *)w, (const T *)w2, out, (T *)out_t, ro);
+    else
+      few_rows_fused_kernel<T, MODE, NORM, 8, P><<<grid, 256, 0, st>>>(M, N, K, a, (const T *)gain, eps, (const T *)w, (const T *)w2, out, (T *)out_t, ro);
+  };
+  if (pieces <= 1) go(std::integral_constant<int, 1>{});
+  else if (pieces <= 2) go(std::integral_constant<int, 2>{});
+  else if constexpr (sizeof(T) == 4) go(std::integral_constant<int, kFusedMostK / 256>{});
+}
+
+template <int MODE, bool NORM>
+static int launch_few_fused(hipStream_t st, int dtype, int M, int N, int K, const void *a, const void *gain, float eps, const void *w,
+                            const void *w2, float *out, void *out_t, const RopeOut &ro) {
+  if (K > kFusedMostK) MC_FAIL(MC_ERR_UNSUPPORTED, "fused layers of few rows: K = %d", K);
+  if (dtype == MC_F32) launch_few_fused_t<float, MODE, NORM>(st, M, N, K, a, gain, eps, w, w2, out, out_t, ro);
+  else launch_few_fused_t<bf16_t, MODE, NORM>(st, M, N, K, a, gain, eps, w, w2, out, out_t, ro);
+  MC_HIP(hipGetLastError());
+  return MC_OK;
+}
+int launch_norm_qkv_rope_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *w, const RopeOut &ro) {
+  return launch_few_fused<FEW_ROPE, true>(st, dtype, M, N, K, x, gain, eps, w, nullptr, nullptr, nullptr, ro);
+}
+int launch_norm_swiglu_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *wg, const void *wu, void *out) {
+  return launch_few_fused<FEW_SWIGLU, true>(st, dtype, M, N, K, x, gain, eps, wg, wu, nullptr, out, RopeOut{});
+}
+int launch_norm_linear_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *w, float *out) {
+  return launch_few_fused<FEW_STORE, true>(st, dtype, M, N, K, x, gain, eps, w, nullptr, out, nullptr, RopeOut{});
+}
+int launch_accumulate_few(hipStream_t st, int dtype, int M, int N, int K, const void *a, const void *w, float *x) {
+  return launch_few_fused<FEW_ACCUM, false>(st, dtype, M, N, K, a, nullptr, 0.f, w, nullptr, x, nullptr, RopeOut{});
+}
+
 int launch_linear_generic(hipStream_t st, int dtype, int M, int N, int K, const void *a,
                           const void *w, float *out, int n_splits) {
   if (M <= 0 || N <= 0) return MC_OK;

@@ -456,6 +456,13 @@ struct LastRows {
   int n, n_items;
 };
 
+// Few rows of a model that is not tiled: the norms run inside the layers behind them, the projections add to the residual stream
+static bool few_rows_fused(const mc_session *s, int rows) {
+  const mc_config &c = s->m->cfg;
+  return !s->m->tiled && norm_vec_ok(c.d_model) &&
+         few_rows_fused_ok(c.dtype, rows, c.d_model, s->m->n_qkv, c.n_q_heads * c.head_dim, c.d_ffn, c.vocab, c.head_dim);
+}
+
 // Run all layers on `rows` rows whose metadata (token, position, KV slot, table row) is on the
 // device already.  prefix_visible: number of prefix keys that exist (for PASS_PREFIX: the end of
 // this chunk).  Leaves the last down-projection's partial sums in `part` (n returned in *tail).
@@ -478,6 +485,7 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
                 *row_off = s->ptr<int32_t>(L.row_off), *row_tab = s->ptr<int32_t>(L.row_tab);
   const int tl = m->tiled;
   const bool embed_norm = norm_vec_ok(d);
+  const bool few = few_rows_fused(s, rows);
   if (!embed_norm) {
     ProfScope ps(s, MC_K_EMBED);
     if (step) MC_TRY(launch_decode_rows(st, rows, *step, s->ptr<int32_t>(L.row_tok)));
@@ -501,7 +509,7 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
     if (l == 0 && embed_norm) {
       ProfScope pe(s, MC_K_EMBED), ps(s, MC_K_ADD_RMSNORM);          // one launch is both
       MC_TRY(launch_embed_rmsnorm(st, dt, rows, d, s->ptr<int32_t>(L.row_tok), step, m->embed, x, W.attn_norm, c.rms_eps, h, tl));
-    } else {
+    } else if (!few) {
       ProfScope ps(s, MC_K_ADD_RMSNORM);
       MC_TRY(launch_add_rmsnorm(st, dt, rows, d, x, part, pending, W.attn_norm, c.rms_eps, h, tl));
     }
@@ -520,14 +528,19 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
     else if (pass == PASS_DECODE || pass == PASS_SUFFIX) { kdst = kl + prefix_bytes; vdst = vl + prefix_bytes; }
     else { kdst = s->ptr<void>(L.kscr); vdst = s->ptr<void>(L.vscr); }
     const double2 *rope_tab = s->ptr<double2>(L.rope_tab);
-    if (fuse_qkv) {
+    if (fuse_qkv || few) {
       // the QKV layer rotates and stores queries, keys and values itself
       RopeOut ro;
       ro.row_pos = row_pos; ro.row_page = row_page; ro.row_off = row_off;
       ro.q_out = q; ro.k_pages = kdst; ro.v_pages = vdst; ro.table = rope_tab;
       ro.Hq = c.n_q_heads; ro.Hkv = c.n_kv_heads; ro.hd = c.head_dim; ro.pg = s->p.page_tokens;
       ProfScope ps(s, MC_K_LINEAR_QKV);
-      MC_TRY(launch_linear_qkv_rope(st, rows, m->n_qkv, d, h, W.wqkv, ro));
+      if (few) {                                              // one launch is three (layer 0: its norm is the gather's too)
+        ProfScope pr(s, MC_K_ROPE_KV), pn(s, l == 0 ? MC_K_NONE : MC_K_ADD_RMSNORM);
+        MC_TRY(launch_norm_qkv_rope_few(st, dt, rows, m->n_qkv, d, x, W.attn_norm, c.rms_eps, W.wqkv, ro));
+      } else {
+        MC_TRY(launch_linear_qkv_rope(st, rows, m->n_qkv, d, h, W.wqkv, ro));
+      }
     } else {
       {
         ProfScope ps(s, MC_K_LINEAR_QKV);
@@ -607,6 +620,19 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
       MC_TRY(launch_attention_generic(st, dt, a));
       }
     }
+    if (few) {
+      {
+        ProfScope ps(s, MC_K_LINEAR_O);
+        MC_TRY(launch_accumulate_few(st, dt, rows, d, qd, ao, W.wo, x));
+      }
+      {
+        ProfScope ps(s, MC_K_ADD_RMSNORM), pg(s, MC_K_LINEAR_GATE_UP);
+        MC_TRY(launch_norm_swiglu_few(st, dt, rows, c.d_ffn, d, x, W.ffn_norm, c.rms_eps, W.w_gate, W.w_up, act));
+      }
+      ProfScope ps(s, MC_K_LINEAR_DOWN);
+      MC_TRY(launch_accumulate_few(st, dt, rows, d, c.d_ffn, act, W.w_down, x));
+      continue;
+    }
     // a large product on the tiled path adds to the residual stream in its own epilogue
     const bool acc_o = tl && linear_accumulate_fused(rows, d, qd);
     const int s2 = acc_o ? 0 : splits_for(d, qd);
@@ -648,6 +674,11 @@ static int lm_head(mc_session *s, int rows_in_x, int tail_splits, int n_rows, bo
   hipStream_t st = s->stream;
   float *x = s->ptr<float>(L.x);
   const void *hin;
+  if (!gather && tail_splits == 0 && few_rows_fused(s, rows_in_x)) {
+    if (lists_written) *lists_written = false;
+    ProfScope pn(s, MC_K_ADD_RMSNORM), ps(s, MC_K_LINEAR_LM_HEAD);
+    return launch_norm_linear_few(st, c.dtype, rows_in_x, c.vocab, c.d_model, x, m->final_norm, c.rms_eps, m->lm_head, dst);
+  }
   if (gather) {
     // fold the pending partial sums into x (normalised output unused), then gather rows
     if (tail_splits > 0) {

@@ -38,6 +38,26 @@ def test_tiny_config_teacher_forced_logits_pages_and_sampler(tiny):
     np.testing.assert_array_equal(tab[:, :ref.shape[1]], ref)
 
 
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,hd,F,cands", [
+    ("f32", 20, 2, 1, 6, 12, 3),            # a part of one piece of K; odd halves
+    ("f32", 256, 4, 4, 64, 260, 5),         # a full piece, one element quad of a second; eight rows per wave
+    ("f32", 516, 3, 1, 172, 1020, 9),       # four pieces, a second block of rows
+    ("f32", 1024, 8, 2, 128, 1024, 4),      # the widest
+    ("f32", 64, 2, 1, 32, 1028, 4),         # one past it: the layers in pieces
+    ("bf16", 72, 3, 1, 24, 136, 4), ("bf16", 1016, 1, 1, 254, 520, 9)])
+def test_few_rows_with_the_norms_inside_the_layers(dtype, d, Hq, Hkv, hd, F, cands):
+    """Decode steps of models that are not tiled, whose norms, rotation and residual updates run inside the products, at the edges
+    of the widths and row counts that take that path."""
+    # the mean signed error of n independent errors scatters by 1 / sqrt(n) of their RMS: with 1600 logits a row the bar of 0.1 is four
+    # standard deviations (with 96 it is one, and the prefix row, which other kernels compute, was beyond it)
+    s = small_shape("few rows", 2, d, Hq, Hkv, hd, F, 1600, 1.0e4, dtype)
+    w = synth.make_weights(s, 911)
+    prefix, suffix = synth.tokens(912, 1, (70,), s.vocab), synth.tokens(912, 2, (cands, 4), s.vocab)
+    print("case: few rows", s, cands, flush=True)
+    pl, steps, sess, model = teacher_forced_gpu(s, w, prefix, suffix, 4)
+    check_against_oracle(s, w, prefix, suffix, pl, steps)
+
+
 def test_tiny_sampler_on_device_logits(tiny):
     wl, w = tiny
     s = wl.shape
