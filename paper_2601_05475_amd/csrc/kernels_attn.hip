@@ -19,7 +19,8 @@
 //   suffix item (candidate b, kv head, key split): columns are b's G query heads.
 // Every item leaves an un-normalised partial (max m, sum l, weighted values o) per query head;
 // a second small kernel merges the partials of each (candidate, head) and writes bf16.  (An item
-// that holds the only partial of its rows normalises and writes them itself.)
+// that holds the only partial of its rows normalises and writes them itself.)  Short contexts take one workgroup per candidate and
+// KV head instead (decode_attention_whole_kernel).
 //
 // Scores are computed transposed, S^T = K Q^T, so that a lane owns ONE query column: the softmax
 // reductions are 16 in-lane steps plus one cross-half shuffle, the running rescale of O^T is a
@@ -62,6 +63,7 @@ __device__ inline void zero_padding(bf16_t *out, int B, int b, int k, int K) {
 
 constexpr int PG = 64;                       // keys per page (the only page size of this kernel)
 constexpr int kMaxSuffixSplits = 8;
+constexpr int kWholeWaves = 8;                // waves per workgroup of the form for short contexts
 
 struct AttnItems {
   int n_prefix_items, n_suffix_items;
@@ -528,6 +530,180 @@ __global__ __launch_bounds__(HD) void decode_attention_merge_kernel(
   if (out_tiled == TILED_ZERO) zero_padding<1>(out, B, b, head * HD + d, Hq * HD);
 }
 
+// softmax_block of the kernel above as a function (used there too, that kernel takes 210 registers instead of 195 and 15.7 us instead of 15.6 at the 8B
+// shape): the block's scores to packed probabilities, against the lane's reference m as it stands unless their sum leaves the range.
+template <int HD>
+__device__ __forceinline__ void softmax_of_block(f32x16 &s, int n_valid, int h, float scale2, float &m, float &l, f32x16 (&o)[HD / 32], v4u (&pb)[2]) {
+  if (n_valid < 32) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (8 * (r >> 2) + 4 * h + (r & 3) >= n_valid) s[r] = -INFINITY;
+  }
+  f32x16 p;
+  auto probs = [&]() __attribute__((always_inline)) -> float {
+    float rs = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale2, -m));
+      rs += p[r];
+    }
+    return rs;
+  };
+  float rs = probs();
+  if (__any(!(rs <= kSoftmaxSumLimit))) {
+    float mx = max16f(s);
+    mx = fmaxf(mx, other_half(mx));
+    const float m_new = fmaxf(m, mx * scale2);              // finite: a processed block has a valid key
+    const float corr = __builtin_amdgcn_exp2f(m - m_new);   // m = -inf at the start: 0
+    l *= corr;
+    m = m_new;
+#pragma unroll
+    for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[dt][r] *= corr;
+    rs = probs();
+  }
+  rs += other_half(rs);
+  l += rs;
+  pb[0] = make_v4u(pack2_bf16(p[0], p[1]), pack2_bf16(p[2], p[3]), pack2_bf16(p[4], p[5]), pack2_bf16(p[6], p[7]));
+  pb[1] = make_v4u(pack2_bf16(p[8], p[9]), pack2_bf16(p[10], p[11]), pack2_bf16(p[12], p[13]), pack2_bf16(p[14], p[15]));
+}
+
+// Short contexts: one workgroup of eight waves per (candidate, KV head), wave w takes blocks w, w + 8, ... of the prefix and
+// then of the candidate's suffix, and the states meet in LDS: one launch, no partial states in memory.  The prefix comes from L2 once per
+// candidate, so a long context is better split as above (see whole_form).  What bounds it is the launch, one trip to memory for queries, page
+// ids and the first blocks, 0.4 us (head_dim 64) to 0.7 us (128) per block of the longest wave, and the meeting in LDS.
+template <int HD>
+__global__ __launch_bounds__(512, 2)
+void decode_attention_whole_kernel(DecodeAttnArgs a) {
+  constexpr int NF = HD / 16, BLK = 32 * HD, SOLD = HD + 4, W = kWholeWaves;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, G = Hq / Hkv, B = a.n_cands;
+  const int kvh = blockIdx.x % Hkv, b = blockIdx.x / Hkv;
+  const int len = a.suffix_len == 0 ? 0 : a.row_len ? min(max(a.row_len[b], 1), a.suffix_len) : a.suffix_len;
+  const int n_pre = (a.prefix_len + 31) >> 5, n = n_pre + ((len + 31) >> 5);
+  const int n_mine = (n - wave + W - 1) / W;                  // <= 0: idle wave
+  // page ids of this wave's blocks, one per lane
+  int my_pid = 0;
+  {
+    const int j = wave + lane * W;
+    if (j < n_pre) my_pid = j >> 1;
+    else if (j < n) my_pid = a.page_table[(size_t)(a.row_cand ? a.row_cand[b] : b) * a.table_stride + ((j - n_pre) >> 1)];
+  }
+  const bool col_valid = col < G;
+  v4u qf[NF], kf[NF], vf[NF];
+  const bf16_t *qrow = (const bf16_t *)a.q + ((size_t)b * Hq + kvh * G + (col_valid ? col : 0)) * HD + 8 * h;
+#pragma unroll
+  for (int c = 0; c < NF; ++c) qf[c] = *(const v4u *)(qrow + 16 * c);
+  const float scale2 = 1.4426950408889634f / sqrtf((float)HD);
+  f32x16 o[HD / 32];
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  const size_t page_stride = (size_t)Hkv * PG * HD, head_off = (size_t)kvh * PG * HD;
+  // Block i of this wave: where it starts in its pool, how many of its keys exist.  Past the last block: the first again, all lanes its first
+  // 16 bytes, as in the kernel above (no branch around the loads); so do lanes whose keys do not exist.
+  auto block = [&](int i, bool &prefix, uint32_t &voff, int &n_valid) __attribute__((always_inline)) -> size_t {
+    const bool real = i < n_mine;
+    const int ii = real ? i : 0, j = wave + ii * W;
+    prefix = j < n_pre;
+    const int g = prefix ? j : j - n_pre;
+    voff = real ? lane * 16u : 0u;
+    n_valid = (prefix ? a.prefix_len : len) - 32 * g;
+    return ((size_t)(uint32_t)__builtin_amdgcn_readlane(my_pid, ii) * page_stride + head_off + (size_t)(g & 1) * BLK) * sizeof(bf16_t);
+  };
+  auto issue_k = [&](int i) __attribute__((always_inline)) {
+    bool prefix;
+    uint32_t voff;
+    int n_valid;
+    const size_t at = block(i, prefix, voff, n_valid);
+    const char *kb = (const char *)(prefix ? a.k_prefix : a.k_suffix) + at;
+    if (col >= n_valid) voff = 0u;
+#pragma unroll
+    for (int c = 0; c < NF; ++c) kf[c] = *(const v4u *)(kb + voff + 1024 * c);
+  };
+  auto issue_v = [&](int i) __attribute__((always_inline)) {
+    bool prefix;
+    uint32_t voff;
+    int n_valid;
+    const size_t at = block(i, prefix, voff, n_valid);
+    const char *vb = (const char *)(prefix ? a.v_prefix : a.v_suffix) + at;
+#pragma unroll
+    for (int c = 0; c < NF; ++c) vf[c] = *(const v4u *)(vb + ((16 * (c & 1) + 4 * h >= n_valid) ? 0u : voff) + 1024 * c);
+  };
+  if (n_mine > 0) {
+    issue_k(0);
+    issue_v(0);
+    for (int i = 0; i < n_mine; ++i) {
+      const int j = wave + i * W, n_valid = min(32, j < n_pre ? a.prefix_len - 32 * j : len - 32 * (j - n_pre));
+      f32x16 s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NF; ++c) s = mfma32a(kf[c], qf[c], s);
+      issue_k(i + 1);
+      v4u pb[2];
+      softmax_of_block<HD>(s, n_valid, h, scale2, m, l, o, pb);
+#pragma unroll
+      for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) o[dt] = mfma32a(vf[dt * 2 + sl], pb[sl], o[dt]);
+      issue_v(i + 1);
+    }
+  }
+  // eight states of the same columns meet
+  float *sm = (float *)lds_raw, *sl = sm + W * 32, *lsum = sl + W * 32;       // [W][32] m, [W][32] l, [32] merged l
+  float *so = lsum + 32;                                                       // [W][G][SOLD]
+  if (h == 0) {
+    sm[wave * 32 + col] = m;
+    sl[wave * 32 + col] = l;
+  }
+  __syncthreads();
+  float mm = sm[col];
+#pragma unroll
+  for (int w = 1; w < W; ++w) mm = fmaxf(mm, sm[w * 32 + col]);
+  const float f = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mm);    // a wave that saw no key contributes nothing
+  if (wave == 0 && h == 0) {
+    float lg = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const float mw = sm[w * 32 + col];
+      lg += (mw == -INFINITY) ? 0.f : sl[w * 32 + col] * __builtin_amdgcn_exp2f(mw - mm);
+    }
+    lsum[col] = lg;
+  }
+  if (col_valid) {
+    float *dst = so + (size_t)(wave * G + col) * SOLD + 4 * h;
+#pragma unroll
+    for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        *(float4 *)(dst + dt * 32 + 8 * r4) = make_float4(o[dt][4 * r4] * f, o[dt][4 * r4 + 1] * f, o[dt][4 * r4 + 2] * f, o[dt][4 * r4 + 3] * f);
+  }
+  __syncthreads();
+  for (int e = tid; e < G * (HD / 4); e += 64 * W) {
+    const int c = e / (HD / 4), d = (e % (HD / 4)) * 4;
+    float4 v = *(const float4 *)(so + (size_t)c * SOLD + d);
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+      const float4 u = *(const float4 *)(so + (size_t)(w * G + c) * SOLD + d);
+      v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+    }
+    const float lg = lsum[c];
+    const int hq = kvh * G + c;
+    const size_t at = a.out_tiled ? tiled_offset(b, hq * HD + d, Hq * HD) : ((size_t)b * Hq + hq) * HD + d;
+    uint2 pk;
+    pk.x = pack2_bf16(v.x / lg, v.y / lg);
+    pk.y = pack2_bf16(v.z / lg, v.w / lg);
+    *(uint2 *)((bf16_t *)a.out + at) = pk;
+    if (a.out_tiled == TILED_ZERO) zero_padding<4>((bf16_t *)a.out, B, b, hq * HD + d, Hq * HD);
+  }
+}
+
 static AttnItems plan_items(const DecodeAttnArgs &a) {
   AttnItems it;
   const int G = a.n_q_heads / a.n_kv_heads;
@@ -606,6 +782,31 @@ size_t decode_attention_mfma_ws_bytes(int n_cands, int Hq, int Hkv, int hd, int 
   return parts * n_cands * Hq * (size_t)(hd + 2) * sizeof(float) + 512;
 }
 
+// Where one workgroup per (candidate, KV head) takes no longer on the device than the split items and their merge; on the host it is a launch
+// less in any case (one layer-step called from Python: 15.3 -> 12.5 us).  us on the device, split / whole, prefix + suffix
+// keys: head_dim 64, 8 candidates of 8 KV heads, 100 + 10 7.3 / 4.7, 777 + 37 8.1 / 6.1, 1500 + 10 8.5 / 7.7, 1500 + 200 (54 blocks) 8.6 / 8.3, 3000 + 10
+// 8.7 / 11.0; 64 candidates (512 workgroups) 300 + 200 11.0 / 7.6, 1500 + 10 12.5 / 11.6, 1500 + 200 12.5 / 12.9; head_dim 128, 32 candidates, 100 + 10 9.4 /
+// 5.8, 777 + 200 (32 blocks) 11.7 / 9.4, 1500 + 200 12.5 / 12.7, one candidate 777 + 200 10.1 / 9.8, 1500 + 10 10.3 / 11.6; 64 candidates 777 + 10 (26 blocks)
+// 17.3 / 15.2, 777 + 200 19.2 / 19.4.  More workgroups than 512 were not measured.
+static bool whole_form(const DecodeAttnArgs &a) {
+  const long groups = (long)a.n_cands * a.n_kv_heads;
+  const int blocks = (a.prefix_len + 31) / 32 + (a.suffix_len + 31) / 32, most = a.head_dim == 64 ? 48 : groups <= 256 ? 32 : 28;
+  return a.prefix_splits <= 0 && groups <= 512 && blocks <= most;     // (a caller's split count asks for the split form)
+}
+
+template <int HD>
+static int launch_decode_attention_whole(hipStream_t st, const DecodeAttnArgs &a) {
+  const int G = a.n_q_heads / a.n_kv_heads;
+  const int lds = (2 * kWholeWaves * 32 + 32 + kWholeWaves * G * (HD + 4)) * (int)sizeof(float);
+  MC_TRY(raise_dynamic_lds_limit((const void *)decode_attention_whole_kernel<HD>, 160 * 1024 - 1024));
+  const LaunchEvents ev = take_launch_events();
+  const dim3 grid(a.n_cands * a.n_kv_heads);
+  if (ev.start || ev.stop) hipExtLaunchKernelGGL(decode_attention_whole_kernel<HD>, grid, dim3(64 * kWholeWaves), (uint32_t)lds, st, ev.start, ev.stop, 0, a);
+  else decode_attention_whole_kernel<HD><<<grid, 64 * kWholeWaves, lds, st>>>(a);
+  MC_HIP(hipGetLastError());
+  return MC_OK;
+}
+
 template <int HD>
 static int launch_decode_attention_t(hipStream_t st, const DecodeAttnArgs &a, const AttnItems &it_in) {
   const int n_parts = (a.prefix_len > 0 ? it_in.splits : 0) + (a.suffix_len > 0 ? it_in.suffix_splits : 0);
@@ -660,8 +861,9 @@ int decode_attention_plan(const DecodeAttnArgs &a, int32_t out[9]) {
 
 int launch_attention_decode_mfma(hipStream_t st, const DecodeAttnArgs &a) {
   if (!decode_attention_mfma_supported(a)) MC_FAIL(MC_ERR_UNSUPPORTED, "decode attention: shape not covered");
+  if (a.prefix_len + a.suffix_len < 1) MC_FAIL(MC_ERR_INVALID, "decode attention without keys");
+  if (whole_form(a)) return a.head_dim == 128 ? launch_decode_attention_whole<128>(st, a) : launch_decode_attention_whole<64>(st, a);
   const AttnItems it = plan_items(a);
-  if (it.n_prefix_items + it.n_suffix_items == 0) MC_FAIL(MC_ERR_INVALID, "decode attention without keys");
   return a.head_dim == 128 ? launch_decode_attention_t<128>(st, a, it) : launch_decode_attention_t<64>(st, a, it);
 }
 

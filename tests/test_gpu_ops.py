@@ -258,6 +258,23 @@ def test_attention_decode_mfma_shapes(B, Hq, Hkv, hd, P, t, stride):
     assert worst < ATT_REL["bf16"], worst
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,hd,P,t,splits", [
+    # one workgroup per candidate and KV head: its most blocks at each head_dim and workgroup count and the first past them, fewer blocks
+    # than waves, 32 query heads per KV head, one, no prefix, no suffix
+    (2, 8, 2, 64, 1504, 32, 0), (2, 8, 2, 64, 1505, 32, 0), (3, 8, 2, 128, 801, 193, 0), (3, 8, 2, 128, 833, 193, 0), (64, 8, 8, 128, 641, 250, 0),
+    (64, 8, 8, 128, 673, 250, 0), (2, 32, 1, 128, 95, 33, 0), (3, 2, 2, 64, 1, 1, 0), (5, 4, 2, 128, 0, 65, 0), (6, 8, 4, 64, 257, 0, 0),
+    (65, 8, 8, 64, 70, 40, 0),             # 520 workgroups: split
+    # the split form at sizes that no longer take it by themselves
+    (64, 32, 8, 128, 100, 0, 1), (72, 32, 8, 128, 700, 40, 1), (2, 8, 8, 128, 63, 65, 1), (3, 8, 4, 64, 65, 64, 2), (48, 16, 4, 128, 130, 5, 1),
+    (7, 4, 2, 128, 0, 200, 1), (1, 32, 1, 64, 128, 129, 1), (4, 6, 2, 64, 250, 70, 2)])
+def test_attention_decode_short_contexts(B, Hq, Hkv, hd, P, t, splits):
+    plant = [(B - 1, Hq - 1, "prefix", P - 1)] if P > 1 else []
+    if t > 1:
+        plant.append((B // 2, 0, "suffix", t - 1))
+    worst, _, planted = attention_case("bf16", B, Hq, Hkv, hd, 64, P, t, stride=max(1, B * Hq // 150), splits=splits, plant=plant)
+    assert max(planted, default=0.0) < ATT_REL["bf16"] and worst < ATT_REL["bf16"], (worst, planted)
+
+
 @pytest.mark.parametrize("Hq,hd,B,P", [(8, 128, 57, 20), (8, 64, 57, 33), (8, 128, 57, 96), (8, 64, 72, 127), (8, 128, 72, 160),
                                        (10, 128, 64, 415)])
 def test_attention_decode_ring(Hq, hd, B, P):
