@@ -404,8 +404,10 @@ def average_rank(max_speedup) -> np.ndarray:
 
 
 def _stream():
+    """The current device's current stream.  torch.cuda.current_stream() builds a Stream object for it, 2.9 us of the 11.6 that a
+    short decode attention takes on the host; the handle alone takes 0.2."""
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _code_of(t) -> int:

@@ -325,6 +325,14 @@ def test_attention_split_count_invariance_many_rows():
         assert rel.max() < 6e-3, rel.max()
 
 
+def test_stream_handle_is_the_current_stream():
+    import torch
+    assert binding._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(torch.cuda.Stream()):
+        assert binding._stream() == torch.cuda.current_stream().cuda_stream != 0
+    assert binding._stream() == torch.cuda.current_stream().cuda_stream
+
+
 def test_kernels_are_run_to_run_identical():
     """Every MFMA kernel twice on the same inputs: bit-identical outputs.  (A vector instruction
     that reads matrix-core results before they have landed shows up here as last-bit noise long
