@@ -5,6 +5,7 @@
 // positions 32 (w / 4) .. + 31 of the item, which are its MFMA columns.  Two waves per SIMD let
 // one wave's softmax run under the other's MFMAs, and the LDS only reaches its full read rate
 // with eight waves per CU.
+// One or two heads past a multiple of four take several items of a sequence to a workgroup (REST).
 // Where that gives fewer workgroups than the chip has compute units, two waves share the 32
 // columns of a head (prefill_attention_split_kernel), or four that score and four that add take two heads' (prefill_attention_pair_kernel): they
 // score different key blocks and add different
@@ -216,7 +217,12 @@ constexpr size_t kL2Bytes = 32u << 20;         // of the eight XCDs together
 // Waves per SIMD: two at head_dim 128 (190 registers); at head_dim 64 (125 registers, 52 KB of LDS) two workgroups
 // share a compute unit.  (With an upper bound of two there the second stays out: 8 x 1024 rows after 4096
 // keys, 32 / 8 heads of 64, 339 -> 390 us.)
-template <int HD>
+//
+// REST: the heads past a multiple of four, one or two of them, would leave six or four of the eight waves idle, so their
+// workgroup takes four or two neighbouring items, where those have the same keys.  Each of these items has a workgroup of its own in the grid
+// (the lists are on the device), at its end and the first of each four or two before the others; those whose item an earlier one takes end at once.
+// (In the items' order, workgroups that stay and others in turn, the dispatcher deals all that stay to the same quarter or half of the units.)
+template <int HD, bool REST>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, HD == 64 ? 4 : 2)))
 void prefill_attention_kernel(PrefillAttnArgs a) {
   using TL = PTile<HD>;
@@ -232,16 +238,51 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   // KV heads first: with eight of them an XCD (workgroups are dealt to the eight in turn) meets one
   // head's keys and values only
   const int kvh = id % Hkv; id /= Hkv;
-  const int hg = id % HG; id /= HG;
-  // head within the group, half of the item's rows
-  const int hw = wave % 4, half = wave >> 2;
-  const int4 item = a.items[id];               // row_start, n_rows (<= 64), pos_start, table row
-  const int n_rows = item.y, tab = item.w;
+  int hg, n_near = 1, slot = 0;                 // items that the workgroup may take, this one's place among them
+  if (REST && id >= a.n_items * (G / 4)) {
+    hg = G / 4;
+    n_near = 4 / (G % 4);
+    id -= a.n_items * hg;
+    const int groups = (a.n_items + n_near - 1) / n_near;
+    slot = id / groups;
+    id = id % groups * n_near + slot;
+    if (id >= a.n_items) return;
+  } else {
+    hg = id % (REST ? G / 4 : HG);
+    id /= REST ? G / 4 : HG;
+  }
+  // head within the group, half of the item's rows, the wave's item
+  int hw = wave % 4, half = wave >> 2, mine = id;
+  const int4 first = a.items[id];              // row_start, n_rows (<= 64), pos_start, table row
+  const int tab = first.w;
+  int last_pos = first.z + first.y - 1;        // of the whole workgroup: pages every wave helps to stage
+  bool has_item = true;
+  if (n_near > 1) {
+    const int rest = G % 4, n_left = min(n_near - slot, a.n_items - id);
+    const int before = a.items[max(id - 1, 0)].w;
+    int4 near[4];                                // one round trip for all
+#pragma unroll
+    for (int i = 1; i < 4; ++i) near[i] = a.items[min(id + i, a.n_items - 1)];
+    if (slot > 0 && before == tab) return;       // an earlier one has this item
+    int n = 1;
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+      if (n == i && i < n_left && near[i].w == tab) {
+        last_pos = max(last_pos, near[i].z + near[i].y - 1);
+        n = i + 1;
+      }
+    hw = wave % rest;
+    half = wave / rest & 1;
+    has_item = wave / rest / 2 < n;
+    mine = has_item ? id + wave / rest / 2 : id;
+  }
+  const int4 item = REST ? a.items[mine] : first;
+  const int n_rows = item.y;
   const int row_start = item.x + 32 * half;     // this wave's rows and their first position
   const int pos_start = item.z + 32 * half;
   const int my_rows = min(32, n_rows - 32 * half);
   const int g = 4 * hg + hw;
-  const bool wave_active = g < G && my_rows > 0;   // uniform per wave
+  const bool wave_active = g < G && my_rows > 0 && has_item;   // uniform per wave
   const int head = kvh * G + (g < G ? g : 0);
   const bool col_valid = col < my_rows;
   const int my_pos = pos_start + (col_valid ? col : 0);
@@ -249,7 +290,6 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
 
   // visible keys: prefix [0, nA), then own suffix [0, nB) at absolute positions prefix_len + j.  (PPages says the
   // same; with it here 8 x 1024 rows after 4096 keys took 597 instead of 586 us.)
-  const int last_pos = item.z + n_rows - 1;        // of the whole item: pages every wave helps to stage
   const int nA = min(a.prefix_len, last_pos + 1);
   const int nB = (tab >= 0 && last_pos >= a.prefix_len) ? last_pos - a.prefix_len + 1 : 0;
   const int nPA = (nA + PPG - 1) / PPG, nPB = (nB + PPG - 1) / PPG, n_pages = nPA + nPB;
@@ -933,10 +973,26 @@ bool prefill_attention_mfma_supported(int page_tokens, int head_dim, int Hq, int
 
 enum { PREFILL_WHOLE, PREFILL_SPLIT, PREFILL_PAIR };
 
+// Whole items: do the heads past a multiple of four go by several items to a workgroup?  Where the workgroups of an item each are more than the
+// compute units; in one round nothing is won, and eight busy waves walk the keys slower than two (160 workgroups, 8 / 8 heads of 128, 5 x 200
+// rows after 1000 keys 34 / 37 us).  us, a workgroup per item / several items: 40 / 8 heads of 128, 8 x 1024 rows after 4096 keys 978 / 771 (0.55 -> 0.70
+// PFLOP/s), 8 x 300 after 2000 178 / 137, 5 x 200 after 1000 68 / 40, one sequence of 4096 after 4096 638 / 575, 128 x 64 after 300 (no neighbours of one
+// sequence: what is won is the order of the workgroups) 138 / 126; 8 / 8 heads of 128, 8 x 1024 after 4096 482 / 163; 16 / 8 heads of 64 276 / 187.
+// A single head per workgroup used to keep a unit as long as four did, and in turn with full ones they filled half of the units each.
+constexpr long kComputeUnits = 256;
+static bool rest_heads(const PrefillAttnArgs &a) {
+  const int G = a.n_q_heads / a.n_kv_heads;
+  return (G % 4 == 1 || G % 4 == 2) && (long)a.n_items * a.n_kv_heads * ((G + 3) / 4) > kComputeUnits;
+}
+
 // workgroups of a form
 template <int HD>
 static long prefill_grid(const PrefillAttnArgs &a, int form) {
   const int heads = form == PREFILL_PAIR ? PPair<HD>::HEADS : 4, G = a.n_q_heads / a.n_kv_heads;
+  if (form == PREFILL_WHOLE && rest_heads(a)) {
+    const int near = 4 / (G % 4);
+    return (long)a.n_kv_heads * (a.n_items * (G / 4) + (a.n_items + near - 1) / near * near);
+  }
   return (long)a.n_items * (form == PREFILL_WHOLE ? 1 : 2) * a.n_kv_heads * ((G + heads - 1) / heads);
 }
 
@@ -950,7 +1006,6 @@ static long prefill_grid(const PrefillAttnArgs &a, int form) {
 // 3000 66 / 65, heads of 64 52 / 46; 4 of 400 after 1024 keys (896 workgroups) 50 / 73.
 template <int HD>
 static int prefill_form(const PrefillAttnArgs &a) {
-  constexpr long kComputeUnits = 256;
   const long pairs = prefill_grid<HD>(a, PREFILL_PAIR);
   const bool shared = a.page_table == nullptr || a.prefix_len >= kPairSharedKeys;
   if (pairs <= (shared ? 2 : 1) * kComputeUnits) return PREFILL_PAIR;
@@ -969,11 +1024,12 @@ static int launch_prefill_hd(hipStream_t st, const PrefillAttnArgs &a) {
     prefill_attention_split_kernel<HD><<<n_main + n_zero, 512, PSplit<HD>::LDS_BYTES, st>>>(a, (int)n_main);
   } else {
     const int lds = PWhole<HD>::LDS_BYTES + kPrefillMaxPids * (int)sizeof(int);
-    MC_TRY(raise_dynamic_lds_limit((const void *)prefill_attention_kernel<HD>, lds));
+    const auto kernel = rest_heads(a) ? prefill_attention_kernel<HD, true> : prefill_attention_kernel<HD, false>;
+    MC_TRY(raise_dynamic_lds_limit((const void *)kernel, lds));
     const size_t pieces = (size_t)padded_rows(a.rows) * a.n_q_heads * HD / 8;
     if (n_zero && pieces * 16 <= kL2Bytes) zero_rows_kernel<<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((v4u *)a.out, pieces);
     else if (n_zero) zero_uncovered_rows_kernel<<<n_zero, 512, 0, st>>>(a);
-    prefill_attention_kernel<HD><<<n_main, 512, lds, st>>>(a);
+    kernel<<<n_main, 512, lds, st>>>(a);
   }
   MC_HIP(hipGetLastError());
   return MC_OK;

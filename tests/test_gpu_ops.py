@@ -1223,3 +1223,40 @@ def test_attention_prefill_pairs_of_heads(Hq, Hkv, hd, P, rows):
     assert not torch.isnan(full.view(torch.bfloat16)).any()
     for seqs in ([n // 2], [0, n - 1]):
         assert torch.equal(score(seqs), score(seqs)) and torch.equal(score(seqs), full[seqs])
+
+
+@pytest.mark.parametrize("Hq,Hkv,hd", [(5, 1, 128), (10, 2, 64), (6, 1, 128), (2, 2, 64), (8, 4, 128)])
+def test_attention_prefill_rest_heads_of_neighbouring_items(Hq, Hkv, hd):
+    """One or two heads past a multiple of four: their workgroup takes up to four neighbouring items of one sequence.  Sequences of one to
+    seven items, so that the groups of neighbours break at every place, short last items, two neighbours of one sequence that do not follow each
+    other, prefix-only items at the end; each has the bits that it has alone (other kernels)."""
+    import torch
+    pg, P, G = 64, 200, Hq // Hkv
+    lens = [64, 130, 5, 300, 64, 70, 448, 1, 193, 256]
+    while sum(-(-n // 64) for n in lens) * 2 * Hkv * -(-G // 4) <= 300:        # more workgroups than two waves per head are used for
+        lens = lens + lens[1:]
+    per = max(-(-n // 64) for n in lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(77 + Hq + hd)
+    normal = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)  # noqa: E731
+    kp, vp = binding.kv_pages_pack(normal(-(-P // pg), Hkv, pg, hd), normal(-(-P // pg), Hkv, pg, hd))
+    ks, vs = binding.kv_pages_pack(normal(len(lens) * per, Hkv, pg, hd), normal(len(lens) * per, Hkv, pg, hd))
+    table = torch.randperm(len(lens) * per, generator=g, device="cuda").to(torch.int32).reshape(len(lens), per)
+    items, row = [], 0
+    for c, n in enumerate(lens):
+        items += [[row + r, min(64, n - r), P + r, c] for r in range(0, n, 64)]
+        row += n
+    items += [[row, 64, 0, -1], [row + 64, 64, 64, -1], [row + 128, 8, P - 8, -1], [row + 136, 30, 10, -1]]
+    row += 166
+    items[4], items[5] = items[5], items[4]
+    q = normal(row, Hq, hd)
+
+    def run(some):
+        print("case: prefill rest heads", Hq, Hkv, hd, len(some), flush=True)
+        return binding.op_attention_prefill(q, torch.tensor(some, dtype=torch.int32, device="cuda"), kp, vp, ks, vs, table, P, pg).reshape(row, Hq, hd)
+
+    full = run(items)
+    assert not full.isnan().any()
+    for i in list(range(0, 24)) + list(range(len(items) - 6, len(items))):
+        r, n = items[i][:2]
+        assert torch.equal(run([items[i]])[r: r + n], full[r: r + n]), (i, items[i])
