@@ -421,7 +421,7 @@ int mc_op_attention_decode_static(void *stream, int32_t dtype, int32_t n_cands, 
 
 /* Host-only: the work-item plan of mc_op_attention_decode's split form for these sizes on the bf16
  * MFMA path (MC_ERR_UNSUPPORTED for shapes that path does not cover).  Short contexts with prefix_splits 0 are launched as one
- * workgroup per candidate and KV head instead, without partial states.  out9 (host, nine values):
+ * workgroup per candidate and KV head instead, without partial states (a session's decode steps keep the split form).  out9 (host, nine values):
  * prefix items incl. padding ids, suffix items, prefix key splits, 32-key blocks per prefix split,
  * suffix key splits, blocks per suffix split, partial states per (candidate, head), id distance
  * between the items of one prefix split, blocks of 32 query rows per prefix item (1 or 4). */

@@ -139,6 +139,7 @@ struct DecodeAttnArgs {
   // clamped); nullptr = suffix_len for every row (lock-step)
   const int32_t *row_len = nullptr;
   int32_t prefix_splits;         // 0 = automatic
+  bool split_only = false;       // a session's step: never the form for short contexts (see whole_form)
   void *workspace;
   size_t workspace_bytes;
   void *out;

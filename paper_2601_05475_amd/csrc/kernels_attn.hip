@@ -20,7 +20,7 @@
 // Every item leaves an un-normalised partial (max m, sum l, weighted values o) per query head;
 // a second small kernel merges the partials of each (candidate, head) and writes bf16.  (An item
 // that holds the only partial of its rows normalises and writes them itself.)  Short contexts take one workgroup per candidate and
-// KV head instead (decode_attention_whole_kernel).
+// KV head instead (decode_attention_whole_kernel), but for a session's steps.
 //
 // Scores are computed transposed, S^T = K Q^T, so that a lane owns ONE query column: the softmax
 // reductions are 16 in-lane steps plus one cross-half shuffle, the running rescale of O^T is a
@@ -795,10 +795,12 @@ size_t decode_attention_mfma_ws_bytes(int n_cands, int Hq, int Hkv, int hd, int 
 // 8.7 / 11.0; 64 candidates (512 workgroups) 300 + 200 11.0 / 7.6, 1500 + 10 12.5 / 11.6, 1500 + 200 12.5 / 12.9; head_dim 128, 32 candidates, 100 + 10 9.4 /
 // 5.8, 777 + 200 (32 blocks) 11.7 / 9.4, 1500 + 200 12.5 / 12.7, one candidate 777 + 200 10.1 / 9.8, 1500 + 10 10.3 / 11.6; 64 candidates 777 + 10 (26 blocks)
 // 17.3 / 15.2, 777 + 200 19.2 / 19.4.  More workgroups than 512 were not measured.
+// A session's steps keep the split form: this one adds in another order (each is as far from 64 bits as the other, 2.2e-3), logits of two layers move by 6e-3,
+// and with them almost a third of the sampled ids, which a session's user has on record.
 static bool whole_form(const DecodeAttnArgs &a) {
   const long groups = (long)a.n_cands * a.n_kv_heads;
   const int blocks = (a.prefix_len + 31) / 32 + (a.suffix_len + 31) / 32, most = a.head_dim == 64 ? 48 : groups <= 256 ? 32 : 28;
-  return a.prefix_splits <= 0 && groups <= 512 && blocks <= most;     // (a caller's split count asks for the split form)
+  return !a.split_only && a.prefix_splits <= 0 && groups <= 512 && blocks <= most;     // (a caller's split count asks for the split form)
 }
 
 template <int HD>

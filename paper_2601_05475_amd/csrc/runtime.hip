@@ -597,6 +597,7 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
       a.prefix_len = s->prefix_len; a.suffix_len = s->suffix_len + 1;
       a.row_len = s->ragged ? s->ptr<int32_t>(L.row_len) : nullptr;
       a.prefix_splits = s->prefix_splits;
+      a.split_only = true;
       a.row_cand = s->dropped_any ? row_tab : nullptr;
       a.workspace = s->ptr<void>(L.attn_ws); a.workspace_bytes = L.attn_ws_bytes; a.out = ao;
       a.out_tiled = tl;

@@ -58,6 +58,18 @@ def test_few_rows_with_the_norms_inside_the_layers(dtype, d, Hq, Hkv, hd, F, can
     check_against_oracle(s, w, prefix, suffix, pl, steps)
 
 
+def test_session_steps_of_short_contexts_keep_the_split_attention():
+    """A short bf16 context: the steps have the bits that they have with the plan's split count asked for, as the layer call by itself
+    need not (it takes another order of additions there)."""
+    s = small_shape("short steps", 2, 256, 8, 2, 64, 512, 1600, 1.0e4, "bf16")
+    w = synth.make_weights(s, 921)
+    prefix, suffix = synth.tokens(922, 1, (600,), s.vocab), synth.tokens(922, 2, (3, 5), s.vocab)
+    splits = {binding.op_attention_decode_plan(3, 8, 2, 64, 64, 600, t, 0)["splits"] for t in range(1, 6)}
+    assert len(splits) == 1
+    got = [teacher_forced_gpu(s, w, prefix, suffix, 64, prefix_splits=n)[1] for n in (0, splits.pop())]
+    np.testing.assert_array_equal(got[0], got[1])
+
+
 def test_tiny_sampler_on_device_logits(tiny):
     wl, w = tiny
     s = wl.shape
