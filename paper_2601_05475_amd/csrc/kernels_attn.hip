@@ -63,7 +63,6 @@ __device__ inline void zero_padding(bf16_t *out, int B, int b, int k, int K) {
 
 constexpr int PG = 64;                       // keys per page (the only page size of this kernel)
 constexpr int kMaxSuffixSplits = 8;
-constexpr int kCrowdedPrefixItems = 288;      // see plan_items
 constexpr int kWholeWaves = 8;                // waves per workgroup of the form for short contexts
 
 struct AttnItems {
@@ -734,10 +733,6 @@ static AttnItems plan_items(const DecodeAttnArgs &a) {
   // fetches in one batch) where that is enough.  Measured, attention + merge, 64 candidates:
   //   40 heads, prefix  4096: 16 splits 28 + 7 us,  8 splits 23 + 5;   16384: 10: 50 + 5, 15: 45 + 6, 16: 47 + 6, 21: 54 + 8
   //   32 heads, prefix  4096: 24 splits 25 + 7 us,  8 splits 21 + 4;   16384: 12: 44 + 5, 16: 38 + 5, 24: 42 + 7
-  // Where the suffixes are one and a half times the prefix or more (candidates of different lengths count three quarters), prefix items beyond
-  // about one per CU take the places in which suffix items would stream beside them.  us, attention + merge, 40 heads, 384 items at most / 288: 64
-  // candidates 16384 + 512 keys 59.3 / 56.9, 57 candidates 9000 + 300 38.6 / 36.3, 54 of 12000 + 400 44.3 / 41.2, 58 of up to 1000 after 14000
-  // 67.1 / 62.2; fewer suffixes lose: 64 of up to 420 after 16384 50.3 / 53.2, 64 of 256 47.4 / 51.8.
   it.rb_per_item = it.row_blocks >= 8 ? 4 : 1;
   const int rb_groups = (it.row_blocks + it.rb_per_item - 1) / it.rb_per_item;
   if (it.rb_per_item == 4 && it.n_prefix_blocks > 0) {
@@ -749,8 +744,6 @@ static AttnItems plan_items(const DecodeAttnArgs &a) {
       splits = std::min(splits, std::max(it.n_prefix_blocks / 16, splits_for(128)));
       // more items than CUs: leave one of the sixteen parts to the suffix
       if (a.suffix_len > 0 && splits == 16 && groups > 16) splits = 15;
-      const long suffix_blocks = (long)a.n_cands * it.n_suffix_blocks * (a.row_len ? 3 : 4) / 4;     // per KV head
-      if (2 * suffix_blocks >= 3L * it.n_prefix_blocks) splits = std::min(splits, std::max(kCrowdedPrefixItems / groups, 1));
     }
     splits = std::max(1, std::min(splits, max_splits));
     it.blocks_per_split = (it.n_prefix_blocks + splits - 1) / splits;

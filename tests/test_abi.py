@@ -155,6 +155,13 @@ def test_tiled_entry_points_refuse_what_the_plain_ones_refuse(lib):
     assert lib.mc_op_attention_decode(None, 1, *sizes, *tail, p, 1 << 30, p, 2) == -1
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,P", [(64, 40, 8, 16384), (57, 40, 8, 9000), (64, 32, 8, 4096), (64, 32, 4, 2048)])
+def test_decode_attention_prefix_splits_do_not_follow_the_suffixes(B, Hq, Hkv, P):
+    """Many query rows: the plan tells the splits of a launch whose candidates differ in length too (it is not told of them), and
+    a rollout's prefix splits stay what they are while its suffixes grow."""
+    assert len({binding.op_attention_decode_plan(B, Hq, Hkv, 128, 64, P, t, 0)["splits"] for t in (1, 64, 200, 353, 512, 1024, 4096)}) == 1
+
+
 def test_gemm_plan_takes_96_rows_only_for_a_third_more_workgroups(lib):
     """Host logic of the many-row GEMM: one round of workgroups where a listed shape can have it, and the 96-row form in
     place of 128 x 64 only over a long K and where it has at least 4/3 of the workgroups (with 1.17 and 1.20 of
