@@ -590,7 +590,7 @@ void decode_attention_whole_kernel(DecodeAttnArgs a) {
   {
     const int j = wave + lane * W;
     if (j < n_pre) my_pid = j >> 1;
-    else if (j < n) my_pid = a.page_table[(size_t)(a.row_cand ? a.row_cand[b] : b) * a.table_stride + ((j - n_pre) >> 1)];
+    else if (j < n) my_pid = a.page_table[(size_t)b * a.table_stride + ((j - n_pre) >> 1)];
   }
   const bool col_valid = col < G;
   v4u qf[NF], kf[NF], vf[NF];
@@ -782,18 +782,26 @@ size_t decode_attention_mfma_ws_bytes(int n_cands, int Hq, int Hkv, int hd, int 
   return parts * n_cands * Hq * (size_t)(hd + 2) * sizeof(float) + 512;
 }
 
-// Where one workgroup per (candidate, KV head) takes no longer on the device than the split items and their merge; on the host it is a launch
-// less in any case (one layer-step called from Python: 15.3 -> 12.5 us).  us on the device, split / whole, prefix + suffix
-// keys: head_dim 64, 8 candidates of 8 KV heads, 100 + 10 7.3 / 4.7, 777 + 37 8.1 / 6.1, 1500 + 10 8.5 / 7.7, 1500 + 200 (54 blocks) 8.6 / 8.3, 3000 + 10
-// 8.7 / 11.0; 64 candidates (512 workgroups) 300 + 200 11.0 / 7.6, 1500 + 10 12.5 / 11.6, 1500 + 200 12.5 / 12.9; head_dim 128, 32 candidates, 100 + 10 9.4 /
-// 5.8, 777 + 200 (32 blocks) 11.7 / 9.4, 1500 + 200 12.5 / 12.7, one candidate 777 + 200 10.1 / 9.8, 1500 + 10 10.3 / 11.6; 64 candidates 777 + 10 (26 blocks)
-// 17.3 / 15.2, 777 + 200 19.2 / 19.4.  More workgroups than 512 were not measured.
-// A session's steps keep the split form: this one adds in another order (each is as far from 64 bits as the other, 2.2e-3), logits of two layers move by 6e-3,
-// and with them almost a third of the sampled ids, which a session's user has on record.
+// Where one workgroup per (candidate, KV head) takes no longer on the device than the split items and their merge.  Measured at 1 to 512
+// workgroups, 1 to 48 blocks of 32 keys, 1 to 16 query heads per KV head, with and without prefix and suffixes; split / whole is the ratio of the
+// times, of the worst head count.
+// Up to 256 workgroups (one to a compute unit; 512 threads leave no room for a second at head_dim 128): head_dim 64 1.6 at 4 blocks, 1.2 at 24,
+// 1.06 at 40, 0.99 at 44 and 48; head_dim 128 1.45 at 4, 1.2 at 12, 1.02 at 24, 0.97 at 26, 0.92 at 30.
+// Without suffixes the split form is a single launch up to 16 blocks: head_dim 128, up to 32 workgroups 1.06 at 4 blocks, 0.96 at 8 to 16, 1.05 from
+// 20 on; more workgroups or head_dim 64 1.0 to 1.4.
+// 257 to 512 workgroups take two rounds: head_dim 64 1.5 at 4 blocks, 1.14 at 16, 1.0 at 20, 0.73 at 48; head_dim 128 1.05 at 4, 0.88 at 8, 0.69 at 28;
+// without prefix or without suffixes 0.6 to 1.1.
+// us, split / whole: 8 candidates of 32 / 8 heads of 64, 777 + 37 keys 8.1 / 6.1; 32 candidates of 32 / 8 heads of 128, 250 + 30 10.0 / 6.2.
+// A session's steps keep the split form: this one adds in another order (its error against 64 bits is 0.984 +- 0.004 of the other's, 60 calls), logits of
+// two layers move by 6e-3, and with them almost a third of the sampled ids, which a session's user has on record.
 static bool whole_form(const DecodeAttnArgs &a) {
+  if (a.split_only || a.row_cand || a.prefix_splits > 0) return false;                       // (a caller's split count asks for the split form)
   const long groups = (long)a.n_cands * a.n_kv_heads;
-  const int blocks = (a.prefix_len + 31) / 32 + (a.suffix_len + 31) / 32, most = a.head_dim == 64 ? 48 : groups <= 256 ? 32 : 28;
-  return !a.split_only && a.prefix_splits <= 0 && groups <= 512 && blocks <= most;     // (a caller's split count asks for the split form)
+  const int blocks = (a.prefix_len + 31) / 32 + (a.suffix_len + 31) / 32;
+  const bool narrow = a.head_dim == 64;
+  if (groups > 256) return groups <= 512 && a.prefix_len > 0 && a.suffix_len > 0 && blocks <= (narrow ? 16 : 4);
+  if (a.suffix_len == 0 && !narrow && groups <= 32 && blocks > 4 && blocks <= 16) return false;
+  return blocks <= (narrow ? 40 : 24);
 }
 
 template <int HD>
@@ -801,10 +809,7 @@ static int launch_decode_attention_whole(hipStream_t st, const DecodeAttnArgs &a
   const int G = a.n_q_heads / a.n_kv_heads;
   const int lds = (2 * kWholeWaves * 32 + 32 + kWholeWaves * G * (HD + 4)) * (int)sizeof(float);
   MC_TRY(raise_dynamic_lds_limit((const void *)decode_attention_whole_kernel<HD>, 160 * 1024 - 1024));
-  const LaunchEvents ev = take_launch_events();
-  const dim3 grid(a.n_cands * a.n_kv_heads);
-  if (ev.start || ev.stop) hipExtLaunchKernelGGL(decode_attention_whole_kernel<HD>, grid, dim3(64 * kWholeWaves), (uint32_t)lds, st, ev.start, ev.stop, 0, a);
-  else decode_attention_whole_kernel<HD><<<grid, 64 * kWholeWaves, lds, st>>>(a);
+  decode_attention_whole_kernel<HD><<<a.n_cands * a.n_kv_heads, 64 * kWholeWaves, lds, st>>>(a);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }

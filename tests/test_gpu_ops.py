@@ -261,9 +261,13 @@ def test_attention_decode_mfma_shapes(B, Hq, Hkv, hd, P, t, stride):
 @pytest.mark.parametrize("B,Hq,Hkv,hd,P,t,splits", [
     # one workgroup per candidate and KV head: its most blocks at each head_dim and workgroup count and the first past them, fewer blocks
     # than waves, 32 query heads per KV head, one, no prefix, no suffix
-    (2, 8, 2, 64, 1504, 32, 0), (2, 8, 2, 64, 1505, 32, 0), (3, 8, 2, 128, 801, 193, 0), (3, 8, 2, 128, 833, 193, 0), (64, 8, 8, 128, 641, 250, 0),
-    (64, 8, 8, 128, 673, 250, 0), (2, 32, 1, 128, 95, 33, 0), (3, 2, 2, 64, 1, 1, 0), (5, 4, 2, 128, 0, 65, 0), (6, 8, 4, 64, 257, 0, 0),
+    (2, 8, 2, 64, 1248, 32, 0), (2, 8, 2, 64, 1249, 32, 0), (3, 8, 2, 128, 513, 193, 0), (3, 8, 2, 128, 545, 193, 0), (33, 8, 8, 64, 417, 40, 0),
+    (33, 8, 8, 64, 449, 40, 0), (64, 8, 8, 128, 64, 40, 0), (64, 8, 8, 128, 65, 40, 0), (3, 8, 8, 128, 128, 0, 0), (3, 8, 8, 128, 129, 0, 0),
+    (3, 8, 8, 128, 512, 0, 0), (3, 8, 8, 128, 513, 0, 0), (2, 32, 1, 128, 95, 33, 0), (3, 2, 2, 64, 1, 1, 0), (5, 4, 2, 128, 0, 65, 0), (6, 8, 4, 64, 257, 0, 0),
     (65, 8, 8, 64, 70, 40, 0),             # 520 workgroups: split
+    # blocks that were past the first edges of that form
+    (2, 8, 2, 64, 1504, 32, 0), (2, 8, 2, 64, 1505, 32, 0), (3, 8, 2, 128, 801, 193, 0), (3, 8, 2, 128, 833, 193, 0), (64, 8, 8, 128, 641, 250, 0),
+    (64, 8, 8, 128, 673, 250, 0),
     # the split form at sizes that no longer take it by themselves
     (64, 32, 8, 128, 100, 0, 1), (72, 32, 8, 128, 700, 40, 1), (2, 8, 8, 128, 63, 65, 1), (3, 8, 4, 64, 65, 64, 2), (48, 16, 4, 128, 130, 5, 1),
     (7, 4, 2, 128, 0, 200, 1), (1, 32, 1, 64, 128, 129, 1), (4, 6, 2, 64, 250, 70, 2)])
@@ -273,6 +277,27 @@ def test_attention_decode_short_contexts(B, Hq, Hkv, hd, P, t, splits):
         plant.append((B // 2, 0, "suffix", t - 1))
     worst, _, planted = attention_case("bf16", B, Hq, Hkv, hd, 64, P, t, stride=max(1, B * Hq // 150), splits=splits, plant=plant)
     assert max(planted, default=0.0) < ATT_REL["bf16"] and worst < ATT_REL["bf16"], (worst, planted)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,hd,P,t", [
+    (64, 32, 8, 128, 640, 250), (33, 8, 8, 128, 300, 40), (33, 8, 8, 128, 96, 40), (16, 32, 32, 64, 1472, 64), (64, 8, 8, 64, 500, 33),
+    (64, 32, 8, 64, 1504, 1), (4, 8, 8, 128, 700, 100), (2, 8, 8, 64, 1280, 33), (64, 8, 8, 128, 0, 64), (40, 8, 8, 64, 0, 300), (40, 8, 8, 64, 300, 0),
+    (3, 8, 8, 128, 200, 0), (3, 8, 8, 128, 512, 0)])
+def test_attention_decode_keeps_the_split_form_where_it_is_faster(B, Hq, Hkv, hd, P, t):
+    """Contexts past those of one workgroup per candidate and KV head, two rounds of such workgroups, prefixes or suffixes alone: the
+    bits of the split form, which a split count asks for."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17 * P + t)
+    normal = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)  # noqa: E731
+    per = max(1, -(-t // 64))
+    q, k, v = normal(B, Hq, hd), normal(max(1, -(-P // 64)), Hkv, 64 * hd), normal(max(1, -(-P // 64)), Hkv, 64 * hd)
+    ks, vs = normal(B * per, Hkv, 64 * hd), normal(B * per, Hkv, 64 * hd)
+    table = torch.randperm(B * per, generator=g, device="cuda").to(torch.int32).reshape(B, per)
+    splits = max(1, binding.op_attention_decode_plan(B, Hq, Hkv, hd, 64, P, t, 0)["splits"])
+    print("case: split form", B, Hq, Hkv, hd, P, t, splits, flush=True)
+    got = [binding.op_attention_decode(q, k, v, ks, vs, table, P, t, 64, prefix_splits=n) for n in (0, splits)]
+    assert not got[0].isnan().any() and torch.equal(got[0], got[1])
 
 
 @pytest.mark.parametrize("Hq,hd,B,P", [(8, 128, 57, 20), (8, 64, 57, 33), (8, 128, 57, 96), (8, 64, 72, 127), (8, 128, 72, 160),
