@@ -233,8 +233,10 @@ int launch_rope_kv(hipStream_t st, int dtype, int rows, int Hq, int Hkv, int hd,
                    const int32_t *row_page, const int32_t *row_off, void *q_out, void *k_pages,
                    void *v_pages, const double2 *table = nullptr, int qk_interleaved = 0);
 // Few rows of models that are not tiled: the norm inside the layer behind it (x: the fp32 residual stream, not changed), the
-// QKV layer with the rotation and the stores, products that add to x.  few_rows_fused_ok: the shapes that all of them take.
+// QKV layer with the rotation and the stores, products that add to x.  few_rows_fused_ok: the shapes that the layers take,
+// few_rows_lm_head_ok: of those, the ones that launch_norm_linear_few takes as well.
 bool few_rows_fused_ok(int dtype, int rows, int d, int n_qkv, int qd, int F, int vocab, int head_dim);
+bool few_rows_lm_head_ok(int dtype, int rows, int vocab);
 int launch_norm_qkv_rope_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *w, const RopeOut &ro);
 int launch_norm_swiglu_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *wg, const void *wu, void *out);
 int launch_norm_linear_few(hipStream_t st, int dtype, int M, int N, int K, const float *x, const void *gain, float eps, const void *w, float *out);

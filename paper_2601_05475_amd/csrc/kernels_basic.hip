@@ -509,14 +509,14 @@ static void launch_few_rows(hipStream_t st, int M, int N, int K, int kps, int n_
   else linear_few_rows_kernel<T, SWIGLU, 8><<<grid, 256, 0, st>>>(M, N, K, kps, A, W, W2, out, (T *)out_t);
 }
 
-// Whole layers of few rows: the norm inside the product behind it, the QKV layer with rotation and stores, products that add to the
+// Whole layers of up to eight rows: the norm inside the product behind it, the QKV layer with rotation and stores, products that add to the
 // residual stream.  A layer is then five launches (norm + QKV + rotary, attention, output projection, norm + SwiGLU, down projection) where it was
 // eight.  As above a wave takes an output column (two for SwiGLU and for a rotary pair), with P pieces of 16 bytes of K per lane, all asked for at
 // once.  NORM: a is fp32 x, and the operand is x * gain / sqrt(mean(x^2) + eps) rounded to the model's type; every wave takes the mean itself:
 // rows of this path are a few KB, whose sum is a wave's shuffles away, where a norm launch takes 2.5 us and the gap before it.  What bounds the
 // kernels is the launch and one trip to memory.
-// 16 steps of the two-layer fp32 model (4 candidates, d 256, F 688, vocabulary 4096, pages of 4, every token read by the host): 19 launches a step -> 13,
-// 73 -> 67 us in kernels, 1745 -> 1460 us in all.  Two loads deep over K in place of all at once: 1480.
+// A step of the two-layer fp32 model (4 candidates, d 256, F 688, vocabulary 4096): 19 launches -> 13, 61.6 -> 56.0 us.  Two loads deep over K in place
+// of all at once: 16 steps 1480 against 1460 us.
 // FEW_ROPE: a wave takes the members i and i + hd / 2 of a query or key head, or two coordinates of a value head.
 enum { FEW_STORE = 0, FEW_SWIGLU = 1, FEW_ROPE = 2, FEW_ACCUM = 3 };
 template <typename T, int MODE, bool NORM, int MR, int P>
@@ -525,13 +525,13 @@ __global__ __launch_bounds__(256) void few_rows_fused_kernel(int M, int N, int K
                                                              T *__restrict__ out_t, RopeOut ro) {
   constexpr int V = Vec16<T>::N;
   constexpr bool TWO = MODE == FEW_SWIGLU || MODE == FEW_ROPE;           // two weight rows per wave
-  const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6), m0 = blockIdx.y * MR;
+  const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (n >= (MODE == FEW_ROPE ? N / 2 : N)) return;
   const T *wr = w + (size_t)n * K, *ur = TWO ? w2 + (size_t)n * K : nullptr;
   int head = 0, i = 0, slot = 0, page = 0;
   double2 turn = {1.0, 0.0};
   if (MODE == FEW_ROPE) {
-    const int half = ro.hd >> 1, row = min(m0 + (lane & (MR - 1)), M - 1);      // the row that this lane will store
+    const int half = ro.hd >> 1, row = min(lane & (MR - 1), M - 1);      // the row that this lane will store
     head = n / half;
     i = n % half;
     const bool turned = head < ro.Hq + ro.Hkv;
@@ -541,14 +541,14 @@ __global__ __launch_bounds__(256) void few_rows_fused_kernel(int M, int N, int K
     page = ro.row_page[row];
     if (turned) turn = ro.table[(size_t)ro.row_pos[row] * half + i];
   }
-  // pieces past K: the last one again, with weights of zero
+  // pieces past K: the last one again, left out of the sums
   float av[MR][P][V], wv[P][V], uv[P][V], gv[P][V];
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int k = min((p * 64 + lane) * V, K - V);
 #pragma unroll
     for (int m = 0; m < MR; ++m) {
-      const size_t at = (size_t)min(m0 + m, M - 1) * K + k;
+      const size_t at = (size_t)min(m, M - 1) * K + k;
       if (NORM) {
 #pragma unroll
         for (int j = 0; j < V; j += 4) Vec16<float>::load((const float *)a + at + j, av[m][p] + j);
@@ -593,21 +593,21 @@ __global__ __launch_bounds__(256) void few_rows_fused_kernel(int M, int N, int K
   }
 #pragma unroll
   for (int m = 0; m < MR; ++m) {
-    if (lane != m || m0 + m >= M) continue;
+    if (lane != m || m >= M) continue;
     const float g = acc[m];
     if (MODE == FEW_SWIGLU) {
-      out_t[(size_t)(m0 + m) * N + n] = Cvt<T>::from_f32(g / (1.0f + expf(-g)) * acc2[m]);
+      out_t[(size_t)m * N + n] = Cvt<T>::from_f32(g / (1.0f + expf(-g)) * acc2[m]);
     } else if (MODE == FEW_ACCUM) {
-      out[(size_t)(m0 + m) * N + n] += g;
+      out[(size_t)m * N + n] += g;
     } else if (MODE == FEW_STORE) {
-      out[(size_t)(m0 + m) * N + n] = g;
+      out[(size_t)m * N + n] = g;
     } else {
       const int hd = ro.hd, half = hd >> 1;
       const size_t at = (size_t)page * ro.Hkv * hd * ro.pg;
       const double lo = g, hi = acc2[m];
       if (head < ro.Hq + ro.Hkv) {
         const bool query = head < ro.Hq;
-        T *dst = query ? (T *)ro.q_out + ((size_t)(m0 + m) * ro.Hq + head) * hd : (T *)ro.k_pages + at + (size_t)(head - ro.Hq) * ro.pg * hd;
+        T *dst = query ? (T *)ro.q_out + ((size_t)m * ro.Hq + head) * hd : (T *)ro.k_pages + at + (size_t)(head - ro.Hq) * ro.pg * hd;
         dst[query ? (size_t)i : k_elem_offset(slot, i, ro.pg, hd)] = Cvt<T>::from_f32((float)(lo * turn.x - hi * turn.y));
         dst[query ? (size_t)(i + half) : k_elem_offset(slot, i + half, ro.pg, hd)] = Cvt<T>::from_f32((float)(hi * turn.x + lo * turn.y));
       } else {
@@ -619,26 +619,33 @@ __global__ __launch_bounds__(256) void few_rows_fused_kernel(int M, int N, int K
   }
 }
 
-// Where every product of the model goes by columns as it stands and K is at most 1024: above, the mean that each wave takes and a K that is
-// not split over workgroups cost more.
-constexpr int kFusedMostK = 1024;
+// Where every product of the model goes by columns as it stands, K is at most 1024 (above, a K that is not split over workgroups costs more)
+// and the rows are at most eight: every wave reads all its rows and takes their means, which 16 rows or a wide output pay for once per column.
+// us per step, separate launches / this, two layers: d 256, F 688 58.7 / 52.5 for one row, 61.6 / 57.0 for 4, 74.3 / 72.0 for 8; d 512, F 1024
+// 66.3 / 58.7, 69.0 / 63.6, 86.9 / 80.3; d 1024, F 1024 91.9 / 80.3, 98.3 / 86.0, 124 / 106; bf16, d 504 63.5 / 60.4, 67.7 / 65.6, 94.1 / 89.9;
+// d 20 72.7 / 64.3, 73.7 / 69.6, 84.5 / 89.6.  With 16 rows
+// and the LM head so too d 768 190 / 350, with 32 rows bf16 d 1016 255 / 629.
+constexpr int kFusedMostK = 1024, kFusedMostRows = 8;
 bool few_rows_fused_ok(int dtype, int rows, int d, int n_qkv, int qd, int F, int vocab, int head_dim) {
-  if (head_dim % 2 || std::max(d, std::max(qd, F)) > kFusedMostK) return false;
+  if (rows > (d < 64 ? 4 : kFusedMostRows) || head_dim % 2 || std::max(d, std::max(qd, F)) > kFusedMostK) return false;
   // (the operands are rows of the model's and the session's arenas, aligned for 16-byte loads)
   auto ok = [&](int N, int K, bool swiglu) { return few_rows_ok(dtype, rows, N, K, K, 1, nullptr, nullptr, swiglu ? (const void *)16 : nullptr); };
   return ok(n_qkv, d, false) && ok(d, qd, false) && ok(F, d, true) && ok(d, F, false) && ok(vocab, d, false);
 }
+// The LM head with the final norm inside: fp32, up to four rows and a vocabulary of 4096.  us per step, norm and LM head apart / together, d 256: vocabulary
+// 4096 57.0 / 56.0 for 4 rows, 72.0 / 72.2 for 8, 8192 58.1 / 58.3, 16384 60.6 / 63.1, 32000 67.1 / 74.0 and for 8 rows 88.4 / 102.8; bf16, d 504, vocabulary
+// 4096 65.6 / 67.1.
+bool few_rows_lm_head_ok(int dtype, int rows, int vocab) { return dtype == MC_F32 && rows <= 4 && vocab <= 4096; }
 
 template <typename T, int MODE, bool NORM>
 static void launch_few_fused_t(hipStream_t st, int M, int N, int K, const void *a, const void *gain, float eps, const void *w, const void *w2,
                                float *out, void *out_t, const RopeOut &ro) {
-  const int mr = M <= 4 ? 4 : 8, columns = MODE == FEW_ROPE ? N / 2 : N, pieces = (K + 64 * Vec16<T>::N - 1) / (64 * Vec16<T>::N);
-  const dim3 grid((columns + 3) / 4, (M + mr - 1) / mr);
+  const int columns = MODE == FEW_ROPE ? N / 2 : N, pieces = (K + 64 * Vec16<T>::N - 1) / (64 * Vec16<T>::N), grid = (columns + 3) / 4;
   auto go = [&](auto p) {
     constexpr int P = decltype(p)::value;
-    if (mr == 4)
+    if (M <= 4)
       few_rows_fused_kernel<T, MODE, NORM, 4, P><<<grid, 256, 0, st>>>(M, N, K, a, (const T *)gain, eps, (const T *)w, (const T *)w2, out, (T *)out_t, ro);
-    else
+    else if constexpr (MODE != FEW_STORE)
       few_rows_fused_kernel<T, MODE, NORM, 8, P><<<grid, 256, 0, st>>>(M, N, K, a, (const T *)gain, eps, (const T *)w, (const T *)w2, out, (T *)out_t, ro);
   };
   if (pieces <= 1) go(std::integral_constant<int, 1>{});
@@ -649,9 +656,11 @@ static void launch_few_fused_t(hipStream_t st, int M, int N, int K, const void *
 template <int MODE, bool NORM>
 static int launch_few_fused(hipStream_t st, int dtype, int M, int N, int K, const void *a, const void *gain, float eps, const void *w,
                             const void *w2, float *out, void *out_t, const RopeOut &ro) {
-  if (K > kFusedMostK) MC_FAIL(MC_ERR_UNSUPPORTED, "fused layers of few rows: K = %d", K);
+  const bool lm_head = MODE == FEW_STORE;
+  if (K > kFusedMostK || M > (lm_head ? 4 : kFusedMostRows) || (lm_head && dtype != MC_F32))
+    MC_FAIL(MC_ERR_UNSUPPORTED, "fused layers of few rows: %d rows, K = %d", M, K);
   if (dtype == MC_F32) launch_few_fused_t<float, MODE, NORM>(st, M, N, K, a, gain, eps, w, w2, out, out_t, ro);
-  else launch_few_fused_t<bf16_t, MODE, NORM>(st, M, N, K, a, gain, eps, w, w2, out, out_t, ro);
+  else if constexpr (MODE != FEW_STORE) launch_few_fused_t<bf16_t, MODE, NORM>(st, M, N, K, a, gain, eps, w, w2, out, out_t, ro);
   MC_HIP(hipGetLastError());
   return MC_OK;
 }

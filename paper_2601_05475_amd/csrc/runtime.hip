@@ -675,7 +675,7 @@ static int lm_head(mc_session *s, int rows_in_x, int tail_splits, int n_rows, bo
   hipStream_t st = s->stream;
   float *x = s->ptr<float>(L.x);
   const void *hin;
-  if (!gather && tail_splits == 0 && few_rows_fused(s, rows_in_x)) {
+  if (!gather && tail_splits == 0 && few_rows_fused(s, rows_in_x) && few_rows_lm_head_ok(c.dtype, rows_in_x, c.vocab)) {
     if (lists_written) *lists_written = false;
     ProfScope pn(s, MC_K_ADD_RMSNORM), ps(s, MC_K_LINEAR_LM_HEAD);
     return launch_norm_linear_few(st, c.dtype, rows_in_x, c.vocab, c.d_model, x, m->final_norm, c.rms_eps, m->lm_head, dst);

@@ -41,10 +41,11 @@ def test_tiny_config_teacher_forced_logits_pages_and_sampler(tiny):
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,hd,F,cands", [
     ("f32", 20, 2, 1, 6, 12, 3),            # a part of one piece of K; odd halves
     ("f32", 256, 4, 4, 64, 260, 5),         # a full piece, one element quad of a second; eight rows per wave
-    ("f32", 516, 3, 1, 172, 1020, 9),       # four pieces, a second block of rows
+    ("f32", 516, 3, 1, 172, 1020, 8),       # four pieces, the most rows
+    ("f32", 516, 3, 1, 172, 1020, 9),       # one past them
     ("f32", 1024, 8, 2, 128, 1024, 4),      # the widest
     ("f32", 64, 2, 1, 32, 1028, 4),         # one past it: the layers in pieces
-    ("bf16", 72, 3, 1, 24, 136, 4), ("bf16", 1016, 1, 1, 254, 520, 9)])
+    ("bf16", 72, 3, 1, 24, 136, 4), ("bf16", 1016, 1, 1, 254, 520, 8), ("bf16", 1016, 1, 1, 254, 520, 9)])
 def test_few_rows_with_the_norms_inside_the_layers(dtype, d, Hq, Hkv, hd, F, cands):
     """Decode steps of models that are not tiled, whose norms, rotation and residual updates run inside the products, at the edges
     of the widths and row counts that take that path."""
@@ -56,6 +57,25 @@ def test_few_rows_with_the_norms_inside_the_layers(dtype, d, Hq, Hkv, hd, F, can
     print("case: few rows", s, cands, flush=True)
     pl, steps, sess, model = teacher_forced_gpu(s, w, prefix, suffix, 4)
     check_against_oracle(s, w, prefix, suffix, pl, steps)
+
+
+@pytest.mark.parametrize("dtype,d,V,cands", [("f32", 256, 1600, 9), ("f32", 256, 1600, 5), ("f32", 512, 4100, 4), ("f32", 1024, 32000, 1),
+                                             ("f32", 1024, 4096, 32), ("bf16", 248, 1600, 1), ("bf16", 504, 4096, 16)])
+def test_few_rows_lm_head_by_itself(dtype, d, V, cands):
+    """More rows or a wider vocabulary than the LM head takes with the final norm inside, where that is slower: the bits of the
+    norm and the product by themselves.  The projections are zero, so the last rows are the embeddings."""
+    import torch
+    s = small_shape("lm head", 1, d, 4, 2, 16, 64, V, 1.0e4, dtype)
+    w = synth.make_weights(s, 931)
+    for name in ("wo", "w_down"):
+        w["layers"][0][name] = np.zeros_like(w["layers"][0][name])
+    prefix, suffix = synth.tokens(932, 1, (7,), V), synth.tokens(932, 2, (cands, 1), V)
+    print("case: few rows, LM head", s, cands, flush=True)
+    got = teacher_forced_gpu(s, w, prefix, suffix, 4)[1][0]
+    dev = lambda a: (torch.from_numpy(a) if a.dtype == np.float32 else torch.from_numpy(a.view(np.int16)).view(torch.bfloat16)).cuda()  # noqa: E731
+    x = dev(w["embed"])[torch.from_numpy(suffix[:, 0].astype(np.int64)).cuda()].float()
+    want = binding.op_linear(binding.op_add_rmsnorm(x, None, dev(w["final_norm"]), s.rms_eps), dev(w["lm_head"]))[0].cpu().numpy()
+    np.testing.assert_array_equal(got, want)
 
 
 def test_session_steps_of_short_contexts_keep_the_split_attention():
