@@ -580,12 +580,16 @@ __global__ __launch_bounds__(256) void few_rows_fused_kernel(int M, int N, int K
   for (int p = 0; p < P; ++p)
     if ((p * 64 + lane) * V < K)
 #pragma unroll
-      for (int m = 0; m < MR; ++m)
+      for (int m = 0; m < MR; ++m) {
+        float s = 0.f, s2 = 0.f;                 // a piece by itself: short chains round less (K is not split over workgroups here)
 #pragma unroll
         for (int j = 0; j < V; ++j) {
-          acc[m] += av[m][p][j] * wv[p][j];
-          if (TWO) acc2[m] += av[m][p][j] * uv[p][j];
+          s += av[m][p][j] * wv[p][j];
+          if (TWO) s2 += av[m][p][j] * uv[p][j];
         }
+        acc[m] += s;
+        if (TWO) acc2[m] += s2;
+      }
 #pragma unroll
   for (int m = 0; m < MR; ++m) {
     acc[m] = wave_sum(acc[m]);
