@@ -221,7 +221,7 @@ constexpr int weight_pieces(int blocks, int waves) {
 // units (a multiple of D) whose weights are asked for at once, at the start of the B units before them, where otherwise every unit
 // asks for one.  A wave's loads return in order, so an activation fragment that L2 has waits for every weight load
 // from HBM before it; in bursts that wait comes once per B units.  Gains where the compute units' load path is full: 500 x
-// 4096 x 14336 by 128 x 64 85 -> 76 us, 300 x 5120 x 27648 165 -> 140, 1000 x 4096 x 14336 by 256 x 64 142 -> 119; eight units at once are no better, and
+// 4096 x 14336 by 128 x 64 86 -> 77 us, 640 x 2048 x 8192 49 -> 43 (see plain_form); eight units at once are no better, and
 // the SwiGLU form loses (300 x 14336 x 4096 by 320 rows 75 -> 88).
 template <int MODE, int TM, int TN, int D, int WV, bool NT, int B>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(WV > 8 ? 3 : 2, WV > 8 ? 3 : 2)))
@@ -478,12 +478,16 @@ bool gemm256_supported(int M, int N, int K, bool swiglu) {
 // more it is slower: 2048 x 12288, 576 rows (160 and 192) 57 / 61, 641 rows (192 and 224) 55 / 61; 3072 x 16384, 448 rows (192 and 240)
 // 78 / 78; 4096 x 14336, 288 rows (192 both) 66 / 75.  So it is over a short K (2048 x 8192, 768 rows 35 / 36; 4096 x 4096, 384 rows
 // 20 / 21); between 8192 and 12288 nothing was measured.
-// Weights in bursts (see the kernel): 128 x 64 from K = 2048 on where the row tiles are full to seven eighths, and from K = 4096 on two more forms ahead of 128 x 128,
-// 192 x 64 and 256 x 64, the latter where it has no more rows to spare than 128 x 128.  us, 128 x 64 unit by unit / in bursts: 4096 x 14336, 450 rows 80 / 72, 512 rows
-// 87 / 77, 300 rows 70 / 72; 6144 x 4096 with the rotary epilogue, 300 rows (three row tiles of 96 columns) 40 / 38 and 384 rows 45 / 38 by 192 x 64 (128 x 128 before);
-// 2048 x 2048, 1000 rows 16.5 / 15.5; 400 of 512 rows x 2048 x 8192 39 / 40; K = 256, 512 rows x 4096 7.3 / 7.6.  128 x 128 / 192 x 64: 4096 x 14336, 600 rows 115 / 100, 768 rows 126 / 105;
-// 2048 x 8192, 1100 rows 68 / 58, 1500 rows 69 / 62; 5120 x 5120, 500 rows 49 / 41; K = 2048, 600 rows x 4096 17.9 / 19.8, 1500 rows x 2048 21 / 22.  128 x 128 / 256 x 64:
-// 4096 x 14336, 1000 rows 130 / 119, 800 rows (seven row tiles or four) 102 / 111; 4096 x 4096, 1000 rows 43 / 40; 3072 x 2048, 1000 rows 26 / 27.
+// Weights in bursts (see the kernel): 128 x 64 from K = 2048 on where the row tiles are full to seven eighths and the last one by half, and from K = 4096 on
+// two more forms ahead of 128 x 128, 192 x 64 and, up to K = 5120 and where the last row tile is full to three quarters, 256 x 64.  Unit by unit a last row tile
+// of few rows leaves the load path to the others; a burst takes it whatever is in it.  us, weights from HBM (each call another matrix).
+// 128 x 64 unit by unit / in bursts: 4096 x 14336, 450 rows 81 / 75, 512 rows 86 / 77, 400 rows (the last tile 16) 74 / 77; 2048 x 8192, 640 rows 49 / 43, 1000 rows
+// 51 / 47, 800 rows (32) 42.2 / 43.4, 900 rows (4) 43.3 / 44.5; 2048 x 2048, 1000 rows 17.1 / 16.6; 3072 x 2048, 500 rows 16.4 / 15.2.
+// 128 x 128 / 192 x 64: 4096 x 14336, 640 rows 125 / 106, 700 rows 108 / 105; 2048 x 8192, 1100 rows 69 / 59, 1300 rows 59.7 / 60.4; 5120 x 5120, 500 rows 50 / 42;
+// 5120 x 27648, 576 rows 229 / 212; 7168 x 5120, 384 rows 52 / 43; K = 2048, 4096 columns 600 rows 18 / 20.
+// 128 x 128 / 256 x 64: 6144 x 4096, 450 rows 40 / 37; 7168 x 5120, 512 rows 53 / 48, 400 rows (the last tile 144) 44 / 45; 4096 x 4096, 1024 rows 43 / 41, 900 rows (132)
+// 38 / 40; 5120 x 5120, 768 rows 52 / 48, 700 rows (188) 46 / 47; over a long K 4096 x 8192, 1024 rows 76 / 78, 900 rows 67 / 72, 2048 x 8192, 2000 rows 75 / 78, 4096 x 14336,
+// 1000 rows 130 / 126, 900 rows 114 / 136, 5120 x 27648, 768 rows 247 / 261.  Between K = 5120 and 8192 nothing was measured.
 struct GemmForm { int waves, tm, tn; bool burst = false; };
 constexpr long kComputeUnits = 256;
 static GemmForm plain_form(int M, int N, int K) {
@@ -492,11 +496,12 @@ static GemmForm plain_form(int M, int N, int K) {
     const int rows = 32 * f.waves * f.tm;
     const long row_tiles = (M + rows - 1) / rows;
     if (row_tiles * (N / 32) / f.tn > kComputeUnits) continue;
-    if (f.burst && (K < 4096 || (f.tm == 2 && 2 * row_tiles > (M + 127) / 128))) continue;
+    const long last = M - (row_tiles - 1) * rows;              // rows of the last row tile
+    if (f.burst && (K < 4096 || (f.tm == 2 && (K > 5120 || 4 * last < 3 * rows)))) continue;
     if (f.waves == 4 && f.tm == 1 && f.tn == 2) {
       const long by_96 = (M + 95) / 96;
       if (K >= 12288 && 3 * by_96 >= 4 * row_tiles && by_96 * (N / 64) <= kComputeUnits) return GemmForm{3, 1, 2};
-      return GemmForm{4, 1, 2, K >= 2048 && 8L * M > 7L * 128 * row_tiles};
+      return GemmForm{4, 1, 2, K >= 2048 && 8L * M > 7L * rows * row_tiles && 2 * last >= rows};
     }
     return f;
   }

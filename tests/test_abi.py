@@ -185,6 +185,17 @@ def test_gemm_plan_takes_96_rows_only_for_a_third_more_workgroups(lib):
     assert lib.mc_op_gemm_plan(65, 4096, 4096, 2, out) == -1 and lib.mc_op_gemm_plan(65, 4096, 4096, 0, None) == -1
 
 
+@pytest.mark.parametrize("M,N,K,form", [
+    (900, 4096, 14336, (128, 128)), (1000, 4096, 14336, (128, 128)), (768, 5120, 27648, (128, 128)), (900, 4096, 8192, (128, 128)), (2000, 2048, 8192, (128, 128)),
+    (900, 4096, 4096, (128, 128)), (400, 6144, 4096, (128, 128)), (400, 7168, 5120, (128, 128)), (959, 4096, 4096, (128, 128)),
+    (960, 4096, 4096, (256, 64)), (1000, 4096, 4096, (256, 64)), (450, 6144, 4096, (256, 64)), (512, 7168, 5120, (256, 64)), (768, 5120, 5120, (256, 64)),
+    (500, 5120, 5120, (192, 64)), (600, 4096, 14336, (192, 64)), (1000, 3072, 2048, (128, 128))])
+def test_gemm_plan_takes_256_x_64_only_with_full_row_tiles_and_a_short_k(lib, M, N, K, form):
+    """Weights in bursts by 256 x 64 lose where the last row tile is not full to three quarters (4096 x 14336, 900 rows 136 us by it, 114 by
+    128 x 128) and over a K above 5120."""
+    assert binding.op_gemm_plan(M, N, K)[:2] == form
+
+
 @pytest.mark.parametrize("rows,K,calls", [(1, 64, 1), (32, 2048, 1), (33, 4096, 1), (55, 5120, 1), (64, 128, 1), (300, 4096, 1),
                                           (300, 14336, 3)])
 def test_tiled_outputs_cost_one_torch_call_and_have_zero_padding(rows, K, calls):
