@@ -451,6 +451,12 @@ int mc_op_attention_prefill_tiled(void *stream, int32_t rows, int32_t n_items, c
                                   const void *v_suffix, const int32_t *page_table,
                                   int32_t table_stride, void *out);
 
+/* Host-only: the kernel that mc_op_attention_prefill runs for these sizes (table_stride 0: a call without a page table).  out2
+ * (host): 0 whole items, 1 two waves per head, 2 scoring and adding waves, 3 whole items with the heads past a multiple of four by
+ * neighbouring items; number of workgroups.  All give the same bits. */
+int mc_op_attention_prefill_plan(int32_t n_items, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                 int32_t page_tokens, int32_t prefix_len, int32_t table_stride, int32_t *out2);
+
 /* HBM read-rate probe (a measurement aid): reads `bytes` of device memory once (a multiple of
  * 64 MiB; larger than the 256 MB memory-side cache for an HBM figure) with 16-byte streaming
  * loads and nothing else; out_word: device, 4 bytes, may be written. */

@@ -112,6 +112,7 @@ SIGNATURES = {
     "mc_op_mfma_probe": (C.c_int, [_vp, _vp, _vp, _i32, _i32]),
     "mc_op_attention_prefill": (C.c_int, [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp, _i32]),
     "mc_op_attention_prefill_tiled": (C.c_int, [_vp, _i32, _i32, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp]),
+    "mc_op_attention_prefill_plan": (C.c_int, [_i32] * 7 + [_vp]),
     "mc_op_top_list_bytes": (_sz, [_i32, _i32]),
     "mc_op_lm_head": (C.c_int, [_vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp]),
     "mc_op_sample_lists": (C.c_int, [_vp, _i32, _i32, _vp, _sz, _vp, _f32, _i32, _vp, _vp, _vp]),
@@ -647,6 +648,15 @@ def op_attention_decode_plan(n_cands, n_q_heads, n_kv_heads, head_dim, page_toke
     keys = ("prefix_items", "suffix_items", "splits", "blocks_per_split", "suffix_splits", "suffix_bps",
             "n_parts", "prefix_stride", "rb_per_item")
     return dict(zip(keys, (int(v) for v in out)))
+
+
+def op_attention_prefill_plan(n_items, n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len, table_stride=0):
+    """Host-only: (kernel, workgroups) of a prefill attention call, kernel "whole", "split", "pair" or "rest" (whole items, the heads past
+    a multiple of four by neighbouring items).  table_stride 0: no page table."""
+    out = np.zeros(2, np.int32)
+    _check(load_library().mc_op_attention_prefill_plan(n_items, n_q_heads, n_kv_heads, head_dim, page_tokens, prefix_len,
+                                                       table_stride, out.ctypes.data))
+    return ("whole", "split", "pair", "rest")[out[0]], int(out[1])
 
 
 def op_read_probe(buf, out_word):

@@ -139,6 +139,7 @@ struct PrefillAttnArgs {
 };
 bool prefill_attention_mfma_supported(int page_tokens, int head_dim, int Hq, int Hkv);
 int launch_attention_prefill_mfma(hipStream_t st, const PrefillAttnArgs &a);
+void prefill_attention_plan(const PrefillAttnArgs &a, int32_t out[2]);        // see mc_op_attention_prefill_plan; a.page_table only as set or not
 
 bool decode_attention_mfma_supported(const DecodeAttnArgs &a);
 size_t decode_attention_mfma_ws_bytes(int n_cands, int Hq, int Hkv, int hd, int prefix_len,

@@ -66,7 +66,6 @@ template <int HD> struct PSplit {              // two waves per head: a step is 
 };
 
 constexpr int kPrefillMaxPids = 1024;
-constexpr int kPairSharedKeys = 2048;          // see prefill_form
 typedef __attribute__((address_space(3))) int lds_int;
 
 // All but the newest N vector memory operations of this wave have landed, loads into LDS among them,
@@ -689,8 +688,12 @@ void prefill_attention_pair_kernel(PrefillAttnArgs a, int n_main) {
   int id = blockIdx.x;
   const int kvh = id % Hkv; id /= Hkv;
   const int hg = id % HG; id /= HG;
-  const int half = id & 1;
-  const int4 item = a.items[id >> 1];
+  // Several sequences: second halves of the items last.  Items of up to 32 rows have none, and workgroups that end at once in turn with others
+  // leave the dispatcher half of the units (32 sequences of 20 rows after 3000 keys, 8 / 8 heads of 128: 52 -> 29 us).  One sequence, whose
+  // items are full: in turn (1000 rows of the 8B heads after 256 keys 30, 34 apart).
+  const bool apart = a.page_table != nullptr;
+  const int half = apart ? id >= a.n_items : id & 1;
+  const int4 item = a.items[apart ? id - (half ? a.n_items : 0) : id >> 1];
   const int row_start = item.x + 32 * half, pos_start = item.z + 32 * half, my_rows = min(32, item.y - 32 * half);
   if (my_rows <= 0) return;                     // the whole workgroup: the item has no second half
   const bool both = NH * hg + 1 < G;            // the second head exists
@@ -998,18 +1001,26 @@ static long prefill_grid(const PrefillAttnArgs &a, int form) {
 
 // A workgroup is a chain over all keys of its rows, so as long as one round of workgroups (a compute
 // unit holds one) leaves units idle, more of them with shorter steps are faster.  All forms give the same bits.  A second round
-// of the pair form, whose step is the shortest for its work, still gains for one sequence, which all its workgroups walk together, and for several
-// behind a long prefix; behind a short one the suffix pages and the fixed part of a workgroup weigh more, and two waves per head or
-// whole items are better.  us, whole items or two waves per head / pairs: one sequence, 8B heads, 560 rows after 512 / 4096 keys 29 / 24, 95 / 86,
-// 800 after 256 27.8 / 23.1, 1000 after 256 / 1024 / 4096 (512 workgroups) 31 / 26, 46 / 38, 103 / 92, heads of 64 24 / 18 after 256, 79 / 62 after 4096;
-// 40 heads, 600 after 4096 117 / 84; several sequences, 5 of 100 after 300 16.0 / 19.5, heads of 64 11.8 / 13.7, 8 of 112 after 1211 33.7 / 36.9, 5 of 150 after
-// 3000 66 / 65, heads of 64 52 / 46; 4 of 400 after 1024 keys (896 workgroups) 50 / 73.
+// of the pair form, whose step is the shortest for its work, gains against whole items at any length for one sequence, which all its workgroups walk
+// together, and behind a long prefix for several; against two waves per head, which have half of its workgroups, behind a longer one, as its workgroups' fixed
+// part counts twice.  Measured at 257 to 512 workgroups of it, one sequence of 300 to 1500 rows after 64 to 8192 keys, 2 to 100 sequences of 20 to 320
+// rows after 64 to 8192, 1 to 8 heads per KV head; the other form's time / this one's:
+// one sequence: whole items 1.3 to 1.6; two waves per head, head_dim 64, 0.97 (400 rows after 64 keys), 1.03 from 500 after 64 on, 1.2 after 8192; 128, up to four
+// heads 0.98 (600 after 64), 1.02 to 1.08 from 800 after 64 on, five to eight heads 0.90 to 1.02 up to 1024 keys, 1.00 to 1.07 after 2048;
+// several: whole items 0.7 to 0.9 up to 300 keys, 1.0 to 1.2 at 1000, 1.13 to 1.7 at 2047; two waves per head, head_dim 64, 0.8 to 0.9 up to 300 keys, 1.01 to 1.07 at
+// 2047, 1.1 at 3000; 128 0.7 to 0.9 up to 1000, 0.91 to 0.97 at 2047, 0.96 to 1.04 at 3000 (items of up to 32 rows, half of whose workgroups end at once, 1.8).
 template <int HD>
 static int prefill_form(const PrefillAttnArgs &a) {
   const long pairs = prefill_grid<HD>(a, PREFILL_PAIR);
-  const bool shared = a.page_table == nullptr || a.prefix_len >= kPairSharedKeys;
-  if (pairs <= (shared ? 2 : 1) * kComputeUnits) return PREFILL_PAIR;
-  return prefill_grid<HD>(a, PREFILL_SPLIT) <= kComputeUnits ? PREFILL_SPLIT : PREFILL_WHOLE;
+  const bool split = prefill_grid<HD>(a, PREFILL_SPLIT) <= kComputeUnits;
+  if (pairs <= kComputeUnits) return PREFILL_PAIR;
+  if (pairs <= 2 * kComputeUnits) {
+    int least;                                  // keys from which the second round is faster
+    if (a.page_table) least = split && HD == 128 ? 3072 : 2048;
+    else least = !split ? 0 : HD == 64 ? 512 : a.n_q_heads / a.n_kv_heads <= 4 ? 768 : 2048;
+    if (a.prefix_len >= least) return PREFILL_PAIR;
+  }
+  return split ? PREFILL_SPLIT : PREFILL_WHOLE;
 }
 
 template <int HD>
@@ -1040,6 +1051,12 @@ int launch_attention_prefill_mfma(hipStream_t st, const PrefillAttnArgs &a) {
   if (!prefill_attention_mfma_supported(a.page_tokens, a.head_dim, a.n_q_heads, a.n_kv_heads))
     MC_FAIL(MC_ERR_UNSUPPORTED, "prefill attention: shape not covered");
   return a.head_dim == 128 ? launch_prefill_hd<128>(st, a) : launch_prefill_hd<64>(st, a);
+}
+
+void prefill_attention_plan(const PrefillAttnArgs &a, int32_t out[2]) {
+  const int form = a.head_dim == 128 ? prefill_form<128>(a) : prefill_form<64>(a);
+  out[0] = form == PREFILL_WHOLE && rest_heads(a) ? 3 : form;
+  out[1] = (int32_t)(a.head_dim == 128 ? prefill_grid<128>(a, form) : prefill_grid<64>(a, form));
 }
 
 }  // namespace mc

@@ -458,6 +458,20 @@ extern "C" int mc_op_attention_prefill_tiled(void *stream, int32_t rows, int32_t
                               v_prefix, k_suffix, v_suffix, page_table, table_stride, out, TILED_ZERO);
 }
 
+extern "C" int mc_op_attention_prefill_plan(int32_t n_items, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                            int32_t page_tokens, int32_t prefix_len, int32_t table_stride, int32_t *out2) {
+  if (!out2 || n_items < 1 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads || prefix_len < 1 || table_stride < 0)
+    MC_FAIL(MC_ERR_INVALID, "bad sizes");
+  if (!prefill_attention_mfma_supported(page_tokens, head_dim, n_q_heads, n_kv_heads))
+    MC_FAIL(MC_ERR_UNSUPPORTED, "prefill attention: bf16, 64-token pages, head_dim 64 or 128 only");
+  PrefillAttnArgs a{};
+  a.n_items = n_items; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
+  a.page_tokens = page_tokens; a.prefix_len = prefix_len; a.table_stride = table_stride;
+  a.page_table = table_stride ? out2 : nullptr;             // set or not, never followed
+  prefill_attention_plan(a, out2);
+  return MC_OK;
+}
+
 extern "C" size_t mc_op_top_list_bytes(int32_t rows, int32_t N) {
   if (rows < 1 || N < 64 || N % 64) return 0;
   return (size_t)rows * (N / 64) * kTopPerGroup * 8;

@@ -196,6 +196,36 @@ def test_gemm_plan_takes_256_x_64_only_with_full_row_tiles_and_a_short_k(lib, M,
     assert binding.op_gemm_plan(M, N, K)[:2] == form
 
 
+@pytest.mark.parametrize("n,Hq,Hkv,hd,keys,stride,form", [
+    # one round of workgroups of scoring and adding waves: always
+    (5, 32, 8, 128, 4396, 0, "pair"), (8, 32, 8, 64, 65, 1, "pair"), (16, 16, 8, 128, 100, 2, "pair"),
+    # a second round, one sequence (keys: its rows among them): against two waves per head from a length on, against whole items always
+    (10, 32, 8, 128, 767, 0, "split"), (10, 32, 8, 128, 768, 0, "pair"), (16, 32, 8, 128, 1256, 0, "pair"), (5, 64, 8, 128, 1324, 0, "split"),
+    (5, 64, 8, 128, 2348, 0, "pair"), (7, 40, 8, 128, 464, 0, "split"), (7, 48, 8, 64, 464, 0, "split"), (8, 48, 8, 64, 564, 0, "pair"),
+    (10, 40, 8, 128, 664, 0, "pair"), (17, 8, 8, 128, 1100, 0, "pair"),
+    # a second round, several sequences
+    (16, 32, 8, 128, 3071, 1, "split"), (16, 32, 8, 128, 3072, 1, "pair"), (16, 32, 8, 64, 2047, 1, "split"), (16, 32, 8, 64, 2048, 1, "pair"),
+    (32, 16, 8, 128, 2047, 1, "whole"), (32, 16, 8, 128, 2048, 1, "pair"),
+    # more workgroups
+    (17, 32, 8, 128, 4096, 0, "whole"), (128, 32, 8, 128, 4096, 16, "whole"), (33, 32, 8, 64, 9000, 1, "whole")])
+def test_prefill_attention_takes_a_second_round_where_it_is_faster(lib, n, Hq, Hkv, hd, keys, stride, form):
+    """Host logic of the prefill attention launcher at both sides of its lines (300 rows of 64 / 8 heads after 256 keys: 20.1 us by scoring and
+    adding waves, 18.0 by two waves per head)."""
+    kernel, groups = binding.op_attention_prefill_plan(n, Hq, Hkv, hd, 64, keys, stride)
+    G = Hq // Hkv
+    assert kernel == form
+    assert groups == n * Hkv * {"whole": -(-G // 4), "split": 2 * -(-G // 4), "pair": 2 * -(-G // 2)}[kernel]
+
+
+def test_prefill_attention_plan_refuses_what_the_launch_refuses(lib):
+    out = (C.c_int32 * 2)()
+    plan = lib.mc_op_attention_prefill_plan
+    assert plan(5, 32, 8, 128, 64, 300, 0, out) == 0 and plan(5, 32, 8, 128, 64, 300, 0, None) == -1
+    for bad in ((0, 32, 8, 128, 64, 300, 0), (5, 32, 7, 128, 64, 300, 0), (5, 32, 8, 128, 64, 0, 0), (5, 32, 8, 128, 64, 300, -1)):
+        assert plan(*bad, out) == -1, bad
+    assert plan(5, 32, 8, 96, 64, 300, 0, out) == -5 and plan(5, 32, 8, 128, 32, 300, 0, out) == -5
+
+
 @pytest.mark.parametrize("rows,K,calls", [(1, 64, 1), (32, 2048, 1), (33, 4096, 1), (55, 5120, 1), (64, 128, 1), (300, 4096, 1),
                                           (300, 14336, 3)])
 def test_tiled_outputs_cost_one_torch_call_and_have_zero_padding(rows, K, calls):
