@@ -238,26 +238,28 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
   // head's keys and values only
   const int kvh = id % Hkv; id /= Hkv;
   int hg, n_near = 1, slot = 0;                 // items that the workgroup may take, this one's place among them
-  if (REST && id >= a.n_items * (G / 4)) {
-    hg = G / 4;
-    n_near = 4 / (G % 4);
+  const int rest = G & 3, two = rest >> 1;        // REST: one head or two (two = 0, 1) past a multiple of four
+  if (REST && id >= a.n_items * (G >> 2)) {
+    hg = G >> 2;
+    n_near = 4 >> two;
     id -= a.n_items * hg;
-    const int groups = (a.n_items + n_near - 1) / n_near;
-    slot = id / groups;
-    id = id % groups * n_near + slot;
+    const int groups = (a.n_items + n_near - 1) >> (2 - two);
+    slot = (id >= groups) + (id >= 2 * groups) + (id >= 3 * groups);
+    id = ((id - slot * groups) << (2 - two)) + slot;
     if (id >= a.n_items) return;
   } else {
     hg = id % (REST ? G / 4 : HG);
     id /= REST ? G / 4 : HG;
   }
   // head within the group, half of the item's rows, the wave's item
-  int hw = wave % 4, half = wave >> 2, mine = id;
+  int hw = wave % 4, half = wave >> 2;
   const int4 first = a.items[id];              // row_start, n_rows (<= 64), pos_start, table row
+  int4 item = first;
   const int tab = first.w;
   int last_pos = first.z + first.y - 1;        // of the whole workgroup: pages every wave helps to stage
   bool has_item = true;
   if (n_near > 1) {
-    const int rest = G % 4, n_left = min(n_near - slot, a.n_items - id);
+    const int n_left = min(n_near - slot, a.n_items - id);
     const int before = a.items[max(id - 1, 0)].w;
     int4 near[4];                                // one round trip for all
 #pragma unroll
@@ -270,12 +272,14 @@ void prefill_attention_kernel(PrefillAttnArgs a) {
         last_pos = max(last_pos, near[i].z + near[i].y - 1);
         n = i + 1;
       }
-    hw = wave % rest;
-    half = wave / rest & 1;
-    has_item = wave / rest / 2 < n;
-    mine = has_item ? id + wave / rest / 2 : id;
+    hw = wave & two;
+    half = wave >> two & 1;
+    const int which = wave >> (1 + two);
+    has_item = which < n;
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+      if (has_item && which == i) item = near[i];
   }
-  const int4 item = REST ? a.items[mine] : first;
   const int n_rows = item.y;
   const int row_start = item.x + 32 * half;     // this wave's rows and their first position
   const int pos_start = item.z + 32 * half;
@@ -976,16 +980,25 @@ bool prefill_attention_mfma_supported(int page_tokens, int head_dim, int Hq, int
 
 enum { PREFILL_WHOLE, PREFILL_SPLIT, PREFILL_PAIR };
 
-// Whole items: do the heads past a multiple of four go by several items to a workgroup?  Where the workgroups of an item each are more than the
-// compute units; in one round nothing is won, and eight busy waves walk the keys slower than two (160 workgroups, 8 / 8 heads of 128, 5 x 200
-// rows after 1000 keys 34 / 37 us).  us, a workgroup per item / several items: 40 / 8 heads of 128, 8 x 1024 rows after 4096 keys 978 / 771 (0.55 -> 0.70
-// PFLOP/s), 8 x 300 after 2000 178 / 137, 5 x 200 after 1000 68 / 40, one sequence of 4096 after 4096 638 / 575, 128 x 64 after 300 (no neighbours of one
-// sequence: what is won is the order of the workgroups) 138 / 126; 8 / 8 heads of 128, 8 x 1024 after 4096 482 / 163; 16 / 8 heads of 64 276 / 187.
-// A single head per workgroup used to keep a unit as long as four did, and in turn with full ones they filled half of the units each.
+// Whole items: do the heads past a multiple of four go by several items to a workgroup?  Measured at 257 to 3200 workgroups of whole items, sequences of
+// 20 to 300 rows after 64 to 8192 keys, 1, 2, 5 and 6 heads per KV head; the time with a workgroup per item / this one's:
+// sequences of several items 1.1 to 2.1 (40 / 8 heads of 128, 8 x 1024 rows after 4096 keys 978 / 771 us, 5 x 200 after 1000 68 / 40; 8 / 8 heads, 8 x 1024 after 4096
+// 482 / 163), but not in one round of workgroups, where nothing is won (160 workgroups, 5 x 200 rows after 1000 keys 34 / 37 us), nor where even the
+// neighbours all found leave as many rounds (40 / 8 heads, 8 x 256: 320 of 512, 0.94 to 1.00).
+// Sequences of one item: five and six heads 1.0 to 1.5, as the full workgroups go first; one and two heads, whose waves spread over more SIMDs, 1.1 to 1.4
+// from 1000 keys on, but 0.83 to 1.1 up to 300, and items of up to 32 rows 0.88 to 1.0.
+// One head of 64, whose workgroups go two to a unit: 0.89 to 1.00 up to 512 workgroups, 1.1 to 1.7 above.
 constexpr long kComputeUnits = 256;
+constexpr int kRestShortKeys = 1000;
 static bool rest_heads(const PrefillAttnArgs &a) {
   const int G = a.n_q_heads / a.n_kv_heads;
-  return (G % 4 == 1 || G % 4 == 2) && (long)a.n_items * a.n_kv_heads * ((G + 3) / 4) > kComputeUnits;
+  if (G % 4 != 1 && G % 4 != 2) return false;
+  const int near = 4 / (G % 4), stride = a.page_table ? a.table_stride : near;         // a sequence's pages: its items at most
+  const long whole = (long)a.n_kv_heads * a.n_items * ((G + 3) / 4), least = (long)a.n_kv_heads * ((long)a.n_items * (G / 4) + (a.n_items + near - 1) / near);
+  auto rounds = [](long groups) { return (groups + kComputeUnits - 1) / kComputeUnits; };
+  if (whole <= (a.head_dim == 64 && G == 1 ? 2 : 1) * kComputeUnits) return false;
+  if (G < 4 && stride == 1) return a.prefix_len >= kRestShortKeys;
+  return stride < near || rounds(least) < rounds(whole);
 }
 
 // workgroups of a form

@@ -1258,9 +1258,9 @@ def test_attention_prefill_rest_heads_of_neighbouring_items(Hq, Hkv, hd):
     import torch
     pg, P, G = 64, 200, Hq // Hkv
     lens = [64, 130, 5, 300, 64, 70, 448, 1, 193, 256]
-    while sum(-(-n // 64) for n in lens) * 2 * Hkv * -(-G // 4) <= 300:        # more workgroups than two waves per head are used for
-        lens = lens + lens[1:]
     per = max(-(-n // 64) for n in lens)
+    while binding.op_attention_prefill_plan(sum(-(-n // 64) for n in lens) + 4, Hq, Hkv, hd, pg, P, per)[0] != "rest":
+        lens = lens + lens[1:]
     g = torch.Generator(device="cuda")
     g.manual_seed(77 + Hq + hd)
     normal = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)  # noqa: E731
