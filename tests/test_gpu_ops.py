@@ -197,11 +197,13 @@ def test_attention_decode_generic_quads(dtype, B, Hq, Hkv, hd, pg, P, t):
     assert worst < ATT_REL[dtype], worst
 
 
-@pytest.mark.parametrize("dtype,B,Hq,Hkv,hd,pg,P,t", [
-    ("f32", 5, 4, 2, 64, 4, 30, 19), ("bf16", 6, 8, 2, 128, 64, 300, 200), ("bf16", 9, 32, 8, 128, 64, 1000, 333),
-    ("bf16", 4, 8, 4, 64, 64, 0, 130), ("bf16", 3, 8, 2, 96, 64, 100, 70),
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,hd,pg,P,t,splits", [
+    ("f32", 5, 4, 2, 64, 4, 30, 19, 0), ("bf16", 3, 8, 2, 96, 64, 100, 70, 0),                             # the generic kernel
+    ("bf16", 6, 8, 2, 128, 64, 300, 200, 0), ("bf16", 4, 8, 4, 64, 64, 0, 130, 0),                          # a workgroup per candidate and KV head
+    ("bf16", 9, 32, 8, 128, 64, 1000, 333, 0), ("bf16", 6, 8, 2, 128, 64, 300, 200, 2), ("bf16", 4, 8, 4, 64, 64, 0, 130, 1),   # split keys
+    ("bf16", 64, 8, 2, 128, 64, 400, 130, 3),                                                               # ... four row blocks per prefix item
 ])
-def test_attention_decode_candidates_of_different_lengths(dtype, B, Hq, Hkv, hd, pg, P, t):
+def test_attention_decode_candidates_of_different_lengths(dtype, B, Hq, Hkv, hd, pg, P, t, splits):
     """row_len: every candidate attends to its own number of suffix keys (1 .. t; some end inside
     the first block, some on a block or page edge, one is at the maximum), against the oracle's
     attention on exactly those keys."""
@@ -222,7 +224,7 @@ def test_attention_decode_candidates_of_different_lengths(dtype, B, Hq, Hkv, hd,
     qd, qv = to_dev(q, dtype)
     print("case: ragged attention", dtype, B, Hq, Hkv, hd, pg, P, t, lens.tolist(), flush=True)
     out = binding.op_attention_decode(qd, kpd if P else None, vpd if P else None, ksd, vsd,
-                                      torch.from_numpy(table).cuda(), P, t, pg,
+                                      torch.from_numpy(table).cuda(), P, t, pg, splits,
                                       row_len=torch.from_numpy(lens).cuda()).float().cpu().numpy()
     G = Hq // Hkv
     worst = 0.0
@@ -248,6 +250,7 @@ def test_attention_decode_candidates_of_different_lengths(dtype, B, Hq, Hkv, hd,
     (1, 32, 1, 64, 128, 129, 1), (7, 4, 2, 128, 0, 200, 1), (33, 8, 2, 128, 257, 1, 1),
     # many query rows per KV head
     (50, 32, 8, 128, 1000, 70, 3),       # 7 row blocks (the last of 8 rows), last page of 40 keys
+    # (these two by a workgroup per candidate and KV head; test_attention_decode_short_contexts asks for their split form)
     (64, 32, 2, 64, 200, 33, 17),        # head_dim 64, 32 row blocks, last page of 8 keys
     (48, 16, 4, 128, 130, 5, 1),         # 6 row blocks, 3 pages (the last with 2 keys)
     (64, 32, 8, 128, 100, 0, 3),         # 8 row blocks, one key split, no suffix: every item writes its outputs itself
@@ -270,7 +273,7 @@ def test_attention_decode_mfma_shapes(B, Hq, Hkv, hd, P, t, stride):
     (64, 8, 8, 128, 673, 250, 0),
     # the split form at sizes that no longer take it by themselves
     (64, 32, 8, 128, 100, 0, 1), (72, 32, 8, 128, 700, 40, 1), (2, 8, 8, 128, 63, 65, 1), (3, 8, 4, 64, 65, 64, 2), (48, 16, 4, 128, 130, 5, 1),
-    (7, 4, 2, 128, 0, 200, 1), (1, 32, 1, 64, 128, 129, 1), (4, 6, 2, 64, 250, 70, 2)])
+    (7, 4, 2, 128, 0, 200, 1), (1, 32, 1, 64, 128, 129, 1), (4, 6, 2, 64, 250, 70, 2), (64, 32, 2, 64, 200, 33, 2)])
 def test_attention_decode_short_contexts(B, Hq, Hkv, hd, P, t, splits):
     plant = [(B - 1, Hq - 1, "prefix", P - 1)] if P > 1 else []
     if t > 1:
@@ -995,29 +998,47 @@ def test_attention_prefill_item_sizes(item_rows):
     assert worst < ATT_REL["bf16"], worst
 
 
-@pytest.mark.parametrize("Hq,Hkv,hd,P,seqs,stride", [
-    # four waves per head: two pages a step, an odd number of pages, a prefix that ends inside its last
+def prefill_kernel(Hq, Hkv, hd, P, seqs):
+    """The kernel that prefill_case runs for these sizes."""
+    stride = -(-max(n for _, n in seqs) // 64) if any(p0 >= P for p0, _ in seqs) else 0
+    return binding.op_attention_prefill_plan(sum(-(-n // 64) for _, n in seqs), Hq, Hkv, hd, 64, P, stride)[0]
+
+
+@pytest.mark.parametrize("Hq,Hkv,hd,P,seqs,stride,kernel", [
+    # scoring and adding waves: two pages a step, an odd number of pages, a prefix that ends inside its last
     # page's first block, three query heads for two per workgroup; more of a prefix, scored suffixes
-    (8, 2, 128, 2593, [(2593, 40), (2593, 1)], 3), (6, 2, 128, 2700, [(2700, 50)], 3), (8, 2, 64, 2626, [(2596, 30)], 1),
-    # two waves per head (too many items for four): suffixes of one page each, a late part of a prefix
-    (32, 8, 128, 2570, [(2570, 64)] * 10, 97), (32, 8, 64, 3130, [(2600, 530)], 211),
-    # the last item count of each form, and the first of the next
-    (32, 8, 128, 3112, [(2600, 512)], 401), (32, 8, 64, 3113, [(2600, 513)], 401), (32, 8, 128, 3624, [(2600, 1024)], 1601),
-    (32, 8, 64, 3625, [(2600, 1025)], 1601),
+    (8, 2, 128, 2593, [(2593, 40), (2593, 1)], 3, "pair"), (6, 2, 128, 2700, [(2700, 50)], 3, "pair"), (8, 2, 64, 2626, [(2596, 30)], 1, "pair"),
+    # a second round of them: several sequences behind a long prefix, a late part of a prefix
+    (32, 8, 128, 3100, [(3100, 64)] * 10, 97, "pair"), (32, 8, 64, 3130, [(2600, 530)], 211, "pair"),
+    # item counts at the ends of the rounds, and the first past them
+    (32, 8, 128, 3112, [(2600, 512)], 401, "pair"), (32, 8, 64, 3113, [(2600, 513)], 401, "pair"), (32, 8, 128, 3624, [(2600, 1024)], 1601, "pair"),
+    (32, 8, 64, 3625, [(2600, 1025)], 1601, "whole"),
+    # two waves per head: suffixes of one page each behind prefixes that end in a page's first block, its second, at its end
+    (32, 8, 128, 2570, [(2570, 64)] * 10, 97, "split"), (32, 8, 64, 1965, [(1965, 64)] * 10, 97, "split"), (32, 8, 64, 1920, [(1920, 33)] * 16, 61, "split"),
+    # ... three, five and eight query heads for four per workgroup, items of one half
+    (6, 2, 128, 700, [(700, 20)] * 40, 61, "split"), (10, 2, 64, 741, [(741, 64)] * 25, 211, "split"), (16, 2, 128, 129, [(129, 40)] * 20, 97, "split"),
+    (64, 8, 128, 500, [(200, 300)], 301, "split"),
+    # ... page ids in registers of 64: a prefix and suffixes that go through two of them
+    (8, 1, 128, 3000, [(3000, 1200), (3000, 1000)], 401, "split"), (8, 1, 64, 2000, [(2000, 2200)], 401, "split"),
     # whole pages only and suffixes that end early; rows at the prefix's begin: waves whose blocks no row sees
-    (8, 2, 128, 2560, [(2560, 33)], 1), (8, 2, 64, 2561, [(0, 70)], 1),
+    (8, 2, 128, 2560, [(2560, 33)], 1, "pair"), (8, 2, 64, 2561, [(0, 70)], 1, "pair"),
     # page ids in registers of 64: a suffix that goes through two of them, a prefix that goes through three
-    (2, 1, 128, 100, [(100, 4300)], 97), (2, 1, 64, 4032, [(4032, 130)], 7), (4, 2, 128, 8250, [(8250, 20)], 1),
+    (2, 1, 128, 100, [(100, 4300)], 97, "pair"), (2, 1, 64, 4032, [(4032, 130)], 7, "pair"), (4, 2, 128, 8250, [(8250, 20)], 1, "pair"),
 ])
-def test_attention_prefill_key_groups(Hq, Hkv, hd, P, seqs, stride):
+def test_attention_prefill_key_groups(Hq, Hkv, hd, P, seqs, stride, kernel):
+    assert prefill_kernel(Hq, Hkv, hd, P, seqs) == kernel
     worst, _ = prefill_case(Hq, Hkv, hd, P, seqs, stride)
     assert worst < ATT_REL["bf16"], worst
 
 
-@pytest.mark.parametrize("hd,P,rows", [(128, 300, 100), (64, 300, 100), (128, 2700, 70), (64, 2700, 70), (128, 4097, 33), (128, 8200, 40)])
-def test_attention_prefill_rows_do_not_depend_on_the_launch(hd, P, rows):
-    """A candidate's rows scored alone, with a few others and in a full chunk, which take one, two and four
-    waves per head: the same bits.  Some keys outgrow the softmax's reference far into the walk, in every
+@pytest.mark.parametrize("hd,P,rows,kernels", [
+    (128, 300, 100, ("pair", "pair", "split", "whole", "whole")), (64, 300, 100, ("pair", "pair", "split", "whole", "whole")),
+    (128, 2700, 70, ("pair", "pair", "split", "whole", "whole")), (64, 2700, 70, ("pair", "pair", "pair", "whole", "whole")),
+    (128, 4097, 33, ("pair", "pair", "pair", "pair", "whole")), (128, 2050, 40, ("pair", "pair", "pair", "split", "whole")),
+    (128, 8200, 40, ("pair", "pair", "pair", "pair", "whole"))])
+def test_attention_prefill_rows_do_not_depend_on_the_launch(hd, P, rows, kernels):
+    """A candidate's rows scored alone, with a few others and in a full chunk, which take scoring and adding waves, two waves
+    per head and whole items: the same bits.  Some keys outgrow the softmax's reference far into the walk, in every
     place of a step of four blocks."""
     import torch
     Hq, Hkv, pg, n = 32, 8, 64, 24
@@ -1040,6 +1061,7 @@ def test_attention_prefill_rows_do_not_depend_on_the_launch(hd, P, rows):
         return out.view(torch.int16).reshape(len(cands), rows, Hq, hd)
 
     print("case: prefill rows alone and together", hd, P, rows, flush=True)
+    assert tuple(prefill_kernel(Hq, Hkv, hd, P, [(P, rows)] * m) for m in (1, 4, 8, 14, n)) == kernels
     full = score(list(range(n)))
     assert torch.equal(score(list(range(n))), full)
     assert not torch.isnan(full.view(torch.bfloat16)).any()
@@ -1062,8 +1084,16 @@ def test_attention_with_peaked_and_flat_softmax(qscale):
     assert worst < 2 * ATT_REL["bf16"], worst
     worst, _, _ = attention_case("bf16", 4, 4, 4, 64, 64, 0, 257, qscale=qscale)
     assert worst < 2 * ATT_REL["bf16"], worst
+    # short contexts: a workgroup per candidate and KV head (0), split keys; many rows: four row blocks per prefix item
+    for B, P, t, splits in ((9, 500, 130, 0), (9, 500, 130, 3), (4, 0, 257, 1), (64, 500, 130, 3)):
+        worst, _, _ = attention_case("bf16", B, 8, 2, 128, 64, P, t, splits=splits, qscale=qscale, stride=1 + B // 4)
+        assert worst < 2 * ATT_REL["bf16"], (worst, B, splits)
     worst, _ = prefill_case(8, 2, 128, 150, [(150, 130)], qscale=qscale, stride=3)
     assert worst < 2 * ATT_REL["bf16"], worst
+    for Hq, Hkv, hd, seqs, kernel in ((32, 8, 128, [(150, 64)] * 10, "split"), (32, 8, 64, [(150, 64)] * 40, "whole"), (40, 8, 128, [(150, 40)] * 20, "rest")):
+        assert prefill_kernel(Hq, Hkv, hd, 150, seqs) == kernel
+        worst, _ = prefill_case(Hq, Hkv, hd, 150, seqs, qscale=qscale, stride=211)
+        assert worst < 2 * ATT_REL["bf16"], (worst, kernel)
 
 
 def test_mfma_probe_counts_what_it_claims():
@@ -1113,9 +1143,12 @@ def test_swiglu_writes_its_padding_rows(M, N, K):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,hd,pg,P,t,splits", [
-    (8, 32, 8, 64, 64, 777, 37, 0), (1, 8, 2, 128, 64, 300, 5, 0), (33, 8, 2, 128, 64, 300, 5, 0),     # merged partial states
+    (8, 32, 8, 64, 64, 777, 37, 0), (1, 8, 2, 128, 64, 300, 5, 0), (33, 8, 2, 128, 64, 300, 5, 0),     # a workgroup per candidate and KV head
+    (5, 8, 2, 128, 64, 20, 0, 0), (9, 8, 4, 64, 64, 0, 30, 0),                                         # ... prefix, suffix alone
+    (8, 32, 8, 64, 64, 777, 37, 2), (1, 8, 2, 128, 64, 300, 5, 1), (33, 8, 2, 128, 64, 300, 5, 3),     # merged partial states
+    (64, 32, 8, 128, 64, 700, 33, 4),                                                                  # ... four row blocks per prefix item
     (3, 8, 2, 64, 64, 3000, 1, 64),                                                                    # more of them than one batch
-    (5, 8, 2, 128, 64, 20, 0, 0), (9, 8, 4, 64, 64, 0, 30, 0), (57, 32, 8, 128, 64, 100, 0, 0),        # one: the items write
+    (5, 8, 2, 128, 64, 20, 0, 1), (9, 8, 4, 64, 64, 0, 30, 1), (57, 32, 8, 128, 64, 100, 0, 1),        # one: the items write
     (5, 8, 2, 96, 64, 100, 9, 0), (7, 4, 2, 64, 16, 33, 4, 0)])                                        # the generic kernel
 def test_decode_attention_writes_its_padding_rows(B, Hq, Hkv, hd, pg, P, t, splits):
     import torch
@@ -1176,7 +1209,8 @@ def test_tiled_outputs_leave_rows_that_are_not_theirs():
     want = binding.tiled_to_rowmajor(binding.op_linear_swiglu(am, wg, wu, tiled_shape=(M, N, 256)), M, N)
     assert torch.equal(got[:M], want) and torch.all(got[M:] == -7)
     Hq, Hkv, pg = 8, 2, 64
-    for hd, P, t in ((64, 300, 20), (128, 20, 0), (96, 50, 9)):          # merged states, one state, the generic kernel
+    # a workgroup per candidate and KV head, merged states, one state, the generic kernel
+    for hd, P, t, splits in ((64, 300, 20, 0), (64, 300, 20, 2), (128, 20, 0, 1), (96, 50, 9, 0)):
         for static in (False, True):
             kp, vp, _, _ = make_pools("bf16", -(-P // pg), Hkv, pg, hd, 966)
             ks, vs, _, _ = make_pools("bf16", 30, Hkv, pg, hd, 968)
@@ -1185,7 +1219,7 @@ def test_tiled_outputs_leave_rows_that_are_not_theirs():
             out = torch.full((64 * Hq * hd,), -7.0, dtype=torch.bfloat16, device="cuda")
             want = torch.full((30, Hq * hd), -7.0, dtype=torch.bfloat16, device="cuda")
             for r0, rows in _tile_calls(n):
-                part = (q[r0:r0 + rows].contiguous(), kp, vp, ks, vs, table[r0:r0 + rows].contiguous(), P, t, pg)
+                part = (q[r0:r0 + rows].contiguous(), kp, vp, ks, vs, table[r0:r0 + rows].contiguous(), P, t, pg, splits)
                 binding.op_attention_decode(*part, out_tiled=True, out=out[8 * r0:], static_scratch=static)
                 want[r0:r0 + rows] = binding.op_attention_decode(*part).reshape(rows, -1)
             _assert_tile(out, want, Hq * hd, 30)
@@ -1193,10 +1227,11 @@ def test_tiled_outputs_leave_rows_that_are_not_theirs():
             assert not _padding_of(whole, rows, Hq * hd).any()
 
 
-@pytest.mark.parametrize("Hq,hd,lens", [(8, 128, (300,)), (8, 64, (33,)), (8, 128, (1000, 70, 40)), (8, 64, (1000, 1000, 71)),
-                                        (64, 128, (1000, 65, 1000, 30))])
-def test_prefill_attention_zeroes_the_rows_that_no_item_covers(Hq, hd, lens):
-    """Padding rows, and rows between the items: in all forms (few and many workgroups, the last with an output
+@pytest.mark.parametrize("Hq,hd,lens,kernel", [
+    (8, 128, (300,), "pair"), (8, 64, (33,), "pair"), (8, 128, (1000, 70, 40), "pair"), (8, 64, (1000, 1000, 71), "pair"),
+    (64, 128, (300,), "split"), (64, 64, (300,), "split"), (40, 128, (400, 1, 150), "split"), (64, 128, (1000, 65, 1000, 30), "whole"), (18, 64, (4000,) * 4, "rest")])
+def test_prefill_attention_zeroes_the_rows_that_no_item_covers(Hq, hd, lens, kernel):
+    """Padding rows, and rows between the items: in all forms (few and many workgroups, the last two with an output
     larger than the L2s)."""
     import torch
     Hkv, pg, P = 2, 64, 200
@@ -1206,6 +1241,7 @@ def test_prefill_attention_zeroes_the_rows_that_no_item_covers(Hq, hd, lens):
         holes += list(range(row + n, row + n + 7))
         row += n + 7                                    # seven rows that nobody computes
     rows = row
+    assert binding.op_attention_prefill_plan(len(items), Hq, Hkv, hd, pg, P + max(lens))[0] == kernel
     kp, vp, _, _ = make_pools("bf16", -(-(P + max(lens)) // pg), Hkv, pg, hd, 927)
     q = to_dev(rnd(928, (rows, Hq, hd)), "bf16")[0]
     it = torch.tensor(items, dtype=torch.int32, device="cuda")
