@@ -507,7 +507,8 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW &W = m->layers[l];
     if (l == 0 && embed_norm) {
-      ProfScope pe(s, MC_K_EMBED), ps(s, MC_K_ADD_RMSNORM);          // one launch is both
+      // one launch is both (its norm goes unread where the QKV layer takes its own: a gather without one is two launches, with the rows' metadata)
+      ProfScope pe(s, MC_K_EMBED), ps(s, few ? MC_K_NONE : MC_K_ADD_RMSNORM);
       MC_TRY(launch_embed_rmsnorm(st, dt, rows, d, s->ptr<int32_t>(L.row_tok), step, m->embed, x, W.attn_norm, c.rms_eps, h, tl));
     } else if (!few) {
       ProfScope ps(s, MC_K_ADD_RMSNORM);
@@ -535,8 +536,8 @@ static int run_layers(mc_session *s, int rows, int pass, int prefix_visible, int
       ro.q_out = q; ro.k_pages = kdst; ro.v_pages = vdst; ro.table = rope_tab;
       ro.Hq = c.n_q_heads; ro.Hkv = c.n_kv_heads; ro.hd = c.head_dim; ro.pg = s->p.page_tokens;
       ProfScope ps(s, MC_K_LINEAR_QKV);
-      if (few) {                                              // one launch is three (layer 0: its norm is the gather's too)
-        ProfScope pr(s, MC_K_ROPE_KV), pn(s, l == 0 ? MC_K_NONE : MC_K_ADD_RMSNORM);
+      if (few) {                                              // one launch is three
+        ProfScope pr(s, MC_K_ROPE_KV), pn(s, MC_K_ADD_RMSNORM);
         MC_TRY(launch_norm_qkv_rope_few(st, dt, rows, m->n_qkv, d, x, W.attn_norm, c.rms_eps, W.wqkv, ro));
       } else {
         MC_TRY(launch_linear_qkv_rope(st, rows, m->n_qkv, d, h, W.wqkv, ro));
