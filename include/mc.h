@@ -383,7 +383,10 @@ int mc_op_rope_kv_write(void *stream, int32_t dtype, int32_t rows, int32_t n_q_h
  * clamped into that range) for candidates of different lengths.
  * q, out: (T)[n_cands][Hq][hd].  workspace: fp32 scratch of mc_op_attention_decode_ws
  * bytes.  prefix_splits: key-axis splits of the prefix (0 = automatic).  out_tiled = 1 stores
- * out as a tiled [n_cands][Hq*hd] matrix. */
+ * out as a tiled [n_cands][Hq*hd] matrix.
+ * Short bf16 contexts with prefix_splits 0 are computed by one workgroup per candidate and KV head, which leaves the
+ * workspace alone and adds in another order than split keys.  A session's decode steps always split the keys: a call has
+ * a step's bits where prefix_splits is the split count that mc_op_attention_decode_plan gives for the step's sizes. */
 size_t mc_op_attention_decode_ws(int32_t n_cands, int32_t n_q_heads, int32_t n_kv_heads,
                                  int32_t head_dim, int32_t prefix_len, int32_t suffix_len,
                                  int32_t page_tokens);
@@ -420,8 +423,8 @@ int mc_op_attention_decode_static(void *stream, int32_t dtype, int32_t n_cands, 
                                   void *out, int32_t out_tiled);
 
 /* Host-only: the work-item plan of mc_op_attention_decode's split form for these sizes on the bf16
- * MFMA path (MC_ERR_UNSUPPORTED for shapes that path does not cover).  Short contexts with prefix_splits 0 are launched as one
- * workgroup per candidate and KV head instead, without partial states (a session's decode steps keep the split form).  out9 (host, nine values):
+ * MFMA path (MC_ERR_UNSUPPORTED for shapes that path does not cover), with and without row_len alike.  Short contexts with
+ * prefix_splits 0 are launched as one workgroup per candidate and KV head instead, without partial states.  out9 (host, nine values):
  * prefix items incl. padding ids, suffix items, prefix key splits, 32-key blocks per prefix split,
  * suffix key splits, blocks per suffix split, partial states per (candidate, head), id distance
  * between the items of one prefix split, blocks of 32 query rows per prefix item (1 or 4). */
