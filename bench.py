@@ -40,10 +40,10 @@ TRAFFIC_GATE_UP = {"fetch_kib": 115761.0, "fetch_scale": 2.0, "write_kib": 896.0
 
 # Decode attention + merge at suffix lengths 255..258 (the same two counter runs: four timed steps
 # sit at the middle of the 512-step workload, whose average suffix length is 256.5).
-TRAFFIC_ATTN = {"fetch_kib": 26452.4, "merge_fetch_kib": 2922.5, "write_kib": 4680.0, "merge_write_kib": 256.0,
+TRAFFIC_ATTN = {"fetch_kib": 26439.1, "merge_fetch_kib": 2922.5, "write_kib": 4680.0, "merge_write_kib": 256.0,
                 "fetch_scale": 2.0, "write_scale": 1.0, "suffix_len": 256.5,
                 "source": "paper_2601_05475_amd/csrc/kernels_attn.hip",
-                "sha256": "1e9c6f88b01320a65d5cc1bf00a7729b759aca73f76702fc86ae045c52b5d7fe"}
+                "sha256": "fad2d8f886d27533a259def7582dd81f75307457c98e4942ed0b3471cb333e36"}
 
 
 def measured_attention_traffic_bytes(workload, mean_suffix_len):
